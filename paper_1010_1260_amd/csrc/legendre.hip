@@ -50,149 +50,170 @@ __global__ void k_prescale(const double2 *__restrict__ alm, const double *__rest
 template <int CH>
 struct Chains {
     double x[CH];
-    int rn[CH], rs[CH];
+    int rn[CH], rs[CH], ilim[CH];
 };
 
+// The ring pairs of this lane's chains: 64-pair blocks blk0..blk0 + CH - 1.
+template <int CH>
+__device__ inline void load_chains(Chains<CH> &g, const PairDesc *__restrict__ pairs, int npairs,
+                                   int blk0)
+{
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        const int p = (blk0 + c) * 64 + (int)threadIdx.x;
+        if (p < npairs) {
+            const PairDesc d = pairs[p];
+            g.x[c] = d.x; g.rn[c] = d.rn; g.rs[c] = d.rs; g.ilim[c] = d.ilim;
+        } else {
+            g.x[c] = 0.0; g.rn[c] = -1; g.rs[c] = -1; g.ilim[c] = 0;
+        }
+    }
+}
+
+// Wave-uniform data that no kernel writes while it reads it comes through the
+// constant address space: scalar loads, also where the compiler cannot prove
+// that the kernel's stores leave it alone (the batch's workspace holds both
+// the coefficients and Delta).
+typedef const int __attribute__((address_space(4))) *CIp;
+typedef const long long __attribute__((address_space(4))) *CLp;
+typedef const double __attribute__((address_space(4))) *CDp;
+
 // One m of an m-pair for CH chains per lane: forward accumulation.
-template <int CH, bool CAS>
-__device__ inline void fwd_one_m(const Chains<CH> &g, const double (&s)[CH], int m, int i,
-                                 long long off, double mum, int lmax,
-                                 const double *__restrict__ A, const double2 *__restrict__ ap,
-                                 double2 *__restrict__ delta, long long dbase, int nrings)
+// full: write the Delta of every ring, also of the m that are dead on it
+// (the ring stage reads the positions below ilim only).
+template <int CH>
+__device__ inline void fwd_one_m(const Chains<CH> &g, const LiveTab &lt, int blk0, int m, int i,
+                                 long long off, int lmax, const double *__restrict__ A,
+                                 const double2 *__restrict__ ap, double2 *__restrict__ delta,
+                                 long long dbase, int nrings, bool full)
 {
     const int len = lmax - m + 1;
-    // The coefficients are only read here and their addresses are uniform
-    // across the wave.  CAS: read them through the constant address space,
-    // so that they come in by scalar loads also when the kernel stores Delta
-    // into the same buffer (the batched kernel's workspace), where the
-    // compiler cannot prove that the loads are not clobbered.
-    typedef const double __attribute__((address_space(4))) *CDp;
-    const double *__restrict__ Ag = A + off;
-    const double2 *__restrict__ apg = ap + off;
-    const CDp Ac = (CDp)(A + off);
-    const CDp amd = (CDp)(ap + off);   // a'_lm as (re, im) pairs
-    auto Am = [&](int k) -> double {
-        if constexpr (CAS) return Ac[k]; else return Ag[k];
-    };
-    auto am = [&](int k) -> double2 {
-        if constexpr (CAS) return make_double2(amd[2 * k], amd[2 * k + 1]); else return apg[k];
-    };
-    double u0[CH], u1[CH], Er[CH], Ei[CH], Or[CH], Oi[CH];
-    int k[CH];
+    const CDp Am = (CDp)(A + off);
+    const CDp am = (CDp)(ap + off);   // a'_lm as (re, im) pairs
+    // rows [8 lo, 8 hi]: where this wave's pairs start
+    int lo = kNeverLive, hi = 0;
     {
-        const double2 a0 = am(0);
+        const CIp jr = (CIp)(lt.jr + (long long)i * lt.nb);
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+            if (blk0 + c < lt.nb) {
+                const int v = jr[blk0 + c];
+                lo = min(lo, v & 0xffff);
+                hi = max(hi, (int)((unsigned)v >> 16));
+            }
+    }
+    double Er[CH], Ei[CH], Or[CH], Oi[CH];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) { Er[c] = 0.0; Ei[c] = 0.0; Or[c] = 0.0; Oi[c] = 0.0; }
+    if (lo != kNeverLive) {
+        double u0[CH], u1[CH], s0[CH], s1[CH];
+        int je[CH];
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
-            seed_mm(mum, s[c], m, u0[c], k[c]);
-            Er[c] = a0.x * u0[c];
-            Ei[c] = a0.y * u0[c];
-            Or[c] = 0.0; Oi[c] = 0.0; u1[c] = 0.0;
-        }
-    }
-    if (len >= 2) {
-        const double A1 = Am(1);
-        const double2 a1 = am(1);
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            u1[c] = (A1 * g.x[c]) * u0[c];
-            Or[c] = a1.x * u1[c];
-            Oi[c] = a1.y * u1[c];
-        }
-    }
-    int j = 2;
-    for (; j + 8 <= len; j += 8) {
-#pragma unroll
-        for (int t = 0; t < 8; t += 2) {
-            const double Aa = Am(j + t), Ab = Am(j + t + 1);
-            const double2 aa = am(j + t), ab = am(j + t + 1);
-#pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                const double u2 = fma(Aa * g.x[c], u1[c], -u0[c]);
-                Er[c] = fma(aa.x, u2, Er[c]);
-                Ei[c] = fma(aa.y, u2, Ei[c]);
-                const double u3 = fma(Ab * g.x[c], u2, -u1[c]);
-                Or[c] = fma(ab.x, u3, Or[c]);
-                Oi[c] = fma(ab.y, u3, Oi[c]);
-                u0[c] = u2; u1[c] = u3;
+            u0[c] = 0.0; u1[c] = 0.0; s0[c] = 0.0; s1[c] = 0.0;
+            je[c] = kNeverLive;
+            if (blk0 + c < lt.nb) {
+                const long long e = (long long)i * lt.np + (blk0 + c) * 64 + (int)threadIdx.x;
+                const double2 v = lt.st[e];
+                s0[c] = v.x; s1[c] = v.y;
+                je[c] = lt.je[e];
             }
         }
+        // a chain is zero until its start row, where it takes the table's values
+        auto enter = [&](int jb) {
 #pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            if (fmax(fabs(u0[c]), fabs(u1[c])) > kTwoS) {
-                u0[c] *= kTwoMinusS; u1[c] *= kTwoMinusS;
-                Er[c] *= kTwoMinusS; Ei[c] *= kTwoMinusS;
-                Or[c] *= kTwoMinusS; Oi[c] *= kTwoMinusS;
-                k[c] += 1;
+            for (int c = 0; c < CH; ++c) {
+                const bool on = je[c] == jb;
+                u0[c] = on ? s0[c] : u0[c];
+                u1[c] = on ? s1[c] : u1[c];
             }
+        };
+        auto rows8 = [&](int j) {
+#pragma unroll
+            for (int t = 0; t < 8; t += 2) {
+                const double Aa = Am[j + t], Ab = Am[j + t + 1];
+                const double ar = am[2 * (j + t)], ai = am[2 * (j + t) + 1];
+                const double br = am[2 * (j + t) + 2], bi = am[2 * (j + t) + 3];
+#pragma unroll
+                for (int c = 0; c < CH; ++c) {
+                    const double u2 = fma(Aa * g.x[c], u1[c], -u0[c]);
+                    Er[c] = fma(ar, u2, Er[c]);
+                    Ei[c] = fma(ai, u2, Ei[c]);
+                    const double u3 = fma(Ab * g.x[c], u2, -u1[c]);
+                    Or[c] = fma(br, u3, Or[c]);
+                    Oi[c] = fma(bi, u3, Oi[c]);
+                    u0[c] = u2; u1[c] = u3;
+                }
+            }
+        };
+        int j = lo * kLiveRows;
+        const int jhi = hi * kLiveRows;
+        for (; j <= jhi && j + 8 <= len; j += 8) {
+            enter(j / kLiveRows);
+            rows8(j);
         }
-    }
-    for (; j < len; ++j) {
-        const double Aa = Am(j);
-        const double2 aa = am(j);
-        if (j & 1) {
+        for (; j + 8 <= len; j += 8) rows8(j);
+        if (j < len) {
+            enter(j / kLiveRows);
+            for (; j < len; ++j) {
+                const double Aa = Am[j], ar = am[2 * j], ai = am[2 * j + 1];
+                const bool odd = j & 1;
 #pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                const double u2 = fma(Aa * g.x[c], u1[c], -u0[c]);
-                Or[c] = fma(aa.x, u2, Or[c]);
-                Oi[c] = fma(aa.y, u2, Oi[c]);
-                u0[c] = u1[c]; u1[c] = u2;
-            }
-        } else {
-#pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                const double u2 = fma(Aa * g.x[c], u1[c], -u0[c]);
-                Er[c] = fma(aa.x, u2, Er[c]);
-                Ei[c] = fma(aa.y, u2, Ei[c]);
-                u0[c] = u1[c]; u1[c] = u2;
+                for (int c = 0; c < CH; ++c) {
+                    const double u2 = fma(Aa * g.x[c], u1[c], -u0[c]);
+                    if (odd) {
+                        Or[c] = fma(ar, u2, Or[c]);
+                        Oi[c] = fma(ai, u2, Oi[c]);
+                    } else {
+                        Er[c] = fma(ar, u2, Er[c]);
+                        Ei[c] = fma(ai, u2, Ei[c]);
+                    }
+                    u0[c] = u1[c]; u1[c] = u2;
+                }
             }
         }
     }
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-        const double f = final_scale(k[c]);
+        if (!full && i >= g.ilim[c]) continue;
         // Delta [m][ring]: consecutive lanes write consecutive rings
         if (g.rn[c] >= 0)
             delta[dbase + (long long)i * nrings + g.rn[c]] =
-                make_double2((Er[c] + Or[c]) * f, (Ei[c] + Oi[c]) * f);
+                make_double2(Er[c] + Or[c], Ei[c] + Oi[c]);
         if (g.rs[c] >= 0)
             delta[dbase + (long long)i * nrings + g.rs[c]] =
-                make_double2((Er[c] - Or[c]) * f, (Ei[c] - Oi[c]) * f);
+                make_double2(Er[c] - Or[c], Ei[c] - Oi[c]);
     }
 }
 
 template <int CH>
 __global__ __launch_bounds__(64) void k_legendre_fwd(
-    const PairDesc *__restrict__ pairs, int npairs, int pblocks,
-    const int *__restrict__ mval, const long long *__restrict__ moff,
-    const double *__restrict__ mu, int nm, int nmpairs, int lmax,
-    const double *__restrict__ A, const double2 *__restrict__ ap, long long nalm,
-    double2 *__restrict__ delta, int nrings, long long total)
+    const PairDesc *__restrict__ pairs, int npairs, LiveTab lt, int pblocks,
+    const int *__restrict__ mval, const long long *__restrict__ moff, int nm, int nmpairs,
+    int lmax, const double *__restrict__ A, const double2 *__restrict__ ap, long long nalm,
+    double2 *__restrict__ delta, int nrings, int nmaps, int full)
 {
-    const long long L = xcd_logical(blockIdx.x, total);
-    const int pb = (int)(L % pblocks);
-    const long long rest = L / pblocks;
-    const int q = (int)(rest % nmpairs);
-    const int b = (int)(rest / nmpairs);
-    const int lane = threadIdx.x;
+    // XCD x takes the m-pairs q = x mod 8, one after the other for all ring
+    // blocks of all maps: the waves that share an m-pair's coefficients run
+    // together on one L2, and since the live rows of an m-pair shrink with q
+    // (by half from q = 0 to the last), every XCD gets the same share of them.
+    const int x = (int)(blockIdx.x % 8);
+    const int w = (int)(blockIdx.x / 8);
+    const int pb = w % pblocks;
+    const int rest = w / pblocks;
+    const int b = rest % nmaps;
+    const int q = x + 8 * (rest / nmaps);
+    if (q >= nmpairs) return;
 
     Chains<CH> g;
-    double s[CH];
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        const int p = (pb * CH + c) * 64 + lane;
-        if (p < npairs) {
-            const PairDesc d = pairs[p];
-            g.x[c] = d.x; s[c] = d.s; g.rn[c] = d.rn; g.rs[c] = d.rs;
-        } else {
-            g.x[c] = 0.0; s[c] = 0.0; g.rn[c] = -1; g.rs[c] = -1;
-        }
-    }
+    load_chains(g, pairs, npairs, pb * CH);
     const double2 *apb = ap + (long long)b * nalm;
     const long long dbase = (long long)b * nrings * nm;
     for (int t = 0; t < 2; ++t) {
         const int i = (t == 0) ? q : nm - 1 - q;
         if (t == 1 && i == q) break;
-        fwd_one_m<CH, false>(g, s, mval[i], i, moff[i], mu[i], lmax, A, apb, delta, dbase, nrings);
+        fwd_one_m<CH>(g, lt, pb * CH, ((CIp)mval)[i], i, ((CLp)moff)[i], lmax, A, apb, delta,
+                      dbase, nrings, full != 0);
     }
 }
 
@@ -319,9 +340,9 @@ __global__ __launch_bounds__(64) void k_legendre_adj(
         const int p = (pb * CH + c) * 64 + lane;
         if (p < npairs) {
             const PairDesc d = pairs[p];
-            g.x[c] = d.x; s[c] = d.s; g.rn[c] = d.rn; g.rs[c] = d.rs;
+            g.x[c] = d.x; s[c] = d.s; g.rn[c] = d.rn; g.rs[c] = d.rs; g.ilim[c] = d.ilim;
         } else {
-            g.x[c] = 0.0; s[c] = 0.0; g.rn[c] = -1; g.rs[c] = -1;
+            g.x[c] = 0.0; s[c] = 0.0; g.rn[c] = -1; g.rs[c] = -1; g.ilim[c] = 0;
         }
     }
     const long long dtbase = (long long)b * nrings * nm;
@@ -403,31 +424,15 @@ __global__ __launch_bounds__(64) void k_legendre_fwd_batch(const BatchTile *__re
         const BatchTile tile = tiles[t];
         const BatchMap &bm = maps[tile.map];
         Chains<CH> g;
-        double s[CH];
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            const int p = (tile.pblock * CH + c) * 64 + lane;
-            if (p < bm.npairs) {
-                const PairDesc d = bm.pairs[p];
-                g.x[c] = d.x; s[c] = d.s; g.rn[c] = d.rn; g.rs[c] = d.rs;
-            } else {
-                g.x[c] = 0.0; s[c] = 0.0; g.rn[c] = -1; g.rs[c] = -1;
-            }
-        }
+        load_chains(g, bm.pairs, bm.npairs, tile.pblock * CH);
         const double2 *ap = reinterpret_cast<const double2 *>(ws + bm.ap_off);
         double2 *delta = reinterpret_cast<double2 *>(ws + bm.delta_off);
         const int q = tile.mpair;
-        // the plan's per-m tables are read through the constant address
-        // space (wave-uniform, never written here): scalar loads, so the
-        // offsets and with them every coefficient address stay uniform
-        typedef const int __attribute__((address_space(4))) *CIp;
-        typedef const long long __attribute__((address_space(4))) *CLp;
-        typedef const double __attribute__((address_space(4))) *CDp;
         for (int u = 0; u < 2; ++u) {
             const int i = (u == 0) ? q : bm.nm - 1 - q;
             if (u == 1 && i == q) break;
-            fwd_one_m<CH, true>(g, s, ((CIp)bm.mval)[i], i, ((CLp)bm.moff)[i], ((CDp)bm.mu)[i],
-                          bm.lmax, bm.A, ap, delta, 0, bm.nrings);
+            fwd_one_m<CH>(g, bm.live, tile.pblock * CH, ((CIp)bm.mval)[i], i, ((CLp)bm.moff)[i],
+                          bm.lmax, bm.A, ap, delta, 0, bm.nrings, false);
         }
     }
 }
@@ -457,12 +462,12 @@ int fwd_pblocks(const sht_plan_s *p)
 }
 int adj_pblocks(const sht_plan_s *p) { return (p->npairs + 64 * kAdjChains - 1) / (64 * kAdjChains); }
 
-hipError_t launch_legendre_fwd(const sht_plan_s *p, const double2 *ap, double2 *delta,
+hipError_t launch_legendre_fwd(const sht_plan_s *p, const double2 *ap, double2 *delta, bool full,
                                hipStream_t st)
 {
     const int pblocks = fwd_pblocks(p);
     const int nmpairs = (p->nm + 1) / 2;
-    const long long total = (long long)pblocks * nmpairs * p->nmaps;
+    const long long total = 8LL * ((nmpairs + 7) / 8) * pblocks * p->nmaps;
     if (total <= 0 || total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     auto kern = p->fwd_chains == 1   ? k_legendre_fwd<1>
                 : p->fwd_chains == 2 ? k_legendre_fwd<2>
@@ -470,8 +475,9 @@ hipError_t launch_legendre_fwd(const sht_plan_s *p, const double2 *ap, double2 *
                                      : nullptr;
     if (!kern) return hipErrorInvalidValue;
     hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(64), 0, st,
-                       p->d_pairs, p->npairs, pblocks, p->d_mval, p->d_moff, p->d_mu, p->nm,
-                       nmpairs, p->lmax, p->d_A, ap, p->nalm, delta, p->nrings, total);
+                       p->d_pairs, p->npairs, p->live, pblocks, p->d_mval, p->d_moff, p->nm,
+                       nmpairs, p->lmax, p->d_A, ap, p->nalm, delta, p->nrings, p->nmaps,
+                       full ? 1 : 0);
     return hipGetLastError();
 }
 

@@ -577,6 +577,11 @@ __device__ inline double2 load_mode(const DT *__restrict__ drow, long long dstri
     return (i >= 0) ? widen(drow[(long long)i * dstride]) : make_double2(0.0, 0.0);
 }
 
+// Modes of a ring: the Legendre stage of the plan leaves the m beyond the
+// ring's mlive out (they are dead there, live.hip), so its rings fold
+// m <= mlive (mfull < 0).  A caller's Delta has all of them: m <= mfull.
+__device__ inline int ring_mmax(const RingDesc &d, int mfull) { return mfull < 0 ? d.mlive : mfull; }
+
 // Synthesis: one workgroup per (ring of this size class, map).  LDS: the
 // spectrum / FFT buffer, the twiddle tables and the alias staging slots
 // (RingLds).
@@ -914,9 +919,12 @@ __device__ __attribute__((always_inline)) inline void load_fast(FastModes<NT, DT
 #pragma unroll
         for (int q = 0; q < QM; ++q) {
             const int m = tid + q * NT;
-            raw.v[q] = (m <= mmax) ? drow[(long long)m * dstride] : DT{};
-            // s_waitcnt vmcnt(0) expcnt(7) lgkmcnt(15)
-            if (q + 1 < QM) __builtin_amdgcn_s_waitcnt(0x0F70);
+            raw.v[q] = DT{};
+            if (q * NT <= mmax) {   // uniform: no round for the modes that are dead on the ring
+                if (m <= mmax) raw.v[q] = drow[(long long)m * dstride];
+                // s_waitcnt vmcnt(0) expcnt(7) lgkmcnt(15)
+                if (q + 1 < QM) __builtin_amdgcn_s_waitcnt(0x0F70);
+            }
         }
     } else {
         // every position lookup first, then the loads
@@ -929,7 +937,7 @@ __device__ __attribute__((always_inline)) inline void load_fast(FastModes<NT, DT
 #pragma unroll
         for (int q = 0; q < QM; ++q) {
             raw.v[q] = (pos[q] >= 0) ? drow[(long long)pos[q] * dstride] : DT{};
-            if (q + 1 < QM) __builtin_amdgcn_s_waitcnt(0x0F70);
+            if (q * NT <= mmax && q + 1 < QM) __builtin_amdgcn_s_waitcnt(0x0F70);
         }
     }
 }
@@ -952,6 +960,7 @@ __device__ __attribute__((always_inline)) inline void fold_fast(C *buf, const Ri
 #pragma unroll
     for (int q = 0; q < QM; ++q) {
         const int m = tid + q * NT;
+        if (q * NT > mmax) continue;
         if (m <= mmax) {
             double2 v = widen(raw.v[q]);
             if (m == 0) v.y = 0.0;
@@ -1094,9 +1103,12 @@ __device__ __attribute__((always_inline)) inline void load_fast2(
 #pragma unroll
         for (int q = 0; q < QM; ++q) {
             const int m = tid + q * NT;
-            raw.v[q] = (m <= mmax) ? *reinterpret_cast<const float4 *>(drow + (long long)m * dstride)
-                                   : make_float4(0.f, 0.f, 0.f, 0.f);
-            if (q + 1 < QM) __builtin_amdgcn_s_waitcnt(0x0F70);
+            raw.v[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (q * NT <= mmax) {
+                if (m <= mmax)
+                    raw.v[q] = *reinterpret_cast<const float4 *>(drow + (long long)m * dstride);
+                if (q + 1 < QM) __builtin_amdgcn_s_waitcnt(0x0F70);
+            }
         }
         return;
     }
@@ -1115,7 +1127,7 @@ __device__ __attribute__((always_inline)) inline void load_fast2(
             if (two) e1 = e[1];
         }
         raw.v[q] = make_float4(e0.x, e0.y, e1.x, e1.y);
-        if (q + 1 < QM) __builtin_amdgcn_s_waitcnt(0x0F70);
+        if (q * NT <= mmax && q + 1 < QM) __builtin_amdgcn_s_waitcnt(0x0F70);
     }
 }
 
@@ -1139,6 +1151,7 @@ __device__ __attribute__((always_inline)) inline void fold_fast2(float2 *X0, flo
 #pragma unroll
     for (int q = 0; q < QM; ++q) {
         const int m = tid + q * NT;
+        if (q * NT > mmax) continue;
         if (m <= mmax) {
             const float4 r = raw.v[q];
             double2 v0 = make_double2((double)r.x, (double)r.y);
@@ -1357,7 +1370,7 @@ __device__ __attribute__((always_inline)) inline void fft_fast2(float2 *X0, floa
 __global__ __launch_bounds__(kFastThreads, 2) void k_ring_synth_fast2(
     const int *__restrict__ ids, int count, int nmaps, const RingDesc *__restrict__ rings,
     const float2 *__restrict__ pool32, const float2 *__restrict__ delta,
-    const int *__restrict__ minv, int mcontig, int mmax, DeltaLayout dl,
+    const int *__restrict__ minv, int mcontig, DeltaLayout dl,
     double *__restrict__ map, long long npix, RingLds lds)
 {
     extern __shared__ double2 lds_raw[];
@@ -1378,8 +1391,8 @@ __global__ __launch_bounds__(kFastThreads, 2) void k_ring_synth_fast2(
     long long b = 2LL * pi;
     bool two = b + 1 < nmaps;
     FastModes2<kFastThreads> raw;
-    load_fast2<kFastThreads>(raw, delta + b * dl.map + r * dl.ring, dl.m, minv, mcontig, mmax,
-                             aligned, two);
+    load_fast2<kFastThreads>(raw, delta + b * dl.map + r * dl.ring, dl.m, minv, mcontig,
+                             rings[r].mlive, aligned, two);
     for (bool first = true;; first = false) {
         const RingDesc d = rings[r];
         double *out0 = map + b * npix + d.start;
@@ -1387,7 +1400,7 @@ __global__ __launch_bounds__(kFastThreads, 2) void k_ring_synth_fast2(
         const bool two_now = two;
         if (!first) __syncthreads();   // the previous ring's last pass has read X0, X1, T
         load_tw<kFastThreads>(T, pool32 + d.tw, d.n);
-        fold_fast2<kFastThreads>(X0, X1, d, raw, mmax);
+        fold_fast2<kFastThreads>(X0, X1, d, raw, d.mlive);
         const long long nx = it + per;
         if (nx < hi) {
             xcd_item<true>(nx, count, npairs, x, i, pi);
@@ -1395,7 +1408,7 @@ __global__ __launch_bounds__(kFastThreads, 2) void k_ring_synth_fast2(
             b = 2LL * pi;
             two = b + 1 < nmaps;
             load_fast2<kFastThreads>(raw, delta + b * dl.map + r * dl.ring, dl.m, minv, mcontig,
-                                     mmax, aligned, two);
+                                     rings[r].mlive, aligned, two);
         }
         fft_fast2(X0, X1, T, d, out0, out1, two_now);
         if (nx >= hi) break;
@@ -1426,7 +1439,7 @@ template <typename DT>
 __global__ __launch_bounds__(kFastThreads, FastPrec<DT>::kBlocks) void k_ring_synth_fast(
     const int *__restrict__ ids, int count, int nmaps, const RingDesc *__restrict__ rings,
     const double2 *__restrict__ pool, const DT *__restrict__ delta,
-    const int *__restrict__ minv, int mcontig, int mmax, DeltaLayout dl,
+    const int *__restrict__ minv, int mcontig, int mfull, DeltaLayout dl,
     double *__restrict__ map, long long npix, RingLds lds)
 {
     typedef typename FastPrec<DT>::C C;
@@ -1444,19 +1457,21 @@ __global__ __launch_bounds__(kFastThreads, FastPrec<DT>::kBlocks) void k_ring_sy
     long long b = bi;
     int r = ids[i];
     FastModes<kFastThreads, DT> raw;
-    load_fast<kFastThreads>(raw, delta + b * dl.map + r * dl.ring, dl.m, minv, mcontig, mmax);
+    load_fast<kFastThreads>(raw, delta + b * dl.map + r * dl.ring, dl.m, minv, mcontig,
+                            ring_mmax(rings[r], mfull));
     for (bool first = true;; first = false) {
         const RingDesc d = rings[r];
         double *out = map + b * npix + d.start;
         if (!first) __syncthreads();   // the previous ring's last pass has read buf and T
         load_tw<kFastThreads>(T, pool + d.tw, d.n);
-        fold_fast<kFastThreads>(buf, d, raw, mmax);
+        fold_fast<kFastThreads>(buf, d, raw, ring_mmax(d, mfull));
         const long long nx = it + per;
         if (nx < hi) {
             xcd_item<RingMajor<DT>::value>(nx, count, nmaps, x, i, bi);
             b = bi;
             r = ids[i];
-            load_fast<kFastThreads>(raw, delta + b * dl.map + r * dl.ring, dl.m, minv, mcontig, mmax);
+            load_fast<kFastThreads>(raw, delta + b * dl.map + r * dl.ring, dl.m, minv, mcontig,
+                            ring_mmax(rings[r], mfull));
         }
         fft_fast<kFastThreads, C>(buf, T, d, out);
         if (nx >= hi) break;
@@ -1474,7 +1489,7 @@ __global__ __launch_bounds__(kFastThreads, 2) void k_ring_synth_batch_fast(
     const RingDesc d = bm.rings[it.y];
     const double2 *delta = reinterpret_cast<const double2 *>(ws + bm.delta_off);
     synth_fast<kFastThreads, double2>(buf, buf + lds.fft_entries, d, bm.pool, delta + it.y,
-                                      bm.nrings, bm.minv, bm.mcontig, bm.mmax,
+                                      bm.nrings, bm.minv, bm.mcontig, d.mlive,
                                       outs[it.x] + d.start);
 }
 
@@ -1698,7 +1713,7 @@ __device__ __attribute__((always_inline)) inline void blue_dir(
 __global__ __launch_bounds__(kBlueThreads, 4) void k_ring_synth_blue(
     const int *__restrict__ ids, int count, int nmaps, const RingDesc *__restrict__ rings,
     const float2 *__restrict__ pool32, const float2 *__restrict__ delta,
-    const int *__restrict__ minv, int mcontig, int mmax, DeltaLayout dl,
+    const int *__restrict__ minv, int mcontig, DeltaLayout dl,
     double *__restrict__ map, long long npix, RingLds lds)
 {
     typedef float2 C;
@@ -1723,8 +1738,8 @@ __global__ __launch_bounds__(kBlueThreads, 4) void k_ring_synth_blue(
     long long b = 2LL * pi;
     bool two = b + 1 < nmaps;
     FastModes2<kBlueThreads> raw;
-    load_fast2<kBlueThreads>(raw, delta + b * dl.map + r * dl.ring, dl.m, minv, mcontig, mmax,
-                             aligned, two);
+    load_fast2<kBlueThreads>(raw, delta + b * dl.map + r * dl.ring, dl.m, minv, mcontig,
+                             rings[r].mlive, aligned, two);
     for (bool first = true;; first = false) {
         const RingDesc d = rings[r];
         BlueRing br;
@@ -1741,14 +1756,14 @@ __global__ __launch_bounds__(kBlueThreads, 4) void k_ring_synth_blue(
         FastModes<kBlueThreads, float2> one;
 #pragma unroll
         for (int q = 0; q < QM; ++q) one.v[q] = make_float2(raw.v[q].x, raw.v[q].y);
-        fold_fast<kBlueThreads>(X, d, one, mmax);
+        fold_fast<kBlueThreads>(X, d, one, d.mlive);
         blue_dir<-1, 1>(Xs, Ys, TW, TB, d, br, outA, 1);
         blue_dir<+1, 1>(Xs, Ys, TW, TB, d, br, outA, 1);
         if (twoB) {
 #pragma unroll
             for (int q = 0; q < QM; ++q) one.v[q] = make_float2(raw.v[q].z, raw.v[q].w);
             __syncthreads();   // the first map's last pass has read X and Y
-            fold_fast<kBlueThreads>(X, d, one, mmax);
+            fold_fast<kBlueThreads>(X, d, one, d.mlive);
         }
         const long long nx = it + per;
         if (nx < hi) {
@@ -1757,7 +1772,7 @@ __global__ __launch_bounds__(kBlueThreads, 4) void k_ring_synth_blue(
             b = 2LL * pi;
             two = b + 1 < nmaps;
             load_fast2<kBlueThreads>(raw, delta + b * dl.map + r * dl.ring, dl.m, minv, mcontig,
-                                     mmax, aligned, two);
+                                     rings[r].mlive, aligned, two);
         }
         if (twoB) {
             blue_dir<-1, 1>(Xs, Ys, TW, TB, d, br, outB, 1);
@@ -1772,7 +1787,7 @@ template <int NT, int MAXN, typename DT>
 __global__ __launch_bounds__(NT, 4) void k_ring_synth(
     const int *__restrict__ ids, int count, int nmaps, const RingDesc *__restrict__ rings,
     const double2 *__restrict__ pool, const DT *__restrict__ delta,
-    const int *__restrict__ minv, int mcontig, int mmax, DeltaLayout dl,
+    const int *__restrict__ minv, int mcontig, int mfull, DeltaLayout dl,
     double *__restrict__ map, long long npix, RingLds lds)
 {
     extern __shared__ double2 buf[];
@@ -1785,7 +1800,7 @@ __global__ __launch_bounds__(NT, 4) void k_ring_synth(
     const RingTables rt = {tw, tw + lds.tw_entries};
     synth_ring<NT, MAXN, false, false>(buf, rt, d,
                                pool, delta + b * dl.map + r * dl.ring, dl.m, minv,
-                               mcontig, mmax, map + b * npix + d.start);
+                               mcontig, ring_mmax(d, mfull), map + b * npix + d.start);
 }
 
 // Batched synthesis: work item (map, ring) of a batch of plans.
@@ -1803,7 +1818,7 @@ __global__ __launch_bounds__(NT, 4) void k_ring_synth_batch(
     const RingTables rt = {tw, tw + lds.tw_entries};
     synth_ring<NT, MAXN, false, true>(buf, rt, d,
                                 bm.pool, delta + it.y, bm.nrings, bm.minv, bm.mcontig,
-                                bm.mmax, outs[it.x] + d.start);
+                                d.mlive, outs[it.x] + d.start);
 }
 
 // Analysis (adjoint of the synthesis): G_k by a real DFT, then
@@ -1932,7 +1947,7 @@ hipError_t set_lds(const void *fn, size_t bytes)
 
 template <int NT, int MAXN, typename DT>
 hipError_t synth_class(const sht_plan_s *p, const RingClass &rc, const DT *delta, double *map,
-                       hipStream_t st)
+                       bool full, hipStream_t st)
 {
     if (rc.count == 0) return hipSuccess;
     const size_t lds = (size_t)rc.lds.total() * sizeof(double2);
@@ -1942,7 +1957,8 @@ hipError_t synth_class(const sht_plan_s *p, const RingClass &rc, const DT *delta
     if (items > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL((k_ring_synth<NT, MAXN, DT>), dim3((unsigned)items), dim3(NT), lds, st,
                        rc.d_ids, rc.count, p->nmaps, p->d_rings, p->d_pool, delta, p->d_minv,
-                       p->mcontig, p->mmax, delta_layout(p, delta), map, p->npix, rc.lds);
+                       p->mcontig, full ? p->mmax : -1, delta_layout(p, delta), map, p->npix,
+                       rc.lds);
     return hipGetLastError();
 }
 
@@ -1968,7 +1984,8 @@ hipError_t anal_class(const sht_plan_s *p, int c, const double *map, double2 *dt
 static_assert(kClassThreads[0] == 256 && kClassThreads[1] == 512 && kClassThreads[2] == 1024,
               "class thread counts must match the kernel instantiations");
 template <typename DT>
-hipError_t synth_fast_class(const sht_plan_s *p, const DT *delta, double *map, hipStream_t st)
+hipError_t synth_fast_class(const sht_plan_s *p, const DT *delta, double *map, bool full,
+                            hipStream_t st)
 {
     const RingClass &rc = p->scls[kFastClass];
     if (rc.count == 0) return hipSuccess;
@@ -1982,15 +1999,15 @@ hipError_t synth_fast_class(const sht_plan_s *p, const DT *delta, double *map, h
     grid = ((grid + 7) / 8) * 8;
     hipLaunchKernelGGL((k_ring_synth_fast<DT>), dim3((unsigned)grid), dim3(kFastThreads), lds,
                        st, rc.d_ids, rc.count, p->nmaps, p->d_rings, p->d_pool, delta,
-                       p->d_minv, p->mcontig, p->mmax, delta_layout(p, delta), map, p->npix,
-                       rc.lds);
+                       p->d_minv, p->mcontig, full ? p->mmax : -1, delta_layout(p, delta), map,
+                       p->npix, rc.lds);
     return hipGetLastError();
 }
 
 // complex64 Delta: two maps per workgroup, two workgroups per CU.
 template <>
 hipError_t synth_fast_class<float2>(const sht_plan_s *p, const float2 *delta, double *map,
-                                    hipStream_t st)
+                                    bool, hipStream_t st)
 {
     const RingClass &rc = p->scls[kFastClass];
     if (rc.count == 0) return hipSuccess;
@@ -2005,13 +2022,13 @@ hipError_t synth_fast_class<float2>(const sht_plan_s *p, const float2 *delta, do
     grid = ((grid + 7) / 8) * 8;
     hipLaunchKernelGGL(k_ring_synth_fast2, dim3((unsigned)grid), dim3(kFastThreads), lds, st,
                        rc.d_ids, rc.count, p->nmaps, p->d_rings, p->d_pool32, delta, p->d_minv,
-                       p->mcontig, p->mmax, delta_layout(p, delta), map, p->npix, rc.lds);
+                       p->mcontig, delta_layout(p, delta), map, p->npix, rc.lds);
     return hipGetLastError();
 }
 
 // The Bluestein fast path (complex64 Delta only): two 512-thread
 // workgroups per CU, persistent.
-hipError_t synth_blue_class(const sht_plan_s *p, const float2 *delta, double *map,
+hipError_t synth_blue_class(const sht_plan_s *p, const float2 *delta, double *map, bool,
                             hipStream_t st)
 {
     const RingClass &rc = p->scls[kBlueClass];
@@ -2026,18 +2043,18 @@ hipError_t synth_blue_class(const sht_plan_s *p, const float2 *delta, double *ma
     grid = ((grid + 7) / 8) * 8;
     hipLaunchKernelGGL(k_ring_synth_blue, dim3((unsigned)grid), dim3(kBlueThreads), lds, st,
                        rc.d_ids, rc.count, p->nmaps, p->d_rings, p->d_pool32, delta, p->d_minv,
-                       p->mcontig, p->mmax, delta_layout(p, delta), map, p->npix, rc.lds);
+                       p->mcontig, delta_layout(p, delta), map, p->npix, rc.lds);
     return hipGetLastError();
 }
 
 // complex128 Delta (FP64 plans have no ring in the class; a mixed-form plan
 // given a caller's complex128 Delta): the class's rings by size class.
-hipError_t synth_blue_class(const sht_plan_s *p, const double2 *delta, double *map,
+hipError_t synth_blue_class(const sht_plan_s *p, const double2 *delta, double *map, bool full,
                             hipStream_t st)
 {
-    hipError_t e = synth_class<1024, 8192, double2>(p, p->bcls[2], delta, map, st);
-    if (e == hipSuccess) e = synth_class<512, 4096, double2>(p, p->bcls[1], delta, map, st);
-    if (e == hipSuccess) e = synth_class<256, 2048, double2>(p, p->bcls[0], delta, map, st);
+    hipError_t e = synth_class<1024, 8192, double2>(p, p->bcls[2], delta, map, full, st);
+    if (e == hipSuccess) e = synth_class<512, 4096, double2>(p, p->bcls[1], delta, map, full, st);
+    if (e == hipSuccess) e = synth_class<256, 2048, double2>(p, p->bcls[0], delta, map, full, st);
     return e;
 }
 
@@ -2053,7 +2070,8 @@ hipError_t synth_blue_class(const sht_plan_s *p, const double2 *delta, double *m
 constexpr long long kForkItems = 4096;
 
 template <typename DT>
-static hipError_t ring_synth_dt(const sht_plan_s *p, const DT *delta, double *map, hipStream_t st)
+static hipError_t ring_synth_dt(const sht_plan_s *p, const DT *delta, double *map, bool full,
+                                hipStream_t st)
 {
     const long long fast = (long long)p->scls[kFastClass].count * p->nmaps;
     const long long rest = (long long)(p->scls[0].count + p->scls[1].count + p->scls[2].count +
@@ -2069,11 +2087,11 @@ static hipError_t ring_synth_dt(const sht_plan_s *p, const DT *delta, double *ma
         e = hipEventRecord(p->ev_fork, st);
         if (e == hipSuccess) e = hipStreamWaitEvent(p->aux_stream, p->ev_fork, 0);
     }
-    if (e == hipSuccess) e = synth_fast_class<DT>(p, delta, map, fork ? p->aux_stream : st);
-    if (e == hipSuccess) e = synth_blue_class(p, delta, map, st);
-    if (e == hipSuccess) e = synth_class<1024, 8192, DT>(p, p->scls[2], delta, map, st);
-    if (e == hipSuccess) e = synth_class<512, 4096, DT>(p, p->scls[1], delta, map, st);
-    if (e == hipSuccess) e = synth_class<256, 2048, DT>(p, p->scls[0], delta, map, st);
+    if (e == hipSuccess) e = synth_fast_class<DT>(p, delta, map, full, fork ? p->aux_stream : st);
+    if (e == hipSuccess) e = synth_blue_class(p, delta, map, full, st);
+    if (e == hipSuccess) e = synth_class<1024, 8192, DT>(p, p->scls[2], delta, map, full, st);
+    if (e == hipSuccess) e = synth_class<512, 4096, DT>(p, p->scls[1], delta, map, full, st);
+    if (e == hipSuccess) e = synth_class<256, 2048, DT>(p, p->scls[0], delta, map, full, st);
     if (fork) {
         // join even after a failed launch, so that `st` never runs ahead of
         // work already queued on the auxiliary stream
@@ -2084,16 +2102,16 @@ static hipError_t ring_synth_dt(const sht_plan_s *p, const DT *delta, double *ma
     return e;
 }
 
-hipError_t launch_ring_synth(const sht_plan_s *p, const double2 *delta, double *map,
+hipError_t launch_ring_synth(const sht_plan_s *p, const double2 *delta, double *map, bool full,
                              hipStream_t st)
 {
-    return ring_synth_dt(p, delta, map, st);
+    return ring_synth_dt(p, delta, map, full, st);
 }
 
 hipError_t launch_ring_synth(const sht_plan_s *p, const float2 *delta, double *map,
                              hipStream_t st)
 {
-    return ring_synth_dt(p, delta, map, st);
+    return ring_synth_dt(p, delta, map, false, st);
 }
 
 // Complex64 Delta widened to complex128 (the stage entry point's layout).

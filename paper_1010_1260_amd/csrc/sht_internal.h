@@ -36,7 +36,7 @@ struct RingDesc {
                       // (even- and odd-indexed inputs) and one radix-2 step; the
                       // chirp, nb and kernel spectrum are those of length clen / 2
     int np;           // synthesis fast path: number of Stockham passes (0: not on it)
-    int pad;
+    int mlive;        // greatest m with a live row on the ring (live.hip), -1 if none
     unsigned long long rads;  // their radices (16, 8, 4, 2, 7, 5, 3; product clen),
                               // 5 bits each, pass p at bits 5p..5p+4
 };
@@ -48,6 +48,23 @@ struct PairDesc {
     double s;     // sin(theta)
     int rn;       // ring index of the northern member
     int rs;       // ring index of the southern member, -1 if unpaired
+    int ilim;     // the m at positions >= ilim of the set are dead on the pair (live.hip)
+    int pad;
+};
+
+// Where the recurrence of every (m, ring pair) starts (live.hip): the P_lm of
+// an m grow from far below the smallest double, and the terms before a
+// pair's start row are too small to count.  Rows are l - m in units of
+// kLiveRows; a pair with no live row of an m has kNeverLive.
+constexpr int kLiveRows = 8;
+constexpr int kNeverLive = 0xffff;
+struct LiveTab {
+    const double2 *st;     // [nm][np] recurrence values (u_{j-2}, u_{j-1}) at start row j
+    const uint16_t *je;    // [nm][np] start row
+    const ushort2 *jr;     // [nm][np / 64] least and greatest start row of 64 pairs
+                           // (kNeverLive, 0 if none is live)
+    int np;                // ring pairs, rounded up to 64
+    int nb;                // np / 64
 };
 
 // Rings grouped by FFT length for the Fourier kernels (LDS and register
@@ -223,6 +240,7 @@ struct BatchMap {
     const int32_t *minv;
     const RingDesc *rings;
     const double2 *pool;
+    LiveTab live;
     long long nalm;
     long long ap_off;     // prescaled coefficients (double2 [nalm]) in the workspace
     long long delta_off;  // Delta (double2 [nm][nrings]) in the workspace
@@ -256,6 +274,7 @@ struct sht_plan_s {
     long long *d_moff;
     double *d_mu;        // mu_m for each m of the set (Eq. pmm)
     double *d_A;         // [nalm] normalised recurrence coefficient, see legendre.hip
+    sht::LiveTab live;   // recurrence start of every (m, ring pair)
     double *d_cn;        // [nalm] normalisation c_lm folded into the coefficients
     int32_t *d_minv;     // [mmax + 1] index of m in the set, -1 if absent
     long long *d_boff;   // [nm] first 32-step block of each m (split-BF16 operand packing)
@@ -303,9 +322,17 @@ namespace sht {
 // the entry point's own launches.
 inline void clear_stale_error() { (void)hipGetLastError(); }
 
+// Plan time (live.hip): fills the start table of the plan (d_pairs, d_mval,
+// d_moff, d_mu and d_A uploaded), the pairs' ilim and the rings' mlive.
+// `scratch`: nm doubles on the device, free again once `st` has drained;
+// `pmax`: the pair with the largest sin(theta).
+hipError_t launch_live_table(const sht_plan_s *p, double *scratch, int pmax, hipStream_t st);
+
 // Launchers (legendre.hip / ringfft.hip).  All enqueue on `st` only.
 hipError_t launch_prescale(const sht_plan_s *p, const double *alm, double2 *ap, hipStream_t st);
-hipError_t launch_legendre_fwd(const sht_plan_s *p, const double2 *ap, double2 *delta,
+// full: every Delta entry is written, also those of the m that are dead on a
+// ring, which the ring synthesis of the same plan does not read.
+hipError_t launch_legendre_fwd(const sht_plan_s *p, const double2 *ap, double2 *delta, bool full,
                                hipStream_t st);
 int fwd_pblocks(const sht_plan_s *p);
 hipError_t launch_legendre_adj_ws(const sht_plan_s *p, const double2 *dt, double2 *part,
@@ -326,7 +353,9 @@ hipError_t launch_prescale_f16x2(const sht_plan_s *p, const double *alm, void *B
                                  hipStream_t st);
 hipError_t launch_legendre_mfma_f16x2(const sht_plan_s *p, const void *Bb, float2 *delta,
                                       hipStream_t st);
-hipError_t launch_ring_synth(const sht_plan_s *p, const double2 *delta, double *map,
+// full: Delta is a caller's, with every mode of every ring; otherwise the plan's
+// Legendre stage wrote it and the modes dead on a ring are not read.
+hipError_t launch_ring_synth(const sht_plan_s *p, const double2 *delta, double *map, bool full,
                              hipStream_t st);
 hipError_t launch_ring_synth(const sht_plan_s *p, const float2 *delta, double *map,
                              hipStream_t st);

@@ -169,7 +169,9 @@ void free_tables(sht_plan_s *p)
 {
     void *ptrs[] = {p->d_pairs, p->d_mval, p->d_moff, p->d_mu, p->d_A, p->d_cn,
                     p->d_minv, p->d_rings, p->d_pool, p->d_boff, p->d_boff16, p->d_bm16,
-                    p->d_bm32, p->d_soff, p->d_sbm, p->d_Asb, p->d_pool32};
+                    p->d_bm32, p->d_soff, p->d_sbm, p->d_Asb, p->d_pool32,
+                    const_cast<double2 *>(p->live.st), const_cast<uint16_t *>(p->live.je),
+                    const_cast<ushort2 *>(p->live.jr)};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
     for (int c = 0; c < sht::kNumSynthClasses; ++c) {
@@ -187,6 +189,30 @@ void free_tables(sht_plan_s *p)
     p->d_pool = nullptr; p->d_boff = nullptr; p->d_boff16 = nullptr; p->d_bm16 = nullptr;
     p->d_bm32 = nullptr; p->d_soff = nullptr; p->d_sbm = nullptr; p->d_Asb = nullptr;
     p->d_pool32 = nullptr;
+    p->live = sht::LiveTab{};
+}
+
+// Device memory of the start table, then its kernels (live.hip).
+sht_status build_live_table(sht_plan_s *p, const std::vector<PairDesc> &pairs, size_t *acc)
+{
+    int pmax = 0;
+    for (int i = 1; i < p->npairs; ++i)
+        if (pairs[i].s > pairs[pmax].s) pmax = i;
+    sht::LiveTab &t = p->live;
+    t.nb = (p->npairs + 63) / 64;
+    t.np = 64 * t.nb;
+    const size_t n = (size_t)p->nm * (size_t)t.np, nj = (size_t)p->nm * (size_t)t.nb;
+    double *scratch = nullptr;
+    if (hipMalloc((void **)&t.st, n * sizeof *t.st) != hipSuccess) { t.st = nullptr; return SHT_ERR_OOM; }
+    if (hipMalloc((void **)&t.je, n * sizeof *t.je) != hipSuccess) { t.je = nullptr; return SHT_ERR_OOM; }
+    if (hipMalloc((void **)&t.jr, nj * sizeof *t.jr) != hipSuccess) { t.jr = nullptr; return SHT_ERR_OOM; }
+    if (hipMalloc((void **)&scratch, (size_t)p->nm * sizeof(double)) != hipSuccess)
+        return SHT_ERR_OOM;
+    *acc += n * (sizeof *t.st + sizeof *t.je) + nj * sizeof *t.jr;
+    const bool ok = sht::launch_live_table(p, scratch, pmax, nullptr) == hipSuccess &&
+                    hipDeviceSynchronize() == hipSuccess;
+    (void)hipFree(scratch);
+    return ok ? SHT_OK : SHT_ERR_HIP;
 }
 
 sht_status check_plan(sht_plan_t p)
@@ -294,9 +320,10 @@ struct PoolBuilder {
 static bool delta_f32(const sht_plan_s *p) { return p->precision != SHT_FP64; }
 
 // Prescale + Legendre stage of the forward transform into `delta` (complex64
-// for the mixed forms, complex128 for FP64).
+// for the mixed forms, complex128 for FP64).  full: for a caller of the
+// stage, who sees every entry.
 static sht_status legendre_stage(sht_plan_t p, const double *alm, void *ws, void *delta,
-                                 hipStream_t st, hipEvent_t ev_mid)
+                                 bool full, hipStream_t st, hipEvent_t ev_mid)
 {
     hipError_t e;
     float2 *d32 = (float2 *)delta;
@@ -316,7 +343,7 @@ static sht_status legendre_stage(sht_plan_t p, const double *alm, void *ws, void
         e = sht::launch_prescale(p, alm, (double2 *)ws, st);
         if (e == hipSuccess && ev_mid) e = hipEventRecord(ev_mid, st);
         if (e == hipSuccess)
-            e = sht::launch_legendre_fwd(p, (const double2 *)ws, (double2 *)delta, st);
+            e = sht::launch_legendre_fwd(p, (const double2 *)ws, (double2 *)delta, full, st);
     }
     return e == hipSuccess ? SHT_OK : SHT_ERR_HIP;
 }
@@ -325,7 +352,7 @@ static sht_status legendre_stage(sht_plan_t p, const double *alm, void *ws, void
 static hipError_t synth_stage(const sht_plan_s *p, const void *delta, double *map, hipStream_t st)
 {
     return delta_f32(p) ? sht::launch_ring_synth(p, (const float2 *)delta, map, st)
-                        : sht::launch_ring_synth(p, (const double2 *)delta, map, st);
+                        : sht::launch_ring_synth(p, (const double2 *)delta, map, false, st);
 }
 
 extern "C" {
@@ -524,11 +551,11 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
                 const int rs = it->second.back();
                 it->second.pop_back();
                 used[r] = used[rs] = 1;
-                pairs.push_back({d->cth[r], d->sth[r], r, rs});
+                pairs.push_back({d->cth[r], d->sth[r], r, rs, 0, 0});
             }
         }
         for (int r = 0; r < R; ++r)
-            if (!used[r]) pairs.push_back({d->cth[r], d->sth[r], r, -1});
+            if (!used[r]) pairs.push_back({d->cth[r], d->sth[r], r, -1, 0, 0});
     }
     p->npairs = (int)pairs.size();
 
@@ -634,6 +661,7 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
         if (st == SHT_OK) st = upload(&p->d_Asb, Asb, &tb);
     }
     if (st == SHT_OK) st = upload(&p->d_rings, rings, &tb);
+    if (st == SHT_OK) st = build_live_table(p, pairs, &tb);
     if (st == SHT_OK) st = upload(&p->d_pool, pb.pool, &tb);
     // longest rings first (tail balance); rings of equal length adjacent so
     // that consecutive workgroups, which the kernels place on one XCD, share
@@ -823,12 +851,12 @@ sht_status sht_alm2delta(sht_plan_t p, const double *alm, double *delta, void *w
     if (!alm || !delta) return SHT_ERR_INVALID_ARG;
     if (!delta_f32(p)) {
         if (!ws || ws_bytes < p->ws_ap_bytes) return SHT_ERR_WORKSPACE;
-        return legendre_stage(p, alm, ws, delta, (hipStream_t)stream, nullptr);
+        return legendre_stage(p, alm, ws, delta, true, (hipStream_t)stream, nullptr);
     }
     // mixed forms: complex64 Delta in the workspace, widened into the caller's buffer
     if (!ws || ws_bytes < fwd_workspace_bytes(p)) return SHT_ERR_WORKSPACE;
     float2 *d32 = (float2 *)((char *)ws + p->ws_ap_bytes);
-    s = legendre_stage(p, alm, ws, d32, (hipStream_t)stream, nullptr);
+    s = legendre_stage(p, alm, ws, d32, true, (hipStream_t)stream, nullptr);
     if (s == SHT_OK)
         s = from_hip(sht::launch_widen_delta(p, d32, (double2 *)delta, (hipStream_t)stream));
     return s;
@@ -839,7 +867,8 @@ sht_status sht_delta2map(sht_plan_t p, const double *delta, double *map, void *s
     sht_status s = check_plan(p);
     if (s != SHT_OK) return s;
     if (!delta || !map) return SHT_ERR_INVALID_ARG;
-    return from_hip(sht::launch_ring_synth(p, (const double2 *)delta, map, (hipStream_t)stream));
+    return from_hip(sht::launch_ring_synth(p, (const double2 *)delta, map, true,
+                                           (hipStream_t)stream));
 }
 
 }  // extern "C"
@@ -874,7 +903,7 @@ sht_status forward_transform(sht_plan_t p, const double *alm, double *map, void 
                              hipStream_t st)
 {
     void *delta = (char *)ws + p->ws_ap_bytes;
-    sht_status s = legendre_stage(p, alm, ws, delta, st, nullptr);
+    sht_status s = legendre_stage(p, alm, ws, delta, false, st, nullptr);
     if (s == SHT_OK) s = from_hip(synth_stage(p, delta, map, st));
     return s;
 }
@@ -988,7 +1017,7 @@ sht_status sht_alm2map_events(sht_plan_t p, const double *alm, double *map, void
     hipStream_t st = (hipStream_t)stream;
     void *delta = (char *)ws + p->ws_ap_bytes;
     s = from_hip(hipEventRecord((hipEvent_t)events[0], st));
-    if (s == SHT_OK) s = legendre_stage(p, alm, ws, delta, st, (hipEvent_t)events[1]);
+    if (s == SHT_OK) s = legendre_stage(p, alm, ws, delta, false, st, (hipEvent_t)events[1]);
     if (s == SHT_OK) s = from_hip(hipEventRecord((hipEvent_t)events[2], st));
     if (s == SHT_OK) s = from_hip(synth_stage(p, delta, map, st));
     if (s == SHT_OK) s = from_hip(hipEventRecord((hipEvent_t)events[3], st));
@@ -1047,7 +1076,7 @@ sht_status sht_map2alm(sht_plan_t p, const double *map, const double *ring_weigh
     if (s == SHT_OK) s = from_hip(sht::launch_legendre_adj_ws(p, dt, part, alm, st, false));
     // a <- a + D adjoint(w (s - alm2map(a)))
     for (int it = 0; it < niter && s == SHT_OK; ++it) {
-        s = legendre_stage(p, alm, ws, delta, st, nullptr);
+        s = legendre_stage(p, alm, ws, delta, false, st, nullptr);
         if (s == SHT_OK) s = from_hip(synth_stage(p, delta, tmp_map, st));
         if (s == SHT_OK)
             s = from_hip(sht::launch_residual(map, tmp_map, (long long)p->nmaps * p->npix, st));

@@ -1,0 +1,91 @@
+"""Start table of the recurrence: the terms it leaves out are below the
+rounding of every m's own sum, also where a plan sees an m only deep in its
+growing range (rings near a pole), and the ring stage that skips the dead
+modes agrees with the one that reads a whole Delta."""
+import sys
+
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle import ref
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def P():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1010_1260_amd as P
+    return P
+
+
+def _dev():
+    return torch.device("cuda", 0)
+
+
+def _say(*a):
+    print("[case]", *a, flush=True)
+    sys.stdout.flush()
+
+
+# rings from the pole only (every m small there), around the poles and the
+# equator, one ring, the pole itself (sin = 0), and whole grids; row counts
+# around multiples of 8, ring-pair counts around 64 and 128, gaps in the m-set
+CASES = [
+    ("cap", 512, np.arange(0, 24), 256, None),
+    ("cap pairs", 1000, np.r_[0:40, 1983:2023], 506, None),
+    ("mixed", 301, np.r_[0:10, 120:330], 128, np.r_[0, 1, 7, 8, 9, 150:290:3, 301]),
+    ("one", 257, np.array([3]), 64, None),
+    ("whole", 135, None, 65, None),
+    ("whole few m", 519, None, 33, np.array([2, 500, 518])),
+]
+
+
+def _geom(rings, nside):
+    g = W.healpix_geometry(nside)
+    return g if rings is None else g.subset(rings)
+
+
+@pytest.mark.parametrize("lmax,rings,nside", [(512, np.arange(0, 24), 256),
+                                              (1000, np.r_[0:40, 1983:2023], 506)])
+def test_m_that_only_grow_keep_their_relative_accuracy(P, lmax, rings, nside):
+    """Rings around the poles only: the m above 2 l_max sin(theta_max) never
+    leave their growing range there, where all errors are relative (seed
+    sin^m: m roundings, then at most 3 per step; both sides), although their
+    Delta lies down to 2^-250 below the other m's."""
+    _say("growing m", lmax, nside)
+    g = _geom(rings, nside)
+    a = W.random_alm(lmax, [803, lmax], spectrum="flat")
+    plan = P.Plan(lmax, g)
+    d = plan.alm2delta(torch.from_numpy(a).to(_dev()).reshape(1, -1)).cpu().numpy()[0]   # [m][ring]
+    # |a_lm| P_lm in place of a_lm P_lm: the scale of each m's rounding errors
+    e = ref.delta(lmax, None, g.cth, g.sth, a).T
+    t = ref.delta(lmax, None, np.abs(g.cth), g.sth, np.abs(a) + 0j).T
+    m0 = int(2 * lmax * g.sth.max()) + 1
+    ms = np.arange(m0, lmax + 1)
+    top = np.abs(t).max(axis=1)[m0:]
+    err = np.abs(d - e).max(axis=1)[m0:]
+    seen = top > 2.0 ** -250
+    assert seen.sum() > 20
+    assert np.all(err[seen] <= (8 * (lmax + ms[seen]) * 2.0 ** -53) * top[seen])
+
+
+@pytest.mark.parametrize("prec,tol", [("fp64", 1e-13), ("f16x2_mfma", 1e-6)])
+@pytest.mark.parametrize("name,lmax,rings,nside,mval", CASES, ids=[c[0] for c in CASES])
+def test_whole_and_stagewise_agree(P, prec, tol, name, lmax, rings, nside, mval):
+    """alm2map (dead modes left out) against delta2map of the whole Delta,
+    on buffers that hold NaN beforehand."""
+    _say("whole vs stagewise", prec, name)
+    g = _geom(rings, nside)
+    a = torch.from_numpy(np.stack([W.random_alm(lmax, [802, i], mval=mval) for i in range(3)]))
+    plan = P.Plan(lmax, g, mval=mval, nmaps=3, precision=prec)
+    plan.workspace().view(torch.float64)[: plan.workspace_bytes // 8].fill_(float("nan"))
+    out = torch.zeros((3, plan.npix), dtype=torch.float64, device=_dev())
+    m1 = plan.alm2map(a.to(_dev()), out=out).cpu().numpy()
+    d = plan.alm2delta(a.to(_dev()))
+    m2 = plan.delta2map(d).cpu().numpy()
+    assert np.all(np.isfinite(m1))
+    assert np.linalg.norm(m1 - m2) <= tol * np.linalg.norm(m2)
