@@ -78,18 +78,64 @@ typedef const int __attribute__((address_space(4))) *CIp;
 typedef const long long __attribute__((address_space(4))) *CLp;
 typedef const double __attribute__((address_space(4))) *CDp;
 
-// One m of an m-pair for CH chains per lane: forward accumulation.
-// full: write the Delta of every ring, also of the m that are dead on it
-// (the ring stage reads the positions below ilim only).
-template <int CH>
+// The coefficients of KR rows of one m in scalar registers: A_l, and a'_lm of
+// the wave's NB maps.
+// (Vector-typed loads of 8-byte alignment: one s_load per 64 bytes.)
+typedef double d2a __attribute__((ext_vector_type(2), aligned(8)));
+typedef double d4a __attribute__((ext_vector_type(4), aligned(8)));
+typedef double d8a __attribute__((ext_vector_type(8), aligned(8)));
+
+template <int KR, int NB>
+struct CoefRows {
+    double A[KR], a[2 * KR * NB];   // a: [row][map][re, im]
+
+    template <int N>
+    __device__ static inline void get(double *d, CDp p)
+    {
+        if constexpr (N >= 8) {
+            const d8a v = *(const d8a __attribute__((address_space(4))) *)p;
+#pragma unroll
+            for (int t = 0; t < 8; ++t) d[t] = v[t];
+            if constexpr (N > 8) get<N - 8>(d + 8, p + 8);
+        } else if constexpr (N >= 4) {
+            const d4a v = *(const d4a __attribute__((address_space(4))) *)p;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) d[t] = v[t];
+            if constexpr (N > 4) get<N - 4>(d + 4, p + 4);
+        } else {
+            const d2a v = *(const d2a __attribute__((address_space(4))) *)p;
+            d[0] = v[0];
+            d[1] = v[1];
+        }
+    }
+    __device__ inline void load(CDp Am, CDp am, int j)
+    {
+        get<KR>(A, Am + j);
+        get<2 * KR * NB>(a, am + 2 * NB * j);
+    }
+    __device__ double re(int t, int b) const { return a[2 * (t * NB + b)]; }
+    __device__ double im(int t, int b) const { return a[2 * (t * NB + b) + 1]; }
+};
+
+// One m of an m-pair for CH chains per lane and NB maps: forward accumulation.
+// The recurrence of a chain is shared by the maps: 2 + 2 NB FP64 instructions
+// per (l, m, pair).  ap: the maps' a'_lm, [lm][map].  full: write the Delta of
+// every ring, also of the m that are dead on it (the ring stage reads the
+// positions below ilim only).
+//
+// The rows' coefficients come in scalar loads, a chunk of KR rows ahead of
+// their use: scalar loads return out of order, so a chunk is waited for as a
+// whole, just before the next one is asked for.
+template <int CH, int NB>
 __device__ inline void fwd_one_m(const Chains<CH> &g, const LiveTab &lt, int blk0, int m, int i,
                                  long long off, int lmax, const double *__restrict__ A,
                                  const double2 *__restrict__ ap, double2 *__restrict__ delta,
-                                 long long dbase, int nrings, bool full)
+                                 long long dbase, long long dmap, int nrings, bool full)
 {
+    constexpr int KR = NB == 1 ? 4 : 2;   // two chunks fit the scalar registers
     const int len = lmax - m + 1;
     const CDp Am = (CDp)(A + off);
-    const CDp am = (CDp)(ap + off);   // a'_lm as (re, im) pairs
+    const CDp am = (CDp)(ap + off * NB);   // (re, im) pairs
     // rows [8 lo, 8 hi]: where this wave's pairs start
     int lo = kNeverLive, hi = 0;
     {
@@ -102,9 +148,13 @@ __device__ inline void fwd_one_m(const Chains<CH> &g, const LiveTab &lt, int blk
                 hi = max(hi, (int)((unsigned)v >> 16));
             }
     }
-    double Er[CH], Ei[CH], Or[CH], Oi[CH];
+    double Er[CH][NB], Ei[CH][NB], Or[CH][NB], Oi[CH][NB];
 #pragma unroll
-    for (int c = 0; c < CH; ++c) { Er[c] = 0.0; Ei[c] = 0.0; Or[c] = 0.0; Oi[c] = 0.0; }
+    for (int c = 0; c < CH; ++c)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            Er[c][b] = 0.0; Ei[c][b] = 0.0; Or[c][b] = 0.0; Oi[c][b] = 0.0;
+        }
     if (lo != kNeverLive) {
         double u0[CH], u1[CH], s0[CH], s1[CH];
         int je[CH];
@@ -128,47 +178,78 @@ __device__ inline void fwd_one_m(const Chains<CH> &g, const LiveTab &lt, int blk
                 u1[c] = on ? s1[c] : u1[c];
             }
         };
-        auto rows8 = [&](int j) {
+        auto rows = [&](const CoefRows<KR, NB> &r) {
 #pragma unroll
-            for (int t = 0; t < 8; t += 2) {
-                const double Aa = Am[j + t], Ab = Am[j + t + 1];
-                const double ar = am[2 * (j + t)], ai = am[2 * (j + t) + 1];
-                const double br = am[2 * (j + t) + 2], bi = am[2 * (j + t) + 3];
+            for (int t = 0; t < KR; t += 2) {
 #pragma unroll
                 for (int c = 0; c < CH; ++c) {
-                    const double u2 = fma(Aa * g.x[c], u1[c], -u0[c]);
-                    Er[c] = fma(ar, u2, Er[c]);
-                    Ei[c] = fma(ai, u2, Ei[c]);
-                    const double u3 = fma(Ab * g.x[c], u2, -u1[c]);
-                    Or[c] = fma(br, u3, Or[c]);
-                    Oi[c] = fma(bi, u3, Oi[c]);
+                    const double u2 = fma(r.A[t] * g.x[c], u1[c], -u0[c]);
+                    const double u3 = fma(r.A[t + 1] * g.x[c], u2, -u1[c]);
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+                        Er[c][b] = fma(r.re(t, b), u2, Er[c][b]);
+                        Ei[c][b] = fma(r.im(t, b), u2, Ei[c][b]);
+                        Or[c][b] = fma(r.re(t + 1, b), u3, Or[c][b]);
+                        Oi[c][b] = fma(r.im(t + 1, b), u3, Oi[c][b]);
+                    }
                     u0[c] = u2; u1[c] = u3;
                 }
             }
         };
         int j = lo * kLiveRows;
         const int jhi = hi * kLiveRows;
-        for (; j <= jhi && j + 8 <= len; j += 8) {
-            enter(j / kLiveRows);
-            rows8(j);
+        if (j + 8 <= len) {
+            CoefRows<KR, NB> ca, cb;
+            ca.load(Am, am, j);
+            // s_waitcnt lgkmcnt(0), and nothing moves across
+            auto arrived = [] {
+                __builtin_amdgcn_sched_barrier(0);
+                __builtin_amdgcn_s_waitcnt(0xC07F);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            auto rows8 = [&](int jn) {   // rows j..j + 7; jn: the rows wanted next
+#pragma unroll
+                for (int t = 0; t < 8; t += 2 * KR) {
+                    arrived();
+                    cb.load(Am, am, j + t + KR);
+                    __builtin_amdgcn_sched_barrier(0);
+                    rows(ca);
+                    arrived();
+                    ca.load(Am, am, t + 2 * KR < 8 ? j + t + 2 * KR : jn);
+                    __builtin_amdgcn_sched_barrier(0);
+                    rows(cb);
+                }
+            };
+            // the last chunk's look-ahead stays inside the m
+            for (; j <= jhi && j + 8 <= len; j += 8) {
+                enter(j / kLiveRows);
+                rows8(min(j + 8, len - KR));
+            }
+            for (; j + 8 <= len; j += 8) rows8(min(j + 8, len - KR));
         }
-        for (; j + 8 <= len; j += 8) rows8(j);
         if (j < len) {
             enter(j / kLiveRows);
             for (; j < len; ++j) {
-                const double Aa = Am[j], ar = am[2 * j], ai = am[2 * j + 1];
+                const double Aa = Am[j];
                 const bool odd = j & 1;
 #pragma unroll
                 for (int c = 0; c < CH; ++c) {
                     const double u2 = fma(Aa * g.x[c], u1[c], -u0[c]);
-                    if (odd) {
-                        Or[c] = fma(ar, u2, Or[c]);
-                        Oi[c] = fma(ai, u2, Oi[c]);
-                    } else {
-                        Er[c] = fma(ar, u2, Er[c]);
-                        Ei[c] = fma(ai, u2, Ei[c]);
-                    }
                     u0[c] = u1[c]; u1[c] = u2;
+                }
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    const double ar = am[2 * (j * NB + b)], ai = am[2 * (j * NB + b) + 1];
+#pragma unroll
+                    for (int c = 0; c < CH; ++c) {
+                        if (odd) {
+                            Or[c][b] = fma(ar, u1[c], Or[c][b]);
+                            Oi[c][b] = fma(ai, u1[c], Oi[c][b]);
+                        } else {
+                            Er[c][b] = fma(ar, u1[c], Er[c][b]);
+                            Ei[c][b] = fma(ai, u1[c], Ei[c][b]);
+                        }
+                    }
                 }
             }
         }
@@ -176,13 +257,15 @@ __device__ inline void fwd_one_m(const Chains<CH> &g, const LiveTab &lt, int blk
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
         if (!full && i >= g.ilim[c]) continue;
-        // Delta [m][ring]: consecutive lanes write consecutive rings
-        if (g.rn[c] >= 0)
-            delta[dbase + (long long)i * nrings + g.rn[c]] =
-                make_double2(Er[c] + Or[c], Ei[c] + Oi[c]);
-        if (g.rs[c] >= 0)
-            delta[dbase + (long long)i * nrings + g.rs[c]] =
-                make_double2(Er[c] - Or[c], Ei[c] - Oi[c]);
+        double2 *row = delta + dbase + (long long)i * nrings;
+#pragma unroll
+        for (int b = 0; b < NB; ++b, row += dmap) {
+            // Delta [m][ring]: consecutive lanes write consecutive rings
+            if (g.rn[c] >= 0)
+                row[g.rn[c]] = make_double2(Er[c][b] + Or[c][b], Ei[c][b] + Oi[c][b]);
+            if (g.rs[c] >= 0)
+                row[g.rs[c]] = make_double2(Er[c][b] - Or[c][b], Ei[c][b] - Oi[c][b]);
+        }
     }
 }
 
@@ -212,8 +295,8 @@ __global__ __launch_bounds__(64) void k_legendre_fwd(
     for (int t = 0; t < 2; ++t) {
         const int i = (t == 0) ? q : nm - 1 - q;
         if (t == 1 && i == q) break;
-        fwd_one_m<CH>(g, lt, pb * CH, ((CIp)mval)[i], i, ((CLp)moff)[i], lmax, A, apb, delta,
-                      dbase, nrings, full != 0);
+        fwd_one_m<CH, 1>(g, lt, pb * CH, ((CIp)mval)[i], i, ((CLp)moff)[i], lmax, A, apb, delta,
+                         dbase, 0, nrings, full != 0);
     }
 }
 
@@ -431,8 +514,8 @@ __global__ __launch_bounds__(64) void k_legendre_fwd_batch(const BatchTile *__re
         for (int u = 0; u < 2; ++u) {
             const int i = (u == 0) ? q : bm.nm - 1 - q;
             if (u == 1 && i == q) break;
-            fwd_one_m<CH>(g, bm.live, tile.pblock * CH, ((CIp)bm.mval)[i], i, ((CLp)bm.moff)[i],
-                          bm.lmax, bm.A, ap, delta, 0, bm.nrings, false);
+            fwd_one_m<CH, 1>(g, bm.live, tile.pblock * CH, ((CIp)bm.mval)[i], i,
+                             ((CLp)bm.moff)[i], bm.lmax, bm.A, ap, delta, 0, 0, bm.nrings, false);
         }
     }
 }
