@@ -13,38 +13,56 @@
 // by a prescale kernel.  The seeds are P_mm = mu_m sin^m(theta) (Eq. pmm,
 // exponent m/2 on 1-x^2) and P_{m+1,m} = sqrt(2m+3) x P_mm (Eq. pm1m).
 //
-// Rescaling (Sec. 2.2.2).  A lane carries (v, k) with value v 2^(512 k),
-// k <= 0.  Every 8 steps, if |v| > 2^512, both recurrence values and the
-// accumulators are multiplied by 2^-512 (exact) and k grows by one.  The
-// accumulators therefore always hold sum a' u 2^(512 (k_l - k)), and the
-// result is acc * 2^(512 k): 1 for k = 0, 2^-512 for k = -1, 0 below.
+// Start.  The values of an m are negligible up to l ~ m / sin(theta); every
+// (m, ring pair) starts at the row of the plan's start table (live.hip) from
+// true FP64 values, so the forward kernels neither rescale nor touch the terms
+// before it.  (The adjoint still carries scaled values (v, k), value
+// v 2^(512 k), k <= 0, rescaled every 16 steps, Sec. 2.2.2.)
 //
 // Mapping to CDNA4.  One wavefront owns 64*CH ring pairs (CH chains per
-// lane); the north/south rings of a pair share the recurrence through the
-// parity P_lm(-x) = (-1)^(l+m) P_lm(x): even l-m terms go to E, odd to O,
-// Delta_N = E + O, Delta_S = E - O.  (l, m) is uniform across the wave, so
-// A_l and a'_lm are read with scalar loads into SGPRs and fed straight into
-// the FP64 VALU ops: 4 VALU instructions per (l, m, chain) and no LDS.
+// lane) and NB maps; the north/south rings of a pair share the recurrence
+// through the parity P_lm(-x) = (-1)^(l+m) P_lm(x): even l-m terms go to E,
+// odd to O, Delta_N = E + O, Delta_S = E - O; the maps share it too.  (l, m)
+// is uniform across the wave, so A_l and a'_lm are read with scalar loads
+// into SGPRs, a chunk of rows ahead, and fed straight into the FP64 VALU ops:
+// 2 + 2 NB VALU instructions per (l, m, chain) and no LDS.
 // A wave processes the m-pair (m_i, m_{nm-1-i}) whose lengths sum to a
-// constant, which balances the triangular work.  Block ids are remapped so
-// that the waves sharing an m-pair run on the same XCD (same L2).
+// constant, which balances the triangular work.
+//
+// Bound: FP64 VALU issue.  l_max 4096 / nside 2048, one map: 1.6e9 wave
+// instructions, 2.6 ms at 2.4 GHz (the card runs this kernel near 2.0 GHz),
+// measured 3.84 ms; 4.32 ms with the rows' loads just before their use, 5.63 ms
+// with rescaled chains over all rows.  8 maps at l_max 1024 / nside 512 with
+// prescale: 432 us in fours, 578 us one by one.
+#include <type_traits>
+
 #include "recurrence.h"
 #include "sht_internal.h"
 
 namespace sht {
 namespace {
 
-__global__ void k_prescale(const double2 *__restrict__ alm, const double *__restrict__ cn,
-                           double2 *__restrict__ ap, long long nalm, long long m0len)
+// a'_lm = c_lm a_lm of NB maps, interleaved [lm][map] for the waves that take
+// the NB maps together.
+template <int NB>
+__global__ __launch_bounds__(256) void k_prescale(const double2 *__restrict__ alm,
+                                                  const double *__restrict__ cn,
+                                                  double2 *__restrict__ ap, long long nalm,
+                                                  long long m0len)
 {
     const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long b = blockIdx.y;
+    const long long g = (long long)blockIdx.y * NB;
     if (e >= nalm) return;
-    double2 a = alm[b * nalm + e];
     const double c = cn[e];
-    a.x *= c;
-    a.y = (e < m0len) ? 0.0 : a.y * c;
-    ap[b * nalm + e] = a;
+    double2 a[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) a[b] = alm[(g + b) * nalm + e];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        a[b].x *= c;
+        a[b].y = (e < m0len) ? 0.0 : a[b].y * c;
+        ap[g * nalm + e * NB + b] = a[b];
+    }
 }
 
 template <int CH>
@@ -269,12 +287,13 @@ __device__ inline void fwd_one_m(const Chains<CH> &g, const LiveTab &lt, int blk
     }
 }
 
-template <int CH>
+// groups of NB maps from the first map of ap and delta on
+template <int CH, int NB>
 __global__ __launch_bounds__(64) void k_legendre_fwd(
     const PairDesc *__restrict__ pairs, int npairs, LiveTab lt, int pblocks,
     const int *__restrict__ mval, const long long *__restrict__ moff, int nm, int nmpairs,
     int lmax, const double *__restrict__ A, const double2 *__restrict__ ap, long long nalm,
-    double2 *__restrict__ delta, int nrings, int nmaps, int full)
+    double2 *__restrict__ delta, int nrings, int ngroups, int full)
 {
     // XCD x takes the m-pairs q = x mod 8, one after the other for all ring
     // blocks of all maps: the waves that share an m-pair's coefficients run
@@ -284,19 +303,19 @@ __global__ __launch_bounds__(64) void k_legendre_fwd(
     const int w = (int)(blockIdx.x / 8);
     const int pb = w % pblocks;
     const int rest = w / pblocks;
-    const int b = rest % nmaps;
-    const int q = x + 8 * (rest / nmaps);
+    const long long b = (long long)(rest % ngroups) * NB;
+    const int q = x + 8 * (rest / ngroups);
     if (q >= nmpairs) return;
 
     Chains<CH> g;
     load_chains(g, pairs, npairs, pb * CH);
-    const double2 *apb = ap + (long long)b * nalm;
-    const long long dbase = (long long)b * nrings * nm;
+    const double2 *apb = ap + b * nalm;
+    const long long dmap = (long long)nrings * nm;
     for (int t = 0; t < 2; ++t) {
         const int i = (t == 0) ? q : nm - 1 - q;
         if (t == 1 && i == q) break;
-        fwd_one_m<CH, 1>(g, lt, pb * CH, ((CIp)mval)[i], i, ((CLp)moff)[i], lmax, A, apb, delta,
-                         dbase, 0, nrings, full != 0);
+        fwd_one_m<CH, NB>(g, lt, pb * CH, ((CIp)mval)[i], i, ((CLp)moff)[i], lmax, A, apb, delta,
+                          b * dmap, dmap, nrings, full != 0);
     }
 }
 
@@ -529,13 +548,36 @@ constexpr int kAdjChains = 4;
 
 }  // namespace
 
+// Calls f(first map, groups, std::integral_constant of the group size) for
+// the plan's maps in groups of p->fwd_group, and for the maps left over.
+template <typename F>
+static hipError_t for_map_groups(const sht_plan_s *p, const F &f)
+{
+    auto one = [&](int first, int groups, int nb) {
+        switch (nb) {
+        case 1: return f(first, groups, std::integral_constant<int, 1>());
+        case 2: return f(first, groups, std::integral_constant<int, 2>());
+        case 3: return f(first, groups, std::integral_constant<int, 3>());
+        case 4: return f(first, groups, std::integral_constant<int, 4>());
+        default: return hipErrorInvalidValue;
+        }
+    };
+    const int nb = p->fwd_group, groups = p->nmaps / nb, rest = p->nmaps - groups * nb;
+    hipError_t e = one(0, groups, nb);
+    if (e == hipSuccess && rest > 0) e = one(groups * nb, 1, rest);
+    return e;
+}
+
 hipError_t launch_prescale(const sht_plan_s *p, const double *alm, double2 *ap, hipStream_t st)
 {
     const long long m0len = (p->mval[0] == 0) ? (p->lmax + 1) : 0;
-    dim3 grid((unsigned)((p->nalm + 255) / 256), (unsigned)p->nmaps);
-    hipLaunchKernelGGL(k_prescale, grid, dim3(256), 0, st,
-                       reinterpret_cast<const double2 *>(alm), p->d_cn, ap, p->nalm, m0len);
-    return hipGetLastError();
+    return for_map_groups(p, [&](int first, int groups, auto nb) {
+        dim3 grid((unsigned)((p->nalm + 255) / 256), (unsigned)groups);
+        hipLaunchKernelGGL(k_prescale<decltype(nb)::value>, grid, dim3(256), 0, st,
+                           reinterpret_cast<const double2 *>(alm) + first * p->nalm, p->d_cn,
+                           ap + first * p->nalm, p->nalm, m0len);
+        return hipGetLastError();
+    });
 }
 
 int fwd_pblocks(const sht_plan_s *p)
@@ -545,23 +587,32 @@ int fwd_pblocks(const sht_plan_s *p)
 }
 int adj_pblocks(const sht_plan_s *p) { return (p->npairs + 64 * kAdjChains - 1) / (64 * kAdjChains); }
 
+template <int NB>
+static auto fwd_kernel(int chains) -> decltype(&k_legendre_fwd<1, NB>)
+{
+    return chains == 1   ? k_legendre_fwd<1, NB>
+           : chains == 2 ? k_legendre_fwd<2, NB>
+           : chains == 4 ? k_legendre_fwd<4, NB>
+                         : nullptr;
+}
+
 hipError_t launch_legendre_fwd(const sht_plan_s *p, const double2 *ap, double2 *delta, bool full,
                                hipStream_t st)
 {
     const int pblocks = fwd_pblocks(p);
     const int nmpairs = (p->nm + 1) / 2;
-    const long long total = 8LL * ((nmpairs + 7) / 8) * pblocks * p->nmaps;
-    if (total <= 0 || total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    auto kern = p->fwd_chains == 1   ? k_legendre_fwd<1>
-                : p->fwd_chains == 2 ? k_legendre_fwd<2>
-                : p->fwd_chains == 4 ? k_legendre_fwd<4>
-                                     : nullptr;
-    if (!kern) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(64), 0, st,
-                       p->d_pairs, p->npairs, p->live, pblocks, p->d_mval, p->d_moff, p->nm,
-                       nmpairs, p->lmax, p->d_A, ap, p->nalm, delta, p->nrings, p->nmaps,
-                       full ? 1 : 0);
-    return hipGetLastError();
+    return for_map_groups(p, [&](int first, int groups, auto nb) {
+        const long long total = 8LL * ((nmpairs + 7) / 8) * pblocks * groups;
+        if (total <= 0 || total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+        const auto kern = fwd_kernel<decltype(nb)::value>(p->fwd_chains);
+        if (!kern) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(64), 0, st, p->d_pairs, p->npairs,
+                           p->live, pblocks, p->d_mval, p->d_moff, p->nm, nmpairs, p->lmax, p->d_A,
+                           ap + first * p->nalm, p->nalm,
+                           delta + (long long)first * p->nrings * p->nm, p->nrings, groups,
+                           full ? 1 : 0);
+        return hipGetLastError();
+    });
 }
 
 size_t adj_part_bytes(const sht_plan_s *p)

@@ -303,6 +303,7 @@ struct sht_plan_s {
     sht::RingClass bcls[sht::kNumRingClasses];
     std::vector<int> ring_sclass;  // synthesis class of each ring
     int fwd_chains;      // ring pairs per lane of the FP64 forward Legendre kernel (1, 2, 4)
+    int fwd_group;       // maps that a wave of it takes together (1..4)
     int num_cus;         // compute units of the plan's device
     size_t ws_ap_bytes;  // workspace: prescaled coefficients
     // the fast-path synthesis of large plans runs on aux_stream beside the

@@ -141,13 +141,51 @@ constexpr ChainRule kFwdChainTable[] = {
     {1e300, 2},
 };
 
+double fwd_waves_per_cu(const sht_plan_s *p)
+{
+    return (double)((p->npairs + 63) / 64) * (double)((p->nm + 1) / 2) * (double)p->nmaps /
+           (double)std::max(1, p->num_cus);
+}
+
 int default_fwd_chains(const sht_plan_s *p)
 {
-    const double waves1 = (double)((p->npairs + 63) / 64) * (double)((p->nm + 1) / 2) *
-                          (double)p->nmaps / (double)std::max(1, p->num_cus);
+    const double waves1 = fwd_waves_per_cu(p);
     for (const ChainRule &r : kFwdChainTable)
         if (waves1 <= r.max_waves_per_cu) return r.chains;
     return 2;
+}
+
+// Maps that a wave of the FP64 forward kernel takes together, sharing the
+// recurrence: 2 + 2 n FP64 instructions per (l, m, pair) for n maps instead of
+// 4 n.  It pays once the waves that are left fill the chip; with fewer, the
+// wait for the longer rows of coefficients shows.  Same key as above (waves
+// per CU at one pair per lane and one map per wave).  Measured, Legendre
+// stage with prescale, two pairs per lane: key 32 (l_max 512 / nside 256, 4
+// maps) 61 us alone, 84 in pairs; key 64 (8 maps) 99 alone, 90 in pairs, 96
+// in fours; key 128 (l_max 1024 / nside 512, 4 maps) 304, 288, 228; key 256 (8
+// maps) 578, 495, 432.  The switches sit between measured points.
+struct GroupRule {
+    double max_waves_per_cu;
+    int maps;
+};
+constexpr GroupRule kFwdGroupTable[] = {
+    {48.0, 1},
+    {96.0, 2},
+    {1e300, 4},
+};
+
+int default_fwd_group(const sht_plan_s *p)
+{
+    const double waves1 = fwd_waves_per_cu(p);
+    int top = 1;
+    for (const GroupRule &r : kFwdGroupTable)
+        if (waves1 <= r.max_waves_per_cu) {
+            top = r.maps;
+            break;
+        }
+    // groups of nearly equal size
+    const int groups = (p->nmaps + top - 1) / top;
+    return (p->nmaps + groups - 1) / groups;
 }
 
 template <class T>
@@ -739,6 +777,7 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
                                      (delta_f32(p) ? sizeof(float2) : sizeof(double2)),
                                  256);
     p->fwd_chains = default_fwd_chains(p);
+    p->fwd_group = default_fwd_group(p);
     p->aux_stream = nullptr;
     p->ev_fork = p->ev_join = nullptr;
     if (hipStreamCreateWithFlags(&p->aux_stream, hipStreamNonBlocking) != hipSuccess ||
@@ -782,9 +821,10 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
             sht::log_line("plan fast ring nphi=%d: half length %d = %s", g.n, g.clen, rl);
         }
         sht::log_line("plan workspace forward=%zu full=%zu bytes, device tables=%zu bytes; "
-                      "FP64 forward launch shape %d pair(s) per lane (size table)",
+                      "FP64 forward launch shape %d pair(s) per lane, %d map(s) per wave "
+                      "(size tables)",
                       fwd_workspace_bytes(p), workspace_bytes(p), p->table_bytes,
-                      p->fwd_chains);
+                      p->fwd_chains, p->fwd_group);
     }
     *out = p;
     return SHT_OK;

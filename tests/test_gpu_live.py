@@ -89,3 +89,23 @@ def test_whole_and_stagewise_agree(P, prec, tol, name, lmax, rings, nside, mval)
     m2 = plan.delta2map(d).cpu().numpy()
     assert np.all(np.isfinite(m1))
     assert np.linalg.norm(m1 - m2) <= tol * np.linalg.norm(m2)
+
+
+# waves per CU (256 CUs) of 16 ring blocks x 151 m-pairs per map: 7 maps go in
+# pairs and one alone, 11 in 4 + 4 + 3, 13 in 4 + 4 + 4 + 1, 5 one by one
+@pytest.mark.parametrize("nmaps", [5, 7, 11, 13])
+def test_maps_together_equal_maps_alone(P, nmaps):
+    """A wave that takes several maps does each map's arithmetic unchanged."""
+    _say("maps per wave", nmaps)
+    lmax = 301
+    g = W.ecp_geometry(1999, 8)
+    alms = np.stack([W.random_alm(lmax, [804, i]) for i in range(nmaps)])
+    a = torch.from_numpy(alms).to(_dev())
+    many = P.Plan(lmax, g, nmaps=nmaps)
+    one = P.Plan(lmax, g)
+    got, d = many.alm2map(a).cpu(), many.alm2delta(a).cpu()
+    for i in range(nmaps):
+        assert torch.equal(got[i], one.alm2map(a[i]).cpu()[0]), i
+        assert torch.equal(d[i], one.alm2delta(a[i]).cpu()[0]), i
+    e = ref.alm2map(lmax, g, alms[-1])
+    assert np.linalg.norm(got[-1].numpy() - e) <= 1e-12 * np.linalg.norm(e)
