@@ -15,9 +15,8 @@
 //
 // Start.  The values of an m are negligible up to l ~ m / sin(theta); every
 // (m, ring pair) starts at the row of the plan's start table (live.hip) from
-// true FP64 values, so the forward kernels neither rescale nor touch the terms
-// before it.  (The adjoint still carries scaled values (v, k), value
-// v 2^(512 k), k <= 0, rescaled every 16 steps, Sec. 2.2.2.)
+// true FP64 values, so the kernels neither rescale nor touch the terms before
+// it.
 //
 // Mapping to CDNA4.  One wavefront owns 64*CH ring pairs (CH chains per
 // lane) and NB maps; the north/south rings of a pair share the recurrence
@@ -71,20 +70,15 @@ struct Chains {
     int rn[CH], rs[CH], ilim[CH];
 };
 
-// The ring pairs of this lane's chains: 64-pair blocks blk0..blk0 + CH - 1.
+// The ring pairs of this lane's chains: 64-pair blocks blk0..blk0 + CH - 1
+// (the pairs are padded like the start table).
 template <int CH>
-__device__ inline void load_chains(Chains<CH> &g, const PairDesc *__restrict__ pairs, int npairs,
-                                   int blk0)
+__device__ inline void load_chains(Chains<CH> &g, const PairDesc *__restrict__ pairs, int blk0)
 {
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-        const int p = (blk0 + c) * 64 + (int)threadIdx.x;
-        if (p < npairs) {
-            const PairDesc d = pairs[p];
-            g.x[c] = d.x; g.rn[c] = d.rn; g.rs[c] = d.rs; g.ilim[c] = d.ilim;
-        } else {
-            g.x[c] = 0.0; g.rn[c] = -1; g.rs[c] = -1; g.ilim[c] = 0;
-        }
+        const PairDesc d = pairs[(blk0 + c) * 64 + (int)threadIdx.x];
+        g.x[c] = d.x; g.rn[c] = d.rn; g.rs[c] = d.rs; g.ilim[c] = d.ilim;
     }
 }
 
@@ -103,33 +97,34 @@ typedef double d2a __attribute__((ext_vector_type(2), aligned(8)));
 typedef double d4a __attribute__((ext_vector_type(4), aligned(8)));
 typedef double d8a __attribute__((ext_vector_type(8), aligned(8)));
 
+template <int N>
+__device__ inline void scalar_rows(double *d, CDp p)
+{
+    if constexpr (N >= 8) {
+        const d8a v = *(const d8a __attribute__((address_space(4))) *)p;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) d[t] = v[t];
+        if constexpr (N > 8) scalar_rows<N - 8>(d + 8, p + 8);
+    } else if constexpr (N >= 4) {
+        const d4a v = *(const d4a __attribute__((address_space(4))) *)p;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) d[t] = v[t];
+        if constexpr (N > 4) scalar_rows<N - 4>(d + 4, p + 4);
+    } else {
+        const d2a v = *(const d2a __attribute__((address_space(4))) *)p;
+        d[0] = v[0];
+        d[1] = v[1];
+    }
+}
+
 template <int KR, int NB>
 struct CoefRows {
     double A[KR], a[2 * KR * NB];   // a: [row][map][re, im]
 
-    template <int N>
-    __device__ static inline void get(double *d, CDp p)
-    {
-        if constexpr (N >= 8) {
-            const d8a v = *(const d8a __attribute__((address_space(4))) *)p;
-#pragma unroll
-            for (int t = 0; t < 8; ++t) d[t] = v[t];
-            if constexpr (N > 8) get<N - 8>(d + 8, p + 8);
-        } else if constexpr (N >= 4) {
-            const d4a v = *(const d4a __attribute__((address_space(4))) *)p;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) d[t] = v[t];
-            if constexpr (N > 4) get<N - 4>(d + 4, p + 4);
-        } else {
-            const d2a v = *(const d2a __attribute__((address_space(4))) *)p;
-            d[0] = v[0];
-            d[1] = v[1];
-        }
-    }
     __device__ inline void load(CDp Am, CDp am, int j)
     {
-        get<KR>(A, Am + j);
-        get<2 * KR * NB>(a, am + 2 * NB * j);
+        scalar_rows<KR>(A, Am + j);
+        scalar_rows<2 * KR * NB>(a, am + 2 * NB * j);
     }
     __device__ double re(int t, int b) const { return a[2 * (t * NB + b)]; }
     __device__ double im(int t, int b) const { return a[2 * (t * NB + b) + 1]; }
@@ -159,12 +154,11 @@ __device__ inline void fwd_one_m(const Chains<CH> &g, const LiveTab &lt, int blk
     {
         const CIp jr = (CIp)(lt.jr + (long long)i * lt.nb);
 #pragma unroll
-        for (int c = 0; c < CH; ++c)
-            if (blk0 + c < lt.nb) {
-                const int v = jr[blk0 + c];
-                lo = min(lo, v & 0xffff);
-                hi = max(hi, (int)((unsigned)v >> 16));
-            }
+        for (int c = 0; c < CH; ++c) {
+            const int v = jr[blk0 + c];
+            lo = min(lo, v & 0xffff);
+            hi = max(hi, (int)((unsigned)v >> 16));
+        }
     }
     double Er[CH][NB], Ei[CH][NB], Or[CH][NB], Oi[CH][NB];
 #pragma unroll
@@ -178,14 +172,11 @@ __device__ inline void fwd_one_m(const Chains<CH> &g, const LiveTab &lt, int blk
         int je[CH];
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
-            u0[c] = 0.0; u1[c] = 0.0; s0[c] = 0.0; s1[c] = 0.0;
-            je[c] = kNeverLive;
-            if (blk0 + c < lt.nb) {
-                const long long e = (long long)i * lt.np + (blk0 + c) * 64 + (int)threadIdx.x;
-                const double2 v = lt.st[e];
-                s0[c] = v.x; s1[c] = v.y;
-                je[c] = lt.je[e];
-            }
+            u0[c] = 0.0; u1[c] = 0.0;
+            const long long e = (long long)i * lt.np + (blk0 + c) * 64 + (int)threadIdx.x;
+            const double2 v = lt.st[e];
+            s0[c] = v.x; s1[c] = v.y;
+            je[c] = lt.je[e];
         }
         // a chain is zero until its start row, where it takes the table's values
         auto enter = [&](int jb) {
@@ -290,7 +281,7 @@ __device__ inline void fwd_one_m(const Chains<CH> &g, const LiveTab &lt, int blk
 // groups of NB maps from the first map of ap and delta on
 template <int CH, int NB>
 __global__ __launch_bounds__(64) void k_legendre_fwd(
-    const PairDesc *__restrict__ pairs, int npairs, LiveTab lt, int pblocks,
+    const PairDesc *__restrict__ pairs, LiveTab lt, int pblocks,
     const int *__restrict__ mval, const long long *__restrict__ moff, int nm, int nmpairs,
     int lmax, const double *__restrict__ A, const double2 *__restrict__ ap, long long nalm,
     double2 *__restrict__ delta, int nrings, int ngroups, int full)
@@ -308,7 +299,7 @@ __global__ __launch_bounds__(64) void k_legendre_fwd(
     if (q >= nmpairs) return;
 
     Chains<CH> g;
-    load_chains(g, pairs, npairs, pb * CH);
+    load_chains(g, pairs, pb * CH);
     const double2 *apb = ap + b * nalm;
     const long long dmap = (long long)nrings * nm;
     for (int t = 0; t < 2; ++t) {
@@ -321,157 +312,239 @@ __global__ __launch_bounds__(64) void k_legendre_fwd(
 
 // ------------------------------------------------------------------ adjoint
 //
-// out_lm = c_lm sum_pairs u_l(x_p) (Dt_N + (-1)^(l-m) Dt_S) 2^(512 k_l)
-// A wave owns 64*CH ring pairs and one m-pair; per tile of 16 l-values each
-// lane sums its chains, the 64 lane partials go through LDS (16 x 64
-// complex, wave-private) and are reduced to one partial per (ring block, l).
-// A second kernel adds the ring-block partials in a fixed order and applies
-// c_lm, so the result is bitwise reproducible.
-
+// out_lm = c_lm sum_pairs u_l(x_p) (Dt_N + (-1)^(l-m) Dt_S).
+// A wave owns 64*CH ring pairs and one m-pair and walks the rows l - m in
+// tiles of 16, each chain from its start row (live.hip) on.  Chain after
+// chain adds its tile to the lane's 32 partial sums (16 rows, re and im): two
+// instructions of recurrence and two of accumulation per row, A_l from scalar
+// registers (the next tile's asked for a tile ahead).  The 32 sums are then
+// reduced over the 64 lanes in registers, halving the values and the lanes
+// that hold one at each step (reduce_tile), and one partial per (ring block,
+// l) is written; a second kernel adds the ring blocks' partials in a fixed
+// order and applies c_lm, so the result is bitwise reproducible.
+//
+// The reduction costs 124 instructions per tile whatever CH, against 64 per
+// chain: more chains per lane make it cheap, but leave fewer waves.
+//
+// Bound: VALU issue.  l_max 4096 / nside 2048, one map, with the block sum: 5.94
+// ms (10.47 ms with the lanes' partials reduced through LDS, four chains and
+// every row from l = m on); l_max 1024 / nside 512, 8 maps: 942 us (1405).
 constexpr int kAdjTile = 16;
-// Row length of the reduction buffer: 64 lane partials plus one pad entry.
-// The reduction reads a column (lanes 0..15 take rows 0..15); with rows of
-// exactly 64 entries (1 KB) those reads would all fall in one LDS bank.
-constexpr int kAdjRow = 65;
+
+__device__ inline double2 halves_swapped(double a, double b, bool rows16)
+{
+    const unsigned al = __double2loint(a), ah = __double2hiint(a);
+    const unsigned bl = __double2loint(b), bh = __double2hiint(b);
+    typedef unsigned v2u __attribute__((ext_vector_type(2)));
+    const v2u l = rows16 ? __builtin_amdgcn_permlane16_swap(al, bl, false, false)
+                         : __builtin_amdgcn_permlane32_swap(al, bl, false, false);
+    const v2u h = rows16 ? __builtin_amdgcn_permlane16_swap(ah, bh, false, false)
+                         : __builtin_amdgcn_permlane32_swap(ah, bh, false, false);
+    return make_double2(__hiloint2double((int)h[0], (int)l[0]),
+                        __hiloint2double((int)h[1], (int)l[1]));
+}
+
+template <int CTRL>
+__device__ inline double dpp(double v)
+{
+    const int l = __double2loint(v), h = __double2hiint(v);
+    return __hiloint2double(__builtin_amdgcn_update_dpp(h, h, CTRL, 0xf, 0xf, false),
+                            __builtin_amdgcn_update_dpp(l, l, CTRL, 0xf, 0xf, false));
+}
+
+// Lanes with `up` go on with b, the others with a; each adds the value of its
+// partner lane, whose `up` is the opposite.
+template <int CTRL>
+__device__ inline double take_half(double a, double b, bool up)
+{
+    const double keep = up ? b : a, send = up ? a : b;
+    return keep + dpp<CTRL>(send);
+}
+
+// v[k] of all lanes -> lane 2 k (and 2 k + 1) holds the sum of v[k] over the
+// wave, in a fixed order.
+__device__ inline double reduce_tile(double (&v)[2 * kAdjTile], int lane)
+{
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        const double2 t = halves_swapped(v[k], v[k + 16], false);
+        v[k] = t.x + t.y;
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const double2 t = halves_swapped(v[k], v[k + 8], true);
+        v[k] = t.x + t.y;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = take_half<0x128>(v[k], v[k + 4], lane & 8);   // row_ror:8
+#pragma unroll
+    for (int k = 0; k < 2; ++k) v[k] = take_half<0x141>(v[k], v[k + 2], lane & 4);   // half mirror
+    v[0] = take_half<0x4e>(v[0], v[1], lane & 2);                                    // quad xor 2
+    return v[0] + dpp<0xb1>(v[0]);                                                   // quad xor 1
+}
+
+// First row of the tiles that a wave of CH 64-pair blocks writes for an m, from
+// the blocks' start rows; past any row if none is live.
+template <int CH>
+__device__ inline int adj_first_row(CIp jr, int blk0)
+{
+    int lo = kNeverLive;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) lo = min(lo, jr[blk0 + c] & 0xffff);
+    return (lo * kLiveRows) & ~(kAdjTile - 1);
+}
 
 template <int CH>
-__device__ inline void adj_one_m(const Chains<CH> &g, const double (&s)[CH], int m, int i,
-                                 long long off, double mum, int lmax,
-                                 const double *__restrict__ A,
+__device__ inline void adj_one_m(const PairDesc *__restrict__ pairs, const LiveTab &lt,
+                                 int blk0, int m, int i, long long off,
+                                 int lmax, const double *__restrict__ A,
                                  const double2 *__restrict__ dt, long long dtbase, int nrings,
-                                 double2 *__restrict__ part, double2 (*red)[kAdjRow])
+                                 double2 *__restrict__ part, double2 (*st)[64])
 {
     const int len = lmax - m + 1;
     const int lane = threadIdx.x;
-    const double *__restrict__ Am = A + off;
-    double u0[CH], u1[CH];
-    double WEr[CH], WEi[CH], WOr[CH], WOi[CH];  // pair weights times 2^(512 k) factor
-    double NEr[CH], NEi[CH], NOr[CH], NOi[CH];  // unscaled pair weights
-    int k[CH];
+    const CIp jr = (CIp)(lt.jr + (long long)i * lt.nb);
+    const CDp Am = (CDp)(A + off);
+    int j0 = adj_first_row<CH>(jr, blk0);
+    if (j0 >= len) return;
+    int lo[CH], hi[CH];    // rows where the block's pairs start
+    int je[CH];
+    double x[CH], u0[CH], u1[CH];
+    double WEr[CH], WEi[CH], WOr[CH], WOi[CH];
+    // all loads of the chains first, the pairs' before the Delta~ that they
+    // place: entries that are dead or have no mirror ring are read from a
+    // place in the table and dropped
+    PairDesc d[CH];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) d[c] = pairs[(blk0 + c) * 64 + lane];
+    double2 sv[CH];
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-        double2 wn = make_double2(0.0, 0.0), ws = make_double2(0.0, 0.0);
-        if (g.rn[c] >= 0) wn = dt[dtbase + (long long)i * nrings + g.rn[c]];
-        if (g.rs[c] >= 0) ws = dt[dtbase + (long long)i * nrings + g.rs[c]];
-        NEr[c] = wn.x + ws.x; NEi[c] = wn.y + ws.y;
-        NOr[c] = wn.x - ws.x; NOi[c] = wn.y - ws.y;
-        seed_mm(mum, s[c], m, u0[c], k[c]);
-        u1[c] = (len >= 2) ? (Am[1] * g.x[c]) * u0[c] : 0.0;
-        const double f = final_scale(k[c]);
-        WEr[c] = NEr[c] * f; WEi[c] = NEi[c] * f; WOr[c] = NOr[c] * f; WOi[c] = NOi[c] * f;
+        const int v = jr[blk0 + c];
+        lo[c] = (v & 0xffff) * kLiveRows;
+        hi[c] = (int)((unsigned)v >> 16) * kLiveRows;
+        const long long e = (long long)i * lt.np + (blk0 + c) * 64 + lane;
+        je[c] = lt.je[e];
+        sv[c] = lt.st[e];
     }
-    for (int j0 = 0; j0 < len; j0 += kAdjTile) {
-        double pr[kAdjTile], pi[kAdjTile];
+    const double2 *row = dt + dtbase + (long long)i * nrings;
+    double2 wn[CH], ws[CH];
 #pragma unroll
-        for (int t = 0; t < kAdjTile; ++t) { pr[t] = 0.0; pi[t] = 0.0; }
+    for (int c = 0; c < CH; ++c) {
+        const int rn = max(d[c].rn, 0);
+        wn[c] = row[rn];
+        ws[c] = row[d[c].rs >= 0 ? d[c].rs : rn];
+    }
 #pragma unroll
-        for (int t = 0; t < kAdjTile; ++t) {
-            const int j = j0 + t;
-            if (j < len) {
-                const double Aj = (j >= 2) ? Am[j] : 0.0;
+    for (int c = 0; c < CH; ++c) {
+        st[c][lane] = sv[c];
+        x[c] = d[c].x;
+        u0[c] = 0.0;
+        u1[c] = 0.0;
+        const bool live = i < d[c].ilim, two = live && d[c].rs >= 0;
+        const double nr = live ? wn[c].x : 0.0, ni = live ? wn[c].y : 0.0;
+        const double sr = two ? ws[c].x : 0.0, si = two ? ws[c].y : 0.0;
+        WEr[c] = nr + sr; WEi[c] = ni + si;
+        WOr[c] = nr - sr; WOi[c] = ni - si;
+    }
+    // a chain is zero until its start row
+    auto enter = [&](int c, int jb) {
+        if (je[c] == jb) {
+            const double2 v = st[c][lane];
+            u0[c] = v.x;
+            u1[c] = v.y;
+        }
+    };
+    double a[kAdjTile];
+    scalar_rows<kAdjTile>(a, Am + j0);
+    for (; j0 < len; j0 += kAdjTile) {
+        // rows past the m's end (the table is padded) are computed and not stored
+        double an[kAdjTile], v[2 * kAdjTile];
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+        __builtin_amdgcn_sched_barrier(0);
+        scalar_rows<kAdjTile>(an, Am + j0 + kAdjTile);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int c = 0; c < CH; ++c) {
-                    double u;
-                    if (j == 0) {
-                        u = u0[c];
-                    } else if (j == 1) {
-                        u = u1[c];
-                    } else {
-                        u = fma(Aj * g.x[c], u1[c], -u0[c]);
-                        u0[c] = u1[c]; u1[c] = u;
-                    }
-                    if (t & 1) {  // j0 is even, so t carries the parity of l - m
-                        pr[t] = fma(u, WOr[c], pr[t]);
-                        pi[t] = fma(u, WOi[c], pi[t]);
-                    } else {
-                        pr[t] = fma(u, WEr[c], pr[t]);
-                        pi[t] = fma(u, WEi[c], pi[t]);
-                    }
+        for (int t = 0; t < 2 * kAdjTile; ++t) v[t] = 0.0;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            if (lo[c] >= j0 + kAdjTile) continue;
+#pragma unroll
+            for (int h = 0; h < kAdjTile; h += kLiveRows) {
+                if (j0 + h <= hi[c]) enter(c, (j0 + h) / kLiveRows);
+#pragma unroll
+                for (int t = h; t < h + kLiveRows; t += 2) {
+                    u0[c] = fma(a[t] * x[c], u1[c], -u0[c]);
+                    v[2 * t] = fma(u0[c], WEr[c], v[2 * t]);
+                    v[2 * t + 1] = fma(u0[c], WEi[c], v[2 * t + 1]);
+                    u1[c] = fma(a[t + 1] * x[c], u0[c], -u1[c]);
+                    v[2 * t + 2] = fma(u1[c], WOr[c], v[2 * t + 2]);
+                    v[2 * t + 3] = fma(u1[c], WOi[c], v[2 * t + 3]);
                 }
             }
         }
+        const double s = reduce_tile(v, lane);
+        const int row = j0 + (lane >> 2);
+        if ((lane & 1) == 0 && row < len)
+            reinterpret_cast<double *>(part + off + j0)[lane >> 1] = s;
 #pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            if (fmax(fabs(u0[c]), fabs(u1[c])) > kTwoS) {
-                u0[c] *= kTwoMinusS; u1[c] *= kTwoMinusS;
-                k[c] += 1;
-                const double f = final_scale(k[c]);
-                WEr[c] = NEr[c] * f; WEi[c] = NEi[c] * f;
-                WOr[c] = NOr[c] * f; WOi[c] = NOi[c] * f;
-            }
-        }
-#pragma unroll
-        for (int t = 0; t < kAdjTile; ++t) red[t][lane] = make_double2(pr[t], pi[t]);
-        __syncthreads();
-        {
-            const int t = lane & (kAdjTile - 1);
-            const int seg = lane / kAdjTile;  // 4 segments of 16 lanes
-            double sr = 0.0, si = 0.0;
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const double2 v = red[t][seg * 16 + q];
-                sr += v.x; si += v.y;
-            }
-            sr += __shfl_xor(sr, 16); si += __shfl_xor(si, 16);
-            sr += __shfl_xor(sr, 32); si += __shfl_xor(si, 32);
-            if (seg == 0 && j0 + t < len) part[off + j0 + t] = make_double2(sr, si);
-        }
-        __syncthreads();
+        for (int t = 0; t < kAdjTile; ++t) a[t] = an[t];
     }
 }
 
 template <int CH>
-__global__ __launch_bounds__(64) void k_legendre_adj(
-    const PairDesc *__restrict__ pairs, int npairs, int pblocks,
-    const int *__restrict__ mval, const long long *__restrict__ moff,
-    const double *__restrict__ mu, int nm, int nmpairs, int lmax,
-    const double *__restrict__ A, const double2 *__restrict__ dt, int nrings,
-    double2 *__restrict__ part, long long nalm, long long total)
+__global__ __launch_bounds__(64, CH == 8 ? 2 : CH == 1 ? 4 : 3) void k_legendre_adj(
+    const PairDesc *__restrict__ pairs, LiveTab lt, int pblocks,
+    const int *__restrict__ mval, const long long *__restrict__ moff, int nm, int nmpairs,
+    int lmax, const double *__restrict__ A, const double2 *__restrict__ dt, int nrings,
+    double2 *__restrict__ part, long long nalm, int nmaps)
 {
-    __shared__ double2 red[kAdjTile][kAdjRow];
-    const long long L = xcd_logical(blockIdx.x, total);
-    const int pb = (int)(L % pblocks);
-    const long long rest = L / pblocks;
-    const int q = (int)(rest % nmpairs);
-    const int b = (int)(rest / nmpairs);
-    const int lane = threadIdx.x;
-    Chains<CH> g;
-    double s[CH];
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        const int p = (pb * CH + c) * 64 + lane;
-        if (p < npairs) {
-            const PairDesc d = pairs[p];
-            g.x[c] = d.x; s[c] = d.s; g.rn[c] = d.rn; g.rs[c] = d.rs; g.ilim[c] = d.ilim;
-        } else {
-            g.x[c] = 0.0; s[c] = 0.0; g.rn[c] = -1; g.rs[c] = -1; g.ilim[c] = 0;
-        }
-    }
+    __shared__ double2 st[CH][64];
+    // the same walk as the forward kernel's
+    const int x = (int)(blockIdx.x % 8);
+    const int w = (int)(blockIdx.x / 8);
+    const int pb = w % pblocks;
+    const int rest = w / pblocks;
+    const int b = rest % nmaps;
+    const int q = x + 8 * (rest / nmaps);
+    if (q >= nmpairs) return;
     const long long dtbase = (long long)b * nrings * nm;
     double2 *pp = part + ((long long)b * pblocks + pb) * nalm;
     for (int t = 0; t < 2; ++t) {
         const int i = (t == 0) ? q : nm - 1 - q;
         if (t == 1 && i == q) break;
-        adj_one_m<CH>(g, s, mval[i], i, moff[i], mu[i], lmax, A, dt, dtbase, nrings, pp, red);
+        adj_one_m<CH>(pairs, lt, pb * CH, ((CIp)mval)[i], i, ((CLp)moff)[i], lmax, A, dt,
+                      dtbase, nrings, pp, st);
     }
 }
 
-__global__ void k_adj_reduce(const double2 *__restrict__ part, const double *__restrict__ cn,
-                             double *__restrict__ alm, long long nalm, int pblocks,
-                             long long m0len, int accumulate)
+// Sum of the ring blocks' partials, times c_lm; one thread per row of an m.
+// Blocks that have no live row yet wrote nothing there.
+template <int CH>
+__global__ __launch_bounds__(256) void k_adj_reduce(
+    const double2 *__restrict__ part, const double *__restrict__ cn, LiveTab lt,
+    const int *__restrict__ mval, const long long *__restrict__ moff, int lmax,
+    double *__restrict__ alm, long long nalm, int pblocks, int accumulate)
 {
-    const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    const long long b = blockIdx.y;
-    if (e >= nalm) return;
+    const int i = blockIdx.y;
+    const long long b = blockIdx.z;
+    const int m = mval[i];
+    const int j = blockIdx.x * 256 + threadIdx.x;
+    if (j >= lmax - m + 1) return;
+    const CIp jr = (CIp)(lt.jr + (long long)i * lt.nb);
+    const long long e = moff[i] + j;
     double sr = 0.0, si = 0.0;
     const double2 *p = part + b * pblocks * nalm + e;
     for (int k = 0; k < pblocks; ++k) {
-        const double2 v = p[(long long)k * nalm];
-        sr += v.x; si += v.y;
+        if (j >= adj_first_row<CH>(jr, k * CH)) {
+            const double2 v = p[(long long)k * nalm];
+            sr += v.x; si += v.y;
+        }
     }
     const double c = cn[e];
     double2 *o = reinterpret_cast<double2 *>(alm) + b * nalm + e;
-    const double2 v = make_double2(sr * c, (e < m0len) ? 0.0 : si * c);
+    const double2 v = make_double2(sr * c, m == 0 ? 0.0 : si * c);
     if (accumulate) {
         const double2 a = *o;
         *o = make_double2(a.x + v.x, a.y + v.y);
@@ -526,7 +599,7 @@ __global__ __launch_bounds__(64) void k_legendre_fwd_batch(const BatchTile *__re
         const BatchTile tile = tiles[t];
         const BatchMap &bm = maps[tile.map];
         Chains<CH> g;
-        load_chains(g, bm.pairs, bm.npairs, tile.pblock * CH);
+        load_chains(g, bm.pairs, tile.pblock * CH);
         const double2 *ap = reinterpret_cast<const double2 *>(ws + bm.ap_off);
         double2 *delta = reinterpret_cast<double2 *>(ws + bm.delta_off);
         const int q = tile.mpair;
@@ -538,13 +611,6 @@ __global__ __launch_bounds__(64) void k_legendre_fwd_batch(const BatchTile *__re
         }
     }
 }
-
-// The adjoint reduces every 16 l-rows over the wave's lanes through LDS.
-// Four ring pairs per lane keep that reduction small next to the recurrence
-// and leave registers for two waves per SIMD (224 VGPRs); at l_max 4096 the
-// map2alm built on it takes 11.9 ms, against 13.8 ms with eight pairs (one
-// wave per SIMD) and 16.7 ms with two.
-constexpr int kAdjChains = 4;
 
 }  // namespace
 
@@ -585,7 +651,11 @@ int fwd_pblocks(const sht_plan_s *p)
     const int per = 64 * p->fwd_chains;
     return (p->npairs + per - 1) / per;
 }
-int adj_pblocks(const sht_plan_s *p) { return (p->npairs + 64 * kAdjChains - 1) / (64 * kAdjChains); }
+int adj_pblocks(const sht_plan_s *p)
+{
+    const int per = 64 * p->adj_chains;
+    return (p->npairs + per - 1) / per;
+}
 
 template <int NB>
 static auto fwd_kernel(int chains) -> decltype(&k_legendre_fwd<1, NB>)
@@ -606,8 +676,8 @@ hipError_t launch_legendre_fwd(const sht_plan_s *p, const double2 *ap, double2 *
         if (total <= 0 || total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
         const auto kern = fwd_kernel<decltype(nb)::value>(p->fwd_chains);
         if (!kern) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(64), 0, st, p->d_pairs, p->npairs,
-                           p->live, pblocks, p->d_mval, p->d_moff, p->nm, nmpairs, p->lmax, p->d_A,
+        hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(64), 0, st, p->d_pairs, p->live,
+                           pblocks, p->d_mval, p->d_moff, p->nm, nmpairs, p->lmax, p->d_A,
                            ap + first * p->nalm, p->nalm,
                            delta + (long long)first * p->nrings * p->nm, p->nrings, groups,
                            full ? 1 : 0);
@@ -620,23 +690,36 @@ size_t adj_part_bytes(const sht_plan_s *p)
     return (size_t)p->nmaps * (size_t)adj_pblocks(p) * (size_t)p->nalm * sizeof(double2);
 }
 
-hipError_t launch_legendre_adj_ws(const sht_plan_s *p, const double2 *dt, double2 *part,
-                                  double *alm, hipStream_t st, bool accumulate)
+template <int CH>
+static hipError_t adj_launch(const sht_plan_s *p, const double2 *dt, double2 *part, double *alm,
+                             hipStream_t st, bool accumulate)
 {
     const int pblocks = adj_pblocks(p);
     const int nmpairs = (p->nm + 1) / 2;
-    const long long total = (long long)pblocks * nmpairs * p->nmaps;
+    const long long total = 8LL * ((nmpairs + 7) / 8) * pblocks * p->nmaps;
     if (total <= 0 || total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(k_legendre_adj<kAdjChains>, dim3((unsigned)total), dim3(64), 0, st,
-                       p->d_pairs, p->npairs, pblocks, p->d_mval, p->d_moff, p->d_mu, p->nm,
-                       nmpairs, p->lmax, p->d_A, dt, p->nrings, part, p->nalm, total);
+    hipLaunchKernelGGL(k_legendre_adj<CH>, dim3((unsigned)total), dim3(64), 0, st, p->d_pairs,
+                       p->live, pblocks, p->d_mval, p->d_moff, p->nm, nmpairs, p->lmax,
+                       p->d_A, dt, p->nrings, part, p->nalm, p->nmaps);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const long long m0len = (p->mval[0] == 0) ? (p->lmax + 1) : 0;
-    dim3 grid((unsigned)((p->nalm + 255) / 256), (unsigned)p->nmaps);
-    hipLaunchKernelGGL(k_adj_reduce, grid, dim3(256), 0, st, part, p->d_cn, alm, p->nalm,
-                       pblocks, m0len, accumulate ? 1 : 0);
+    const int longest = p->lmax - p->mval[0] + 1;
+    dim3 grid((unsigned)((longest + 255) / 256), (unsigned)p->nm, (unsigned)p->nmaps);
+    hipLaunchKernelGGL(k_adj_reduce<CH>, grid, dim3(256), 0, st, part, p->d_cn, p->live, p->d_mval,
+                       p->d_moff, p->lmax, alm, p->nalm, pblocks, accumulate ? 1 : 0);
     return hipGetLastError();
+}
+
+hipError_t launch_legendre_adj_ws(const sht_plan_s *p, const double2 *dt, double2 *part,
+                                  double *alm, hipStream_t st, bool accumulate)
+{
+    switch (p->adj_chains) {
+    case 1: return adj_launch<1>(p, dt, part, alm, st, accumulate);
+    case 2: return adj_launch<2>(p, dt, part, alm, st, accumulate);
+    case 4: return adj_launch<4>(p, dt, part, alm, st, accumulate);
+    case 8: return adj_launch<8>(p, dt, part, alm, st, accumulate);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_batch_legendre(const BatchMap *maps, int nmaps, long long max_nalm,

@@ -63,7 +63,7 @@ struct LiveTab {
     const uint16_t *je;    // [nm][np] start row
     const ushort2 *jr;     // [nm][np / 64] least and greatest start row of 64 pairs
                            // (kNeverLive, 0 if none is live)
-    int np;                // ring pairs, rounded up to 64
+    int np;                // ring pairs, rounded up to 512 (the most a wave takes)
     int nb;                // np / 64
 };
 
@@ -303,6 +303,7 @@ struct sht_plan_s {
     sht::RingClass bcls[sht::kNumRingClasses];
     std::vector<int> ring_sclass;  // synthesis class of each ring
     int fwd_chains;      // ring pairs per lane of the FP64 forward Legendre kernel (1, 2, 4)
+    int adj_chains;      // ring pairs per lane of the adjoint Legendre kernel (1, 2, 4, 8)
     int fwd_group;       // maps that a wave of it takes together (1..4)
     int num_cus;         // compute units of the plan's device
     size_t ws_ap_bytes;  // workspace: prescaled coefficients

@@ -188,6 +188,26 @@ int default_fwd_group(const sht_plan_s *p)
     return (p->nmaps + groups - 1) / groups;
 }
 
+// Ring pairs per lane of the adjoint Legendre kernel: its reduction over the
+// lanes costs as much as two pairs' rows whatever their number, so more pairs
+// are cheaper as long as enough waves are left.  Same key.  Measured, Legendre
+// adjoint with the block sum, 1 / 2 / 4 / 8 pairs: key 2 (l_max 256) 19 / 22 / 29 /
+// 30 us; key 8 (512) 50 / 42 / 53 / 77; key 32 (1024) 277 / 199 / 212 / 240; key
+// 64 (1024, 2 maps) 515 / 361 / 297 / 287; key 512 (4096) 11.5 / 7.7 / 6.2 / 5.9 ms.
+constexpr ChainRule kAdjChainTable[] = {
+    {4.0, 1},
+    {48.0, 2},
+    {1e300, 8},
+};
+
+int default_adj_chains(const sht_plan_s *p)
+{
+    const double waves1 = fwd_waves_per_cu(p);
+    for (const ChainRule &r : kAdjChainTable)
+        if (waves1 <= r.max_waves_per_cu) return r.chains;
+    return 8;
+}
+
 template <class T>
 sht_status upload(T **dst, const std::vector<T> &src, size_t *acc)
 {
@@ -237,8 +257,8 @@ sht_status build_live_table(sht_plan_s *p, const std::vector<PairDesc> &pairs, s
     for (int i = 1; i < p->npairs; ++i)
         if (pairs[i].s > pairs[pmax].s) pmax = i;
     sht::LiveTab &t = p->live;
-    t.nb = (p->npairs + 63) / 64;
-    t.np = 64 * t.nb;
+    t.np = (int)align_up((size_t)p->npairs, 512);
+    t.nb = t.np / 64;
     const size_t n = (size_t)p->nm * (size_t)t.np, nj = (size_t)p->nm * (size_t)t.nb;
     double *scratch = nullptr;
     if (hipMalloc((void **)&t.st, n * sizeof *t.st) != hipSuccess) { t.st = nullptr; return SHT_ERR_OOM; }
@@ -627,6 +647,8 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
 
     sht_status st = SHT_OK;
     size_t tb = 0;
+    // padded with pairs of no ring, so that the kernels read whole waves of them
+    pairs.resize(align_up(pairs.size(), 512), PairDesc{0.0, 0.0, -1, -1, 0, 0});
     if (st == SHT_OK) st = upload(&p->d_pairs, pairs, &tb);
     if (st == SHT_OK) st = upload(&p->d_mval, mval, &tb);
     if (st == SHT_OK) st = upload(&p->d_moff, p->moff, &tb);
@@ -778,6 +800,7 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
                                  256);
     p->fwd_chains = default_fwd_chains(p);
     p->fwd_group = default_fwd_group(p);
+    p->adj_chains = default_adj_chains(p);
     p->aux_stream = nullptr;
     p->ev_fork = p->ev_join = nullptr;
     if (hipStreamCreateWithFlags(&p->aux_stream, hipStreamNonBlocking) != hipSuccess ||

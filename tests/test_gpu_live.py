@@ -109,3 +109,25 @@ def test_maps_together_equal_maps_alone(P, nmaps):
         assert torch.equal(d[i], one.alm2delta(a[i]).cpu()[0]), i
     e = ref.alm2map(lmax, g, alms[-1])
     assert np.linalg.norm(got[-1].numpy() - e) <= 1e-12 * np.linalg.norm(e)
+
+
+# launches of 1, 2 and 8 ring pairs per lane (waves per CU at one pair per lane
+# below 4, up to 48, above), row counts around multiples of the 16-row tile, m
+# dead on whole ring blocks, an odd and a single m
+@pytest.mark.parametrize("lmax,nside,rings,mval,nmaps", [
+    (15, 8, None, None, 1),
+    (16, 130, np.r_[0:5, 40:200], np.array([0, 3, 16]), 2),
+    (257, 128, None, np.array([5]), 3),
+    (399, 256, None, None, 2),
+    (303, 512, None, None, 13),
+])
+def test_adjoint_shapes(P, lmax, nside, rings, mval, nmaps):
+    _say("adjoint", lmax, nside, nmaps)
+    g = _geom(rings, nside)
+    maps = np.random.default_rng(805).standard_normal((nmaps, g.npix))
+    plan = P.Plan(lmax, g, mval=mval, nmaps=nmaps)
+    plan.workspace().view(torch.float64)[: plan.workspace_bytes // 8].fill_(float("nan"))
+    got = plan.alm2map_adjoint(torch.from_numpy(maps).to(_dev())).cpu().numpy()
+    for i in (0, nmaps - 1):
+        e = ref.alm2map_adjoint(lmax, g, maps[i], mval=mval)
+        assert np.linalg.norm(got[i] - e) <= 1e-12 * np.linalg.norm(e), i
