@@ -82,41 +82,8 @@ __device__ inline void load_chains(Chains<CH> &g, const PairDesc *__restrict__ p
     }
 }
 
-// Wave-uniform data that no kernel writes while it reads it comes through the
-// constant address space: scalar loads, also where the compiler cannot prove
-// that the kernel's stores leave it alone (the batch's workspace holds both
-// the coefficients and Delta).
-typedef const int __attribute__((address_space(4))) *CIp;
-typedef const long long __attribute__((address_space(4))) *CLp;
-typedef const double __attribute__((address_space(4))) *CDp;
-
 // The coefficients of KR rows of one m in scalar registers: A_l, and a'_lm of
 // the wave's NB maps.
-// (Vector-typed loads of 8-byte alignment: one s_load per 64 bytes.)
-typedef double d2a __attribute__((ext_vector_type(2), aligned(8)));
-typedef double d4a __attribute__((ext_vector_type(4), aligned(8)));
-typedef double d8a __attribute__((ext_vector_type(8), aligned(8)));
-
-template <int N>
-__device__ inline void scalar_rows(double *d, CDp p)
-{
-    if constexpr (N >= 8) {
-        const d8a v = *(const d8a __attribute__((address_space(4))) *)p;
-#pragma unroll
-        for (int t = 0; t < 8; ++t) d[t] = v[t];
-        if constexpr (N > 8) scalar_rows<N - 8>(d + 8, p + 8);
-    } else if constexpr (N >= 4) {
-        const d4a v = *(const d4a __attribute__((address_space(4))) *)p;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) d[t] = v[t];
-        if constexpr (N > 4) scalar_rows<N - 4>(d + 4, p + 4);
-    } else {
-        const d2a v = *(const d2a __attribute__((address_space(4))) *)p;
-        d[0] = v[0];
-        d[1] = v[1];
-    }
-}
-
 template <int KR, int NB>
 struct CoefRows {
     double A[KR], a[2 * KR * NB];   // a: [row][map][re, im]
@@ -210,20 +177,14 @@ __device__ inline void fwd_one_m(const Chains<CH> &g, const LiveTab &lt, int blk
         if (j + 8 <= len) {
             CoefRows<KR, NB> ca, cb;
             ca.load(Am, am, j);
-            // s_waitcnt lgkmcnt(0), and nothing moves across
-            auto arrived = [] {
-                __builtin_amdgcn_sched_barrier(0);
-                __builtin_amdgcn_s_waitcnt(0xC07F);
-                __builtin_amdgcn_sched_barrier(0);
-            };
             auto rows8 = [&](int jn) {   // rows j..j + 7; jn: the rows wanted next
 #pragma unroll
                 for (int t = 0; t < 8; t += 2 * KR) {
-                    arrived();
+                    scalars_arrived();
                     cb.load(Am, am, j + t + KR);
                     __builtin_amdgcn_sched_barrier(0);
                     rows(ca);
-                    arrived();
+                    scalars_arrived();
                     ca.load(Am, am, t + 2 * KR < 8 ? j + t + 2 * KR : jn);
                     __builtin_amdgcn_sched_barrier(0);
                     rows(cb);
@@ -460,9 +421,7 @@ __device__ inline void adj_one_m(const PairDesc *__restrict__ pairs, const LiveT
     for (; j0 < len; j0 += kAdjTile) {
         // rows past the m's end (the table is padded) are computed and not stored
         double an[kAdjTile], v[2 * kAdjTile];
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(0xC07F);
-        __builtin_amdgcn_sched_barrier(0);
+        scalars_arrived();
         scalar_rows<kAdjTile>(an, Am + j0 + kAdjTile);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll

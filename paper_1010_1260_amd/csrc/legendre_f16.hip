@@ -23,17 +23,31 @@
 // zero (a padded copy of the table per super-block), so u stays bounded
 // there and its product with the zero coefficients is zero, never 0 * inf.
 //
-// Fragments and work split are those of the split-BF16 form: a 32x32x16
-// fragment holds K = 0..7 of its 32 columns in lanes 0-31 and K = 8..15 in
-// lanes 32-63; a lane's 16 same-parity values are exchanged across the wave
-// halves as FP32 and then split (one packed conversion per two values, one
-// mixed-precision FMA per residual, one packed conversion per two
-// residuals).  A workgroup of four waves takes 256 ring pairs and an m-pair;
-// per super-block of 128 l-rows the coefficient parts, their scales and A_l
-// are copied global-to-LDS while the previous super-block is multiplied; the
-// workgroup runs the recurrence alone while all its lanes are below 2^-400,
-// then a masked path for its first live super-block, then a path with no
-// mask and no rescaling.
+// there, and its product with the zero coefficients is zero, never 0 * inf.
+//
+// Fragments.  A 32x32x16 fragment holds K = 0..7 of its 32 columns in lanes
+// 0-31 and K = 8..15 in lanes 32-63; a lane's 16 same-parity values are
+// exchanged across the wave halves as FP32 and then split (one packed
+// conversion per two values, one mixed-precision FMA per residual, one packed
+// conversion per two residuals).
+//
+// Work split.  One wave per (64 ring pairs, m-pair, 16 maps), two waves per
+// SIMD.  The waves share nothing: each reads the packed coefficients straight
+// into its fragments (16 bytes per lane, from L2, a block ahead) and A_l
+// through scalar registers, starts at its own first live row (live.hip) and
+// runs the recurrence alone while every operand would be zero in FP16 (below
+// 2^-32).  FP16 matrix instructions run beside FP64 vector ones (measured: an
+// MFMA and eight FP64 FMAs 45 cycles, alone 36 and 36), so the products of a
+// parity are issued among the vector work that follows it.
+//
+// Bound: vector issue at the power limit.  204 vector instructions and 12 MFMA
+// per 32 rows.  l_max 4096 / nside 2048, 16 maps: 7.80 ms (80% of the cycles
+// issue vector work, at 1.8-2.0 GHz); 10.8 ms as workgroups of four waves that
+// shared the coefficients in LDS with a barrier per super-block, every row
+// from l = m on; 8.63 ms so with the live rows and the interleaved products,
+// 8.14 ms with independent waves.
+#include <type_traits>
+
 #include "mixed_common.h"
 
 namespace sht {
@@ -42,8 +56,7 @@ namespace {
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 
-constexpr int kWaves = 4;                   // waves (64 ring pairs each) sharing an m
-constexpr int kThreads = 64 * kWaves;
+constexpr int kWaves = 4;                   // waves of a prescale workgroup
 constexpr int kBlkSteps = 32;               // l-rows per block (K = 16 per parity)
 // Packed B layout per block: [parity 2][level 2][half 2][column 32] x 8 fp16.
 constexpr int kBlkElems = 2 * 2 * 2 * 32;   // 16-byte elements per block
@@ -51,8 +64,6 @@ constexpr int kSuper = 4;                   // blocks per super-block: 64 terms 
 constexpr int kSuperRows = kSuper * kBlkSteps;
 constexpr int kScaleElems = 4;              // 16 FP32 inverse scales (one per map)
 constexpr int kSuperElems = kSuper * kBlkElems + kScaleElems;
-constexpr int kABytes = kSuperRows * 8;     // A of a super-block in LDS
-constexpr int kBufBytes = kABytes + kSuperElems * 16;
 constexpr double kPScale = 0x1p6;           // P_lm operands are u * 2^6
 
 // Two FP32 values rounded to FP16 (round to nearest even), packed.  The
@@ -194,107 +205,176 @@ __global__ __launch_bounds__(256) void k_prescale_f16x2(
     if (tid < kScaleElems) o4[kSuper * kBlkElems + tid] = s4[kSuper * kBlkElems + tid];
 }
 
+// The fragments of one parity of a block (both column halves, high and low
+// parts) and its coefficient parts.
+struct Frags {
+    v4u H0, L0, H1, L1, B0, B1;
+};
+
 // The 16 same-parity values of this lane (K = 0..15 of its ring pair) ->
-// fragments of both column halves, then the three products against the
-// lane's coefficient parts B[level].
-__device__ __forceinline__ void parity_mfma(const float (&v)[16], const v4u (&B)[2], v16f &acc0,
-                                            v16f &acc1)
+// fragments of both column halves.
+__device__ __forceinline__ void split_parity(const float (&v)[16], Frags &f)
 {
     float f0[8], f1[8];
 #pragma unroll
     for (int t = 0; t < 8; ++t) swap_halves(v[t], v[t + 8], f0[t], f1[t]);
-    v4u H0, L0, H1, L1;
-    split_pack(f0, H0, L0);
-    split_pack(f1, H1, L1);
-    acc0 = mfma_h(B[0], H0, acc0);
-    acc1 = mfma_h(B[0], H1, acc1);
-    acc0 = mfma_h(B[0], L0, acc0);
-    acc1 = mfma_h(B[0], L1, acc1);
-    acc0 = mfma_h(B[1], H0, acc0);
-    acc1 = mfma_h(B[1], H1, acc1);
+    split_pack(f0, f.H0, f.L0);
+    split_pack(f1, f.H1, f.L1);
 }
 
-// One block of 32 l-rows from LDS: Ab = its 32 coefficients (as 16 pairs),
-// Bs = the block's packed coefficient parts.  SEED: rows 0..31 of the m,
-// started from P_mm (ua) with P_{m+1,m} = A_1 x P_mm.  MASK: lanes below
-// k = 0 contribute 0, and the scaled exponents are checked every 16 rows.
-template <bool MASK, bool SEED>
-__device__ __forceinline__ void block32(double x, double &ua, double &ub, int &k,
-                                        const double2 *__restrict__ Ab,
-                                        const v4u *__restrict__ Bs, int lane, MfmaTiles &acc)
+// The k-th (0..5) of the products of a parity, against the lane's
+// coefficient parts.  ZERO: the first pair starts the sums.
+template <int k, bool ZERO>
+__device__ __forceinline__ void product(const Frags &f, v16f &acc0, v16f &acc1)
 {
-    const int hi = lane >> 5, col = lane & 31;
+    if constexpr (k == 0) acc0 = mfma_h(f.B0, f.H0, ZERO ? v16f{} : acc0);
+    if constexpr (k == 1) acc1 = mfma_h(f.B0, f.H1, ZERO ? v16f{} : acc1);
+    if constexpr (k == 2) acc0 = mfma_h(f.B0, f.L0, acc0);
+    if constexpr (k == 3) acc1 = mfma_h(f.B0, f.L1, acc1);
+    if constexpr (k == 4) acc0 = mfma_h(f.B1, f.H0, acc0);
+    if constexpr (k == 5) acc1 = mfma_h(f.B1, f.H1, acc1);
+}
+
+template <bool ZERO>
+__device__ __forceinline__ void all_products(const Frags &f, v16f &acc0, v16f &acc1)
+{
+    product<0, ZERO>(f, acc0, acc1);
+    product<1, ZERO>(f, acc0, acc1);
+    product<2, ZERO>(f, acc0, acc1);
+    product<3, ZERO>(f, acc0, acc1);
+    product<4, ZERO>(f, acc0, acc1);
+    product<5, ZERO>(f, acc0, acc1);
+}
+
+// A lane's recurrence on one m: zero until its start row, where it takes the
+// start table's values (`stash`, its LDS slot).
+struct Lane {
+    double x, ua, ub;
+    int je;              // start row, units of kLiveRows
+};
+
+// 8 rows from row r on (coefficients a), as FP32 values of both parities.
+__device__ __forceinline__ void rows8(Lane &l, const double *a, float *ve, float *vo)
+{
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        const double u0 = fma(a[2 * t] * l.x, l.ub, -l.ua);
+        const double u1 = fma(a[2 * t + 1] * l.x, u0, -l.ub);
+        l.ua = u0;
+        l.ub = u1;
+        ve[t] = (float)u0;
+        vo[t] = (float)u1;
+    }
+}
+
+__device__ __forceinline__ void rows8_quiet(Lane &l, const double *a)
+{
+#pragma unroll
+    for (int t = 0; t < 8; t += 2) {
+        l.ua = fma(a[t] * l.x, l.ub, -l.ua);
+        l.ub = fma(a[t + 1] * l.x, l.ua, -l.ub);
+    }
+}
+
+// Lanes that start at row r take their values.  `last`: no lane of the wave
+// starts after it (uniform).
+__device__ __forceinline__ void enter(Lane &l, const double2 *stash, int r, int last)
+{
+    if (r <= last) {
+        asm volatile("");   // a branch of its own, around the lane compare too
+        if (l.je == r / kLiveRows) {
+            const double2 v = *stash;
+            l.ua = v.x * kPScale;
+            l.ub = v.y * kPScale;
+        }
+    }
+}
+
+// The coefficient parts of a block: [parity][level], one 16-byte load each,
+// straight in the fragment layout.
+struct BParts {
+    v4u b[2][2];
+
+    __device__ __forceinline__ void load(const v4u *__restrict__ Bl)
+    {
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int lev = 0; lev < 2; ++lev) b[p][lev] = Bl[(p * 2 + lev) * 64];
+    }
+};
+
+// One block of 32 l-rows from row r0 on.  The matrix core works beside the
+// vector units: the products of a block's odd parity are issued among the
+// next block's recurrence, those of its even parity among the conversions
+// of its odd values.  FIRST: nothing is left from the previous block of the
+// super-block, the sums start here; SECOND: what is left starts the odd sums.
+// On entry a0 holds the coefficients of rows r0..r0 + 15 and B the block's
+// parts (asked for a half block and a block ahead); on return those of rows rn
+// on and of the block at Bn.
+template <bool FIRST, bool SECOND>
+__device__ __forceinline__ void block32(Lane &l, const double2 *stash, int r0, int hi8, CDp Am,
+                                        int rn, double (&a0)[16], const v4u *__restrict__ Bn,
+                                        BParts &B, Frags &odd, MfmaTiles &acc)
+{
     float ve[16], vo[16];
-    bool live = !MASK || k == 0;
+    double a1[16];
+    scalars_arrived();
+    scalar_rows<16>(a1, Am + r0 + 16);
+    __builtin_amdgcn_sched_barrier(0);
+    Frags even;
+    even.B0 = B.b[0][0];
+    even.B1 = B.b[0][1];
+    const v4u bo0 = B.b[1][0], bo1 = B.b[1][1];
+    B.load(Bn);
+    enter(l, stash, r0, hi8);
+    rows8(l, a0, ve, vo);
+    if constexpr (!FIRST) { product<0, SECOND>(odd, acc.o0, acc.o1); product<1, SECOND>(odd, acc.o0, acc.o1); }
+    enter(l, stash, r0 + 8, hi8);
+    rows8(l, a0 + 8, ve + 4, vo + 4);
+    if constexpr (!FIRST) product<2, SECOND>(odd, acc.o0, acc.o1);
+    scalars_arrived();
+    scalar_rows<16>(a0, Am + rn);
+    __builtin_amdgcn_sched_barrier(0);
+    enter(l, stash, r0 + 16, hi8);
+    rows8(l, a1, ve + 8, vo + 8);
+    if constexpr (!FIRST) { product<3, SECOND>(odd, acc.o0, acc.o1); product<4, SECOND>(odd, acc.o0, acc.o1); }
+    enter(l, stash, r0 + 24, hi8);
+    rows8(l, a1 + 8, ve + 12, vo + 12);
+    if constexpr (!FIRST) product<5, SECOND>(odd, acc.o0, acc.o1);
+    split_parity(ve, even);
+    all_products<FIRST>(even, acc.e0, acc.e1);
+    split_parity(vo, odd);
+    odd.B0 = bo0;
+    odd.B1 = bo1;
+    // one product to seven vector instructions (8 exchanges, 32 conversions)
 #pragma unroll
-    for (int t = 0; t < 16; ++t) {
-        const double2 a = Ab[t];
-        double u0, u1;
-        if (SEED && t == 0) {
-            u0 = ua;
-            u1 = (a.y * x) * ua;
-        } else {
-            u0 = fma(a.x * x, ub, -ua);
-            u1 = fma(a.y * x, u0, -ub);
-        }
-        ua = u0;
-        ub = u1;
-        ve[t] = MASK ? opnd(u0, live) : (float)u0;
-        vo[t] = MASK ? opnd(u1, live) : (float)u1;
-        if (MASK && (t == 7 || t == 15)) {
-            rescale_mixed(ua, ub, k);
-            if (t == 7) live = k == 0;
-        }
-    }
-    v4u BE[2], BO[2];
-#pragma unroll
-    for (int lev = 0; lev < 2; ++lev) {
-        BE[lev] = Bs[((0 * 2 + lev) * 2 + hi) * 32 + col];
-        BO[lev] = Bs[((1 * 2 + lev) * 2 + hi) * 32 + col];
-    }
-    parity_mfma(ve, BE, acc.e0, acc.e1);
-    parity_mfma(vo, BO, acc.o0, acc.o1);
-}
-
-// A block in which no lane of the wave has reached k = 0: the recurrence
-// alone (same arithmetic as block32, so the state is bitwise the same).
-template <bool MASK, bool SEED>
-__device__ __forceinline__ void block32_dead(double x, double &ua, double &ub, int &k,
-                                             const double2 *__restrict__ Ab)
-{
-#pragma unroll
-    for (int t = 0; t < 16; ++t) {
-        const double2 a = Ab[t];
-        double u0, u1;
-        if (SEED && t == 0) {
-            u0 = ua;
-            u1 = (a.y * x) * ua;
-        } else {
-            u0 = fma(a.x * x, ub, -ua);
-            u1 = fma(a.y * x, u0, -ub);
-        }
-        ua = u0;
-        ub = u1;
-        if (MASK && (t == 7 || t == 15)) rescale_mixed(ua, ub, k);
+    for (int k = 0; k < 6; ++k) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);
     }
 }
 
 // tot += acc * (inverse scale of the entry's map).  Entry r of a lane's
 // tile row set is row 8 (r/4) + 4 hi + r%4 = 2 map + Re/Im, so the lane's
 // maps are 4 j + 2 hi + {0, 1}, j = 0..3.
-__device__ __forceinline__ void add_tiles_scaled(MfmaTiles &tot, const MfmaTiles &acc,
-                                                 const float *__restrict__ isc, int hi)
-{
-    float s[8];
+struct Scales {
+    float2 s[4];
+
+    __device__ __forceinline__ void load(const v4u *__restrict__ Bs, int hi)
+    {
+        const float2 *p = reinterpret_cast<const float2 *>(Bs + kSuper * kBlkElems) + hi;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const float2 v = reinterpret_cast<const float2 *>(isc)[2 * j + hi];
-        s[2 * j] = v.x;
-        s[2 * j + 1] = v.y;
+        for (int j = 0; j < 4; ++j) s[j] = p[2 * j];
     }
+};
+
+__device__ __forceinline__ void add_tiles_scaled(MfmaTiles &tot, const MfmaTiles &acc,
+                                                 const Scales &sc)
+{
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-        const float f = s[2 * (r >> 2) + ((r & 3) >> 1)];
+        const float f = (r & 2) ? sc.s[r >> 2].y : sc.s[r >> 2].x;
         tot.e0[r] = fmaf(acc.e0[r], f, tot.e0[r]);
         tot.e1[r] = fmaf(acc.e1[r], f, tot.e1[r]);
         tot.o0[r] = fmaf(acc.o0[r], f, tot.o0[r]);
@@ -302,212 +382,143 @@ __device__ __forceinline__ void add_tiles_scaled(MfmaTiles &tot, const MfmaTiles
     }
 }
 
-// Copy of super-block sb of an m (its packed B blocks, their inverse scales
-// and 128 coefficients) global-to-LDS into `buf`; it completes at the
-// workgroup's next barrier.  The padded tables hold whole super-blocks, so
-// the copy never reads past the m's own data.
-__device__ __forceinline__ void super_dma(char *buf, const v4u *__restrict__ Bm,
-                                          const double *__restrict__ Am, int sb, int tid)
+// A block whose operands would all be zero: the recurrence alone.
+__device__ __forceinline__ void block32_quiet(Lane &l, const double2 *stash, int r0, int hi8,
+                                              CDp Am, int rn, double (&a0)[16])
 {
-    // the lane addresses are recomputed at every copy (a few integer
-    // operations) rather than kept live, and spilled, across the loop
-    asm volatile("" : "+v"(tid));
-    const v4u *src = Bm + (long long)sb * kSuperElems;
-    v4u *dst = reinterpret_cast<v4u *>(buf + kABytes);
-#pragma unroll
-    for (int c = 0; c < kSuper * kBlkElems / kThreads; ++c) {
-        const int w = tid + kThreads * c;
-        __builtin_amdgcn_global_load_lds(src + w, dst + w, 16, 0, 0);
-    }
-    if (tid < kScaleElems)
-        __builtin_amdgcn_global_load_lds(src + kSuper * kBlkElems + tid,
-                                         dst + kSuper * kBlkElems + tid, 16, 0, 0);
-    const unsigned *asrc = reinterpret_cast<const unsigned *>(Am + (long long)sb * kSuperRows);
-    __builtin_amdgcn_global_load_lds(asrc + tid, reinterpret_cast<unsigned *>(buf) + tid, 4, 0, 0);
-}
-
-template <bool MASK>
-__device__ __forceinline__ void super_compute(double x, double &ua, double &ub, int &k,
-                                              const char *cur, char *nxt, bool more, int sb,
-                                              int nb, bool seed, const v4u *__restrict__ Bm,
-                                              const double *__restrict__ Am, int tid,
-                                              MfmaTiles &acc, MfmaTiles &tot)
-{
-    const int lane = tid & 63;
-    const double2 *As = reinterpret_cast<const double2 *>(cur);
-    const v4u *Bs = reinterpret_cast<const v4u *>(cur + kABytes);
-    zero_tiles(acc);
-    if (more) super_dma(nxt, Bm, Am, sb + 1, tid);
-    if (seed) {
-        if (wave_any(k == 0))
-            block32<true, true>(x, ua, ub, k, As, Bs, lane, acc);
-        else
-            block32_dead<true, true>(x, ua, ub, k, As);
-    } else if (!MASK || wave_any(k == 0)) {
-        block32<MASK, false>(x, ua, ub, k, As, Bs, lane, acc);
-    } else {
-        block32_dead<MASK, false>(x, ua, ub, k, As);
-    }
-    for (int q = 1; q < nb; ++q) {
-        if (!MASK || wave_any(k == 0))
-            block32<MASK, false>(x, ua, ub, k, As + (kBlkSteps / 2) * q, Bs + kBlkElems * q,
-                                 lane, acc);
-        else
-            block32_dead<MASK, false>(x, ua, ub, k, As + (kBlkSteps / 2) * q);
-    }
-    add_tiles_scaled(tot, acc, reinterpret_cast<const float *>(Bs + kSuper * kBlkElems),
-                     lane >> 5);
-}
-
-// A thread's share of the first live super-block of an m (register staged).
-struct SuperStage {
-    v4u b[kSuper * kBlkElems / kThreads];
-    v4u sc;
-    unsigned a;
-};
-
-__device__ __forceinline__ void super_stage_load(SuperStage &g, const v4u *__restrict__ Bm,
-                                                 const double *__restrict__ Am, int sb, int tid)
-{
-    const v4u *__restrict__ src = Bm + (long long)sb * kSuperElems;
-#pragma unroll
-    for (int c = 0; c < kSuper * kBlkElems / kThreads; ++c) g.b[c] = src[tid + kThreads * c];
-    g.sc = (tid < kScaleElems) ? src[kSuper * kBlkElems + tid] : v4u{};
-    g.a = reinterpret_cast<const unsigned *>(Am + (long long)sb * kSuperRows)[tid];
-}
-
-__device__ __forceinline__ void super_stage_store(const SuperStage &g, char *buf, int tid)
-{
-    v4u *B = reinterpret_cast<v4u *>(buf + kABytes);
-#pragma unroll
-    for (int c = 0; c < kSuper * kBlkElems / kThreads; ++c) B[tid + kThreads * c] = g.b[c];
-    if (tid < kScaleElems) B[kSuper * kBlkElems + tid] = g.sc;
-    reinterpret_cast<unsigned *>(buf)[tid] = g.a;
+    double a1[16];
+    scalars_arrived();
+    scalar_rows<16>(a1, Am + r0 + 16);
+    __builtin_amdgcn_sched_barrier(0);
+    enter(l, stash, r0, hi8);
+    rows8_quiet(l, a0);
+    enter(l, stash, r0 + 8, hi8);
+    rows8_quiet(l, a0 + 8);
+    scalars_arrived();
+    scalar_rows<16>(a0, Am + rn);
+    __builtin_amdgcn_sched_barrier(0);
+    enter(l, stash, r0 + 16, hi8);
+    rows8_quiet(l, a1);
+    enter(l, stash, r0 + 24, hi8);
+    rows8_quiet(l, a1 + 8);
 }
 
 struct MState {
-    int m, i, len, nblk, nsb, sb0;
+    int i, nblk, q0;     // blocks of the m, the first one with a live row of the wave,
+    int q1;              // and the first one with an operand that is not zero
+    int hi8;             // the last row at which a pair starts
     const double *Am;    // padded coefficients of the m, per super-block
-    const v4u *Bm;
-    double ua, ub;
-    int k;
+    const v4u *Bm;       // its packed blocks
+    Lane l;
+    double a[16];
+    BParts B;
+
+    __device__ __forceinline__ const v4u *block(int q) const
+    {
+        return Bm + (long long)(q / kSuper) * kSuperElems + (q % kSuper) * kBlkElems;
+    }
 };
 
-// Seed and phase 1 (recurrence alone while the whole workgroup is below
-// 2^-400, coefficients from the plain table), then the register copy of
-// the first live super-block.
-__device__ void m_begin(MState &st, SuperStage &g, int i, const int *__restrict__ mval,
-                        const long long *__restrict__ moff, const long long *__restrict__ soff,
-                        const double *__restrict__ mu, int lmax, const double *__restrict__ A,
-                        const double *__restrict__ Asb, const v4u *__restrict__ Bg, double x,
-                        double s, int tid)
+// Start of an m: the lane's entry of the start table and the first live
+// block's coefficients.
+__device__ __forceinline__ void m_begin(MState &st, double2 *stash, int i,
+                                        const int *__restrict__ mval,
+                                        const long long *__restrict__ soff, int lmax,
+                                        const LiveTab &lt, const double *__restrict__ Asb,
+                                        const v4u *__restrict__ Bg, int pb, int lane)
 {
     st.i = i;
-    st.m = mval[i];
-    st.len = lmax - st.m + 1;
-    st.nblk = (st.len + kBlkSteps - 1) / kBlkSteps;
-    st.nsb = (st.nblk + kSuper - 1) / kSuper;
-    const double *Ap = A + moff[i];
-    st.Am = Asb + soff[i] * kSuperRows;
-    st.Bm = Bg + soff[i] * kSuperElems;
-    st.ub = 0.0;
-    seed_mm(mu[i], s, st.m, st.ua, st.k);
-    if (st.k == 0 && fabs(st.ua) < kEmergeTrue) {
-        st.ua *= kTwoS;
-        st.k = -1;
+    const long long e = (long long)i * lt.np + pb * 64 + lane;
+    const double2 v = lt.st[e];
+    st.l.je = lt.je[e];
+    const int jr = ((CIp)(lt.jr + (long long)i * lt.nb))[pb];
+    const int len = lmax - ((CIp)mval)[i] + 1;
+    const long long so = ((CLp)soff)[i];
+    st.nblk = (len + kBlkSteps - 1) / kBlkSteps;
+    st.q0 = (jr & 0xffff) * kLiveRows / kBlkSteps;
+    st.hi8 = (int)((unsigned)jr >> 16) * kLiveRows;
+    // jq is read as half of an aligned word
+    const long long o = (long long)i * lt.nb + pb;
+    const int w = ((CIp)lt.jq)[o >> 1];
+    st.q1 = ((o & 1) ? (int)((unsigned)w >> 16) : (w & 0xffff)) * kLiveRows / kBlkSteps;
+    st.Am = Asb + so * kSuperRows;
+    st.Bm = Bg + so * kSuperElems;
+    st.l.ua = 0.0;
+    st.l.ub = 0.0;
+    *stash = v;
+    if (st.q1 < st.nblk) {
+        scalar_rows<16>(st.a, (CDp)st.Am + st.q0 * kBlkSteps);
+        st.B.load(st.block(st.q1) + lane);
     }
-    st.ua *= kPScale;
-    int sb0 = 0;
-    while (sb0 < st.nsb && !__syncthreads_or(st.k == 0)) {
-        const int n16 = min(kSuperRows, st.len - sb0 * kSuperRows + 15) / 16;
-        for (int q = 0; q < n16; ++q) {
-            const int r0 = sb0 * kSuperRows + q * 16;
-            if (r0 == 0)
-                block16_dead_g<true>(x, st.ua, st.ub, Ap, r0);
-            else
-                block16_dead_g<false>(x, st.ua, st.ub, Ap, r0);
-            rescale_mixed(st.ua, st.ub, st.k);
-        }
-        ++sb0;
-    }
-    st.sb0 = sb0;
-    if (sb0 < st.nsb) super_stage_load(g, st.Bm, st.Am, sb0, tid);
 }
 
-__device__ __forceinline__ void m_commit(const MState &st, const SuperStage &g, char *ldsA,
-                                         int tid)
-{
-    if (st.sb0 < st.nsb) super_stage_store(g, ldsA, tid);
-    __syncthreads();
-}
-
-__device__ __forceinline__ void m_step(MState &st, int sb, const char *cur, char *nxt, double x,
-                                       int tid, bool &mask, MfmaTiles &acc, MfmaTiles &tot)
-{
-    const bool more = sb + 1 < st.nsb;
-    const int nb = min(kSuper, st.nblk - sb * kSuper);
-    if (mask) {
-        super_compute<true>(x, st.ua, st.ub, st.k, cur, nxt, more, sb, nb, sb == 0, st.Bm,
-                            st.Am, tid, acc, tot);
-        mask = wave_any(st.k < 0);
-    } else {
-        super_compute<false>(x, st.ua, st.ub, st.k, cur, nxt, more, sb, nb, false, st.Bm,
-                             st.Am, tid, acc, tot);
-    }
-    __syncthreads();
-}
-
-__device__ __forceinline__ void m_compute(MState &st, char *ldsA, char *ldsB, double x, int tid,
+__device__ __forceinline__ void m_compute(MState &st, const double2 *stash, int lane,
                                           MfmaTiles &tot)
 {
-    MfmaTiles acc;
     zero_tiles(tot);
-    bool mask = true;
-    for (int sb = st.sb0; sb < st.nsb; sb += 2) {
-        m_step(st, sb, ldsA, ldsB, x, tid, mask, acc, tot);
-        if (sb + 1 < st.nsb) m_step(st, sb + 1, ldsB, ldsA, x, tid, mask, acc, tot);
+    if (st.q1 >= st.nblk) return;
+    const CDp Am = (CDp)st.Am;
+    for (int q = st.q0; q < st.q1; ++q)
+        block32_quiet(st.l, stash, q * kBlkSteps, st.hi8, Am, (q + 1) * kBlkSteps, st.a);
+    for (int q = st.q1; q < st.nblk;) {
+        const int end = min((q / kSuper + 1) * kSuper, st.nblk);   // of the super-block
+        Scales sc;
+        sc.load(st.block(q & ~(kSuper - 1)), lane >> 5);
+        Frags odd;
+        MfmaTiles acc;
+        // the look-ahead stays at the m's last block
+        auto step = [&](auto first, auto second) {
+            const int qn = min(q + 1, st.nblk - 1);
+            block32<decltype(first)::value, decltype(second)::value>(
+                st.l, stash, q * kBlkSteps, st.hi8, Am, qn * kBlkSteps, st.a,
+                st.block(qn) + lane, st.B, odd, acc);
+            ++q;
+        };
+        step(std::true_type(), std::false_type());
+        if (q < end) {
+            step(std::false_type(), std::true_type());
+            while (q < end) step(std::false_type(), std::false_type());
+            all_products<false>(odd, acc.o0, acc.o1);
+        } else {
+            all_products<true>(odd, acc.o0, acc.o1);
+        }
+        add_tiles_scaled(tot, acc, sc);
     }
 }
 
-__global__ __launch_bounds__(kThreads, 2) void k_legendre_mfma_f16x2(
-    const PairDesc *__restrict__ pairs, int npairs, int pgroups,
-    const int *__restrict__ mval, const long long *__restrict__ moff,
-    const long long *__restrict__ soff, const double *__restrict__ mu, int nm, int nmpairs,
-    int lmax, const double *__restrict__ A, const double *__restrict__ Asb,
-    const v4u *__restrict__ Bb, long long nsuper, float2 *__restrict__ delta, int nrings,
-    int nmaps, long long total)
+// One wave per (64 ring pairs, m-pair, 16 maps), nothing shared between waves:
+// no barrier, and a wave's dead rows cost it nothing.
+__global__ __launch_bounds__(64, 2) void k_legendre_mfma_f16x2(
+    const PairDesc *__restrict__ pairs, int npairs, LiveTab lt, int pblocks,
+    const int *__restrict__ mval, const long long *__restrict__ soff, int nm, int nmpairs,
+    int lmax, const double *__restrict__ Asb, const v4u *__restrict__ Bb, long long nsuper,
+    float2 *__restrict__ delta, int nrings, int nmaps, int groups, int full)
 {
-    __shared__ __attribute__((aligned(16))) char ldsA[kBufBytes];
-    __shared__ __attribute__((aligned(16))) char ldsB[kBufBytes];
-    const long long L = xcd_logical(blockIdx.x, total);
-    const int pg = (int)(L % pgroups);
-    const long long rest = L / pgroups;
-    const int q = (int)(rest % nmpairs);
-    const int grp = (int)(rest / nmpairs);
-    const int tid = threadIdx.x;
-    const int pb = pg * kWaves + (tid >> 6);
-    const int p = pb * 64 + (tid & 63);
-    double x = 0.0, s = 0.0;
-    if (p < npairs) {
-        const PairDesc d = pairs[p];
-        x = d.x; s = d.s;
-    }
+    __shared__ double2 start[64];
+    // XCD x takes the m-pairs q = x mod 8 (see the FP64 kernel)
+    const int xcd = (int)(blockIdx.x % 8);
+    const int w = (int)(blockIdx.x / 8);
+    const int pb = w % pblocks;
+    const int rest = w / pblocks;
+    const int grp = rest % groups;
+    const int q = xcd + 8 * (rest / groups);
+    if (q >= nmpairs) return;
+    const int lane = threadIdx.x;
+    double2 *stash = start + lane;
     const v4u *Bg = Bb + (long long)grp * nsuper * kSuperElems;
     MState st;
-    SuperStage g;
     MfmaTiles tot;
-    m_begin(st, g, q, mval, moff, soff, mu, lmax, A, Asb, Bg, x, s, tid);
-    m_commit(st, g, ldsA, tid);
-    m_compute(st, ldsA, ldsB, x, tid, tot);
+    st.l.x = pairs[pb * 64 + lane].x;
+    m_begin(st, stash, q, mval, soff, lmax, lt, Asb, Bg, pb, lane);
+    m_compute(st, stash, lane, tot);
     const int i1 = st.i;
     const int i2 = nm - 1 - q;
     const bool two = i2 != q;
-    if (two) m_begin(st, g, i2, mval, moff, soff, mu, lmax, A, Asb, Bg, x, s, tid);
-    m_store(tot, i1, delta, pairs, npairs, pb, grp, nmaps, nrings, nm, tid & 63);
+    if (two) m_begin(st, stash, i2, mval, soff, lmax, lt, Asb, Bg, pb, lane);
+    m_store(tot, i1, delta, pairs, npairs, pb, grp, nmaps, nrings, full != 0, lane);
     if (two) {
-        m_commit(st, g, ldsA, tid);
-        m_compute(st, ldsA, ldsB, x, tid, tot);
-        m_store(tot, st.i, delta, pairs, npairs, pb, grp, nmaps, nrings, nm, tid & 63);
+        m_compute(st, stash, lane, tot);
+        m_store(tot, st.i, delta, pairs, npairs, pb, grp, nmaps, nrings, full != 0, lane);
     }
 }
 
@@ -535,19 +546,17 @@ hipError_t launch_prescale_f16x2(const sht_plan_s *p, const double *alm, void *B
 }
 
 hipError_t launch_legendre_mfma_f16x2(const sht_plan_s *p, const void *Bb, float2 *delta,
-                                      hipStream_t st)
+                                      bool full, hipStream_t st)
 {
     const int pblocks = (p->npairs + 63) / 64;
-    const int pgroups = (pblocks + kWaves - 1) / kWaves;
     const int nmpairs = (p->nm + 1) / 2;
     const int groups = (p->nmaps + 15) / 16;
-    const long long total = (long long)pgroups * nmpairs * groups;
+    const long long total = 8LL * ((nmpairs + 7) / 8) * pblocks * groups;
     if (total <= 0 || total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(k_legendre_mfma_f16x2, dim3((unsigned)total), dim3(kThreads), 0, st,
-                       p->d_pairs, p->npairs, pgroups, p->d_mval, p->d_moff, p->d_soff, p->d_mu,
-                       p->nm, nmpairs, p->lmax, p->d_A, p->d_Asb,
-                       reinterpret_cast<const v4u *>(Bb), p->nsuper,
-                       delta, p->nrings, p->nmaps, total);
+    hipLaunchKernelGGL(k_legendre_mfma_f16x2, dim3((unsigned)total), dim3(64), 0, st,
+                       p->d_pairs, p->npairs, p->live, pblocks, p->d_mval, p->d_soff, p->nm,
+                       nmpairs, p->lmax, p->d_Asb, reinterpret_cast<const v4u *>(Bb), p->nsuper,
+                       delta, p->nrings, p->nmaps, groups, full ? 1 : 0);
     return hipGetLastError();
 }
 

@@ -398,11 +398,11 @@ __global__ __launch_bounds__(kThreads, 2) void k_legendre_mfma_f32(
     const int i2 = nm - 1 - q;
     const bool two = i2 != q;
     if (two) m_begin(st, g, i2, mval, soff, boff16, mu, lmax, Asb, Bg, x, s, tid);
-    m_store(tot, i1, delta, pairs, npairs, pb, grp, nmaps, nrings, nm, tid & 63);
+    m_store(tot, i1, delta, pairs, npairs, pb, grp, nmaps, nrings, true, tid & 63);
     if (two) {
         m_commit(st, g, ldsA, tid);
         m_compute(st, ldsA, ldsB, x, tid, tot);
-        m_store(tot, st.i, delta, pairs, npairs, pb, grp, nmaps, nrings, nm, tid & 63);
+        m_store(tot, st.i, delta, pairs, npairs, pb, grp, nmaps, nrings, true, tid & 63);
     }
 }
 

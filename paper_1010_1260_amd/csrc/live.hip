@@ -26,6 +26,7 @@ namespace {
 
 constexpr double kLiveFloor = 0x1p-372;
 constexpr double kLiveRel = 0x1p-192;
+constexpr double kQuiet = 0x1p-32;
 
 // v 2^(512 k), 0 for k <= -2 (below 2^-372 for |v| < 2^652)
 __device__ inline double true_abs(double v, int k) { return fabs(v) * final_scale(k); }
@@ -63,11 +64,14 @@ __global__ __launch_bounds__(64) void k_live_threshold(
 }
 
 // One wave per (64 pairs, m).  The coefficients are uniform over the wave.
+// Beside the start it finds the first rows where a value passes 2^-32: below,
+// the split-FP16 form's operands are zero.  (Padded pairs have no row.)
 __global__ __launch_bounds__(64) void k_live_start(
     PairDesc *__restrict__ pairs, int npairs, const int *__restrict__ mval,
     const long long *__restrict__ moff, const double *__restrict__ mu, int lmax,
     const double *__restrict__ A, const double *__restrict__ thr, int np, int nb,
-    double2 *__restrict__ st, uint16_t *__restrict__ je, ushort2 *__restrict__ jr)
+    double2 *__restrict__ st, uint16_t *__restrict__ je, ushort2 *__restrict__ jr,
+    uint16_t *__restrict__ jq)
 {
     const int blk = blockIdx.x, i = blockIdx.y;
     const int p = blk * 64 + threadIdx.x;
@@ -83,7 +87,7 @@ __global__ __launch_bounds__(64) void k_live_start(
     int k;
     seed_mm(mu[i], s, m, u0, k);
     u0 = -u0;
-    int start = kNeverLive;
+    int start = kNeverLive, loud = kNeverLive;
     double2 v = make_double2(0.0, 0.0);
     for (int j = 0; j < len; j += kLiveRows) {
         const double s0 = u0, s1 = u1;
@@ -103,12 +107,15 @@ __global__ __launch_bounds__(64) void k_live_start(
             const double f = final_scale(sk);
             v = make_double2(s0 * f, s1 * f);
         }
+        if (p < npairs && true_abs(big, sk) > kQuiet) loud = min(loud, j / kLiveRows);
         if (fmax(fabs(u0), fabs(u1)) > kTwoS) {
             u0 *= kTwoMinusS;
             u1 *= kTwoMinusS;
             k += 1;
         }
-        if (__ballot(start == kNeverLive && p < npairs) == 0) break;
+        if (__ballot(start == kNeverLive && p < npairs) == 0 &&
+            __ballot(loud != kNeverLive) != 0)
+            break;
     }
     st[(long long)i * np + p] = v;
     je[(long long)i * np + p] = (uint16_t)start;
@@ -116,9 +123,12 @@ __global__ __launch_bounds__(64) void k_live_start(
     for (int o = 32; o >= 1; o >>= 1) {
         lo = min(lo, __shfl_xor(lo, o));
         hi = max(hi, __shfl_xor(hi, o));
+        loud = min(loud, __shfl_xor(loud, o));
     }
-    if (threadIdx.x == 0)
+    if (threadIdx.x == 0) {
         jr[(long long)i * nb + blk] = make_ushort2((unsigned short)lo, (unsigned short)hi);
+        jq[(long long)i * nb + blk] = (uint16_t)loud;
+    }
     if (start != kNeverLive) atomicMax(&pairs[p].ilim, i + 1);
 }
 
@@ -147,7 +157,8 @@ hipError_t launch_live_table(const sht_plan_s *p, double *scratch, int pmax, hip
     hipLaunchKernelGGL(k_live_start, dim3((unsigned)t.nb, (unsigned)p->nm), dim3(64), 0, st,
                        p->d_pairs, p->npairs, p->d_mval, p->d_moff, p->d_mu, p->lmax, p->d_A,
                        scratch, t.np, t.nb, const_cast<double2 *>(t.st),
-                       const_cast<uint16_t *>(t.je), const_cast<ushort2 *>(t.jr));
+                       const_cast<uint16_t *>(t.je), const_cast<ushort2 *>(t.jr),
+                       const_cast<uint16_t *>(t.jq));
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_live_rings, dim3((unsigned)((p->npairs + 255) / 256)), dim3(256), 0, st,

@@ -102,7 +102,7 @@ __device__ __forceinline__ void block16_dead_g(double x, double &ua, double &ub,
 // contraction carries, so Delta is stored as complex64.
 __device__ __forceinline__ void m_store(const MfmaTiles &tot, int i, float2 *__restrict__ delta,
                                         const PairDesc *__restrict__ pairs, int npairs, int pb,
-                                        int grp, int nmaps, int nrings, int nm, int lane)
+                                        int grp, int nmaps, int nrings, bool full, int lane)
 {
     const int hi = lane >> 5;
     const int col = lane & 31;
@@ -114,6 +114,7 @@ __device__ __forceinline__ void m_store(const MfmaTiles &tot, int i, float2 *__r
         const int pp = pb * 64 + h * 32 + col;
         if (pp < npairs) {
             const PairDesc d = pairs[pp];
+            if (!full && i >= d.ilim) continue;   // dead on the ring, not read
             const long long row = (long long)i * nrings;
             float2 *__restrict__ dn = d2 + (row + d.rn) * nmaps;
             float2 *__restrict__ ds = d2 + (row + (d.rs >= 0 ? d.rs : d.rn)) * nmaps;

@@ -63,6 +63,8 @@ struct LiveTab {
     const uint16_t *je;    // [nm][np] start row
     const ushort2 *jr;     // [nm][np / 64] least and greatest start row of 64 pairs
                            // (kNeverLive, 0 if none is live)
+    const uint16_t *jq;    // [nm][np / 64] first row from which a |u| of 64 pairs passes
+                           // 2^-32 (kNeverLive: none does)
     int np;                // ring pairs, rounded up to 512 (the most a wave takes)
     int nb;                // np / 64
 };
@@ -354,7 +356,7 @@ int f16_super_rows();
 hipError_t launch_prescale_f16x2(const sht_plan_s *p, const double *alm, void *Bb,
                                  hipStream_t st);
 hipError_t launch_legendre_mfma_f16x2(const sht_plan_s *p, const void *Bb, float2 *delta,
-                                      hipStream_t st);
+                                      bool full, hipStream_t st);
 // full: Delta is a caller's, with every mode of every ring; otherwise the plan's
 // Legendre stage wrote it and the modes dead on a ring are not read.
 hipError_t launch_ring_synth(const sht_plan_s *p, const double2 *delta, double *map, bool full,

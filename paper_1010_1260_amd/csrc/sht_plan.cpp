@@ -229,7 +229,7 @@ void free_tables(sht_plan_s *p)
                     p->d_minv, p->d_rings, p->d_pool, p->d_boff, p->d_boff16, p->d_bm16,
                     p->d_bm32, p->d_soff, p->d_sbm, p->d_Asb, p->d_pool32,
                     const_cast<double2 *>(p->live.st), const_cast<uint16_t *>(p->live.je),
-                    const_cast<ushort2 *>(p->live.jr)};
+                    const_cast<ushort2 *>(p->live.jr), const_cast<uint16_t *>(p->live.jq)};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
     for (int c = 0; c < sht::kNumSynthClasses; ++c) {
@@ -264,9 +264,10 @@ sht_status build_live_table(sht_plan_s *p, const std::vector<PairDesc> &pairs, s
     if (hipMalloc((void **)&t.st, n * sizeof *t.st) != hipSuccess) { t.st = nullptr; return SHT_ERR_OOM; }
     if (hipMalloc((void **)&t.je, n * sizeof *t.je) != hipSuccess) { t.je = nullptr; return SHT_ERR_OOM; }
     if (hipMalloc((void **)&t.jr, nj * sizeof *t.jr) != hipSuccess) { t.jr = nullptr; return SHT_ERR_OOM; }
+    if (hipMalloc((void **)&t.jq, nj * sizeof *t.jq) != hipSuccess) { t.jq = nullptr; return SHT_ERR_OOM; }
     if (hipMalloc((void **)&scratch, (size_t)p->nm * sizeof(double)) != hipSuccess)
         return SHT_ERR_OOM;
-    *acc += n * (sizeof *t.st + sizeof *t.je) + nj * sizeof *t.jr;
+    *acc += n * (sizeof *t.st + sizeof *t.je) + nj * (sizeof *t.jr + sizeof *t.jq);
     const bool ok = sht::launch_live_table(p, scratch, pmax, nullptr) == hipSuccess &&
                     hipDeviceSynchronize() == hipSuccess;
     (void)hipFree(scratch);
@@ -396,7 +397,7 @@ static sht_status legendre_stage(sht_plan_t p, const double *alm, void *ws, void
     } else if (p->precision == SHT_F16X2_MFMA) {
         e = sht::launch_prescale_f16x2(p, alm, ws, st);
         if (e == hipSuccess && ev_mid) e = hipEventRecord(ev_mid, st);
-        if (e == hipSuccess) e = sht::launch_legendre_mfma_f16x2(p, ws, d32, st);
+        if (e == hipSuccess) e = sht::launch_legendre_mfma_f16x2(p, ws, d32, full, st);
     } else {
         e = sht::launch_prescale(p, alm, (double2 *)ws, st);
         if (e == hipSuccess && ev_mid) e = hipEventRecord(ev_mid, st);
