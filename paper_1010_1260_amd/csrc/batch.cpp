@@ -151,7 +151,7 @@ sht_status sht_plan_batch(sht_batch_t *out, const sht_plan_t *plans, int32_t n)
         const sht_plan_s *p = plans[i];
         BatchMap &m = maps[i];
         std::memset(&m, 0, sizeof m);
-        m.pairs = p->d_pairs; m.mval = p->d_mval; m.moff = p->d_moff; m.mu = p->d_mu;
+        m.pairs = p->d_pairs; m.mval = p->d_mval; m.moff = p->d_moff;
         m.A = p->d_A; m.cn = p->d_cn; m.minv = p->d_minv; m.rings = p->d_rings;
         m.pool = p->d_pool;
         m.live = p->live;

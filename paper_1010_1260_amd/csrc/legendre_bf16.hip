@@ -22,12 +22,18 @@
 // fragment is passed first, so the tiles hold the transposed product as in
 // the FP32 form, and the same epilogue stores Delta.
 //
-// Work split.  As in the FP32 form: a workgroup of four waves takes 256 ring
-// pairs and an m-pair; per super-block of 128 l-rows (4 blocks of 32) the
-// coefficients A_l and the packed B blocks are copied global-to-LDS while the
-// previous super-block is multiplied; a workgroup runs the recurrence alone
-// while all its lanes are below 2^-400, then a masked path for its first live
-// super-block, then a path with no mask and no rescaling.
+// Work split.  As in the split-FP16 form: one wave per (64 ring pairs, m-pair,
+// 16 maps), two waves per SIMD, nothing shared between waves; each starts at
+// its own first live row (live.hip), reads the packed coefficients straight
+// into its fragments (from L2) and A_l through scalar registers, and issues
+// the products of a parity among the vector work that follows it.
+//
+// Bound: vector issue (300 vector instructions and 24 MFMA per 32 rows, which
+// overlap).  16 maps at l_max 1024 / nside 512: 266 us, the whole transform at
+// l_max 4096 / nside 2048 18.2 ms; 340 us and 21.9 ms as workgroups of four
+// waves with the coefficients in LDS, every row from l = m on.
+#include <type_traits>
+
 #include "mixed_common.h"
 
 namespace sht {
@@ -35,15 +41,11 @@ namespace {
 
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
-constexpr int kWaves = 4;                   // waves (64 ring pairs each) sharing an m
-constexpr int kThreads = 64 * kWaves;
 constexpr int kBlkSteps = 32;               // l-rows per block (K = 16 per parity)
 // Packed B layout per m block: [parity 2][level 3][half 2][column 32] x 8 bf16.
 constexpr int kBlkElems = 2 * 3 * 2 * 32;   // 16-byte elements per block
 constexpr int kSuper = 4;                   // blocks per super-block: 64 terms per parity
 constexpr int kSuperRows = kSuper * kBlkSteps;
-constexpr int kABytes = kSuperRows * 8;     // A of a super-block in LDS
-constexpr int kBufBytes = kABytes + kSuper * kBlkElems * 16;
 
 __device__ inline void split3(float x, __bf16 &h, __bf16 &m, __bf16 &l)
 {
@@ -144,319 +146,192 @@ __device__ __forceinline__ v16f mfma_bf(const v4u &b, const v4u &a, const v16f &
                                                    __builtin_bit_cast(v8bf, a), c, 0, 0, 0);
 }
 
+// The fragments of one parity of a block (both column halves, three parts)
+// and its coefficient parts.
+struct Frags {
+    v4u H0, M0, L0, H1, M1, L1, B[3];
+};
+
 // The 16 same-parity values of this lane (K = 0..15 of its ring pair) ->
-// fragments of both column halves, then the six products against the
-// lane's coefficient parts B[level].
-__device__ __forceinline__ void parity_mfma(const float (&v)[16], const v4u (&B)[3], v16f &acc0,
-                                            v16f &acc1)
+// fragments of both column halves.
+__device__ __forceinline__ void split_parity(const float (&v)[16], Frags &f)
 {
     float f0[8], f1[8];
 #pragma unroll
     for (int t = 0; t < 8; ++t) swap_halves(v[t], v[t + 8], f0[t], f1[t]);
-    v4u H0, M0, L0, H1, M1, L1;
-    split_pack(f0, H0, M0, L0);
-    split_pack(f1, H1, M1, L1);
-    acc0 = mfma_bf(B[0], H0, acc0);
-    acc1 = mfma_bf(B[0], H1, acc1);
-    acc0 = mfma_bf(B[0], M0, acc0);
-    acc1 = mfma_bf(B[0], M1, acc1);
-    acc0 = mfma_bf(B[1], H0, acc0);
-    acc1 = mfma_bf(B[1], H1, acc1);
-    acc0 = mfma_bf(B[0], L0, acc0);
-    acc1 = mfma_bf(B[0], L1, acc1);
-    acc0 = mfma_bf(B[1], M0, acc0);
-    acc1 = mfma_bf(B[1], M1, acc1);
-    acc0 = mfma_bf(B[2], H0, acc0);
-    acc1 = mfma_bf(B[2], H1, acc1);
+    split_pack(f0, f.H0, f.M0, f.L0);
+    split_pack(f1, f.H1, f.M1, f.L1);
 }
 
-// One block of 32 l-rows from LDS: Ab = its 32 coefficients (as 16 pairs),
-// Bs = the block's packed coefficient parts.  SEED: rows 0..31 of the m,
-// started from P_mm (ua) with P_{m+1,m} = A_1 x P_mm.  MASK: lanes below
-// k = 0 contribute 0, and the scaled exponents are checked every 16 rows.
-template <bool MASK, bool SEED>
-__device__ __forceinline__ void block32(double x, double &ua, double &ub, int &k,
-                                        const double2 *__restrict__ Ab,
-                                        const v4u *__restrict__ Bs, int lane, MfmaTiles &acc)
+// Products k0..k1 - 1 (of 12) of a parity, against the lane's coefficient
+// parts.  ZERO: the first pair starts the sums.
+template <int k0, int k1, bool ZERO>
+__device__ __forceinline__ void products(const Frags &f, v16f &acc0, v16f &acc1)
 {
-    const int hi = lane >> 5, col = lane & 31;
+    if constexpr (k0 < k1) {
+        constexpr int t = k0 / 2;   // A_h B_h, A_m B_h, A_h B_m, A_l B_h, A_m B_m, A_h B_l
+        constexpr int lev = t == 2 || t == 4 ? 1 : t == 5 ? 2 : 0;
+        const v4u &b = f.B[lev];
+        if constexpr (k0 & 1) {
+            const v4u &a = t == 1 || t == 4 ? f.M1 : t == 3 ? f.L1 : f.H1;
+            acc1 = mfma_bf(b, a, ZERO && k0 == 1 ? v16f{} : acc1);
+        } else {
+            const v4u &a = t == 1 || t == 4 ? f.M0 : t == 3 ? f.L0 : f.H0;
+            acc0 = mfma_bf(b, a, ZERO && k0 == 0 ? v16f{} : acc0);
+        }
+        products<k0 + 1, k1, ZERO>(f, acc0, acc1);
+    }
+}
+
+// One block of 32 l-rows from row r0 on (see the split-FP16 form).  FIRST:
+// nothing is left from the previous block of the super-block, the sums start
+// here; SECOND: what is left starts the odd sums.  B: the block's packed
+// coefficients (the lane's first); a0: the coefficients of rows r0..r0 + 15
+// on entry, of rows rn..rn + 15 on return.
+template <bool FIRST, bool SECOND>
+__device__ __forceinline__ void block32(Lane &l, const double2 *stash, int r0, int hi8, CDp Am,
+                                        int rn, double (&a0)[16], const v4u *__restrict__ B,
+                                        Frags &odd, MfmaTiles &acc)
+{
     float ve[16], vo[16];
-    bool live = !MASK || k == 0;
+    double a1[16];
+    scalars_arrived();
+    scalar_rows<16>(a1, Am + r0 + 16);
+    __builtin_amdgcn_sched_barrier(0);
+    Frags even;
 #pragma unroll
-    for (int t = 0; t < 16; ++t) {
-        const double2 a = Ab[t];
-        double u0, u1;
-        if (SEED && t == 0) {
-            u0 = ua;
-            u1 = (a.y * x) * ua;
-        } else {
-            u0 = fma(a.x * x, ub, -ua);
-            u1 = fma(a.y * x, u0, -ub);
-        }
-        ua = u0;
-        ub = u1;
-        ve[t] = MASK ? opnd(u0, live) : (float)u0;
-        vo[t] = MASK ? opnd(u1, live) : (float)u1;
-        if (MASK && (t == 7 || t == 15)) {
-            rescale_mixed(ua, ub, k);
-            if (t == 7) live = k == 0;
-        }
-    }
-    v4u BE[3], BO[3];
+    for (int lev = 0; lev < 3; ++lev) even.B[lev] = B[lev * 64];
+    enter(l, stash, r0, hi8);
+    rows8(l, a0, ve, vo);
+    if constexpr (!FIRST) products<0, 3, SECOND>(odd, acc.o0, acc.o1);
+    enter(l, stash, r0 + 8, hi8);
+    rows8(l, a0 + 8, ve + 4, vo + 4);
+    if constexpr (!FIRST) products<3, 6, SECOND>(odd, acc.o0, acc.o1);
+    scalars_arrived();
+    scalar_rows<16>(a0, Am + rn);
+    __builtin_amdgcn_sched_barrier(0);
+    enter(l, stash, r0 + 16, hi8);
+    rows8(l, a1, ve + 8, vo + 8);
+    if constexpr (!FIRST) products<6, 9, SECOND>(odd, acc.o0, acc.o1);
+    enter(l, stash, r0 + 24, hi8);
+    rows8(l, a1 + 8, ve + 12, vo + 12);
+    if constexpr (!FIRST) products<9, 12, SECOND>(odd, acc.o0, acc.o1);
 #pragma unroll
-    for (int lev = 0; lev < 3; ++lev) {
-        BE[lev] = Bs[((0 * 3 + lev) * 2 + hi) * 32 + col];
-        BO[lev] = Bs[((1 * 3 + lev) * 2 + hi) * 32 + col];
-    }
-    parity_mfma(ve, BE, acc.e0, acc.e1);
-    parity_mfma(vo, BO, acc.o0, acc.o1);
-}
-
-// A block in which no lane of the wave has reached k = 0: the recurrence
-// alone (same arithmetic as block32, so the state is bitwise the same).
-template <bool MASK, bool SEED>
-__device__ __forceinline__ void block32_dead(double x, double &ua, double &ub, int &k,
-                                             const double2 *__restrict__ Ab)
-{
+    for (int lev = 0; lev < 3; ++lev) odd.B[lev] = B[(3 + lev) * 64];
+    split_parity(ve, even);
+    products<0, 12, FIRST>(even, acc.e0, acc.e1);
+    split_parity(vo, odd);
+    // one product to eight vector instructions (8 exchanges, 88 of the split)
 #pragma unroll
-    for (int t = 0; t < 16; ++t) {
-        const double2 a = Ab[t];
-        double u0, u1;
-        if (SEED && t == 0) {
-            u0 = ua;
-            u1 = (a.y * x) * ua;
-        } else {
-            u0 = fma(a.x * x, ub, -ua);
-            u1 = fma(a.y * x, u0, -ub);
-        }
-        ua = u0;
-        ub = u1;
-        if (MASK && (t == 7 || t == 15)) rescale_mixed(ua, ub, k);
+    for (int k = 0; k < 12; ++k) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
     }
-}
-
-// Copy of super-block sb of an m (its 4 packed B blocks and 128
-// coefficients) global-to-LDS into `buf`; it completes at the workgroup's
-// next barrier.  Past the m's last block or row the copy reads
-// neighbouring data or the padding after the tables, which lands only in
-// rows that are never used or are multiplied by B = 0.
-__device__ __forceinline__ void super_dma(char *buf, const v4u *__restrict__ Bm,
-                                          const double *__restrict__ Am, int sb, int tid)
-{
-    // the lane addresses are recomputed at every copy (a few integer
-    // operations) rather than kept live, and spilled, across the loop
-    asm volatile("" : "+v"(tid));
-    const v4u *src = Bm + (long long)sb * kSuper * kBlkElems;
-    v4u *dst = reinterpret_cast<v4u *>(buf + kABytes);
-#pragma unroll
-    for (int c = 0; c < kSuper * kBlkElems / kThreads; ++c) {
-        const int w = tid + kThreads * c;
-        __builtin_amdgcn_global_load_lds(src + w, dst + w, 16, 0, 0);
-    }
-    const unsigned *asrc = reinterpret_cast<const unsigned *>(Am + (long long)sb * kSuperRows);
-    __builtin_amdgcn_global_load_lds(asrc + tid, reinterpret_cast<unsigned *>(buf) + tid, 4, 0, 0);
-}
-
-template <bool MASK>
-__device__ __forceinline__ void super_compute(double x, double &ua, double &ub, int &k,
-                                              const char *cur, char *nxt, bool more, int sb,
-                                              int nb, bool seed, const v4u *__restrict__ Bm,
-                                              const double *__restrict__ Am, int tid,
-                                              MfmaTiles &acc, MfmaTiles &tot)
-{
-    const int lane = tid & 63;
-    const double2 *As = reinterpret_cast<const double2 *>(cur);
-    const v4u *Bs = reinterpret_cast<const v4u *>(cur + kABytes);
-    zero_tiles(acc);
-    if (more) super_dma(nxt, Bm, Am, sb + 1, tid);
-    if (seed) {
-        if (wave_any(k == 0))
-            block32<true, true>(x, ua, ub, k, As, Bs, lane, acc);
-        else
-            block32_dead<true, true>(x, ua, ub, k, As);
-    } else if (!MASK || wave_any(k == 0)) {
-        block32<MASK, false>(x, ua, ub, k, As, Bs, lane, acc);
-    } else {
-        block32_dead<MASK, false>(x, ua, ub, k, As);
-    }
-    for (int q = 1; q < nb; ++q) {
-        if (!MASK || wave_any(k == 0))
-            block32<MASK, false>(x, ua, ub, k, As + (kBlkSteps / 2) * q, Bs + kBlkElems * q,
-                                 lane, acc);
-        else
-            block32_dead<MASK, false>(x, ua, ub, k, As + (kBlkSteps / 2) * q);
-    }
-    add_tiles(tot, acc);
-}
-
-// A thread's share of the first live super-block of an m (register staged).
-struct SuperStage {
-    v4u b[kSuper * kBlkElems / kThreads];
-    unsigned a;
-};
-
-__device__ __forceinline__ void super_stage_load(SuperStage &g, const v4u *__restrict__ Bm,
-                                                 int nblk, const double *__restrict__ Am,
-                                                 int len, int sb, int tid)
-{
-    const int b0 = sb * kSuper;
-    const int nw = min(kSuper, nblk - b0) * kBlkElems;  // 16-byte words present
-    const v4u *__restrict__ src = Bm + (long long)b0 * kBlkElems;
-#pragma unroll
-    for (int c = 0; c < kSuper * kBlkElems / kThreads; ++c) {
-        const int w = tid + kThreads * c;
-        g.b[c] = (w < nw) ? src[w] : v4u{};
-    }
-    const int r = sb * kSuperRows + (tid >> 1);  // dword tid of the 128 coefficients
-    g.a = (r < len) ? reinterpret_cast<const unsigned *>(Am + r)[tid & 1] : 0u;
-}
-
-__device__ __forceinline__ void super_stage_store(const SuperStage &g, char *buf, int tid)
-{
-    v4u *B = reinterpret_cast<v4u *>(buf + kABytes);
-#pragma unroll
-    for (int c = 0; c < kSuper * kBlkElems / kThreads; ++c) B[tid + kThreads * c] = g.b[c];
-    reinterpret_cast<unsigned *>(buf)[tid] = g.a;
 }
 
 struct MState {
-    int m, i, len, nblk, nsb, sb0;
-    const double *Am;
-    const v4u *Bm;
-    double ua, ub;
-    int k;
+    int i, nblk, q0;     // blocks of the m, the first one with a live row of the wave
+    int hi8;             // the last row at which a pair starts
+    const double *Am;    // padded coefficients of the m, per super-block
+    const v4u *Bm;       // its packed blocks, the lane's first entry
+    Lane l;
+    double a[16];
 };
 
-// Seed and phase 1 (recurrence alone while the whole workgroup is below
-// 2^-400), then the register copy of the first live super-block.
-__device__ void m_begin(MState &st, SuperStage &g, int i, const int *__restrict__ mval,
-                        const long long *__restrict__ soff, const long long *__restrict__ boff,
-                        const double *__restrict__ mu, int lmax, const double *__restrict__ Asb,
-                        const v4u *__restrict__ Bg, double x, double s, int tid)
+// Start of an m: the lane's entry of the start table and the first live
+// block's coefficients.
+__device__ __forceinline__ void m_begin(MState &st, double2 *stash, int i,
+                                        const int *__restrict__ mval,
+                                        const long long *__restrict__ boff,
+                                        const long long *__restrict__ soff, int lmax,
+                                        const LiveTab &lt, const double *__restrict__ Asb,
+                                        const v4u *__restrict__ Bg, int pb, int lane)
 {
     st.i = i;
-    st.m = mval[i];
-    st.len = lmax - st.m + 1;
-    st.nblk = (st.len + kBlkSteps - 1) / kBlkSteps;
-    st.nsb = (st.nblk + kSuper - 1) / kSuper;
-    // coefficients from the per-super-block copy, zero past the m's last row:
-    // the copies of a super-block run past the m's end, and with A = 0 there
-    // the recurrence of the unused rows stays bounded (u_l = -u_{l-2})
-    st.Am = Asb + soff[i] * kSuperRows;
-    st.Bm = Bg + boff[i] * kBlkElems;
-    st.ub = 0.0;
-    seed_mm(mu[i], s, st.m, st.ua, st.k);
-    if (st.k == 0 && fabs(st.ua) < kEmergeTrue) {
-        st.ua *= kTwoS;
-        st.k = -1;
-    }
-    int sb0 = 0;
-    while (sb0 < st.nsb && !__syncthreads_or(st.k == 0)) {
-        const int n16 = min(kSuperRows, st.len - sb0 * kSuperRows + 15) / 16;
-        for (int q = 0; q < n16; ++q) {
-            const int r0 = sb0 * kSuperRows + q * 16;
-            if (r0 == 0)
-                block16_dead_g<true>(x, st.ua, st.ub, st.Am, r0);
-            else
-                block16_dead_g<false>(x, st.ua, st.ub, st.Am, r0);
-            rescale_mixed(st.ua, st.ub, st.k);
-        }
-        ++sb0;
-    }
-    st.sb0 = sb0;
-    if (sb0 < st.nsb) super_stage_load(g, st.Bm, st.nblk, st.Am, st.len, sb0, tid);
+    const long long e = (long long)i * lt.np + pb * 64 + lane;
+    const double2 v = lt.st[e];
+    st.l.je = lt.je[e];
+    const int jr = ((CIp)(lt.jr + (long long)i * lt.nb))[pb];
+    const int len = lmax - ((CIp)mval)[i] + 1;
+    st.nblk = (len + kBlkSteps - 1) / kBlkSteps;
+    st.q0 = (jr & 0xffff) * kLiveRows / kBlkSteps;
+    st.hi8 = (int)((unsigned)jr >> 16) * kLiveRows;
+    st.Am = Asb + ((CLp)soff)[i] * kSuperRows;
+    st.Bm = Bg + ((CLp)boff)[i] * kBlkElems + lane;
+    st.l.ua = 0.0;
+    st.l.ub = 0.0;
+    *stash = v;
+    if (st.q0 < st.nblk) scalar_rows<16>(st.a, (CDp)st.Am + st.q0 * kBlkSteps);
 }
 
-__device__ __forceinline__ void m_commit(const MState &st, const SuperStage &g, char *ldsA,
-                                         int tid)
+__device__ __forceinline__ void m_compute(MState &st, const double2 *stash, MfmaTiles &tot)
 {
-    if (st.sb0 < st.nsb) super_stage_store(g, ldsA, tid);
-    __syncthreads();
-}
-
-__device__ __forceinline__ void m_step(MState &st, int sb, const char *cur, char *nxt, double x,
-                                       int tid, bool &mask, MfmaTiles &acc, MfmaTiles &tot)
-{
-    const bool more = sb + 1 < st.nsb;
-    const int nb = min(kSuper, st.nblk - sb * kSuper);
-    if (mask) {
-        super_compute<true>(x, st.ua, st.ub, st.k, cur, nxt, more, sb, nb, sb == 0, st.Bm,
-                            st.Am, tid, acc, tot);
-        mask = wave_any(st.k < 0);
-    } else {
-        super_compute<false>(x, st.ua, st.ub, st.k, cur, nxt, more, sb, nb, false, st.Bm,
-                             st.Am, tid, acc, tot);
-    }
-    __syncthreads();
-}
-
-__device__ __forceinline__ void m_compute(MState &st, char *ldsA, char *ldsB, double x, int tid,
-                                          MfmaTiles &tot)
-{
-    MfmaTiles acc;
     zero_tiles(tot);
-    bool mask = true;
-    for (int sb = st.sb0; sb < st.nsb; sb += 2) {
-        m_step(st, sb, ldsA, ldsB, x, tid, mask, acc, tot);
-        if (sb + 1 < st.nsb) m_step(st, sb + 1, ldsB, ldsA, x, tid, mask, acc, tot);
+    for (int q = st.q0; q < st.nblk;) {
+        const int end = min((q / kSuper + 1) * kSuper, st.nblk);   // of the super-block
+        Frags odd;
+        MfmaTiles acc;
+        // the look-ahead stays at the m's last block
+        auto step = [&](auto first, auto second) {
+            block32<decltype(first)::value, decltype(second)::value>(
+                st.l, stash, q * kBlkSteps, st.hi8, (CDp)st.Am,
+                min(q + 1, st.nblk - 1) * kBlkSteps, st.a, st.Bm + (long long)q * kBlkElems, odd,
+                acc);
+            ++q;
+        };
+        step(std::true_type(), std::false_type());
+        if (q < end) {
+            step(std::false_type(), std::true_type());
+            while (q < end) step(std::false_type(), std::false_type());
+            products<0, 12, false>(odd, acc.o0, acc.o1);
+        } else {
+            products<0, 12, true>(odd, acc.o0, acc.o1);
+        }
+        add_tiles(tot, acc);
     }
 }
 
-__global__ __launch_bounds__(kThreads, 2) void k_legendre_mfma_bf16x3(
-    const PairDesc *__restrict__ pairs, int npairs, int pgroups,
-    const int *__restrict__ mval, const long long *__restrict__ soff,
-    const long long *__restrict__ boff, const double *__restrict__ mu, int nm, int nmpairs,
-    int lmax, const double *__restrict__ Asb, const v4u *__restrict__ Bb, long long nblocks,
-    float2 *__restrict__ delta, int nrings, int nmaps, long long total)
+__global__ __launch_bounds__(64, 2) void k_legendre_mfma_bf16x3(
+    const PairDesc *__restrict__ pairs, int npairs, LiveTab lt, int pblocks,
+    const int *__restrict__ mval, const long long *__restrict__ boff,
+    const long long *__restrict__ soff, int nm, int nmpairs, int lmax,
+    const double *__restrict__ Asb, const v4u *__restrict__ Bb, long long nblocks,
+    float2 *__restrict__ delta, int nrings, int nmaps, int groups, int full)
 {
-    __shared__ __attribute__((aligned(16))) char ldsA[kBufBytes];
-    __shared__ __attribute__((aligned(16))) char ldsB[kBufBytes];
-    const long long L = xcd_logical(blockIdx.x, total);
-    const int pg = (int)(L % pgroups);
-    const long long rest = L / pgroups;
-    const int q = (int)(rest % nmpairs);
-    const int grp = (int)(rest / nmpairs);
-    const int tid = threadIdx.x;
-    const int pb = pg * kWaves + (tid >> 6);
-    const int p = pb * 64 + (tid & 63);
-    double x = 0.0, s = 0.0;
-    if (p < npairs) {
-        const PairDesc d = pairs[p];
-        x = d.x; s = d.s;
-    }
+    __shared__ double2 start[64];
+    // XCD x takes the m-pairs q = x mod 8 (see the FP64 kernel)
+    const int xcd = (int)(blockIdx.x % 8);
+    const int w = (int)(blockIdx.x / 8);
+    const int pb = w % pblocks;
+    const int rest = w / pblocks;
+    const int grp = rest % groups;
+    const int q = xcd + 8 * (rest / groups);
+    if (q >= nmpairs) return;
+    const int lane = threadIdx.x;
+    double2 *stash = start + lane;
     const v4u *Bg = Bb + (long long)grp * nblocks * kBlkElems;
     MState st;
-    SuperStage g;
     MfmaTiles tot;
-    m_begin(st, g, q, mval, soff, boff, mu, lmax, Asb, Bg, x, s, tid);
-    m_commit(st, g, ldsA, tid);
-    m_compute(st, ldsA, ldsB, x, tid, tot);
+    st.l.x = pairs[pb * 64 + lane].x;
+    m_begin(st, stash, q, mval, boff, soff, lmax, lt, Asb, Bg, pb, lane);
+    m_compute(st, stash, tot);
     const int i1 = st.i;
     const int i2 = nm - 1 - q;
     const bool two = i2 != q;
-    if (two) m_begin(st, g, i2, mval, soff, boff, mu, lmax, Asb, Bg, x, s, tid);
-    m_store(tot, i1, delta, pairs, npairs, pb, grp, nmaps, nrings, true, tid & 63);
+    if (two) m_begin(st, stash, i2, mval, boff, soff, lmax, lt, Asb, Bg, pb, lane);
+    m_store(tot, i1, delta, pairs, npairs, pb, grp, nmaps, nrings, full != 0, lane);
     if (two) {
-        m_commit(st, g, ldsA, tid);
-        m_compute(st, ldsA, ldsB, x, tid, tot);
-        m_store(tot, st.i, delta, pairs, npairs, pb, grp, nmaps, nrings, true, tid & 63);
+        m_compute(st, stash, tot);
+        m_store(tot, st.i, delta, pairs, npairs, pb, grp, nmaps, nrings, full != 0, lane);
     }
 }
 
 }  // namespace
 
-long long bf16_blocks(const sht_plan_s *p)
-{
-    long long nb = 0;
-    for (int i = 0; i < p->nm; ++i) nb += (p->lmax - p->mval[i] + 1 + kBlkSteps - 1) / kBlkSteps;
-    return nb;
-}
-
 size_t bf16_bytes(const sht_plan_s *p)
 {
     const size_t groups = (size_t)((p->nmaps + 15) / 16);
-    // plus one super-block: the copies of an m's last super-block may read past it
-    return (groups * (size_t)bf16_blocks(p) + kSuper) * kBlkElems * 16;
+    return groups * (size_t)p->nblk32 * kBlkElems * 16;
 }
 
 hipError_t launch_prescale_bf16x3(const sht_plan_s *p, const double *alm, void *Bb,
@@ -464,7 +339,7 @@ hipError_t launch_prescale_bf16x3(const sht_plan_s *p, const double *alm, void *
 {
     const long long m0len = (p->mval[0] == 0) ? (p->lmax + 1) : 0;
     const int groups = (p->nmaps + 15) / 16;
-    const long long nblocks = bf16_blocks(p);
+    const long long nblocks = p->nblk32;
     const long long nwg = (nblocks + kPreBlocks - 1) / kPreBlocks;
     if (nwg <= 0 || nwg > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(k_prescale_bf16x3, dim3((unsigned)nwg, (unsigned)groups), dim3(256), 0, st,
@@ -475,21 +350,19 @@ hipError_t launch_prescale_bf16x3(const sht_plan_s *p, const double *alm, void *
 }
 
 hipError_t launch_legendre_mfma_bf16x3(const sht_plan_s *p, const void *Bb, float2 *delta,
-                                       hipStream_t st)
+                                       bool full, hipStream_t st)
 {
     const int pblocks = (p->npairs + 63) / 64;
-    const int pgroups = (pblocks + kWaves - 1) / kWaves;
     const int nmpairs = (p->nm + 1) / 2;
     const int groups = (p->nmaps + 15) / 16;
-    const long long total = (long long)pgroups * nmpairs * groups;
+    const long long total = 8LL * ((nmpairs + 7) / 8) * pblocks * groups;
     // the plan's zero-padded coefficient copy has the super-block length of this kernel
     if (f16_super_rows() != kSuperRows) return hipErrorInvalidConfiguration;
     if (total <= 0 || total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(k_legendre_mfma_bf16x3, dim3((unsigned)total), dim3(kThreads), 0, st,
-                       p->d_pairs, p->npairs, pgroups, p->d_mval, p->d_soff, p->d_boff, p->d_mu, p->nm,
-                       nmpairs, p->lmax, p->d_Asb, reinterpret_cast<const v4u *>(Bb),
-                       bf16_blocks(p), delta, p->nrings, p->nmaps,
-                       total);
+    hipLaunchKernelGGL(k_legendre_mfma_bf16x3, dim3((unsigned)total), dim3(64), 0, st,
+                       p->d_pairs, p->npairs, p->live, pblocks, p->d_mval, p->d_boff, p->d_soff,
+                       p->nm, nmpairs, p->lmax, p->d_Asb, reinterpret_cast<const v4u *>(Bb),
+                       p->nblk32, delta, p->nrings, p->nmaps, groups, full ? 1 : 0);
     return hipGetLastError();
 }
 

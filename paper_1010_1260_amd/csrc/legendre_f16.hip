@@ -246,47 +246,12 @@ __device__ __forceinline__ void all_products(const Frags &f, v16f &acc0, v16f &a
     product<5, ZERO>(f, acc0, acc1);
 }
 
-// A lane's recurrence on one m: zero until its start row, where it takes the
-// start table's values (`stash`, its LDS slot).
-struct Lane {
-    double x, ua, ub;
-    int je;              // start row, units of kLiveRows
-};
-
-// 8 rows from row r on (coefficients a), as FP32 values of both parities.
-__device__ __forceinline__ void rows8(Lane &l, const double *a, float *ve, float *vo)
-{
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const double u0 = fma(a[2 * t] * l.x, l.ub, -l.ua);
-        const double u1 = fma(a[2 * t + 1] * l.x, u0, -l.ub);
-        l.ua = u0;
-        l.ub = u1;
-        ve[t] = (float)u0;
-        vo[t] = (float)u1;
-    }
-}
-
 __device__ __forceinline__ void rows8_quiet(Lane &l, const double *a)
 {
 #pragma unroll
     for (int t = 0; t < 8; t += 2) {
         l.ua = fma(a[t] * l.x, l.ub, -l.ua);
         l.ub = fma(a[t + 1] * l.x, l.ua, -l.ub);
-    }
-}
-
-// Lanes that start at row r take their values.  `last`: no lane of the wave
-// starts after it (uniform).
-__device__ __forceinline__ void enter(Lane &l, const double2 *stash, int r, int last)
-{
-    if (r <= last) {
-        asm volatile("");   // a branch of its own, around the lane compare too
-        if (l.je == r / kLiveRows) {
-            const double2 v = *stash;
-            l.ua = v.x * kPScale;
-            l.ub = v.y * kPScale;
-        }
     }
 }
 
@@ -327,19 +292,19 @@ __device__ __forceinline__ void block32(Lane &l, const double2 *stash, int r0, i
     even.B1 = B.b[0][1];
     const v4u bo0 = B.b[1][0], bo1 = B.b[1][1];
     B.load(Bn);
-    enter(l, stash, r0, hi8);
+    enter(l, stash, r0, hi8, kPScale);
     rows8(l, a0, ve, vo);
     if constexpr (!FIRST) { product<0, SECOND>(odd, acc.o0, acc.o1); product<1, SECOND>(odd, acc.o0, acc.o1); }
-    enter(l, stash, r0 + 8, hi8);
+    enter(l, stash, r0 + 8, hi8, kPScale);
     rows8(l, a0 + 8, ve + 4, vo + 4);
     if constexpr (!FIRST) product<2, SECOND>(odd, acc.o0, acc.o1);
     scalars_arrived();
     scalar_rows<16>(a0, Am + rn);
     __builtin_amdgcn_sched_barrier(0);
-    enter(l, stash, r0 + 16, hi8);
+    enter(l, stash, r0 + 16, hi8, kPScale);
     rows8(l, a1, ve + 8, vo + 8);
     if constexpr (!FIRST) { product<3, SECOND>(odd, acc.o0, acc.o1); product<4, SECOND>(odd, acc.o0, acc.o1); }
-    enter(l, stash, r0 + 24, hi8);
+    enter(l, stash, r0 + 24, hi8, kPScale);
     rows8(l, a1 + 8, ve + 12, vo + 12);
     if constexpr (!FIRST) product<5, SECOND>(odd, acc.o0, acc.o1);
     split_parity(ve, even);
@@ -390,16 +355,16 @@ __device__ __forceinline__ void block32_quiet(Lane &l, const double2 *stash, int
     scalars_arrived();
     scalar_rows<16>(a1, Am + r0 + 16);
     __builtin_amdgcn_sched_barrier(0);
-    enter(l, stash, r0, hi8);
+    enter(l, stash, r0, hi8, kPScale);
     rows8_quiet(l, a0);
-    enter(l, stash, r0 + 8, hi8);
+    enter(l, stash, r0 + 8, hi8, kPScale);
     rows8_quiet(l, a0 + 8);
     scalars_arrived();
     scalar_rows<16>(a0, Am + rn);
     __builtin_amdgcn_sched_barrier(0);
-    enter(l, stash, r0 + 16, hi8);
+    enter(l, stash, r0 + 16, hi8, kPScale);
     rows8_quiet(l, a1);
-    enter(l, stash, r0 + 24, hi8);
+    enter(l, stash, r0 + 24, hi8, kPScale);
     rows8_quiet(l, a1 + 8);
 }
 

@@ -1,7 +1,6 @@
-// Pieces shared by the two mixed-precision Legendre kernels (FP32 and
-// 3-way split BF16 matrix-core operands): the lane state rule of the
-// recurrence, the exchange of fragment halves, the output tiles and the
-// Delta epilogue.
+// Pieces shared by the mixed-precision Legendre kernels: the lanes' recurrence,
+// and, for the two split forms, the exchange of fragment halves, the output
+// tiles and the Delta epilogue.
 #pragma once
 
 #include "recurrence.h"
@@ -14,32 +13,6 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef unsigned int v2u __attribute__((ext_vector_type(2)));
 typedef unsigned int v4u __attribute__((ext_vector_type(4)));
-
-// Lane state of the mixed kernels.  u = P_l / c_l is carried as v 2^(512 k),
-// k <= 0, as in the FP64 kernel, but a lane moves up to k = 0 as soon as its
-// true value passes 2^-400 (|v| > 2^112 at k = -1).  Checked every 16 steps
-// (growth below 2^140), every lane with k < 0 then holds a true value below
-// 2^-260, which is zero in FP32: the matrix operand is (float)v for k = 0 and
-// 0 otherwise.  Values at k = 0 are bounded by sqrt((2l+1)/4pi)/c_l < 2^9
-// (addition theorem), so a wave whose lanes all reached k = 0 -- almost every
-// wave past its first l-steps -- needs neither the mask nor any rescaling.
-constexpr double kEmerge = 0x1p112;
-constexpr double kEmergeTrue = 0x1p-400;
-
-__device__ inline void rescale_mixed(double &ua, double &ub, int &k)
-{
-    if (k < 0) {
-        const double lim = (k == -1) ? kEmerge : kTwoS;
-        if (fmax(fabs(ua), fabs(ub)) > lim) {
-            ua *= kTwoMinusS; ub *= kTwoMinusS;
-            k += 1;
-        }
-    }
-}
-
-__device__ inline bool wave_any(bool c) { return __builtin_amdgcn_ballot_w64(c) != 0; }
-
-__device__ inline float opnd(double u, bool live) { return live ? (float)u : 0.0f; }
 
 __device__ inline void swap_halves(float a, float b, float &lo, float &hi)
 {
@@ -63,32 +36,42 @@ __device__ __forceinline__ void add_tiles(MfmaTiles &tot, const MfmaTiles &acc)
     tot.e0 += acc.e0; tot.e1 += acc.e1; tot.o0 += acc.o0; tot.o1 += acc.o1;
 }
 
-// 16 rows of the recurrence alone, the coefficients read straight from the
-// table, used while the whole workgroup is still below 2^-400 (nothing
-// staged in LDS; every matrix operand would be 0).  The
-// block may run past the m's last row (the table is padded by 16 entries):
-// the state is then never used, since the m has no live rows left.
-template <bool SEED>
-__device__ __forceinline__ void block16_dead_g(double x, double &ua, double &ub,
-                                               const double *__restrict__ Am, int r0)
+// A lane's recurrence on one m: zero until its start row, where it takes the
+// start table's values (`stash`, its LDS slot).  Before it the true values are
+// below 2^-180, which is zero in FP32, so a lane's operands need no mask, and
+// from there on they are plain FP64 values bounded by sqrt((2l+1)/4pi)/c_l <
+// 2^9 (addition theorem).
+struct Lane {
+    double x, ua, ub;
+    int je;              // start row, units of kLiveRows
+};
+
+// 8 rows from row r on (coefficients a), as FP32 values of both parities.
+__device__ __forceinline__ void rows8(Lane &l, const double *a, float *ve, float *vo)
 {
-    double a[16];
-#pragma unroll
-    for (int t = 0; t < 16; ++t) a[t] = Am[r0 + t];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-        double u0, u1;
-        if (SEED && t == 0) {
-            u0 = ua;
-            u1 = (a[1] * x) * ua;
-        } else {
-            u0 = fma(a[4 * t] * x, ub, -ua);
-            u1 = fma(a[4 * t + 1] * x, u0, -ub);
+        const double u0 = fma(a[2 * t] * l.x, l.ub, -l.ua);
+        const double u1 = fma(a[2 * t + 1] * l.x, u0, -l.ub);
+        l.ua = u0;
+        l.ub = u1;
+        ve[t] = (float)u0;
+        vo[t] = (float)u1;
+    }
+}
+
+// Lanes that start at row r take their values, times `scale`.  `last`: no
+// lane of the wave starts after it (uniform).
+__device__ __forceinline__ void enter(Lane &l, const double2 *stash, int r, int last,
+                                      double scale = 1.0)
+{
+    if (r <= last) {
+        asm volatile("");   // a branch of its own, around the lane compare too
+        if (l.je == r / kLiveRows) {
+            const double2 v = *stash;
+            l.ua = v.x * scale;
+            l.ub = v.y * scale;
         }
-        const double u2 = fma(a[4 * t + 2] * x, u1, -u0);
-        const double u3 = fma(a[4 * t + 3] * x, u2, -u1);
-        ua = u2;
-        ub = u3;
     }
 }
 

@@ -45,15 +45,6 @@ __device__ inline double final_scale(int k)
     return k == 0 ? 1.0 : (k == -1 ? kTwoMinusS : 0.0);
 }
 
-// Block id -> logical id so that consecutive logical ids share an XCD.
-__device__ inline long long xcd_logical(long long b, long long total)
-{
-    const long long nx = 8;
-    long long x = b % nx, i = b / nx;
-    long long q = total / nx, r = total % nx;
-    return x * q + (x < r ? x : r) + i;
-}
-
 // Wave-uniform data that no kernel writes while it reads it comes through the
 // constant address space: scalar loads, also where the compiler cannot prove
 // that the kernel's stores leave it alone (the batch's workspace holds both

@@ -14,11 +14,11 @@ namespace sht {
 constexpr uint64_t kPlanMagic = 0x53485450'4c414e31ull;  // "SHTPLAN1"
 constexpr uint64_t kDeadMagic = 0xdeadbeefdeadbeefull;
 
-// Values of the Legendre recurrence are carried as v * 2^(kScaleStep * k),
-// k <= 0 (Sec. 2.2.2: real-time rescaling).  A value is rescaled when its
-// magnitude exceeds 2^kScaleStep; checks happen every 8 steps, over which
-// the normalised recurrence grows by less than 2^140 for l <= 16383, so
-// |v| < 2^652 always.  Terms with k <= -2 are below 2^-372 and dropped.
+// At plan time (live.hip) values of the Legendre recurrence are carried as
+// v * 2^(kScaleStep * k), k <= 0 (Sec. 2.2.2: real-time rescaling).  A value is
+// rescaled when its magnitude exceeds 2^kScaleStep; checks happen every 8
+// steps, over which the normalised recurrence grows by less than 2^140 for
+// l <= 16383, so |v| < 2^652 always.  Values with k <= -2 are below 2^-372.
 constexpr int kScaleStep = 512;
 
 // Per-ring description for the Fourier kernels (device side).
@@ -236,7 +236,6 @@ struct BatchMap {
     const PairDesc *pairs;
     const int32_t *mval;
     const long long *moff;
-    const double *mu;
     const double *A;
     const double *cn;
     const int32_t *minv;
@@ -284,6 +283,7 @@ struct sht_plan_s {
     long long *d_boff16; // [nm] first 16-row block of each m (FP32 matrix-core operand packing)
     int32_t *d_bm16;     // [nblk16] index of the m that owns each 16-row block
     long long nblk16;    // 16-row blocks over all m
+    long long nblk32;    // 32-row blocks over all m
     long long *d_soff;   // [nm] first 128-row super-block of each m (split-FP16 operand packing)
     int32_t *d_sbm;      // [nsuper] index of the m that owns each super-block
     double *d_Asb;       // [nsuper][128] d_A per super-block, zero past each m's last row
@@ -345,12 +345,12 @@ size_t adj_part_bytes(const sht_plan_s *p);
 size_t mfma_bf_bytes(const sht_plan_s *p);
 hipError_t launch_prescale_f32(const sht_plan_s *p, const double *alm, float *Bf, hipStream_t st);
 hipError_t launch_legendre_mfma_f32(const sht_plan_s *p, const float *Bf, float2 *delta,
-                                    hipStream_t st);
+                                    bool full, hipStream_t st);
 size_t bf16_bytes(const sht_plan_s *p);
 hipError_t launch_prescale_bf16x3(const sht_plan_s *p, const double *alm, void *Bb,
                                   hipStream_t st);
 hipError_t launch_legendre_mfma_bf16x3(const sht_plan_s *p, const void *Bb, float2 *delta,
-                                       hipStream_t st);
+                                       bool full, hipStream_t st);
 size_t f16_bytes(const sht_plan_s *p);
 int f16_super_rows();
 hipError_t launch_prescale_f16x2(const sht_plan_s *p, const double *alm, void *Bb,

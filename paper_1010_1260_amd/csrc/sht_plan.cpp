@@ -389,11 +389,11 @@ static sht_status legendre_stage(sht_plan_t p, const double *alm, void *ws, void
     if (p->precision == SHT_FP32_MFMA) {
         e = sht::launch_prescale_f32(p, alm, (float *)ws, st);
         if (e == hipSuccess && ev_mid) e = hipEventRecord(ev_mid, st);
-        if (e == hipSuccess) e = sht::launch_legendre_mfma_f32(p, (const float *)ws, d32, st);
+        if (e == hipSuccess) e = sht::launch_legendre_mfma_f32(p, (const float *)ws, d32, full, st);
     } else if (p->precision == SHT_BF16X3_MFMA) {
         e = sht::launch_prescale_bf16x3(p, alm, ws, st);
         if (e == hipSuccess && ev_mid) e = hipEventRecord(ev_mid, st);
-        if (e == hipSuccess) e = sht::launch_legendre_mfma_bf16x3(p, ws, d32, st);
+        if (e == hipSuccess) e = sht::launch_legendre_mfma_bf16x3(p, ws, d32, full, st);
     } else if (p->precision == SHT_F16X2_MFMA) {
         e = sht::launch_prescale_f16x2(p, alm, ws, st);
         if (e == hipSuccess && ev_mid) e = hipEventRecord(ev_mid, st);
@@ -668,6 +668,7 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
             boff[i] = acc_b;
             acc_b += (d->lmax - mval[i] + 1 + 31) / 32;
         }
+        p->nblk32 = acc_b;
         st = upload(&p->d_boff, boff, &tb);
         if (st == SHT_OK) {
             std::vector<int32_t> bm32((size_t)acc_b);

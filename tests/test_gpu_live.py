@@ -131,3 +131,22 @@ def test_adjoint_shapes(P, lmax, nside, rings, mval, nmaps):
     for i in (0, nmaps - 1):
         e = ref.alm2map_adjoint(lmax, g, maps[i], mval=mval)
         assert np.linalg.norm(got[i] - e) <= 1e-12 * np.linalg.norm(e), i
+
+
+# FP32 operands: 1..8 map pairs per wave, a last pair of one map, groups of 16
+# and a rest; row counts around the 16-row block
+@pytest.mark.parametrize("nmaps", [2, 3, 5, 8, 9, 11, 14, 16, 17, 21])
+@pytest.mark.parametrize("lmax,nside", [(31, 40), (144, 72)])
+def test_fp32_maps_equal_maps_alone(P, lmax, nside, nmaps):
+    """Every product adds one term in the order of l, so a map's result does
+    not depend on the maps beside it."""
+    _say("fp32 maps", lmax, nside, nmaps)
+    g = W.healpix_geometry(nside)
+    alms = np.stack([W.random_alm(lmax, [806, i]) for i in range(nmaps)])
+    a = torch.from_numpy(alms).to(_dev())
+    got = P.Plan(lmax, g, nmaps=nmaps, precision="fp32_mfma").alm2delta(a).cpu()
+    one = P.Plan(lmax, g, precision="fp32_mfma")
+    for i in range(nmaps):
+        assert torch.equal(got[i], one.alm2delta(a[i]).cpu()[0]), i
+    e = ref.delta(lmax, None, g.cth, g.sth, alms[-1]).T
+    assert np.linalg.norm(got[-1].numpy() - e) <= 1e-6 * np.linalg.norm(e)
