@@ -155,6 +155,7 @@ sht_status sht_plan_batch(sht_batch_t *out, const sht_plan_t *plans, int32_t n)
         m.A = p->d_A; m.cn = p->d_cn; m.minv = p->d_minv; m.rings = p->d_rings;
         m.pool = p->d_pool;
         m.live = p->live;
+        m.dl = sht::delta_blocked(p->nm, p->nrings);
         m.nalm = p->nalm;
         m.ap_off = (long long)off;
         off = align_up(off + (size_t)p->nalm * sizeof(double2), 256);

@@ -110,7 +110,7 @@ template <int CH, int NB>
 __device__ inline void fwd_one_m(const Chains<CH> &g, const LiveTab &lt, int blk0, int m, int i,
                                  long long off, int lmax, const double *__restrict__ A,
                                  const double2 *__restrict__ ap, double2 *__restrict__ delta,
-                                 long long dbase, long long dmap, int nrings, bool full)
+                                 const DeltaLayout &dl, bool full)
 {
     constexpr int KR = NB == 1 ? 4 : 2;   // two chunks fit the scalar registers
     const int len = lmax - m + 1;
@@ -227,14 +227,15 @@ __device__ inline void fwd_one_m(const Chains<CH> &g, const LiveTab &lt, int blk
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
         if (!full && i >= g.ilim[c]) continue;
-        double2 *row = delta + dbase + (long long)i * nrings;
+        // consecutive lanes write consecutive rings
+        double2 *n = delta + dl.row(max(g.rn[c], 0)) + i * dl.mstride(g.rn[c]);
+        double2 *so = delta + dl.row(max(g.rs[c], 0)) + i * dl.mstride(g.rs[c]);
 #pragma unroll
-        for (int b = 0; b < NB; ++b, row += dmap) {
-            // Delta [m][ring]: consecutive lanes write consecutive rings
+        for (int b = 0; b < NB; ++b) {
             if (g.rn[c] >= 0)
-                row[g.rn[c]] = make_double2(Er[c][b] + Or[c][b], Ei[c][b] + Oi[c][b]);
+                n[b * dl.map] = make_double2(Er[c][b] + Or[c][b], Ei[c][b] + Oi[c][b]);
             if (g.rs[c] >= 0)
-                row[g.rs[c]] = make_double2(Er[c][b] - Or[c][b], Ei[c][b] - Oi[c][b]);
+                so[b * dl.map] = make_double2(Er[c][b] - Or[c][b], Ei[c][b] - Oi[c][b]);
         }
     }
 }
@@ -245,7 +246,7 @@ __global__ __launch_bounds__(64) void k_legendre_fwd(
     const PairDesc *__restrict__ pairs, LiveTab lt, int pblocks,
     const int *__restrict__ mval, const long long *__restrict__ moff, int nm, int nmpairs,
     int lmax, const double *__restrict__ A, const double2 *__restrict__ ap, long long nalm,
-    double2 *__restrict__ delta, int nrings, int ngroups, int full)
+    double2 *__restrict__ delta, DeltaLayout dl, int ngroups, int full)
 {
     // XCD x takes the m-pairs q = x mod 8, one after the other for all ring
     // blocks of all maps: the waves that share an m-pair's coefficients run
@@ -262,12 +263,11 @@ __global__ __launch_bounds__(64) void k_legendre_fwd(
     Chains<CH> g;
     load_chains(g, pairs, pb * CH);
     const double2 *apb = ap + b * nalm;
-    const long long dmap = (long long)nrings * nm;
     for (int t = 0; t < 2; ++t) {
         const int i = (t == 0) ? q : nm - 1 - q;
         if (t == 1 && i == q) break;
-        fwd_one_m<CH, NB>(g, lt, pb * CH, ((CIp)mval)[i], i, ((CLp)moff)[i], lmax, A, apb, delta,
-                          b * dmap, dmap, nrings, full != 0);
+        fwd_one_m<CH, NB>(g, lt, pb * CH, ((CIp)mval)[i], i, ((CLp)moff)[i], lmax, A, apb,
+                          delta + b * dl.map, dl, full != 0);
     }
 }
 
@@ -359,7 +359,7 @@ template <int CH>
 __device__ inline void adj_one_m(const PairDesc *__restrict__ pairs, const LiveTab &lt,
                                  int blk0, int m, int i, long long off,
                                  int lmax, const double *__restrict__ A,
-                                 const double2 *__restrict__ dt, long long dtbase, int nrings,
+                                 const double2 *__restrict__ dt, const DeltaLayout &dl,
                                  double2 *__restrict__ part, double2 (*st)[64])
 {
     const int len = lmax - m + 1;
@@ -388,13 +388,12 @@ __device__ inline void adj_one_m(const PairDesc *__restrict__ pairs, const LiveT
         je[c] = lt.je[e];
         sv[c] = lt.st[e];
     }
-    const double2 *row = dt + dtbase + (long long)i * nrings;
     double2 wn[CH], ws[CH];
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-        const int rn = max(d[c].rn, 0);
-        wn[c] = row[rn];
-        ws[c] = row[d[c].rs >= 0 ? d[c].rs : rn];
+        const int rn = max(d[c].rn, 0), rs = d[c].rs >= 0 ? d[c].rs : rn;
+        wn[c] = dt[dl.row(rn) + i * dl.mstride(rn)];
+        ws[c] = dt[dl.row(rs) + i * dl.mstride(rs)];
     }
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
@@ -456,7 +455,7 @@ template <int CH>
 __global__ __launch_bounds__(64, CH == 8 ? 2 : CH == 1 ? 4 : 3) void k_legendre_adj(
     const PairDesc *__restrict__ pairs, LiveTab lt, int pblocks,
     const int *__restrict__ mval, const long long *__restrict__ moff, int nm, int nmpairs,
-    int lmax, const double *__restrict__ A, const double2 *__restrict__ dt, int nrings,
+    int lmax, const double *__restrict__ A, const double2 *__restrict__ dt, DeltaLayout dl,
     double2 *__restrict__ part, long long nalm, int nmaps)
 {
     __shared__ double2 st[CH][64];
@@ -468,13 +467,12 @@ __global__ __launch_bounds__(64, CH == 8 ? 2 : CH == 1 ? 4 : 3) void k_legendre_
     const int b = rest % nmaps;
     const int q = x + 8 * (rest / nmaps);
     if (q >= nmpairs) return;
-    const long long dtbase = (long long)b * nrings * nm;
     double2 *pp = part + ((long long)b * pblocks + pb) * nalm;
     for (int t = 0; t < 2; ++t) {
         const int i = (t == 0) ? q : nm - 1 - q;
         if (t == 1 && i == q) break;
-        adj_one_m<CH>(pairs, lt, pb * CH, ((CIp)mval)[i], i, ((CLp)moff)[i], lmax, A, dt,
-                      dtbase, nrings, pp, st);
+        adj_one_m<CH>(pairs, lt, pb * CH, ((CIp)mval)[i], i, ((CLp)moff)[i], lmax, A,
+                      dt + b * dl.map, dl, pp, st);
     }
 }
 
@@ -566,7 +564,7 @@ __global__ __launch_bounds__(64) void k_legendre_fwd_batch(const BatchTile *__re
             const int i = (u == 0) ? q : bm.nm - 1 - q;
             if (u == 1 && i == q) break;
             fwd_one_m<CH, 1>(g, bm.live, tile.pblock * CH, ((CIp)bm.mval)[i], i,
-                             ((CLp)bm.moff)[i], bm.lmax, bm.A, ap, delta, 0, 0, bm.nrings, false);
+                             ((CLp)bm.moff)[i], bm.lmax, bm.A, ap, delta, bm.dl, false);
         }
     }
 }
@@ -630,6 +628,7 @@ hipError_t launch_legendre_fwd(const sht_plan_s *p, const double2 *ap, double2 *
 {
     const int pblocks = fwd_pblocks(p);
     const int nmpairs = (p->nm + 1) / 2;
+    const DeltaLayout dl = full ? delta_plain(p->nm, p->nrings) : delta_blocked(p->nm, p->nrings);
     return for_map_groups(p, [&](int first, int groups, auto nb) {
         const long long total = 8LL * ((nmpairs + 7) / 8) * pblocks * groups;
         if (total <= 0 || total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
@@ -638,8 +637,7 @@ hipError_t launch_legendre_fwd(const sht_plan_s *p, const double2 *ap, double2 *
         hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(64), 0, st, p->d_pairs, p->live,
                            pblocks, p->d_mval, p->d_moff, p->nm, nmpairs, p->lmax, p->d_A,
                            ap + first * p->nalm, p->nalm,
-                           delta + (long long)first * p->nrings * p->nm, p->nrings, groups,
-                           full ? 1 : 0);
+                           delta + first * dl.map, dl, groups, full ? 1 : 0);
         return hipGetLastError();
     });
 }
@@ -650,8 +648,8 @@ size_t adj_part_bytes(const sht_plan_s *p)
 }
 
 template <int CH>
-static hipError_t adj_launch(const sht_plan_s *p, const double2 *dt, double2 *part, double *alm,
-                             hipStream_t st, bool accumulate)
+static hipError_t adj_launch(const sht_plan_s *p, const double2 *dt, const DeltaLayout &dl,
+                             double2 *part, double *alm, hipStream_t st, bool accumulate)
 {
     const int pblocks = adj_pblocks(p);
     const int nmpairs = (p->nm + 1) / 2;
@@ -659,7 +657,7 @@ static hipError_t adj_launch(const sht_plan_s *p, const double2 *dt, double2 *pa
     if (total <= 0 || total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(k_legendre_adj<CH>, dim3((unsigned)total), dim3(64), 0, st, p->d_pairs,
                        p->live, pblocks, p->d_mval, p->d_moff, p->nm, nmpairs, p->lmax,
-                       p->d_A, dt, p->nrings, part, p->nalm, p->nmaps);
+                       p->d_A, dt, dl, part, p->nalm, p->nmaps);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int longest = p->lmax - p->mval[0] + 1;
@@ -669,14 +667,14 @@ static hipError_t adj_launch(const sht_plan_s *p, const double2 *dt, double2 *pa
     return hipGetLastError();
 }
 
-hipError_t launch_legendre_adj_ws(const sht_plan_s *p, const double2 *dt, double2 *part,
-                                  double *alm, hipStream_t st, bool accumulate)
+hipError_t launch_legendre_adj_ws(const sht_plan_s *p, const double2 *dt, bool plain,
+                                  double2 *part, double *alm, hipStream_t st, bool accumulate)
 {
+    const DeltaLayout dl = plain ? delta_plain(p->nm, p->nrings) : delta_blocked(p->nm, p->nrings);
     switch (p->adj_chains) {
-    case 1: return adj_launch<1>(p, dt, part, alm, st, accumulate);
-    case 2: return adj_launch<2>(p, dt, part, alm, st, accumulate);
-    case 4: return adj_launch<4>(p, dt, part, alm, st, accumulate);
-    case 8: return adj_launch<8>(p, dt, part, alm, st, accumulate);
+    case 1: return adj_launch<1>(p, dt, dl, part, alm, st, accumulate);
+    case 2: return adj_launch<2>(p, dt, dl, part, alm, st, accumulate);
+    case 8: return adj_launch<8>(p, dt, dl, part, alm, st, accumulate);
     default: return hipErrorInvalidValue;
     }
 }

@@ -296,7 +296,7 @@ __global__ __launch_bounds__(64, 2) void k_legendre_mfma_bf16x3(
     const int *__restrict__ mval, const long long *__restrict__ boff,
     const long long *__restrict__ soff, int nm, int nmpairs, int lmax,
     const double *__restrict__ Asb, const v4u *__restrict__ Bb, long long nblocks,
-    float2 *__restrict__ delta, int nrings, int nmaps, int groups, int full)
+    float2 *__restrict__ delta, DeltaLayout dl, int nmaps, int groups, int full)
 {
     __shared__ double2 start[64];
     // XCD x takes the m-pairs q = x mod 8 (see the FP64 kernel)
@@ -319,10 +319,10 @@ __global__ __launch_bounds__(64, 2) void k_legendre_mfma_bf16x3(
     const int i2 = nm - 1 - q;
     const bool two = i2 != q;
     if (two) m_begin(st, stash, i2, mval, boff, soff, lmax, lt, Asb, Bg, pb, lane);
-    m_store(tot, i1, delta, pairs, npairs, pb, grp, nmaps, nrings, full != 0, lane);
+    m_store(tot, i1, delta, pairs, npairs, pb, grp, nmaps, dl, full != 0, lane);
     if (two) {
         m_compute(st, stash, tot);
-        m_store(tot, st.i, delta, pairs, npairs, pb, grp, nmaps, nrings, full != 0, lane);
+        m_store(tot, st.i, delta, pairs, npairs, pb, grp, nmaps, dl, full != 0, lane);
     }
 }
 
@@ -362,7 +362,7 @@ hipError_t launch_legendre_mfma_bf16x3(const sht_plan_s *p, const void *Bb, floa
     hipLaunchKernelGGL(k_legendre_mfma_bf16x3, dim3((unsigned)total), dim3(64), 0, st,
                        p->d_pairs, p->npairs, p->live, pblocks, p->d_mval, p->d_boff, p->d_soff,
                        p->nm, nmpairs, p->lmax, p->d_Asb, reinterpret_cast<const v4u *>(Bb),
-                       p->nblk32, delta, p->nrings, p->nmaps, groups, full ? 1 : 0);
+                       p->nblk32, delta, delta_blocked_maps(p->nm, p->nrings, p->nmaps), p->nmaps, groups, full ? 1 : 0);
     return hipGetLastError();
 }
 

@@ -224,21 +224,21 @@ __device__ __forceinline__ void m_compute(MState<NP> &st, const double2 *stash, 
     }
 }
 
-// Delta of one m ([m][ring][map], see m_store of the other forms): the lane
+// Delta of one m (the maps of a ring contiguous, see m_store of the other forms): the lane
 // holds its pair's parity sums of every map.  North (E + O) and south (E - O)
 // are formed exactly in FP64 and rounded once to FP32.
 template <int NP>
 __device__ __forceinline__ void store_delta(const Sums<NP> &tot, int i,
                                             float2 *__restrict__ delta,
                                             const PairDesc *__restrict__ pairs, int npairs, int p,
-                                            int map0, int nmaps, int nrings, bool full)
+                                            int map0, int nmaps, const DeltaLayout &dl, bool full)
 {
     if (p >= npairs) return;
     const PairDesc d = pairs[p];
     if (!full && i >= d.ilim) return;   // dead on the ring, not read
-    const long long row = (long long)i * nrings;
-    float2 *__restrict__ dn = delta + (row + d.rn) * nmaps;
-    float2 *__restrict__ ds = delta + (row + (d.rs >= 0 ? d.rs : d.rn)) * nmaps;
+    const int rs = d.rs >= 0 ? d.rs : d.rn;
+    float2 *__restrict__ dn = delta + dl.row(d.rn) + i * dl.mstride(d.rn);
+    float2 *__restrict__ ds = delta + dl.row(rs) + i * dl.mstride(rs);
 #pragma unroll
     for (int b = 0; b < NP; ++b) {
         const int m0 = map0 + 2 * b;
@@ -274,7 +274,7 @@ __global__ __launch_bounds__(64) void k_legendre_mfma_f32(
     const int *__restrict__ mval, const long long *__restrict__ soff,
     const long long *__restrict__ boff16, int nm, int nmpairs, int lmax,
     const double *__restrict__ Asb, const float *__restrict__ Bp, long long nblocks,
-    float2 *__restrict__ delta, int nrings, int map0, int nmaps, int groups, int full)
+    float2 *__restrict__ delta, DeltaLayout dl, int map0, int nmaps, int groups, int full)
 {
     __shared__ double2 start[64];
     // XCD x takes the m-pairs q = x mod 8 (see the FP64 kernel)
@@ -300,10 +300,10 @@ __global__ __launch_bounds__(64) void k_legendre_mfma_f32(
     const bool two = i2 != q;
     // the second m's loads go out before the first one's stores
     if (two) m_begin(st, stash, i2, mval, soff, boff16, lmax, lt, Asb, Bg, pb, lane);
-    store_delta(tot, i1, delta, pairs, npairs, p, m0, nmaps, nrings, full != 0);
+    store_delta(tot, i1, delta, pairs, npairs, p, m0, nmaps, dl, full != 0);
     if (two) {
         m_compute(st, stash, tot);
-        store_delta(tot, st.i, delta, pairs, npairs, p, m0, nmaps, nrings, full != 0);
+        store_delta(tot, st.i, delta, pairs, npairs, p, m0, nmaps, dl, full != 0);
     }
 }
 
@@ -336,7 +336,7 @@ hipError_t launch_group(const sht_plan_s *p, const float *Bp, float2 *delta, int
     hipLaunchKernelGGL(k_legendre_mfma_f32<NP>, dim3((unsigned)total), dim3(64), 0, st, p->d_pairs,
                        p->npairs, p->live, pblocks, p->d_mval, p->d_soff, p->d_boff16, p->nm,
                        nmpairs, p->lmax, p->d_Asb, Bp + b_offset(p, first), p->nblk16, delta,
-                       p->nrings, first, p->nmaps, groups, full ? 1 : 0);
+                       delta_blocked_maps(p->nm, p->nrings, p->nmaps), first, p->nmaps, groups, full ? 1 : 0);
     return hipGetLastError();
 }
 

@@ -77,15 +77,16 @@ __device__ __forceinline__ void enter(Lane &l, const double2 *stash, int r, int 
 
 // Delta of one m.  D layout of a 32x32 tile: column = lane % 32 (the ring
 // pair), row = 8 (r/4) + 4 (lane/32) + r % 4 = 2 map + Re/Im, so a lane owns
-// 8 complex values of one pair.  The mixed forms' Delta is [m][ring][map]
-// (maps contiguous): the ring stage reads a ring's modes for all maps at
+// 8 complex values of one pair.  The mixed forms' Delta has the maps
+// of a ring contiguous: the ring stage reads a ring's modes for all maps at
 // once, and the wave writes every map of its rings, so each line is filled
 // by one wave.  The parity sums are FP32; north (E + O) and south (E - O)
 // are formed exactly in FP64 and rounded once to FP32, the precision the
 // contraction carries, so Delta is stored as complex64.
 __device__ __forceinline__ void m_store(const MfmaTiles &tot, int i, float2 *__restrict__ delta,
                                         const PairDesc *__restrict__ pairs, int npairs, int pb,
-                                        int grp, int nmaps, int nrings, bool full, int lane)
+                                        int grp, int nmaps, const DeltaLayout &dl, bool full,
+                                        int lane)
 {
     const int hi = lane >> 5;
     const int col = lane & 31;
@@ -98,9 +99,9 @@ __device__ __forceinline__ void m_store(const MfmaTiles &tot, int i, float2 *__r
         if (pp < npairs) {
             const PairDesc d = pairs[pp];
             if (!full && i >= d.ilim) continue;   // dead on the ring, not read
-            const long long row = (long long)i * nrings;
-            float2 *__restrict__ dn = d2 + (row + d.rn) * nmaps;
-            float2 *__restrict__ ds = d2 + (row + (d.rs >= 0 ? d.rs : d.rn)) * nmaps;
+            const int rs = d.rs >= 0 ? d.rs : d.rn;
+            float2 *__restrict__ dn = d2 + dl.row(d.rn) + i * dl.mstride(d.rn);
+            float2 *__restrict__ ds = d2 + dl.row(rs) + i * dl.mstride(rs);
 #pragma unroll
             for (int r = 0; r < 16; r += 4) {
                 // rows r .. r + 3: maps m0 and m0 + 1, adjacent in Delta, so

@@ -24,7 +24,7 @@
 // with the butterflies held in registers, the half-length pre-processing
 // fused into the first pass and the pixels stored from the last.  Its passes
 // run in complex128 for FP64 plans; for the mixed forms, whose Delta is
-// complex64 [m][ring][map], one workgroup takes two maps of a ring (one
+// complex64 with the maps of a ring contiguous, one workgroup takes two maps of a ring (one
 // 16-byte load per mode) and runs the passes of both in complex64 (the fold
 // adds in FP64 either way).  The mixed forms also take even rings whose half
 // length is twice a non-7-smooth number on a Bluestein fast path: a
@@ -526,15 +526,20 @@ __device__ inline void ring_item(long long it, int count, int nmaps, int &i, int
 
 // The persistent kernels' share of XCD x (workgroups are dealt to the 8 XCDs
 // round-robin): items [lo, hi) of its own numbering, item k -> (i, b).  Map
-// by map: a contiguous eighth of all items.  Ring by ring: the rings
-// i = x mod 8 (the class's rings are sorted by length, so every XCD gets
-// rings of every length), all maps of a ring together.
+// by map: a contiguous eighth of all items.  Ring by ring: every eighth group
+// of 2^shift rings (the class's rings are sorted by length, so every XCD gets
+// rings of every length), all maps of a ring together; the groups hold the
+// rings that share lines of Delta.
 template <bool RM>
-__device__ inline void xcd_share(int count, int nmaps, int x, long long &lo, long long &hi)
+__device__ inline void xcd_share(int count, int nmaps, int x, int shift, long long &lo,
+                                 long long &hi)
 {
     if (RM) {
+        // groups of 2^shift rings, dealt to the XCDs in turn
+        const int g = 1 << shift, all = count >> (shift + 3);
+        const int rest = count - (all << (shift + 3)) - (x << shift);
         lo = 0;
-        hi = (long long)((count - x + 7) / 8) * nmaps;
+        hi = (long long)((all << shift) + (rest < 0 ? 0 : rest < g ? rest : g)) * nmaps;
     } else {
         const long long total = (long long)count * nmaps;
         lo = total * x / 8;
@@ -543,12 +548,12 @@ __device__ inline void xcd_share(int count, int nmaps, int x, long long &lo, lon
 }
 
 template <bool RM>
-__device__ inline void xcd_item(long long k, int count, int nmaps, int x, int &i, int &b)
+__device__ inline void xcd_item(long long k, int count, int nmaps, int x, int shift, int &i, int &b)
 {
     if (RM) {
-        const long long q = k / nmaps;
-        i = (int)(x + 8 * q);
-        b = (int)(k - q * nmaps);
+        const int q = (int)(k / nmaps);
+        i = ((((q >> shift) << 3) + x) << shift) + (q & ((1 << shift) - 1));
+        b = (int)(k - (long long)q * nmaps);
     } else {
         ring_item<false>(k, count, nmaps, i, b);
     }
@@ -798,10 +803,13 @@ __device__ __attribute__((always_inline)) inline void synth_ring(double2 *buf, c
 //
 // One pass of radix R over the h-point buffer (input index j + r h/R,
 // output index (j / Ns) Ns R + j % Ns + r Ns).  T: the ring's n-th roots.
+// tid: the thread's place among the NT that share the buffer; store: the last
+// pass writes the pixels (not for a map that is not there).
 template <int R, int NT, typename C>
 __device__ __attribute__((always_inline)) inline void fast_pass(C *buf, const C *T,
                                                                 int h, int Ns, bool first,
-                                                                bool last, double *__restrict__ out)
+                                                                bool last, double *__restrict__ out,
+                                                                int tid, bool store)
 {
     constexpr int MAXQ = fast_maxq(R);   // the plan admits h / R <= MAXQ * kFastThreads
     const int nb = h / R;
@@ -810,7 +818,6 @@ __device__ __attribute__((always_inline)) inline void fast_pass(C *buf, const C 
     // an opaque copy of the thread index: the passes run in a loop over the
     // ring's radix list, and address arithmetic hoisted out of every radix's
     // case would stay live across all of them
-    int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     C v[MAXQ][R];
 #pragma unroll
@@ -854,7 +861,7 @@ __device__ __attribute__((always_inline)) inline void fast_pass(C *buf, const C 
 #pragma unroll
         for (int q = 0; q < MAXQ; ++q) {
             const int j = tid + q * NT;
-            if (j < nb) {
+            if (store && j < nb) {
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     const int i = j + r * nb;
@@ -897,12 +904,8 @@ struct FastModes {
     DT v[Q];   // as stored (complex64 or complex128), widened at use
 };
 
-// Loads of the fold: modes m = tid + q NT of one ring.  Each load waits for
-// the one before it: the loads of all workgroups then move through the m
-// rows of Delta together, so the DRAM rows they open serve the neighbouring
-// rings too.  Issued all at once they reach DRAM as a burst over thousands
-// of rows, which measured 17% slower (split-FP16 belt rings, 16 maps at
-// l_max 4096 / nside 2048: 3.43 ms paced, 4.00 ms as a burst).
+// Loads of the fold: modes m = tid + q NT of one ring, all at once; they are on
+// their way during the passes of the ring before.
 template <int NT, typename DT>
 __device__ __attribute__((always_inline)) inline void load_fast(FastModes<NT, DT> &raw,
                                                                 const DT *__restrict__ drow,
@@ -920,11 +923,8 @@ __device__ __attribute__((always_inline)) inline void load_fast(FastModes<NT, DT
         for (int q = 0; q < QM; ++q) {
             const int m = tid + q * NT;
             raw.v[q] = DT{};
-            if (q * NT <= mmax) {   // uniform: no round for the modes that are dead on the ring
-                if (m <= mmax) raw.v[q] = drow[(long long)m * dstride];
-                // s_waitcnt vmcnt(0) expcnt(7) lgkmcnt(15)
-                if (q + 1 < QM) __builtin_amdgcn_s_waitcnt(0x0F70);
-            }
+            // uniform: nothing for the rounds of modes that are dead on the ring
+            if (q * NT <= mmax && m <= mmax) raw.v[q] = drow[(long long)m * dstride];
         }
     } else {
         // every position lookup first, then the loads
@@ -937,7 +937,6 @@ __device__ __attribute__((always_inline)) inline void load_fast(FastModes<NT, DT
 #pragma unroll
         for (int q = 0; q < QM; ++q) {
             raw.v[q] = (pos[q] >= 0) ? drow[(long long)pos[q] * dstride] : DT{};
-            if (q * NT <= mmax && q + 1 < QM) __builtin_amdgcn_s_waitcnt(0x0F70);
         }
     }
 }
@@ -1031,7 +1030,8 @@ __device__ __attribute__((always_inline)) inline void fold_fast(C *buf, const Ri
 template <int NT, typename C>
 __device__ __attribute__((always_inline)) inline void fft_fast(C *buf, const C *T,
                                                                const RingDesc &d,
-                                                               double *__restrict__ out);
+                                                               double *__restrict__ out, int tid,
+                                                               bool store);
 
 // Synthesis of one fast-path ring: buf = padded spectrum buffer, T = LDS
 // twiddle table, out = the ring's first pixel.
@@ -1049,7 +1049,7 @@ __device__ __attribute__((always_inline)) inline void synth_fast(C *buf, C *T,
     FastModes<NT, DT> raw;
     load_fast<NT>(raw, drow, dstride, minv, mcontig, mmax);
     fold_fast<NT>(buf, d, raw, mmax);
-    fft_fast<NT, C>(buf, T, d, out);
+    fft_fast<NT, C>(buf, T, d, out, threadIdx.x, true);
 }
 
 // The Stockham passes of a fast-path ring (after the fold) and the pixel
@@ -1057,7 +1057,8 @@ __device__ __attribute__((always_inline)) inline void synth_fast(C *buf, C *T,
 template <int NT, typename C>
 __device__ __attribute__((always_inline)) inline void fft_fast(C *buf, const C *T,
                                                                const RingDesc &d,
-                                                               double *__restrict__ out)
+                                                               double *__restrict__ out, int tid,
+                                                               bool store)
 {
     const int h = d.n / 2;
     int Ns = 1;
@@ -1065,25 +1066,27 @@ __device__ __attribute__((always_inline)) inline void fft_fast(C *buf, const C *
         const int R = (int)((d.rads >> (5 * p)) & 31);
         const bool first = p == 0, last = p == d.np - 1;
         switch (R) {
-        case 16: fast_pass<16, NT, C>(buf, T, h, Ns, first, last, out); break;
-        case 8: fast_pass<8, NT, C>(buf, T, h, Ns, first, last, out); break;
-        case 4: fast_pass<4, NT, C>(buf, T, h, Ns, first, last, out); break;
-        case 2: fast_pass<2, NT, C>(buf, T, h, Ns, first, last, out); break;
-        case 7: fast_pass<7, NT, C>(buf, T, h, Ns, first, last, out); break;
-        case 5: fast_pass<5, NT, C>(buf, T, h, Ns, first, last, out); break;
-        default: fast_pass<3, NT, C>(buf, T, h, Ns, first, last, out); break;
+        case 16: fast_pass<16, NT, C>(buf, T, h, Ns, first, last, out, tid, store); break;
+        case 8: fast_pass<8, NT, C>(buf, T, h, Ns, first, last, out, tid, store); break;
+        case 4: fast_pass<4, NT, C>(buf, T, h, Ns, first, last, out, tid, store); break;
+        case 2: fast_pass<2, NT, C>(buf, T, h, Ns, first, last, out, tid, store); break;
+        case 7: fast_pass<7, NT, C>(buf, T, h, Ns, first, last, out, tid, store); break;
+        case 5: fast_pass<5, NT, C>(buf, T, h, Ns, first, last, out, tid, store); break;
+        default: fast_pass<3, NT, C>(buf, T, h, Ns, first, last, out, tid, store); break;
         }
         Ns *= R;
     }
 }
 
 // ---------------------------------------------------------------------------
-// Fast path, two maps per workgroup (mixed forms, complex64 Delta
-// [m][ring][map]): maps 2p and 2p + 1 of a ring are adjacent in Delta, so one
-// 16-byte load per mode brings both; the two spectra sit in two padded LDS
-// buffers, and every Stockham pass takes its butterflies in both with the
-// same twiddles and one barrier pair.  `two` is false for the last map of an
-// odd map count (its partner's loads read zeros and its stores are skipped).
+// Fast path, two maps per workgroup (mixed forms, complex64 Delta): maps 2p
+// and 2p + 1 of a ring are adjacent in Delta, so one 16-byte load per mode
+// brings both; all 512 threads load and fold, then each half of them runs the
+// Stockham passes of one map's padded LDS buffer, with common barriers.
+// `two` is false for the last map of an odd map count (its partner's loads
+// read zeros and its stores are skipped).
+constexpr int kFast2Threads = 2 * kFastThreads;
+
 template <int NT>
 struct FastModes2 {
     static constexpr int Q = FastModes<NT, float2>::Q;
@@ -1098,17 +1101,13 @@ __device__ __attribute__((always_inline)) inline void load_fast2(
     constexpr int QM = FastModes2<NT>::Q;
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
-    // paced like load_fast: each load waits for the one before it
     if (mcontig && aligned) {
 #pragma unroll
         for (int q = 0; q < QM; ++q) {
             const int m = tid + q * NT;
             raw.v[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (q * NT <= mmax) {
-                if (m <= mmax)
-                    raw.v[q] = *reinterpret_cast<const float4 *>(drow + (long long)m * dstride);
-                if (q + 1 < QM) __builtin_amdgcn_s_waitcnt(0x0F70);
-            }
+            if (q * NT <= mmax && m <= mmax)
+                raw.v[q] = *reinterpret_cast<const float4 *>(drow + (long long)m * dstride);
         }
         return;
     }
@@ -1127,7 +1126,6 @@ __device__ __attribute__((always_inline)) inline void load_fast2(
             if (two) e1 = e[1];
         }
         raw.v[q] = make_float4(e0.x, e0.y, e1.x, e1.y);
-        if (q * NT <= mmax && q + 1 < QM) __builtin_amdgcn_s_waitcnt(0x0F70);
     }
 }
 
@@ -1177,7 +1175,7 @@ __device__ __attribute__((always_inline)) inline void fold_fast2(float2 *X0, flo
             X0[PadIdx::at(k)] = cvt<float2>(F0);
             X1[PadIdx::at(k)] = cvt<float2>(F1);
         }
-    } else if (B >= NT) {
+    } else if (B >= kFastThreads) {
         for (int k = tid; k <= h; k += NT) {
             const int jmax = (mmax + k) / n;
             double s0r = 0.0, s0i = 0.0, s1r = 0.0, s1i = 0.0;
@@ -1197,7 +1195,8 @@ __device__ __attribute__((always_inline)) inline void fold_fast2(float2 *X0, flo
             X1[PadIdx::at(k)] = cplx<float2>(s1r, s1i);
         }
     } else {
-        const int G = NT / B;
+        // G as in fold_fast, so that a ring rounds alike in both
+        const int G = kFastThreads / B;
         const int kk = tid % B, g = tid / B;
         double s0r = 0.0, s0i = 0.0, s1r = 0.0, s1i = 0.0;
         if (g < G) {
@@ -1235,139 +1234,10 @@ __device__ __attribute__((always_inline)) inline void fold_fast2(float2 *X0, flo
     __syncthreads();
 }
 
-// fast_pass over both buffers.
-template <int R>
-__device__ __attribute__((always_inline)) inline void fast_pass2(float2 *X0, float2 *X1,
-                                                                 const float2 *T, int h, int Ns,
-                                                                 bool first, bool last,
-                                                                 double *__restrict__ out0,
-                                                                 double *__restrict__ out1,
-                                                                 bool two)
-{
-    typedef float2 C;
-    constexpr int NT = kFastThreads;
-    constexpr int MAXQ = fast_maxq(R);
-    const int nb = h / R;
-    const int tstep0 = (h / (Ns * R)) * 2;
-    const unsigned magic = (unsigned)((0x100000000ull + (unsigned)Ns - 1) / (unsigned)Ns);
-    int tid = threadIdx.x;
-    asm volatile("" : "+v"(tid));
-    C a[MAXQ][R], b[MAXQ][R];
-#pragma unroll
-    for (int q = 0; q < MAXQ; ++q) {
-        const int j = tid + q * NT;
-        if (j < nb) {
-            if (first) {
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const int k = j + r * nb;
-                    const C w = tw_at(T, k);
-                    const C F0 = X0[PadIdx::at(k)], G0 = X0[PadIdx::at(h - k)];
-                    const C F1 = X1[PadIdx::at(k)], G1 = X1[PadIdx::at(h - k)];
-                    a[q][r] = cadd(cadd(F0, conjd(G0)), muli(cmul(w, csub(F0, conjd(G0))), +1));
-                    b[q][r] = cadd(cadd(F1, conjd(G1)), muli(cmul(w, csub(F1, conjd(G1))), +1));
-                }
-            } else {
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const int k = PadIdx::at(j + r * nb);
-                    a[q][r] = X0[k];
-                    b[q][r] = X1[k];
-                }
-            }
-            if (Ns > 1) {
-                const int jq = (int)__umulhi((unsigned)j, magic);
-                const int ts = tstep0 * (j - jq * Ns);
-                if (ts != 0) {
-                    const C w1 = tw_at(T, ts);
-                    C wr = w1;
-#pragma unroll
-                    for (int r = 1; r < R; ++r) {
-                        a[q][r] = cmul(a[q][r], wr);
-                        b[q][r] = cmul(b[q][r], wr);
-                        wr = cmul(wr, w1);
-                    }
-                }
-            }
-            small_dft<R, C>(a[q], +1);
-            small_dft<R, C>(b[q], +1);
-        }
-    }
-    if (last) {
-        const bool al = ((reinterpret_cast<uintptr_t>(out0) | reinterpret_cast<uintptr_t>(out1)) &
-                         15) == 0;
-        double2 *o0 = reinterpret_cast<double2 *>(out0);
-        double2 *o1 = reinterpret_cast<double2 *>(out1);
-#pragma unroll
-        for (int q = 0; q < MAXQ; ++q) {
-            const int j = tid + q * NT;
-            if (j < nb) {
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const int i = j + r * nb;
-                    if (al) {
-                        o0[i] = todbl(a[q][r]);
-                        if (two) o1[i] = todbl(b[q][r]);
-                    } else {
-                        out0[2 * i] = (double)a[q][r].x;
-                        out0[2 * i + 1] = (double)a[q][r].y;
-                        if (two) {
-                            out1[2 * i] = (double)b[q][r].x;
-                            out1[2 * i + 1] = (double)b[q][r].y;
-                        }
-                    }
-                }
-            }
-        }
-    } else {
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < MAXQ; ++q) {
-            const int j = tid + q * NT;
-            if (j < nb) {
-                const int jq = (Ns == 1) ? j : (int)__umulhi((unsigned)j, magic);
-                const int base = jq * Ns * R + (j - jq * Ns);
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    const int k = PadIdx::at(base + r * Ns);
-                    X0[k] = a[q][r];
-                    X1[k] = b[q][r];
-                }
-            }
-        }
-        __syncthreads();
-    }
-}
-
-__device__ __attribute__((always_inline)) inline void fft_fast2(float2 *X0, float2 *X1,
-                                                                const float2 *T,
-                                                                const RingDesc &d,
-                                                                double *__restrict__ out0,
-                                                                double *__restrict__ out1,
-                                                                bool two)
-{
-    const int h = d.n / 2;
-    int Ns = 1;
-    for (int p = 0; p < d.np; ++p) {
-        const int R = (int)((d.rads >> (5 * p)) & 31);
-        const bool first = p == 0, last = p == d.np - 1;
-        switch (R) {
-        case 16: fast_pass2<16>(X0, X1, T, h, Ns, first, last, out0, out1, two); break;
-        case 8: fast_pass2<8>(X0, X1, T, h, Ns, first, last, out0, out1, two); break;
-        case 4: fast_pass2<4>(X0, X1, T, h, Ns, first, last, out0, out1, two); break;
-        case 2: fast_pass2<2>(X0, X1, T, h, Ns, first, last, out0, out1, two); break;
-        case 7: fast_pass2<7>(X0, X1, T, h, Ns, first, last, out0, out1, two); break;
-        case 5: fast_pass2<5>(X0, X1, T, h, Ns, first, last, out0, out1, two); break;
-        default: fast_pass2<3>(X0, X1, T, h, Ns, first, last, out0, out1, two); break;
-        }
-        Ns *= R;
-    }
-}
-
 // Persistent over (ring, map pair) items, ring by ring (XCD x takes the
 // rings i = x mod 8).  LDS: two spectra of lds.fft_entries each, then the
 // twiddle table.
-__global__ __launch_bounds__(kFastThreads, 2) void k_ring_synth_fast2(
+__global__ __launch_bounds__(kFast2Threads, 4) void k_ring_synth_fast2(
     const int *__restrict__ ids, int count, int nmaps, const RingDesc *__restrict__ rings,
     const float2 *__restrict__ pool32, const float2 *__restrict__ delta,
     const int *__restrict__ minv, int mcontig, DeltaLayout dl,
@@ -1382,35 +1252,36 @@ __global__ __launch_bounds__(kFastThreads, 2) void k_ring_synth_fast2(
     const int per = (int)(gridDim.x / 8);
     const int x = (int)(blockIdx.x % 8), w = (int)(blockIdx.x / 8);
     long long lo, hi;
-    xcd_share<true>(count, npairs, x, lo, hi);
+    xcd_share<true>(count, npairs, x, dl.shift, lo, hi);
     long long it = lo + w;
     if (it >= hi) return;
     int i, pi;
-    xcd_item<true>(it, count, npairs, x, i, pi);
+    xcd_item<true>(it, count, npairs, x, dl.shift, i, pi);
     int r = ids[i];
     long long b = 2LL * pi;
     bool two = b + 1 < nmaps;
-    FastModes2<kFastThreads> raw;
-    load_fast2<kFastThreads>(raw, delta + b * dl.map + r * dl.ring, dl.m, minv, mcontig,
+    FastModes2<kFast2Threads> raw;
+    const int half = threadIdx.x / kFastThreads, htid = threadIdx.x % kFastThreads;
+    float2 *const X = half ? X1 : X0;
+    load_fast2<kFast2Threads>(raw, delta + b * dl.map + dl.row(r), dl.mstride(r), minv, mcontig,
                              rings[r].mlive, aligned, two);
     for (bool first = true;; first = false) {
         const RingDesc d = rings[r];
-        double *out0 = map + b * npix + d.start;
-        double *out1 = two ? out0 + npix : out0;
-        const bool two_now = two;
+        const bool mine = two || half == 0;
+        double *out = map + (mine ? b + half : b) * npix + d.start;
         if (!first) __syncthreads();   // the previous ring's last pass has read X0, X1, T
-        load_tw<kFastThreads>(T, pool32 + d.tw, d.n);
-        fold_fast2<kFastThreads>(X0, X1, d, raw, d.mlive);
+        load_tw<kFast2Threads>(T, pool32 + d.tw, d.n);
+        fold_fast2<kFast2Threads>(X0, X1, d, raw, d.mlive);
         const long long nx = it + per;
         if (nx < hi) {
-            xcd_item<true>(nx, count, npairs, x, i, pi);
+            xcd_item<true>(nx, count, npairs, x, dl.shift, i, pi);
             r = ids[i];
             b = 2LL * pi;
             two = b + 1 < nmaps;
-            load_fast2<kFastThreads>(raw, delta + b * dl.map + r * dl.ring, dl.m, minv, mcontig,
+            load_fast2<kFast2Threads>(raw, delta + b * dl.map + dl.row(r), dl.mstride(r), minv, mcontig,
                                      rings[r].mlive, aligned, two);
         }
-        fft_fast2(X0, X1, T, d, out0, out1, two_now);
+        fft_fast<kFastThreads, float2>(X, T, d, out, htid, mine);
         if (nx >= hi) break;
         it = nx;
     }
@@ -1426,9 +1297,7 @@ __global__ __launch_bounds__(kFastThreads, 2) void k_ring_synth_fast2(
 // This kernel takes complex128 Delta (FP64 plans, or a caller's Delta): its
 // passes run in complex128, two workgroups per CU.  The mixed forms'
 // complex64 Delta goes to k_ring_synth_fast2 (two maps per workgroup, the
-// passes in complex64; measured on the belt rings of 16 maps: complex128 one
-// map per workgroup 3.88 ms, complex64 one map per workgroup at three per CU
-// 3.10 ms, two maps per workgroup 2.47 ms).
+// passes in complex64).
 template <typename DT> struct FastPrec;
 template <> struct FastPrec<double2> {
     typedef double2 C;
@@ -1449,15 +1318,15 @@ __global__ __launch_bounds__(kFastThreads, FastPrec<DT>::kBlocks) void k_ring_sy
     const int per = (int)(gridDim.x / 8);
     const int x = (int)(blockIdx.x % 8), w = (int)(blockIdx.x / 8);
     long long lo, hi;
-    xcd_share<RingMajor<DT>::value>(count, nmaps, x, lo, hi);
+    xcd_share<RingMajor<DT>::value>(count, nmaps, x, dl.shift, lo, hi);
     long long it = lo + w;
     if (it >= hi) return;
     int i, bi;
-    xcd_item<RingMajor<DT>::value>(it, count, nmaps, x, i, bi);
+    xcd_item<RingMajor<DT>::value>(it, count, nmaps, x, dl.shift, i, bi);
     long long b = bi;
     int r = ids[i];
     FastModes<kFastThreads, DT> raw;
-    load_fast<kFastThreads>(raw, delta + b * dl.map + r * dl.ring, dl.m, minv, mcontig,
+    load_fast<kFastThreads>(raw, delta + b * dl.map + dl.row(r), dl.mstride(r), minv, mcontig,
                             ring_mmax(rings[r], mfull));
     for (bool first = true;; first = false) {
         const RingDesc d = rings[r];
@@ -1467,13 +1336,13 @@ __global__ __launch_bounds__(kFastThreads, FastPrec<DT>::kBlocks) void k_ring_sy
         fold_fast<kFastThreads>(buf, d, raw, ring_mmax(d, mfull));
         const long long nx = it + per;
         if (nx < hi) {
-            xcd_item<RingMajor<DT>::value>(nx, count, nmaps, x, i, bi);
+            xcd_item<RingMajor<DT>::value>(nx, count, nmaps, x, dl.shift, i, bi);
             b = bi;
             r = ids[i];
-            load_fast<kFastThreads>(raw, delta + b * dl.map + r * dl.ring, dl.m, minv, mcontig,
+            load_fast<kFastThreads>(raw, delta + b * dl.map + dl.row(r), dl.mstride(r), minv, mcontig,
                             ring_mmax(rings[r], mfull));
         }
-        fft_fast<kFastThreads, C>(buf, T, d, out);
+        fft_fast<kFastThreads, C>(buf, T, d, out, threadIdx.x, true);
         if (nx >= hi) break;
         it = nx;
     }
@@ -1488,8 +1357,8 @@ __global__ __launch_bounds__(kFastThreads, 2) void k_ring_synth_batch_fast(
     const BatchMap &bm = maps[it.x];
     const RingDesc d = bm.rings[it.y];
     const double2 *delta = reinterpret_cast<const double2 *>(ws + bm.delta_off);
-    synth_fast<kFastThreads, double2>(buf, buf + lds.fft_entries, d, bm.pool, delta + it.y,
-                                      bm.nrings, bm.minv, bm.mcontig, d.mlive,
+    synth_fast<kFastThreads, double2>(buf, buf + lds.fft_entries, d, bm.pool,
+                                      delta + bm.dl.row(it.y), bm.dl.mstride(it.y), bm.minv, bm.mcontig, d.mlive,
                                       outs[it.x] + d.start);
 }
 
@@ -1706,7 +1575,7 @@ __device__ __attribute__((always_inline)) inline void blue_dir(
 
 // Persistent like k_ring_synth_fast; complex64 Delta [m][ring][map] only.
 // Items are (ring, map pair), ring by ring: one 16-byte load per mode brings
-// the modes of maps 2p and 2p + 1 (paced like load_fast), and the two maps
+// the modes of maps 2p and 2p + 1 and the two maps
 // are then folded and transformed one after the other in the same buffers
 // (half the load rounds per map: caps of 16 maps at nside 2048 3.73 ->
 // 3.33 ms).  The next pair's loads go out after the second map's fold.
@@ -1729,16 +1598,16 @@ __global__ __launch_bounds__(kBlueThreads, 4) void k_ring_synth_blue(
     const int per = (int)(gridDim.x / 8);
     const int x = (int)(blockIdx.x % 8), w = (int)(blockIdx.x / 8);
     long long lo, hi;
-    xcd_share<true>(count, npairs, x, lo, hi);
+    xcd_share<true>(count, npairs, x, dl.shift, lo, hi);
     long long it = lo + w;
     if (it >= hi) return;
     int i, pi;
-    xcd_item<true>(it, count, npairs, x, i, pi);
+    xcd_item<true>(it, count, npairs, x, dl.shift, i, pi);
     int r = ids[i];
     long long b = 2LL * pi;
     bool two = b + 1 < nmaps;
     FastModes2<kBlueThreads> raw;
-    load_fast2<kBlueThreads>(raw, delta + b * dl.map + r * dl.ring, dl.m, minv, mcontig,
+    load_fast2<kBlueThreads>(raw, delta + b * dl.map + dl.row(r), dl.mstride(r), minv, mcontig,
                              rings[r].mlive, aligned, two);
     for (bool first = true;; first = false) {
         const RingDesc d = rings[r];
@@ -1767,11 +1636,11 @@ __global__ __launch_bounds__(kBlueThreads, 4) void k_ring_synth_blue(
         }
         const long long nx = it + per;
         if (nx < hi) {
-            xcd_item<true>(nx, count, npairs, x, i, pi);
+            xcd_item<true>(nx, count, npairs, x, dl.shift, i, pi);
             r = ids[i];
             b = 2LL * pi;
             two = b + 1 < nmaps;
-            load_fast2<kBlueThreads>(raw, delta + b * dl.map + r * dl.ring, dl.m, minv, mcontig,
+            load_fast2<kBlueThreads>(raw, delta + b * dl.map + dl.row(r), dl.mstride(r), minv, mcontig,
                                      rings[r].mlive, aligned, two);
         }
         if (twoB) {
@@ -1799,7 +1668,7 @@ __global__ __launch_bounds__(NT, 4) void k_ring_synth(
     double2 *tw = buf + lds.fft_entries;
     const RingTables rt = {tw, tw + lds.tw_entries};
     synth_ring<NT, MAXN, false, false>(buf, rt, d,
-                               pool, delta + b * dl.map + r * dl.ring, dl.m, minv,
+                               pool, delta + b * dl.map + dl.row(r), dl.mstride(r), minv,
                                mcontig, ring_mmax(d, mfull), map + b * npix + d.start);
 }
 
@@ -1817,7 +1686,8 @@ __global__ __launch_bounds__(NT, 4) void k_ring_synth_batch(
     double2 *tw = buf + lds.fft_entries;
     const RingTables rt = {tw, tw + lds.tw_entries};
     synth_ring<NT, MAXN, false, true>(buf, rt, d,
-                                bm.pool, delta + it.y, bm.nrings, bm.minv, bm.mcontig,
+                                bm.pool, delta + bm.dl.row(it.y), bm.dl.mstride(it.y), bm.minv,
+                                bm.mcontig,
                                 d.mlive, outs[it.x] + d.start);
 }
 
@@ -1829,8 +1699,8 @@ template <int NT, int MAXN>
 __global__ __launch_bounds__(NT, 4) void k_ring_anal(
     const int *__restrict__ ids, const RingDesc *__restrict__ rings,
     const double2 *__restrict__ pool, const double *__restrict__ map, long long npix,
-    const int *__restrict__ mval, int mcontig, int nm, int nrings, double2 *__restrict__ dt,
-    RingLds lds, const double *__restrict__ rw, double cfac)
+    const int *__restrict__ mval, int mcontig, int nm, DeltaLayout dl, double2 *__restrict__ dt,
+    int mfull, RingLds lds, const double *__restrict__ rw, double cfac)
 {
     extern __shared__ double2 buf[];
     const int r = ids[xcd_logical(blockIdx.x, gridDim.x)];
@@ -1872,7 +1742,9 @@ __global__ __launch_bounds__(NT, 4) void k_ring_anal(
         ring_dft<NT, MAXN, false>(buf, d, -1, pool, rt, ch);
     }
     const int kmax = even ? h : n - 1;
-    double2 *orow = dt + (long long)b * nm * nrings + r;   // [m][ring]
+    double2 *orow = dt + b * dl.map + dl.row(r);
+    const long long om = dl.mstride(r);
+    const int mm = ring_mmax(d, mfull);
     double2 step, ph;   // e^{-i NT phi0}, e^{-i m phi0} for this thread's mode
     {
         double sn, cs;
@@ -1883,6 +1755,7 @@ __global__ __launch_bounds__(NT, 4) void k_ring_anal(
     const double w = rw ? rw[r] : 1.0;
     for (int i = tid; i < nm; i += NT) {
         const int m = mval[i];
+        if (m > mm) break;   // dead on the ring from here on
         const int kk = m % n;
         const double2 G = (kk <= kmax) ? buf[kk] : conjd(buf[n - kk]);
         if (first || !mcontig) {
@@ -1901,7 +1774,7 @@ __global__ __launch_bounds__(NT, 4) void k_ring_anal(
             v.x *= cfac; v.y *= cfac;
         }
         if (rw) { v.x *= w; v.y *= w; }
-        orow[(long long)i * nrings] = v;
+        orow[i * om] = v;
     }
 }
 
@@ -1928,16 +1801,14 @@ __global__ __launch_bounds__(512) void k_bluestein_prep(
         pool[d.bq + k] = make_double2(buf[k].x * inv, buf[k].y * inv);
 }
 
-// The layout of the ring stage's Delta by its element type: complex64 is the
-// mixed Legendre stage's [m][ring][map], complex128 the FP64 stage's (or a
-// caller's) [map][m][ring].
-DeltaLayout delta_layout(const sht_plan_s *p, const float2 *)
+// The layout of the ring stage's Delta by its element type.
+DeltaLayout delta_layout(const sht_plan_s *p, const float2 *, bool)
 {
-    return DeltaLayout{1, p->nmaps, (long long)p->nrings * p->nmaps};
+    return delta_blocked_maps(p->nm, p->nrings, p->nmaps);
 }
-DeltaLayout delta_layout(const sht_plan_s *p, const double2 *)
+DeltaLayout delta_layout(const sht_plan_s *p, const double2 *, bool full)
 {
-    return DeltaLayout{(long long)p->nm * p->nrings, 1, p->nrings};
+    return full ? delta_plain(p->nm, p->nrings) : delta_blocked(p->nm, p->nrings);
 }
 
 hipError_t set_lds(const void *fn, size_t bytes)
@@ -1957,14 +1828,14 @@ hipError_t synth_class(const sht_plan_s *p, const RingClass &rc, const DT *delta
     if (items > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL((k_ring_synth<NT, MAXN, DT>), dim3((unsigned)items), dim3(NT), lds, st,
                        rc.d_ids, rc.count, p->nmaps, p->d_rings, p->d_pool, delta, p->d_minv,
-                       p->mcontig, full ? p->mmax : -1, delta_layout(p, delta), map, p->npix,
+                       p->mcontig, full ? p->mmax : -1, delta_layout(p, delta, full), map, p->npix,
                        rc.lds);
     return hipGetLastError();
 }
 
 template <int NT, int MAXN>
-hipError_t anal_class(const sht_plan_s *p, int c, const double *map, double2 *dt, hipStream_t st,
-                      const double *rw, double cfac)
+hipError_t anal_class(const sht_plan_s *p, int c, const double *map, double2 *dt, bool full,
+                      hipStream_t st, const double *rw, double cfac)
 {
     const RingClass &rc = p->cls[c];
     if (rc.count == 0) return hipSuccess;
@@ -1974,7 +1845,8 @@ hipError_t anal_class(const sht_plan_s *p, int c, const double *map, double2 *dt
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_ring_anal<NT, MAXN>), dim3((unsigned)rc.count, (unsigned)p->nmaps),
                        dim3(NT), lds, st, rc.d_ids, p->d_rings, p->d_pool, map, p->npix,
-                       p->d_mval, p->mcontig, p->nm, p->nrings, dt, rc.lds, rw, cfac);
+                       p->d_mval, p->mcontig, p->nm, delta_layout(p, dt, full), dt,
+                       full ? p->mmax : -1, rc.lds, rw, cfac);
     return hipGetLastError();
 }
 
@@ -1999,7 +1871,7 @@ hipError_t synth_fast_class(const sht_plan_s *p, const DT *delta, double *map, b
     grid = ((grid + 7) / 8) * 8;
     hipLaunchKernelGGL((k_ring_synth_fast<DT>), dim3((unsigned)grid), dim3(kFastThreads), lds,
                        st, rc.d_ids, rc.count, p->nmaps, p->d_rings, p->d_pool, delta,
-                       p->d_minv, p->mcontig, full ? p->mmax : -1, delta_layout(p, delta), map,
+                       p->d_minv, p->mcontig, full ? p->mmax : -1, delta_layout(p, delta, full), map,
                        p->npix, rc.lds);
     return hipGetLastError();
 }
@@ -2007,7 +1879,7 @@ hipError_t synth_fast_class(const sht_plan_s *p, const DT *delta, double *map, b
 // complex64 Delta: two maps per workgroup, two workgroups per CU.
 template <>
 hipError_t synth_fast_class<float2>(const sht_plan_s *p, const float2 *delta, double *map,
-                                    bool, hipStream_t st)
+                                    bool full, hipStream_t st)
 {
     const RingClass &rc = p->scls[kFastClass];
     if (rc.count == 0) return hipSuccess;
@@ -2020,15 +1892,15 @@ hipError_t synth_fast_class<float2>(const sht_plan_s *p, const float2 *delta, do
     long long grid = 2LL * (p->num_cus > 0 ? p->num_cus : 256);
     if (grid > items) grid = items;
     grid = ((grid + 7) / 8) * 8;
-    hipLaunchKernelGGL(k_ring_synth_fast2, dim3((unsigned)grid), dim3(kFastThreads), lds, st,
+    hipLaunchKernelGGL(k_ring_synth_fast2, dim3((unsigned)grid), dim3(kFast2Threads), lds, st,
                        rc.d_ids, rc.count, p->nmaps, p->d_rings, p->d_pool32, delta, p->d_minv,
-                       p->mcontig, delta_layout(p, delta), map, p->npix, rc.lds);
+                       p->mcontig, delta_layout(p, delta, full), map, p->npix, rc.lds);
     return hipGetLastError();
 }
 
 // The Bluestein fast path (complex64 Delta only): two 512-thread
 // workgroups per CU, persistent.
-hipError_t synth_blue_class(const sht_plan_s *p, const float2 *delta, double *map, bool,
+hipError_t synth_blue_class(const sht_plan_s *p, const float2 *delta, double *map, bool full,
                             hipStream_t st)
 {
     const RingClass &rc = p->scls[kBlueClass];
@@ -2043,7 +1915,7 @@ hipError_t synth_blue_class(const sht_plan_s *p, const float2 *delta, double *ma
     grid = ((grid + 7) / 8) * 8;
     hipLaunchKernelGGL(k_ring_synth_blue, dim3((unsigned)grid), dim3(kBlueThreads), lds, st,
                        rc.d_ids, rc.count, p->nmaps, p->d_rings, p->d_pool32, delta, p->d_minv,
-                       p->mcontig, delta_layout(p, delta), map, p->npix, rc.lds);
+                       p->mcontig, delta_layout(p, delta, full), map, p->npix, rc.lds);
     return hipGetLastError();
 }
 
@@ -2131,19 +2003,19 @@ hipError_t launch_narrow(const double2 *s, float2 *d, long long n, hipStream_t s
     return hipGetLastError();
 }
 
-// complex64 [m][ring][map] Delta of the mixed forms -> complex128
-// [map][m][ring] (exact), one thread per output entry.
-__global__ __launch_bounds__(256) void k_widen_delta(const float2 *__restrict__ s,
+// complex64 Delta of the mixed forms -> complex128 [map][m][ring] (exact), one
+// thread per output entry.
+__global__ __launch_bounds__(256) void k_widen_delta(const float2 *__restrict__ s, DeltaLayout dl,
                                                      double2 *__restrict__ d, int nmaps, int nm,
                                                      int nrings)
 {
     const long long n = (long long)nmaps * nm * nrings;
     const long long o = (long long)blockIdx.x * 256 + threadIdx.x;
     if (o >= n) return;
-    const long long per_map = (long long)nm * nrings;
-    const int b = (int)(o / per_map);
-    const long long rem = o - b * per_map;   // i * nrings + r
-    const float2 v = s[rem * nmaps + b];
+    const int r = (int)(o % nrings);
+    const long long t = o / nrings;
+    const int i = (int)(t % nm);
+    const float2 v = s[(t / nm) * dl.map + dl.row(r) + i * dl.mstride(r)];
     d[o] = make_double2((double)v.x, (double)v.y);
 }
 
@@ -2153,17 +2025,18 @@ hipError_t launch_widen_delta(const sht_plan_s *p, const float2 *s, double2 *d, 
     if (n <= 0) return hipSuccess;
     const long long nb = (n + 255) / 256;
     if (nb > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(k_widen_delta, dim3((unsigned)nb), dim3(256), 0, st, s, d, p->nmaps, p->nm,
+    hipLaunchKernelGGL(k_widen_delta, dim3((unsigned)nb), dim3(256), 0, st, s,
+                       delta_layout(p, s, false), d, p->nmaps, p->nm,
                        p->nrings);
     return hipGetLastError();
 }
 
-hipError_t launch_ring_anal(const sht_plan_s *p, const double *map, double2 *dt, hipStream_t st,
-                            const double *rw, double cfac)
+hipError_t launch_ring_anal(const sht_plan_s *p, const double *map, double2 *dt, bool full,
+                            hipStream_t st, const double *rw, double cfac)
 {
-    hipError_t e = anal_class<1024, 8192>(p, 2, map, dt, st, rw, cfac);
-    if (e == hipSuccess) e = anal_class<512, 4096>(p, 1, map, dt, st, rw, cfac);
-    if (e == hipSuccess) e = anal_class<256, 2048>(p, 0, map, dt, st, rw, cfac);
+    hipError_t e = anal_class<1024, 8192>(p, 2, map, dt, full, st, rw, cfac);
+    if (e == hipSuccess) e = anal_class<512, 4096>(p, 1, map, dt, full, st, rw, cfac);
+    if (e == hipSuccess) e = anal_class<256, 2048>(p, 0, map, dt, full, st, rw, cfac);
     return e;
 }
 

@@ -71,17 +71,52 @@ struct LiveTab {
 
 // Rings grouped by FFT length for the Fourier kernels (LDS and register
 // budgets differ per class): class 0 up to 2048 points, 1 up to 4096, 2 up to 8192.
-// Element strides of a Delta buffer, and the order of the ring stage's
-// (map, ring) items.  complex128 Delta (the FP64 Legendre stage's, or a
-// caller's) is [map][m][ring]: neighbouring rings of one map share cache
-// lines, so the items run map by map.  The mixed forms' complex64 Delta is
-// [m][ring][map]: the maps of one ring share lines, so the items run ring by
-// ring.
+// Where the entries of a Delta buffer lie.  A caller's is [map][m][ring]
+// (complex128).  Between the stages the rings come in blocks of 2^shift, the
+// fewest that fill a 128-byte line: complex128 [map][ring / 8][m][ring % 8]
+// (the FP64 Legendre stage's, and the analysis' Delta~), complex64
+// [ring / n][m][ring % n][map] with n = 16 rings for one map, 1 from 16 maps
+// on (the mixed forms'); the last block holds the rings that are left, so no
+// buffer grows.  The Legendre stage then still writes whole lines, and the
+// modes of a ring, which the ring stage reads, are consecutive lines (0.5 MB
+// at l_max 4096) instead of lines on a page of their own each.  More rings in a
+// block would put a ring's lines a power of two apart, on few L2 channels.
 struct DeltaLayout {
-    long long map;    // stride between maps
-    long long ring;   // between rings
-    long long m;      // between the modes of one (map, ring)
+    long long map;      // stride between maps
+    long long blk;      // between blocks of rings
+    long long ring;     // between the rings of a block
+    long long m;        // between the modes of one (map, ring)
+    long long mlast;    // the same in block `lastblk`
+    int lastblk;
+    int shift;
+    __host__ __device__ long long row(int r) const
+    {
+        return (long long)(r >> shift) * blk + (r & ((1 << shift) - 1)) * ring;
+    }
+    __host__ __device__ long long mstride(int r) const
+    {
+        return (r >> shift) == lastblk ? mlast : m;
+    }
 };
+
+// A caller's buffer, and the stages' own: complex128, and complex64 of nmaps.
+inline DeltaLayout delta_plain(int nm, int nrings)
+{
+    return DeltaLayout{(long long)nm * nrings, 1, 0, nrings, nrings, -1, 0};
+}
+inline DeltaLayout delta_blocked(int nm, int nrings)
+{
+    const int sh = 3, n = 1 << sh;
+    return DeltaLayout{(long long)nm * nrings, (long long)n * nm, 1, n, nrings % n, nrings / n, sh};
+}
+inline DeltaLayout delta_blocked_maps(int nm, int nrings, int nmaps)
+{
+    int sh = 4;
+    while (sh > 0 && nmaps >= (32 >> sh)) --sh;
+    const int n = 1 << sh;
+    return DeltaLayout{1, (long long)n * nm * nmaps, nmaps, (long long)n * nmaps,
+                       (long long)(nrings % n) * nmaps, nrings / n, sh};
+}
 
 // LDS of a ring-class workgroup, in complex entries: the spectrum / FFT
 // buffer (which also stages partial alias sums during the fold), the second
@@ -242,9 +277,10 @@ struct BatchMap {
     const RingDesc *rings;
     const double2 *pool;
     LiveTab live;
+    DeltaLayout dl;
     long long nalm;
     long long ap_off;     // prescaled coefficients (double2 [nalm]) in the workspace
-    long long delta_off;  // Delta (double2 [nm][nrings]) in the workspace
+    long long delta_off;  // Delta (complex128, layout dl) in the workspace
     int lmax, mmax, nm, nrings, npairs, mcontig, m0len, pad;
 };
 
@@ -334,13 +370,16 @@ hipError_t launch_live_table(const sht_plan_s *p, double *scratch, int pmax, hip
 
 // Launchers (legendre.hip / ringfft.hip).  All enqueue on `st` only.
 hipError_t launch_prescale(const sht_plan_s *p, const double *alm, double2 *ap, hipStream_t st);
-// full: every Delta entry is written, also those of the m that are dead on a
-// ring, which the ring synthesis of the same plan does not read.
+// full: Delta is a caller's: [map][m][ring], and every entry is written, also
+// those of the m that are dead on a ring, which the ring synthesis of the same
+// plan does not read.
 hipError_t launch_legendre_fwd(const sht_plan_s *p, const double2 *ap, double2 *delta, bool full,
                                hipStream_t st);
 int fwd_pblocks(const sht_plan_s *p);
-hipError_t launch_legendre_adj_ws(const sht_plan_s *p, const double2 *dt, double2 *part,
-                                  double *alm, hipStream_t st, bool accumulate = false);
+// plain: dt is a caller's [map][m][ring], otherwise the analysis' own layout
+hipError_t launch_legendre_adj_ws(const sht_plan_s *p, const double2 *dt, bool plain,
+                                  double2 *part, double *alm, hipStream_t st,
+                                  bool accumulate = false);
 size_t adj_part_bytes(const sht_plan_s *p);
 size_t mfma_bf_bytes(const sht_plan_s *p);
 hipError_t launch_prescale_f32(const sht_plan_s *p, const double *alm, float *Bf, hipStream_t st);
@@ -363,11 +402,13 @@ hipError_t launch_ring_synth(const sht_plan_s *p, const double2 *delta, double *
                              hipStream_t st);
 hipError_t launch_ring_synth(const sht_plan_s *p, const float2 *delta, double *map,
                              hipStream_t st);
-// the mixed forms' complex64 [m][ring][map] Delta -> complex128 [map][m][ring]
+// the mixed forms' complex64 Delta -> a caller's complex128 [map][m][ring]
 hipError_t launch_widen_delta(const sht_plan_s *p, const float2 *s, double2 *d, hipStream_t st);
 hipError_t launch_narrow(const double2 *s, float2 *d, long long n, hipStream_t st);
-hipError_t launch_ring_anal(const sht_plan_s *p, const double *map, double2 *dt, hipStream_t st,
-                            const double *rw = nullptr, double cfac = 2.0);
+// full: dt is a caller's: [map][m][ring], every entry; otherwise the layout of
+// the stages' own, without the modes that are dead on a ring
+hipError_t launch_ring_anal(const sht_plan_s *p, const double *map, double2 *dt, bool full,
+                            hipStream_t st, const double *rw = nullptr, double cfac = 2.0);
 hipError_t launch_residual(const double *s, double *r, long long n, hipStream_t st);
 hipError_t launch_batch_legendre(const BatchMap *maps, int nmaps, long long max_nalm,
                                  const BatchTile *tiles, int ntiles, int chains, int grid_waves,

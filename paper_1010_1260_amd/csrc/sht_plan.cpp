@@ -1094,7 +1094,7 @@ sht_status sht_map2delta_adjoint(sht_plan_t p, const double *map, double *delta,
     sht_status s = check_plan(p);
     if (s != SHT_OK) return s;
     if (!delta || !map) return SHT_ERR_INVALID_ARG;
-    return from_hip(sht::launch_ring_anal(p, map, (double2 *)delta, (hipStream_t)stream));
+    return from_hip(sht::launch_ring_anal(p, map, (double2 *)delta, true, (hipStream_t)stream));
 }
 
 sht_status sht_delta2alm_adjoint(sht_plan_t p, const double *delta, double *alm, void *ws,
@@ -1104,7 +1104,7 @@ sht_status sht_delta2alm_adjoint(sht_plan_t p, const double *delta, double *alm,
     if (s != SHT_OK) return s;
     if (!delta || !alm) return SHT_ERR_INVALID_ARG;
     if (!ws || ws_bytes < sht::adj_part_bytes(p)) return SHT_ERR_WORKSPACE;
-    return from_hip(sht::launch_legendre_adj_ws(p, (const double2 *)delta, (double2 *)ws, alm,
+    return from_hip(sht::launch_legendre_adj_ws(p, (const double2 *)delta, true, (double2 *)ws, alm,
                                                 (hipStream_t)stream));
 }
 
@@ -1118,8 +1118,8 @@ sht_status sht_alm2map_adjoint(sht_plan_t p, const double *map, double *alm, voi
     hipStream_t st = (hipStream_t)stream;
     double2 *dt = (double2 *)ws;
     double2 *part = (double2 *)((char *)ws + p->ws_dt_bytes);
-    s = from_hip(sht::launch_ring_anal(p, map, dt, st));
-    if (s == SHT_OK) s = from_hip(sht::launch_legendre_adj_ws(p, dt, part, alm, st));
+    s = from_hip(sht::launch_ring_anal(p, map, dt, false, st));
+    if (s == SHT_OK) s = from_hip(sht::launch_legendre_adj_ws(p, dt, false, part, alm, st));
     return s;
 }
 
@@ -1137,16 +1137,16 @@ sht_status sht_map2alm(sht_plan_t p, const double *map, const double *ring_weigh
     double2 *part = (double2 *)((char *)ws + p->ws_dt_bytes);
     void *delta = (char *)ws + p->ws_ap_bytes;
     // a = D adjoint(w s): the analysis with c_m = 1 for every m
-    s = from_hip(sht::launch_ring_anal(p, map, dt, st, ring_weight, 1.0));
-    if (s == SHT_OK) s = from_hip(sht::launch_legendre_adj_ws(p, dt, part, alm, st, false));
+    s = from_hip(sht::launch_ring_anal(p, map, dt, false, st, ring_weight, 1.0));
+    if (s == SHT_OK) s = from_hip(sht::launch_legendre_adj_ws(p, dt, false, part, alm, st, false));
     // a <- a + D adjoint(w (s - alm2map(a)))
     for (int it = 0; it < niter && s == SHT_OK; ++it) {
         s = legendre_stage(p, alm, ws, delta, false, st, nullptr);
         if (s == SHT_OK) s = from_hip(synth_stage(p, delta, tmp_map, st));
         if (s == SHT_OK)
             s = from_hip(sht::launch_residual(map, tmp_map, (long long)p->nmaps * p->npix, st));
-        if (s == SHT_OK) s = from_hip(sht::launch_ring_anal(p, tmp_map, dt, st, ring_weight, 1.0));
-        if (s == SHT_OK) s = from_hip(sht::launch_legendre_adj_ws(p, dt, part, alm, st, true));
+        if (s == SHT_OK) s = from_hip(sht::launch_ring_anal(p, tmp_map, dt, false, st, ring_weight, 1.0));
+        if (s == SHT_OK) s = from_hip(sht::launch_legendre_adj_ws(p, dt, false, part, alm, st, true));
     }
     return s;
 }
