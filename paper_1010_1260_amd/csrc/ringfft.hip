@@ -1054,6 +1054,35 @@ __device__ __attribute__((always_inline)) inline void synth_fast(C *buf, C *T,
 
 // The Stockham passes of a fast-path ring (after the fold) and the pixel
 // stores of the last one.
+// DFT with positive sign of the h <= kDirectMax points buf[0..h - 1], in
+// place, by direct sums: four threads per output take every fourth term, and
+// their sums are added in a fixed order.  T: the 2h-th roots.  The buffer
+// holds at least NT entries.  Ends with a barrier.
+template <int NT, typename C>
+__device__ __attribute__((noinline)) void direct_dft(C *buf, const C *T, int h)
+{
+    const int tid = threadIdx.x, j = tid % kDirectMax, g = tid / kDirectMax;
+    C acc = cplx<C>(0.0, 0.0);
+    if (j < h && g < 4) {
+        int t = (j * g) % h;
+        const int step = (4 * j) % h;
+        for (int k = g; k < h; k += 4) {
+            acc = cadd(acc, cmul(buf[PadIdx::at(k)], tw_at(T, 2 * t)));
+            t += step;
+            t = t >= h ? t - h : t;
+        }
+    }
+    __syncthreads();
+    if (g < 4) buf[PadIdx::at(tid)] = acc;
+    __syncthreads();
+    if (tid < h) {
+        C z = acc;
+        for (int q = 1; q < 4; ++q) z = cadd(z, buf[PadIdx::at(q * kDirectMax + tid)]);
+        buf[PadIdx::at(tid)] = z;
+    }
+    __syncthreads();
+}
+
 template <int NT, typename C>
 __device__ __attribute__((always_inline)) inline void fft_fast(C *buf, const C *T,
                                                                const RingDesc &d,
@@ -1061,6 +1090,24 @@ __device__ __attribute__((always_inline)) inline void fft_fast(C *buf, const C *
                                                                bool store)
 {
     const int h = d.n / 2;
+    if (d.rads == 0) {   // no radix list: the direct path
+        C z;
+        if (tid < h) {
+            const C Fk = buf[PadIdx::at(tid)], Fk2 = buf[PadIdx::at(h - tid)];
+            const C e1 = cadd(Fk, conjd(Fk2)), o1 = csub(Fk, conjd(Fk2));
+            z = cadd(e1, muli(cmul(tw_at(T, tid), o1), +1));
+        }
+        __syncthreads();
+        if (tid < h) buf[PadIdx::at(tid)] = z;
+        __syncthreads();
+        direct_dft<NT, C>(buf, T, h);
+        if (tid < h && store) {
+            z = buf[PadIdx::at(tid)];
+            out[2 * tid] = (double)z.x;
+            out[2 * tid + 1] = (double)z.y;
+        }
+        return;
+    }
     int Ns = 1;
     for (int p = 0; p < d.np; ++p) {
         const int R = (int)((d.rads >> (5 * p)) & 31);
@@ -1778,6 +1825,149 @@ __global__ __launch_bounds__(NT, 4) void k_ring_anal(
     }
 }
 
+// ---------------------------------------------------------------------------
+// Fast path of the analysis: the same rings as the synthesis' (7-smooth half
+// length, or a short one by a direct DFT), the same register passes on the
+// padded buffer.  The DFT has negative sign: the pixels enter conjugated (as
+// z_j = g_2j - i g_{2j+1}) and the passes' results are conjugated where they
+// are read.  The first pass takes the pixels straight from the map; G_k of a
+// mode is formed from Z_k and Z_{h-k} when the mode is written.
+template <int R>
+__device__ __attribute__((always_inline)) inline void anal_pass(double2 *buf, const double2 *T,
+                                                                int h, int Ns, bool first,
+                                                                const double *__restrict__ in)
+{
+    typedef double2 C;
+    constexpr int NT = kFastThreads;
+    constexpr int MAXQ = fast_maxq(R);
+    const int nb = h / R;
+    const int tstep0 = (h / (Ns * R)) * 2;
+    const unsigned magic = (unsigned)((0x100000000ull + (unsigned)Ns - 1) / (unsigned)Ns);
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    C v[MAXQ][R];
+    const bool al = (reinterpret_cast<uintptr_t>(in) & 15) == 0;
+#pragma unroll
+    for (int q = 0; q < MAXQ; ++q) {
+        const int j = tid + q * NT;
+        if (j < nb) {
+            if (first) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const int i = j + r * nb;
+                    v[q][r] = conjd(al ? reinterpret_cast<const C *>(in)[i]
+                                       : make_double2(in[2 * i], in[2 * i + 1]));
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < R; ++r) v[q][r] = buf[PadIdx::at(j + r * nb)];
+                const int jq = (int)__umulhi((unsigned)j, magic);
+                const int ts = tstep0 * (j - jq * Ns);
+                if (ts != 0) {
+                    const C w1 = tw_at(T, ts);
+                    C wr = w1;
+#pragma unroll
+                    for (int r = 1; r < R; ++r) {
+                        v[q][r] = cmul(v[q][r], wr);
+                        wr = cmul(wr, w1);
+                    }
+                }
+            }
+            small_dft<R, C>(v[q], +1);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < MAXQ; ++q) {
+        const int j = tid + q * NT;
+        if (j < nb) {
+            const int jq = first ? j : (int)__umulhi((unsigned)j, magic);
+            const int base = jq * Ns * R + (j - jq * Ns);
+#pragma unroll
+            for (int r = 0; r < R; ++r) buf[PadIdx::at(base + r * Ns)] = v[q][r];
+        }
+    }
+    __syncthreads();
+}
+
+__global__ __launch_bounds__(kFastThreads, 2) void k_ring_anal_fast(
+    const int *__restrict__ ids, const RingDesc *__restrict__ rings,
+    const double2 *__restrict__ pool, const double *__restrict__ map, long long npix,
+    const int *__restrict__ mval, int mcontig, int nm, DeltaLayout dl, double2 *__restrict__ dt,
+    int mfull, RingLds lds, const double *__restrict__ rw, double cfac)
+{
+    extern __shared__ double2 buf[];
+    double2 *T = buf + lds.fft_entries;
+    const int r = ids[xcd_logical(blockIdx.x, gridDim.x)];
+    const int b = blockIdx.y;
+    const RingDesc d = rings[r];
+    const int tid = threadIdx.x;
+    const double *in = map + (long long)b * npix + d.start;
+    const int n = d.n, h = n / 2;
+    load_tw<kFastThreads>(T, pool + d.tw, n);
+    if (d.rads == 0) {
+        if (tid < h) buf[PadIdx::at(tid)] = make_double2(in[2 * tid], -in[2 * tid + 1]);
+        __syncthreads();
+        direct_dft<kFastThreads, double2>(buf, T, h);
+    } else {
+        int Ns = 1;
+        for (int p = 0; p < d.np; ++p) {
+            const int R = (int)((d.rads >> (5 * p)) & 31);
+            switch (R) {
+            case 16: anal_pass<16>(buf, T, h, Ns, p == 0, in); break;
+            case 8: anal_pass<8>(buf, T, h, Ns, p == 0, in); break;
+            case 4: anal_pass<4>(buf, T, h, Ns, p == 0, in); break;
+            case 2: anal_pass<2>(buf, T, h, Ns, p == 0, in); break;
+            case 7: anal_pass<7>(buf, T, h, Ns, p == 0, in); break;
+            case 5: anal_pass<5>(buf, T, h, Ns, p == 0, in); break;
+            default: anal_pass<3>(buf, T, h, Ns, p == 0, in); break;
+            }
+            Ns *= R;
+        }
+    }
+    double2 *orow = dt + b * dl.map + dl.row(r);
+    const long long om = dl.mstride(r);
+    const int mm = ring_mmax(d, mfull);
+    const double w = rw ? rw[r] : 1.0;
+    double2 step, ph;   // e^{-i NT phi0}, e^{-i m phi0} for this thread's mode
+    {
+        double sn, cs;
+        sincos((double)kFastThreads * d.phi0, &sn, &cs);
+        step = make_double2(cs, -sn);
+    }
+    bool first = true;
+    for (int i = tid; i < nm; i += kFastThreads) {
+        const int m = mval[i];
+        if (m > mm) break;   // dead on the ring from here on
+        if (first || !mcontig) {
+            double sn, cs;
+            sincos((double)m * d.phi0, &sn, &cs);
+            ph = make_double2(cs, -sn);
+            first = false;
+        } else {
+            ph = cmul(ph, step);
+        }
+        // G_k = (Z_k + conj Z_{h-k})/2 - (i/2) e^{-2 pi i k/n} (Z_k - conj Z_{h-k})
+        // (the buffer holds conj Z), and G_{n-k} = conj G_k
+        const int kk = m % n, k = kk <= h ? kk : n - kk;
+        const double2 Zk = conjd(buf[PadIdx::at(k == h ? 0 : k)]);
+        const double2 Zc = buf[PadIdx::at(k == 0 ? 0 : h - k)];
+        const double2 a = cadd(Zk, Zc), o = csub(Zk, Zc);
+        double2 G = csub(a, muli(cmul(conjd(tw_at(T, k)), o), +1));
+        G.x *= 0.5;
+        G.y *= kk <= h ? 0.5 : -0.5;
+        double2 v;
+        if (m == 0) {
+            v = make_double2(G.x, 0.0);
+        } else {
+            v = cmul(G, ph);
+            v.x *= cfac; v.y *= cfac;
+        }
+        if (rw) { v.x *= w; v.y *= w; }
+        orow[i * om] = v;
+    }
+}
+
 // Spectrum of the Bluestein kernel b_k = conj(c_k) (wrapped to negative k),
 // scaled by 1 / nb, one workgroup per listed ring.
 __global__ __launch_bounds__(512) void k_bluestein_prep(
@@ -1845,6 +2035,21 @@ hipError_t anal_class(const sht_plan_s *p, int c, const double *map, double2 *dt
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_ring_anal<NT, MAXN>), dim3((unsigned)rc.count, (unsigned)p->nmaps),
                        dim3(NT), lds, st, rc.d_ids, p->d_rings, p->d_pool, map, p->npix,
+                       p->d_mval, p->mcontig, p->nm, delta_layout(p, dt, full), dt,
+                       full ? p->mmax : -1, rc.lds, rw, cfac);
+    return hipGetLastError();
+}
+
+hipError_t anal_fast_class(const sht_plan_s *p, const double *map, double2 *dt, bool full,
+                           hipStream_t st, const double *rw, double cfac)
+{
+    const RingClass &rc = p->scls[kFastClass];
+    if (rc.count == 0) return hipSuccess;
+    const size_t lds = (size_t)rc.lds.total() * sizeof(double2);
+    hipError_t e = set_lds((const void *)k_ring_anal_fast, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_ring_anal_fast, dim3((unsigned)rc.count, (unsigned)p->nmaps),
+                       dim3(kFastThreads), lds, st, rc.d_ids, p->d_rings, p->d_pool, map, p->npix,
                        p->d_mval, p->mcontig, p->nm, delta_layout(p, dt, full), dt,
                        full ? p->mmax : -1, rc.lds, rw, cfac);
     return hipGetLastError();
@@ -2034,7 +2239,8 @@ hipError_t launch_widen_delta(const sht_plan_s *p, const float2 *s, double2 *d, 
 hipError_t launch_ring_anal(const sht_plan_s *p, const double *map, double2 *dt, bool full,
                             hipStream_t st, const double *rw, double cfac)
 {
-    hipError_t e = anal_class<1024, 8192>(p, 2, map, dt, full, st, rw, cfac);
+    hipError_t e = anal_fast_class(p, map, dt, full, st, rw, cfac);
+    if (e == hipSuccess) e = anal_class<1024, 8192>(p, 2, map, dt, full, st, rw, cfac);
     if (e == hipSuccess) e = anal_class<512, 4096>(p, 1, map, dt, full, st, rw, cfac);
     if (e == hipSuccess) e = anal_class<256, 2048>(p, 0, map, dt, full, st, rw, cfac);
     return e;

@@ -152,6 +152,11 @@ constexpr int kNumSynthClasses = 5;
 constexpr int kFastThreads = 256;
 constexpr int kFastMaxH = 4096;
 constexpr int kFastMaxModes = 17 * kFastThreads;   // the fold holds m < 4352 in registers
+// FP64 plans also take even rings of any half length up to kDirectMax on the
+// fast path, as one direct DFT (radix list 0): four threads per output point.
+// Bluestein's two dozen passes over so few points are all latency: the 18
+// rings of 44..124 pixels at nside 32 took 18 us.
+constexpr int kDirectMax = kFastThreads / 4;
 constexpr int kBlueThreads = 512;
 constexpr int kBlueMaxN = 4096;
 // padded LDS index of the fast path (one spare entry per 16)
@@ -334,7 +339,7 @@ struct sht_plan_s {
     std::vector<int> ring_need;   // LDS double2 entries of each ring's spectrum / FFT
     std::vector<int> ring_n;      // pixels of each ring
     std::vector<int> ring_nb;     // Bluestein length of each ring (0: none)
-    sht::RingClass cls[sht::kNumRingClasses];     // analysis: every ring
+    sht::RingClass cls[sht::kNumRingClasses];     // analysis: the rings off the fast path
     sht::RingClass scls[sht::kNumSynthClasses];   // synthesis
     // the Bluestein fast path's rings by size class, for synthesis from a
     // caller's complex128 Delta (sht_delta2map), which that path does not take

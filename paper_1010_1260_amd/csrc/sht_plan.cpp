@@ -538,11 +538,17 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
         const int need = std::max(spec, fftlen);
         const int c = fftlen <= 2048 ? 0 : (fftlen <= 4096 ? 1 : 2);
         ring_class[r] = c;
-        sht::ring_lds_add(class_lds[c], c, g.n, g.nb, need);
         g.np = (n % 2 == 0 && g.nb == 0 && mval.back() < sht::kFastMaxModes)
                    ? sht::fast_radices(g.clen, &g.rads) : 0;
+        // a short half length that has no radix list: one direct pass
+        const bool direct = g.np == 0 && d->precision == SHT_FP64 && n % 2 == 0 &&
+                            g.clen <= sht::kDirectMax && mval.back() < sht::kFastMaxModes;
+        if (direct) {
+            g.np = 1;
+            g.rads = 0;
+        }
         if (g.np == 0 && g.half && blue_ok) g.np = sht::blue_radices(g.nb, &g.rads);
-        if (g.np > 0 && g.nb == 0) {
+        if (direct || (g.np > 0 && g.nb == 0)) {
             ring_sclass[r] = sht::kFastClass;
             sht::fast_lds_add(sclass_lds[sht::kFastClass], g.n, mval.back());
         } else if (g.np > 0) {
@@ -554,6 +560,12 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
             ring_sclass[r] = c;
             sht::ring_lds_add(sclass_lds[c], c, g.n, g.nb, need);
         }
+        // the analysis takes the fast path's rings on its own fast path, in
+        // every precision, and the others by size class
+        if (ring_sclass[r] == sht::kFastClass)
+            ring_class[r] = -1;
+        else
+            sht::ring_lds_add(class_lds[c], c, g.n, g.nb, need);
     }
 
     sht_plan_s *p = new (std::nothrow) sht_plan_s();
@@ -819,7 +831,7 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
         static const char *kPrec[] = {"fp64", "fp32_mfma", "bf16x3_mfma", "f16x2_mfma"};
         int nblue = 0, nfast = 0;
         for (int r = 0; r < R; ++r) {
-            nblue += rings[r].nb != 0 && ring_sclass[r] != sht::kBlueClass;
+            nblue += rings[r].nb != 0 && ring_sclass[r] < sht::kNumRingClasses;
             nfast += ring_sclass[r] == sht::kFastClass;
         }
         sht::log_line("plan l_max=%d nm=%d m_max=%d rings=%d pairs=%d maps=%d precision=%s "
@@ -842,7 +854,7 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
             int o = 0;
             for (int q = 0; q < g.np; ++q)
                 o += std::snprintf(rl + o, sizeof rl - o, q ? "x%d" : "%d",
-                                   (int)((g.rads >> (5 * q)) & 31));
+                                   g.rads ? (int)((g.rads >> (5 * q)) & 31) : g.clen);
             sht::log_line("plan fast ring nphi=%d: half length %d = %s", g.n, g.clen, rl);
         }
         sht::log_line("plan workspace forward=%zu full=%zu bytes, device tables=%zu bytes; "
