@@ -208,6 +208,9 @@ sht_status sht_plan_batch(sht_batch_t *out, const sht_plan_t *plans, int32_t n)
                     items.push_back(make_int2(i, r));
                     if (c == sht::kFastClass)
                         sht::fast_lds_add(lds, p->ring_n[r], p->mmax);
+                    else if (c >= sht::kBlue64Class)
+                        sht::blue_lds_add(lds, p->ring_n[r], p->ring_nb[r], p->ring_mlive[r],
+                                          sht::kBlue64Threads[c - sht::kBlue64Class]);
                     else
                         sht::ring_lds_add(lds, c, p->ring_n[r], p->ring_nb[r], p->ring_need[r]);
                 }

@@ -15,33 +15,38 @@
 // Analysis (adjoint): G_k = sum_j g_j e^{-2 pi i j k / n} by the reverse
 // construction, then Dt_m = c_m e^{-i m phi0} G_{m mod n} (c_0 = 1, c_m = 2).
 //
-// One workgroup per ring and map; the whole ring lives in LDS.  The
-// synthesis of even rings whose half length is 7-smooth and at most 4096
-// (every HEALPix belt ring, and the caps' smooth rings) takes a fast path: a
-// persistent 256-thread kernel that loads a ring's modes all at once (the
-// next ring's while the current one is transformed), folds them through a
-// padded LDS buffer and runs Stockham passes of radix 16, 8, 4, 2, 7, 5, 3
-// with the butterflies held in registers, the half-length pre-processing
-// fused into the first pass and the pixels stored from the last.  Its passes
-// run in complex128 for FP64 plans; for the mixed forms, whose Delta is
-// complex64 with the maps of a ring contiguous, one workgroup takes two maps of a ring (one
-// 16-byte load per mode) and runs the passes of both in complex64 (the fold
-// adds in FP64 either way).  The mixed forms also take even rings whose half
-// length is twice a non-7-smooth number on a Bluestein fast path: a
-// persistent 512-thread kernel that loads two maps of a ring per item and,
-// map by map, runs the even- and odd-indexed Bluestein convolutions side by
-// side in two complex64 buffers.  The other rings are
-// grouped by FFT length into three size classes (up to 2048, 4096 and 8192
-// points) run by 256-, 512- and 1024-thread workgroups, each with an LDS
-// layout computed on the host for the class.  There, DFTs of 7-smooth length run as
-// a Stockham auto-sort FFT (radices 8, 4, 2, 3, 5 and 7; every pass loads its
-// butterfly inputs into registers, barriers, and stores in place, so one LDS
-// buffer suffices).  Other lengths use Bluestein's chirp-z algorithm with a
-// 7-smooth convolution length whose kernel spectrum is precomputed at plan
-// time; an even length whose half is not 7-smooth is split into the DFTs of
-// its even- and odd-indexed inputs (two Bluestein transforms of half length)
-// joined by one radix-2 step.  Twiddles come from per-length tables computed
-// on the host in extended precision.
+// The whole ring lives in LDS, one workgroup to a ring and map (two maps in the
+// mixed forms).  What each ring takes, in this order:
+//  - fast path (k_ring_synth_fast, k_ring_anal_fast): even rings whose half
+//    length is 7-smooth and at most 4096 (every HEALPix belt ring and the caps'
+//    smooth ones).  A persistent kernel loads a ring's modes all at once (the
+//    next ring's while the current one is transformed), folds them through a
+//    padded LDS buffer and runs Stockham passes of radix 16, 8, 4, 2, 7, 5, 3
+//    with the butterflies held in registers, the half-length pre-processing
+//    fused into the first pass and the pixels stored from the last; the
+//    analysis is the reverse, pixels into the first pass and modes out of LDS.
+//    FP64 plans run it in complex128, and also take even rings of at most 64
+//    points of half length on it, as a direct DFT.  The mixed forms, whose
+//    Delta is complex64 with the maps of a ring contiguous, run the synthesis
+//    in complex64, two maps of a ring per workgroup and one 16-byte load per
+//    mode (the fold adds in FP64 either way).
+//  - Bluestein fast path (k_ring_synth_blue and, in complex128 and also for
+//    the analysis, k_ring_synth_blue64 / k_ring_anal_blue64): even rings whose
+//    half length is even and not 7-smooth.  The even- and odd-indexed
+//    convolutions run side by side in two buffers, with the chirps, the kernel
+//    spectrum, the pre-processing and the stores inside the passes.
+//  - everything else (odd lengths, half lengths above 4096 or odd and not
+//    smooth, mixed-form analysis, a caller's whole Delta): size classes by FFT
+//    length (up to 2048, 4096 and 8192 points) on 256-, 512- and 1024-thread
+//    workgroups.  DFTs of 7-smooth length run as an in-place Stockham FFT
+//    (radices 8, 4, 2, 3, 5 and 7; every pass loads its butterfly inputs into
+//    registers, barriers, and stores); other lengths use Bluestein's chirp-z
+//    algorithm with a 7-smooth convolution length whose kernel spectrum is
+//    precomputed at plan time; an even length whose half is not 7-smooth is
+//    split into the DFTs of its even- and odd-indexed inputs joined by one
+//    radix-2 step.
+// Twiddles come from per-length tables computed on the host in extended
+// precision.
 #include "sht_internal.h"
 
 // Every fused multiply-add in this file is written out (fma, cmul): no
@@ -941,6 +946,9 @@ __device__ __attribute__((always_inline)) inline void load_fast(FastModes<NT, DT
     }
 }
 
+template <int NT, typename C>
+__device__ __attribute__((always_inline)) inline void fold_bins(C *buf, const RingDesc &d, int mmax);
+
 template <int NT, typename C, typename DT>
 __device__ __attribute__((always_inline)) inline void fold_fast(C *buf, const RingDesc &d,
                                                                 const FastModes<NT, DT> &raw,
@@ -968,6 +976,15 @@ __device__ __attribute__((always_inline)) inline void fold_fast(C *buf, const Ri
         ph = cmul(ph, step);
     }
     __syncthreads();
+    fold_bins<NT, C>(buf, d, mmax);
+}
+
+// The bins of a fast-path ring from its phased modes, in place (see
+// fold_fast).  Ends with a barrier.
+template <int NT, typename C>
+__device__ __attribute__((always_inline)) inline void fold_bins(C *buf, const RingDesc &d, int mmax)
+{
+    const int tid = threadIdx.x;
     const int n = d.n;
     const int h = n / 2;
     const int B = h + 1;
@@ -1424,13 +1441,33 @@ __global__ __launch_bounds__(kFastThreads, 2) void k_ring_synth_batch_fast(
 // combines E and O and writes the pixels.  The chirp
 // c_k = e^{i pi k^2 / len} = e^{2 pi i (k^2 mod h) / h} is read from the
 // ring's n-th roots (n = 2 h) in LDS.
-enum BlueIn { kBlueInZ, kBlueInBuf, kBlueInBq };
+// What the first pass of a direction reads and the last one writes: the folded
+// spectrum, the buffers, the buffers times the kernel's spectrum, or a ring's
+// pixels (analysis); the buffers, the pixels, or the transform in X (analysis).
+enum BlueIn { kBlueInZ, kBlueInBuf, kBlueInBq, kBlueInPix };
+enum BlueOut { kBlueOutBuf, kBlueOutPix, kBlueOutZ };
 
+template <typename C>
 struct BlueRing {
     int h, len;
     float inv_h;         // 1 / h, rounded
-    const float2 *bq;    // kernel spectrum DFT^-(conj chirp, wrapped) / nb
+    const C *bq;         // kernel spectrum DFT^-(conj chirp, wrapped) / nb
+    double *out;         // first pixel of the ring (synthesis)
+    const double *in;    // the same (analysis)
 };
+
+template <typename C>
+__device__ inline BlueRing<C> blue_ring(const RingDesc &d, const C *pool)
+{
+    BlueRing<C> br;
+    br.h = d.n / 2;
+    br.len = br.h / 2;
+    br.inv_h = 1.0f / (float)br.h;
+    br.bq = pool + d.bq;
+    br.out = nullptr;
+    br.in = nullptr;
+    return br;
+}
 
 // k^2 mod h for k < 2^11 and h < 2^13, exactly: k^2 < 2^22 is exact in
 // FP32, and the rounded quotient k^2 * (1/h) is within 0.05 of k^2 / h, so
@@ -1444,54 +1481,59 @@ __device__ inline int sq_mod(int k, int h, float inv_h)
     return (r >= h) ? r - h : r;
 }
 
-// One pass of radix R over both nb-point buffers of each of NM maps (input
-// index j + r nb/R, output index (j / Ns) Ns R + j % Ns + r Ns); TB holds the
-// nb-th roots, TW the n-th roots; the maps share every twiddle.  last:
-// Ns R = nb, the pass ends in the pixel stores (of the first nout maps).
-// The kernel runs one map per workgroup: two maps (four buffers) fit one
-// workgroup per CU and measured slower (caps of 16 maps at nside 2048:
-// 4.01 against 3.75 ms), unlike the fast path's two-map kernel.
-template <int R, int sign, int NM>
-__device__ __attribute__((always_inline)) inline void blue_pass(
-    float2 *const (&X)[NM], float2 *const (&Y)[NM], const float2 *TW, const float2 *TB, int L,
-    int Ns, int in, bool last, const BlueRing &br, double *const (&out)[NM], int nout)
+// One pass of radix R over both nb-point buffers (input index j + r nb/R,
+// output index (j / Ns) Ns R + j % Ns + r Ns); TB holds the nb-th roots, TW the
+// n-th roots.
+template <typename C, int NT, int R, int sign>
+__device__ __attribute__((always_inline)) inline void blue_pass(C *X, C *Y, const C *TW,
+                                                                const C *TB, int L, int Ns, int in,
+                                                                int outm, const BlueRing<C> &br)
 {
-    typedef float2 C;
-    constexpr int NT = kBlueThreads;
     const int nbf = L / R;   // the plan admits nb / R <= NT: one butterfly per thread
     const int tstep0 = L / (Ns * R);
     const unsigned magic = (unsigned)((0x100000000ull + (unsigned)Ns - 1) / (unsigned)Ns);
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int j = tid;
-    C a[NM][R], b[NM][R];
+    C a[R], b[R];
     if (j < nbf) {
-        if (in == kBlueInZ) {
+        if (in == kBlueInZ || in == kBlueInPix) {
             const int h = br.h;
+            const bool al = (reinterpret_cast<uintptr_t>(br.in) & 15) == 0;
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const int k = j + r * nbf;
                 if (k < br.len) {
-                    // Z_t = (F_t + conj F_{h-t}) + i e^{2 pi i t/n} (F_t - conj F_{h-t}),
-                    // t = 2k and 2k + 1
                     const int t0 = 2 * k, t1 = t0 + 1;
-                    const C w0 = tw_at(TW, t0), w1 = tw_at(TW, t1);
                     const C c = tw_at(TW, 2 * sq_mod(k, h, br.inv_h));
-#pragma unroll
-                    for (int mm = 0; mm < NM; ++mm) {
-                        const C F0 = X[mm][PadIdx::at(t0)], G0 = X[mm][PadIdx::at(h - t0)];
-                        const C F1 = X[mm][PadIdx::at(t1)], G1 = X[mm][PadIdx::at(h - t1)];
-                        const C z0 = cadd(cadd(F0, conjd(G0)), muli(cmul(w0, csub(F0, conjd(G0))), +1));
-                        const C z1 = cadd(cadd(F1, conjd(G1)), muli(cmul(w1, csub(F1, conjd(G1))), +1));
-                        a[mm][r] = cmul(z0, c);
-                        b[mm][r] = cmul(z1, c);
+                    C z0, z1;
+                    if (sizeof(C) == 16 && in == kBlueInPix) {
+                        // the DFT of the analysis has negative sign: conjugated
+                        // pixels in, conjugated transform out
+                        const double *g = br.in + 2 * t0;
+                        if (al) {
+                            const double2 p0 = reinterpret_cast<const double2 *>(g)[0];
+                            const double2 p1 = reinterpret_cast<const double2 *>(g)[1];
+                            z0 = cplx<C>(p0.x, -p0.y);
+                            z1 = cplx<C>(p1.x, -p1.y);
+                        } else {
+                            z0 = cplx<C>(g[0], -g[1]);
+                            z1 = cplx<C>(g[2], -g[3]);
+                        }
+                    } else {
+                        // Z_t = (F_t + conj F_{h-t}) + i e^{2 pi i t/n} (F_t - conj F_{h-t}),
+                        // t = 2k and 2k + 1
+                        const C w0 = tw_at(TW, t0), w1 = tw_at(TW, t1);
+                        const C F0 = X[PadIdx::at(t0)], G0 = X[PadIdx::at(h - t0)];
+                        const C F1 = X[PadIdx::at(t1)], G1 = X[PadIdx::at(h - t1)];
+                        z0 = cadd(cadd(F0, conjd(G0)), muli(cmul(w0, csub(F0, conjd(G0))), +1));
+                        z1 = cadd(cadd(F1, conjd(G1)), muli(cmul(w1, csub(F1, conjd(G1))), +1));
                     }
+                    a[r] = cmul(z0, c);
+                    b[r] = cmul(z1, c);
                 } else {
-#pragma unroll
-                    for (int mm = 0; mm < NM; ++mm) {
-                        a[mm][r] = make_float2(0.f, 0.f);
-                        b[mm][r] = make_float2(0.f, 0.f);
-                    }
+                    a[r] = cplx<C>(0.0, 0.0);
+                    b[r] = cplx<C>(0.0, 0.0);
                 }
             }
         } else if (in == kBlueInBq) {
@@ -1502,21 +1544,15 @@ __device__ __attribute__((always_inline)) inline void blue_pass(
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const int k = PadIdx::at(j + r * nbf);
-#pragma unroll
-                for (int mm = 0; mm < NM; ++mm) {
-                    a[mm][r] = cmul(X[mm][k], wq[r]);
-                    b[mm][r] = cmul(Y[mm][k], wq[r]);
-                }
+                a[r] = cmul(X[k], wq[r]);
+                b[r] = cmul(Y[k], wq[r]);
             }
         } else {
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const int k = PadIdx::at(j + r * nbf);
-#pragma unroll
-                for (int mm = 0; mm < NM; ++mm) {
-                    a[mm][r] = X[mm][k];
-                    b[mm][r] = Y[mm][k];
-                }
+                a[r] = X[k];
+                b[r] = Y[k];
             }
         }
         if (Ns > 1) {
@@ -1528,54 +1564,16 @@ __device__ __attribute__((always_inline)) inline void blue_pass(
                 C wr = w1;
 #pragma unroll
                 for (int r = 1; r < R; ++r) {
-#pragma unroll
-                    for (int mm = 0; mm < NM; ++mm) {
-                        a[mm][r] = cmul(a[mm][r], wr);
-                        b[mm][r] = cmul(b[mm][r], wr);
-                    }
+                    a[r] = cmul(a[r], wr);
+                    b[r] = cmul(b[r], wr);
                     wr = cmul(wr, w1);
                 }
             }
         }
-#pragma unroll
-        for (int mm = 0; mm < NM; ++mm) {
-            small_dft<R, C>(a[mm], sign);
-            small_dft<R, C>(b[mm], sign);
-        }
+        small_dft<R, C>(a, sign);
+        small_dft<R, C>(b, sign);
     }
-    if (last) {
-        // j < Ns: outputs o = j + r nbf; for o < len, E_o = c_o a, O_o = c_o b
-        const int h = br.h, len = br.len;
-        if (j < nbf) {
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const int o = j + r * nbf;
-                if (o < len) {
-                    const C c = tw_at(TW, 2 * sq_mod(o, h, br.inv_h));
-                    const C w = tw_at(TW, 2 * o);
-#pragma unroll
-                    for (int mm = 0; mm < NM; ++mm) {
-                        if (mm < nout) {
-                            const C E = cmul(a[mm][r], c);
-                            const C t = cmul(w, cmul(b[mm][r], c));
-                            const double2 z0 = todbl(cadd(E, t)), z1 = todbl(csub(E, t));
-                            double *op = out[mm];
-                            if ((reinterpret_cast<uintptr_t>(op) & 15) == 0) {
-                                double2 *o2 = reinterpret_cast<double2 *>(op);
-                                o2[o] = z0;
-                                o2[o + len] = z1;
-                            } else {
-                                op[2 * o] = z0.x;
-                                op[2 * o + 1] = z0.y;
-                                op[2 * (o + len)] = z1.x;
-                                op[2 * (o + len) + 1] = z1.y;
-                            }
-                        }
-                    }
-                }
-            }
-        }
-    } else {
+    if (outm == kBlueOutBuf) {
         __syncthreads();
         if (j < nbf) {
             const int jq = (Ns == 1) ? j : (int)__umulhi((unsigned)j, magic);
@@ -1583,41 +1581,83 @@ __device__ __attribute__((always_inline)) inline void blue_pass(
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const int k = PadIdx::at(base + r * Ns);
-#pragma unroll
-                for (int mm = 0; mm < NM; ++mm) {
-                    X[mm][k] = a[mm][r];
-                    Y[mm][k] = b[mm][r];
-                }
+                X[k] = a[r];
+                Y[k] = b[r];
             }
         }
         __syncthreads();
+    } else {
+        // j < Ns: outputs o = j + r nbf; for o < len, E_o = c_o a, O_o = c_o b
+        const int h = br.h, len = br.len;
+        if (outm == kBlueOutZ) __syncthreads();
+        if (j < nbf) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int o = j + r * nbf;
+                if (o < len) {
+                    const C c = tw_at(TW, 2 * sq_mod(o, h, br.inv_h));
+                    const C w = tw_at(TW, 2 * o);
+                    const C E = cmul(a[r], c);
+                    const C t = cmul(w, cmul(b[r], c));
+                    if (outm == kBlueOutZ) {
+                        X[PadIdx::at(o)] = cadd(E, t);
+                        X[PadIdx::at(o + len)] = csub(E, t);
+                    } else {
+                        const double2 z0 = todbl(cadd(E, t)), z1 = todbl(csub(E, t));
+                        double *op = br.out;
+                        if ((reinterpret_cast<uintptr_t>(op) & 15) == 0) {
+                            double2 *o2 = reinterpret_cast<double2 *>(op);
+                            o2[o] = z0;
+                            o2[o + len] = z1;
+                        } else {
+                            op[2 * o] = z0.x;
+                            op[2 * o + 1] = z0.y;
+                            op[2 * (o + len)] = z1.x;
+                            op[2 * (o + len) + 1] = z1.y;
+                        }
+                    }
+                }
+            }
+        }
+        if (outm == kBlueOutZ) __syncthreads();
     }
 }
 
 // The passes of one direction of a Bluestein fast-path ring's convolutions:
-// sign -1 (forward, from the folded spectra) or +1 (inverse, ending in the
-// pixel stores).
-template <int sign, int NM>
-__device__ __attribute__((always_inline)) inline void blue_dir(
-    float2 *const (&X)[NM], float2 *const (&Y)[NM], const float2 *TW, const float2 *TB,
-    const RingDesc &d, const BlueRing &br, double *const (&out)[NM], int nout)
+// sign -1 (forward, its first pass reading in0) or +1 (inverse, its last pass
+// writing outl).
+template <typename C, int NT, int sign>
+__device__ __attribute__((always_inline)) inline void blue_dir(C *X, C *Y, const C *TW,
+                                                               const C *TB, const RingDesc &d,
+                                                               const BlueRing<C> &br, int in0,
+                                                               int outl)
 {
     const int L = d.nb;
     int Ns = 1;
     for (int p = 0; p < d.np; ++p) {
         const int R = (int)((d.rads >> (5 * p)) & 31);
-        const int in = (p > 0) ? kBlueInBuf : (sign < 0 ? kBlueInZ : kBlueInBq);
-        const bool last = sign > 0 && p == d.np - 1;
+        const int in = p > 0 ? kBlueInBuf : in0;
+        const int outm = p == d.np - 1 ? outl : kBlueOutBuf;
         switch (R) {
-        case 8: blue_pass<8, sign, NM>(X, Y, TW, TB, L, Ns, in, last, br, out, nout); break;
-        case 4: blue_pass<4, sign, NM>(X, Y, TW, TB, L, Ns, in, last, br, out, nout); break;
-        case 2: blue_pass<2, sign, NM>(X, Y, TW, TB, L, Ns, in, last, br, out, nout); break;
-        case 7: blue_pass<7, sign, NM>(X, Y, TW, TB, L, Ns, in, last, br, out, nout); break;
-        case 5: blue_pass<5, sign, NM>(X, Y, TW, TB, L, Ns, in, last, br, out, nout); break;
-        default: blue_pass<3, sign, NM>(X, Y, TW, TB, L, Ns, in, last, br, out, nout); break;
+        case 8: blue_pass<C, NT, 8, sign>(X, Y, TW, TB, L, Ns, in, outm, br); break;
+        case 4: blue_pass<C, NT, 4, sign>(X, Y, TW, TB, L, Ns, in, outm, br); break;
+        case 2: blue_pass<C, NT, 2, sign>(X, Y, TW, TB, L, Ns, in, outm, br); break;
+        case 7: blue_pass<C, NT, 7, sign>(X, Y, TW, TB, L, Ns, in, outm, br); break;
+        case 5: blue_pass<C, NT, 5, sign>(X, Y, TW, TB, L, Ns, in, outm, br); break;
+        default: blue_pass<C, NT, 3, sign>(X, Y, TW, TB, L, Ns, in, outm, br); break;
         }
         Ns *= R;
     }
+}
+
+template <typename C, int NT>
+__device__ __attribute__((always_inline)) inline void blue_conv(C *X, C *Y, const C *TW,
+                                                                const C *TB, const RingDesc &d,
+                                                                const BlueRing<C> &br, int in0,
+                                                                int outl)
+{
+    blue_dir<C, NT, -1>(X, Y, TW, TB, d, br, in0, kBlueOutBuf);
+    blue_dir<C, NT, +1>(X, Y, TW, TB, d, br, kBlueInBq, outl);
 }
 
 // Persistent like k_ring_synth_fast; complex64 Delta [m][ring][map] only.
@@ -1639,7 +1679,6 @@ __global__ __launch_bounds__(kBlueThreads, 4) void k_ring_synth_blue(
     C *Y = X + lds.fft_entries;
     C *TW = Y + lds.y_entries;
     C *TB = TW + lds.tw_entries;
-    float2 *const Xs[1] = {X}, *const Ys[1] = {Y};
     const int npairs = (nmaps + 1) / 2;
     const bool aligned = (nmaps % 2) == 0;
     const int per = (int)(gridDim.x / 8);
@@ -1658,13 +1697,8 @@ __global__ __launch_bounds__(kBlueThreads, 4) void k_ring_synth_blue(
                              rings[r].mlive, aligned, two);
     for (bool first = true;; first = false) {
         const RingDesc d = rings[r];
-        BlueRing br;
-        br.h = d.n / 2;
-        br.len = br.h / 2;
-        br.inv_h = 1.0f / (float)br.h;
-        br.bq = pool32 + d.bq;
-        double *const outA[1] = {map + b * npix + d.start};
-        double *const outB[1] = {map + (b + 1) * npix + d.start};
+        BlueRing<C> br = blue_ring<C>(d, pool32);
+        br.out = map + b * npix + d.start;
         const bool twoB = two;
         if (!first) __syncthreads();   // the previous ring's last pass has read TW
         load_tw<kBlueThreads>(TW, pool32 + d.tw, d.n);
@@ -1673,8 +1707,8 @@ __global__ __launch_bounds__(kBlueThreads, 4) void k_ring_synth_blue(
 #pragma unroll
         for (int q = 0; q < QM; ++q) one.v[q] = make_float2(raw.v[q].x, raw.v[q].y);
         fold_fast<kBlueThreads>(X, d, one, d.mlive);
-        blue_dir<-1, 1>(Xs, Ys, TW, TB, d, br, outA, 1);
-        blue_dir<+1, 1>(Xs, Ys, TW, TB, d, br, outA, 1);
+        blue_conv<C, kBlueThreads>(X, Y, TW, TB, d, br, kBlueInZ, kBlueOutPix);
+        br.out += npix;
         if (twoB) {
 #pragma unroll
             for (int q = 0; q < QM; ++q) one.v[q] = make_float2(raw.v[q].z, raw.v[q].w);
@@ -1691,12 +1725,94 @@ __global__ __launch_bounds__(kBlueThreads, 4) void k_ring_synth_blue(
                                      rings[r].mlive, aligned, two);
         }
         if (twoB) {
-            blue_dir<-1, 1>(Xs, Ys, TW, TB, d, br, outB, 1);
-            blue_dir<+1, 1>(Xs, Ys, TW, TB, d, br, outB, 1);
+            blue_conv<C, kBlueThreads>(X, Y, TW, TB, d, br, kBlueInZ, kBlueOutPix);
         }
         if (nx >= hi) break;
         it = nx;
     }
+}
+
+// ---------------------------------------------------------------------------
+// The same path in complex128 (FP64 plans), one map of a ring per workgroup.
+// Against the size-class kernels it has both convolutions in one set of passes
+// and the chirps, the kernel spectrum, the pre-processing and the stores inside
+// them: a third of the barriers.
+// Bound by the latency of its passes (LDS and barriers, 50-60 % of the FP64
+// issue slots idle).  Rings of one map, against the size-class kernels: nside
+// 512, synthesis 47 to 37 us for the stage, transform 176 to 161 us; nside
+// 2048, analysis 740 to 540 us, transform 4.50 to 4.23 ms; a batch of 64 maps
+// of l_max 200 to 2000, 3.3 to 2.4 ms for the stage.
+template <int NT>
+__device__ __attribute__((always_inline)) inline void synth_blue64(
+    double2 *X, const RingLds &lds, const RingDesc &d, const double2 *__restrict__ pool,
+    const double2 *__restrict__ drow, long long dstride, const int *__restrict__ minv, int mcontig,
+    double *__restrict__ out)
+{
+    double2 *Y = X + lds.fft_entries, *TW = Y + lds.y_entries, *TB = TW + lds.tw_entries;
+    const int tid = threadIdx.x, mm = d.mlive;
+    load_tw<NT>(TW, pool + d.tw, d.n);
+    load_tw<NT>(TB, pool + d.twb, d.nb);
+    double2 ph, step;   // e^{i m phi0} of this thread's mode, e^{i NT phi0}
+    {
+        double sn, cs;
+        sincos((double)tid * d.phi0, &sn, &cs);
+        ph = make_double2(cs, sn);
+        sincos((double)NT * d.phi0, &sn, &cs);
+        step = make_double2(cs, sn);
+    }
+    constexpr int U = 4;
+    for (int m0 = tid; m0 <= mm; m0 += U * NT) {
+        double2 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int m = m0 + u * NT;
+            v[u] = m <= mm ? load_mode(drow, dstride, minv, mcontig, m) : make_double2(0.0, 0.0);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int m = m0 + u * NT;
+            if (m <= mm) {
+                if (m == 0) v[u].y = 0.0;
+                X[PadIdx::at(m)] = cmul(ph, v[u]);
+            }
+            ph = cmul(ph, step);
+        }
+    }
+    __syncthreads();
+    fold_bins<NT, double2>(X, d, mm);
+    BlueRing<double2> br = blue_ring<double2>(d, pool);
+    br.out = out;
+    blue_conv<double2, NT>(X, Y, TW, TB, d, br, kBlueInZ, kBlueOutPix);
+}
+
+template <int NT>
+__global__ __launch_bounds__(NT, 4) void k_ring_synth_blue64(
+    const int *__restrict__ ids, int count, int nmaps, const RingDesc *__restrict__ rings,
+    const double2 *__restrict__ pool, const double2 *__restrict__ delta,
+    const int *__restrict__ minv, int mcontig, DeltaLayout dl, double *__restrict__ map,
+    long long npix, RingLds lds)
+{
+    extern __shared__ double2 buf[];
+    int i, b;
+    ring_item<false>(xcd_logical(blockIdx.x, gridDim.x), count, nmaps, i, b);
+    const int r = ids[i];
+    const RingDesc d = rings[r];
+    synth_blue64<NT>(buf, lds, d, pool, delta + b * dl.map + dl.row(r), dl.mstride(r), minv,
+                     mcontig, map + b * npix + d.start);
+}
+
+template <int NT>
+__global__ __launch_bounds__(NT, 4) void k_ring_synth_batch_blue64(
+    const int2 *__restrict__ items, const BatchMap *__restrict__ maps,
+    double *const *__restrict__ outs, const char *__restrict__ ws, RingLds lds)
+{
+    extern __shared__ double2 buf[];
+    const int2 it = items[xcd_logical(blockIdx.x, gridDim.x)];
+    const BatchMap &bm = maps[it.x];
+    const RingDesc d = bm.rings[it.y];
+    const double2 *delta = reinterpret_cast<const double2 *>(ws + bm.delta_off);
+    synth_blue64<NT>(buf, lds, d, bm.pool, delta + bm.dl.row(it.y), bm.dl.mstride(it.y), bm.minv,
+                     bm.mcontig, outs[it.x] + d.start);
 }
 
 template <int NT, int MAXN, typename DT>
@@ -1890,6 +2006,54 @@ __device__ __attribute__((always_inline)) inline void anal_pass(double2 *buf, co
     __syncthreads();
 }
 
+// The modes of a ring from conj Z in the padded buffer: Dt_m = c_m e^{-i m phi0}
+// G_{m mod n}, times the pixel weight w when `weighted`.  T: the n-th roots.
+template <int NT>
+__device__ __attribute__((always_inline)) inline void anal_modes(
+    const double2 *buf, const double2 *T, const RingDesc &d, const int *__restrict__ mval,
+    int mcontig, int nm, int mm, double2 *__restrict__ orow, long long om, double w, bool weighted,
+    double cfac)
+{
+    const int tid = threadIdx.x, n = d.n, h = n / 2;
+    double2 step, ph;   // e^{-i NT phi0}, e^{-i m phi0} for this thread's mode
+    {
+        double sn, cs;
+        sincos((double)NT * d.phi0, &sn, &cs);
+        step = make_double2(cs, -sn);
+    }
+    bool first = true;
+    for (int i = tid; i < nm; i += NT) {
+        const int m = mval[i];
+        if (m > mm) break;   // dead on the ring from here on
+        if (first || !mcontig) {
+            double sn, cs;
+            sincos((double)m * d.phi0, &sn, &cs);
+            ph = make_double2(cs, -sn);
+            first = false;
+        } else {
+            ph = cmul(ph, step);
+        }
+        // G_k = (Z_k + conj Z_{h-k})/2 - (i/2) e^{-2 pi i k/n} (Z_k - conj Z_{h-k})
+        // (the buffer holds conj Z), and G_{n-k} = conj G_k
+        const int kk = m % n, k = kk <= h ? kk : n - kk;
+        const double2 Zk = conjd(buf[PadIdx::at(k == h ? 0 : k)]);
+        const double2 Zc = buf[PadIdx::at(k == 0 ? 0 : h - k)];
+        const double2 a = cadd(Zk, Zc), o = csub(Zk, Zc);
+        double2 G = csub(a, muli(cmul(conjd(tw_at(T, k)), o), +1));
+        G.x *= 0.5;
+        G.y *= kk <= h ? 0.5 : -0.5;
+        double2 v;
+        if (m == 0) {
+            v = make_double2(G.x, 0.0);
+        } else {
+            v = cmul(G, ph);
+            v.x *= cfac; v.y *= cfac;
+        }
+        if (weighted) { v.x *= w; v.y *= w; }
+        orow[i * om] = v;
+    }
+}
+
 __global__ __launch_bounds__(kFastThreads, 2) void k_ring_anal_fast(
     const int *__restrict__ ids, const RingDesc *__restrict__ rings,
     const double2 *__restrict__ pool, const double *__restrict__ map, long long npix,
@@ -1925,47 +2089,32 @@ __global__ __launch_bounds__(kFastThreads, 2) void k_ring_anal_fast(
             Ns *= R;
         }
     }
-    double2 *orow = dt + b * dl.map + dl.row(r);
-    const long long om = dl.mstride(r);
-    const int mm = ring_mmax(d, mfull);
-    const double w = rw ? rw[r] : 1.0;
-    double2 step, ph;   // e^{-i NT phi0}, e^{-i m phi0} for this thread's mode
-    {
-        double sn, cs;
-        sincos((double)kFastThreads * d.phi0, &sn, &cs);
-        step = make_double2(cs, -sn);
-    }
-    bool first = true;
-    for (int i = tid; i < nm; i += kFastThreads) {
-        const int m = mval[i];
-        if (m > mm) break;   // dead on the ring from here on
-        if (first || !mcontig) {
-            double sn, cs;
-            sincos((double)m * d.phi0, &sn, &cs);
-            ph = make_double2(cs, -sn);
-            first = false;
-        } else {
-            ph = cmul(ph, step);
-        }
-        // G_k = (Z_k + conj Z_{h-k})/2 - (i/2) e^{-2 pi i k/n} (Z_k - conj Z_{h-k})
-        // (the buffer holds conj Z), and G_{n-k} = conj G_k
-        const int kk = m % n, k = kk <= h ? kk : n - kk;
-        const double2 Zk = conjd(buf[PadIdx::at(k == h ? 0 : k)]);
-        const double2 Zc = buf[PadIdx::at(k == 0 ? 0 : h - k)];
-        const double2 a = cadd(Zk, Zc), o = csub(Zk, Zc);
-        double2 G = csub(a, muli(cmul(conjd(tw_at(T, k)), o), +1));
-        G.x *= 0.5;
-        G.y *= kk <= h ? 0.5 : -0.5;
-        double2 v;
-        if (m == 0) {
-            v = make_double2(G.x, 0.0);
-        } else {
-            v = cmul(G, ph);
-            v.x *= cfac; v.y *= cfac;
-        }
-        if (rw) { v.x *= w; v.y *= w; }
-        orow[i * om] = v;
-    }
+    anal_modes<kFastThreads>(buf, T, d, mval, mcontig, nm, ring_mmax(d, mfull),
+                             dt + b * dl.map + dl.row(r), dl.mstride(r), rw ? rw[r] : 1.0, rw != nullptr,
+                             cfac);
+}
+
+// The Bluestein fast path of the analysis (FP64 plans).
+template <int NT>
+__global__ __launch_bounds__(NT, 4) void k_ring_anal_blue64(
+    const int *__restrict__ ids, const RingDesc *__restrict__ rings,
+    const double2 *__restrict__ pool, const double *__restrict__ map, long long npix,
+    const int *__restrict__ mval, int mcontig, int nm, DeltaLayout dl, double2 *__restrict__ dt,
+    int mfull, RingLds lds, const double *__restrict__ rw, double cfac)
+{
+    extern __shared__ double2 buf[];
+    double2 *X = buf, *Y = X + lds.fft_entries, *TW = Y + lds.y_entries, *TB = TW + lds.tw_entries;
+    const int r = ids[xcd_logical(blockIdx.x, gridDim.x)];
+    const int b = blockIdx.y;
+    const RingDesc d = rings[r];
+    load_tw<NT>(TW, pool + d.tw, d.n);
+    load_tw<NT>(TB, pool + d.twb, d.nb);
+    __syncthreads();
+    BlueRing<double2> br = blue_ring<double2>(d, pool);
+    br.in = map + (long long)b * npix + d.start;
+    blue_conv<double2, NT>(X, Y, TW, TB, d, br, kBlueInPix, kBlueOutZ);
+    anal_modes<NT>(X, TW, d, mval, mcontig, nm, ring_mmax(d, mfull), dt + b * dl.map + dl.row(r),
+                   dl.mstride(r), rw ? rw[r] : 1.0, rw != nullptr, cfac);
 }
 
 // Spectrum of the Bluestein kernel b_k = conj(c_k) (wrapped to negative k),
@@ -2037,6 +2186,41 @@ hipError_t anal_class(const sht_plan_s *p, int c, const double *map, double2 *dt
                        dim3(NT), lds, st, rc.d_ids, p->d_rings, p->d_pool, map, p->npix,
                        p->d_mval, p->mcontig, p->nm, delta_layout(p, dt, full), dt,
                        full ? p->mmax : -1, rc.lds, rw, cfac);
+    return hipGetLastError();
+}
+
+template <int q>
+hipError_t anal_blue64_class(const sht_plan_s *p, const double *map, double2 *dt, bool full,
+                             hipStream_t st, const double *rw, double cfac)
+{
+    const RingClass &rc = p->scls[kBlue64Class + q];
+    if (rc.count == 0) return hipSuccess;
+    constexpr int NT = kBlue64Threads[q];
+    const size_t lds = (size_t)rc.lds.total() * sizeof(double2);
+    hipError_t e = set_lds((const void *)k_ring_anal_blue64<NT>, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_ring_anal_blue64<NT>, dim3((unsigned)rc.count, (unsigned)p->nmaps),
+                       dim3(NT), lds, st, rc.d_ids, p->d_rings, p->d_pool, map, p->npix, p->d_mval,
+                       p->mcontig, p->nm, delta_layout(p, dt, full), dt, full ? p->mmax : -1,
+                       rc.lds, rw, cfac);
+    return hipGetLastError();
+}
+
+template <int q>
+hipError_t synth_blue64_class(const sht_plan_s *p, const double2 *delta, double *map,
+                              hipStream_t st)
+{
+    const RingClass &rc = p->scls[kBlue64Class + q];
+    if (rc.count == 0) return hipSuccess;
+    constexpr int NT = kBlue64Threads[q];
+    const size_t lds = (size_t)rc.lds.total() * sizeof(double2);
+    hipError_t e = set_lds((const void *)k_ring_synth_blue64<NT>, lds);
+    if (e != hipSuccess) return e;
+    const long long items = (long long)rc.count * p->nmaps;
+    if (items > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(k_ring_synth_blue64<NT>, dim3((unsigned)items), dim3(NT), lds, st, rc.d_ids,
+                       rc.count, p->nmaps, p->d_rings, p->d_pool, delta, p->d_minv, p->mcontig,
+                       delta_layout(p, delta, false), map, p->npix, rc.lds);
     return hipGetLastError();
 }
 
@@ -2124,11 +2308,18 @@ hipError_t synth_blue_class(const sht_plan_s *p, const float2 *delta, double *ma
     return hipGetLastError();
 }
 
-// complex128 Delta (FP64 plans have no ring in the class; a mixed-form plan
-// given a caller's complex128 Delta): the class's rings by size class.
+// complex128 Delta: an FP64 plan's own goes to the complex128 path; a caller's
+// has modes that this path's buffers do not hold (FP64 plans) or that the plan
+// never transforms (mixed-form plans): those rings by size class.
 hipError_t synth_blue_class(const sht_plan_s *p, const double2 *delta, double *map, bool full,
                             hipStream_t st)
 {
+    if (!full) {
+        hipError_t e = synth_blue64_class<2>(p, delta, map, st);
+        if (e == hipSuccess) e = synth_blue64_class<1>(p, delta, map, st);
+        if (e == hipSuccess) e = synth_blue64_class<0>(p, delta, map, st);
+        return e;
+    }
     hipError_t e = synth_class<1024, 8192, double2>(p, p->bcls[2], delta, map, full, st);
     if (e == hipSuccess) e = synth_class<512, 4096, double2>(p, p->bcls[1], delta, map, full, st);
     if (e == hipSuccess) e = synth_class<256, 2048, double2>(p, p->bcls[0], delta, map, full, st);
@@ -2152,7 +2343,9 @@ static hipError_t ring_synth_dt(const sht_plan_s *p, const DT *delta, double *ma
 {
     const long long fast = (long long)p->scls[kFastClass].count * p->nmaps;
     const long long rest = (long long)(p->scls[0].count + p->scls[1].count + p->scls[2].count +
-                                       p->scls[kBlueClass].count) *
+                                       p->scls[kBlueClass].count + p->scls[kBlue64Class].count +
+                                       p->scls[kBlue64Class + 1].count +
+                                       p->scls[kBlue64Class + 2].count) *
                            p->nmaps;
     const bool fork = p->aux_stream && fast > 0 && rest > 0 && fast + rest >= kForkItems;
     // the fork and join events belong to the plan: calls from several host
@@ -2240,6 +2433,9 @@ hipError_t launch_ring_anal(const sht_plan_s *p, const double *map, double2 *dt,
                             hipStream_t st, const double *rw, double cfac)
 {
     hipError_t e = anal_fast_class(p, map, dt, full, st, rw, cfac);
+    if (e == hipSuccess) e = anal_blue64_class<2>(p, map, dt, full, st, rw, cfac);
+    if (e == hipSuccess) e = anal_blue64_class<1>(p, map, dt, full, st, rw, cfac);
+    if (e == hipSuccess) e = anal_blue64_class<0>(p, map, dt, full, st, rw, cfac);
     if (e == hipSuccess) e = anal_class<1024, 8192>(p, 2, map, dt, full, st, rw, cfac);
     if (e == hipSuccess) e = anal_class<512, 4096>(p, 1, map, dt, full, st, rw, cfac);
     if (e == hipSuccess) e = anal_class<256, 2048>(p, 0, map, dt, full, st, rw, cfac);
@@ -2276,6 +2472,21 @@ hipError_t synth_batch_class(const BatchClass &bc, const BatchMap *maps, double 
     return hipGetLastError();
 }
 
+template <int q>
+hipError_t synth_batch_blue64(const BatchClass *cls, const BatchMap *maps, double *const *outs,
+                              const void *ws, hipStream_t st)
+{
+    const BatchClass &bc = cls[kBlue64Class + q];
+    if (bc.count == 0) return hipSuccess;
+    constexpr int NT = kBlue64Threads[q];
+    const size_t lds = (size_t)bc.lds.total() * sizeof(double2);
+    hipError_t e = set_lds((const void *)k_ring_synth_batch_blue64<NT>, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_ring_synth_batch_blue64<NT>, dim3((unsigned)bc.count), dim3(NT), lds, st,
+                       bc.d_items, maps, outs, (const char *)ws, bc.lds);
+    return hipGetLastError();
+}
+
 hipError_t launch_ring_synth_batch(const BatchClass *cls, const BatchMap *maps,
                                    double *const *outs, const void *ws, hipStream_t st)
 {
@@ -2291,6 +2502,9 @@ hipError_t launch_ring_synth_batch(const BatchClass *cls, const BatchMap *maps,
             e = hipGetLastError();
         }
     }
+    if (e == hipSuccess) e = synth_batch_blue64<2>(cls, maps, outs, ws, st);
+    if (e == hipSuccess) e = synth_batch_blue64<1>(cls, maps, outs, ws, st);
+    if (e == hipSuccess) e = synth_batch_blue64<0>(cls, maps, outs, ws, st);
     if (e == hipSuccess) e = synth_batch_class<1024, 8192>(cls[2], maps, outs, ws, st);
     if (e == hipSuccess) e = synth_batch_class<512, 4096>(cls[1], maps, outs, ws, st);
     if (e == hipSuccess) e = synth_batch_class<256, 2048>(cls[0], maps, outs, ws, st);

@@ -148,7 +148,18 @@ constexpr int kClassThreads[kNumRingClasses] = {256, 512, 1024};
 // that take the even- and odd-indexed convolutions side by side.
 constexpr int kFastClass = 3;
 constexpr int kBlueClass = 4;
-constexpr int kNumSynthClasses = 5;
+// FP64 plans have the same path in complex128, for synthesis and analysis, in
+// classes by convolution length (kBlue64MaxN points, kBlue64Threads threads),
+// so that short rings do not reserve the LDS of long ones: two buffers of
+// 1024, 2048 or 4096 points leave four, two or one workgroup on a CU. One map
+// at nside 2048, against the size-class kernels: analysis 0.74 to 0.54 ms,
+// synthesis (beside the fast path) 1.1 to 0.58 ms; without the third class
+// the analysis takes 0.62 ms.
+constexpr int kBlue64Class = 5;
+constexpr int kNumBlue64 = 3;
+constexpr int kNumSynthClasses = kBlue64Class + kNumBlue64;
+constexpr int kBlue64MaxN[kNumBlue64] = {1024, 2048, 4096};
+constexpr int kBlue64Threads[kNumBlue64] = {256, 512, 512};
 constexpr int kFastThreads = 256;
 constexpr int kFastMaxH = 4096;
 constexpr int kFastMaxModes = 17 * kFastThreads;   // the fold holds m < 4352 in registers
@@ -194,14 +205,24 @@ inline int fast_radices(int h, unsigned long long *rads)
 
 // Radices of the Bluestein fast path for a convolution length nb (7-smooth,
 // 1 < nb <= kBlueMaxN): as many 8s as possible, then 4, 2, 7, 5, 3.  Every
-// pass holds at most one butterfly per thread (nb / R <= kBlueThreads).
+// pass holds at most one butterfly per thread (nb / R <= threads).
 // Returns the number of passes, 0 if nb is not eligible.
-inline int blue_radices(int nb, unsigned long long *rads)
+// fours: 4 x 4 in place of 8 x 2 (complex128: fewer butterflies in a pass).
+inline int blue_radices(int nb, unsigned long long *rads, int threads = kBlueThreads,
+                        int max_n = kBlueMaxN, bool fours = false)
 {
     int rad[12];
-    if (nb < 2 || nb > kBlueMaxN) return 0;
+    if (nb < 2 || nb > max_n) return 0;
     int np = 0, r = nb;
-    while (r % 8 == 0 && np < 12) { rad[np++] = 8; r /= 8; }
+    while (r % 8 == 0 && np < 12) {
+        if (fours && r % 16 == 0 && r % 32 != 0) {   // 16 x odd is left
+            rad[np++] = 4;
+            r /= 4;
+            break;
+        }
+        rad[np++] = 8;
+        r /= 8;
+    }
     if (r % 4 == 0 && np < 12) { rad[np++] = 4; r /= 4; }
     if (r % 2 == 0 && np < 12) { rad[np++] = 2; r /= 2; }
     for (int f : {7, 5, 3})
@@ -209,7 +230,7 @@ inline int blue_radices(int nb, unsigned long long *rads)
     if (r != 1) return 0;
     *rads = 0;
     for (int p = 0; p < np; ++p) {
-        if (nb / rad[p] > kBlueThreads) return 0;
+        if (nb / rad[p] > threads) return 0;
         *rads |= (unsigned long long)rad[p] << (5 * p);
     }
     return np;
@@ -220,9 +241,9 @@ inline int blue_radices(int nb, unsigned long long *rads)
 // modes, the spectrum and the alias staging, then the even-indexed
 // convolution; the second the odd-indexed one; then the twiddle tables of
 // n and nb.
-inline void blue_lds_add(RingLds &l, int n, int nb, int mmax)
+inline void blue_lds_add(RingLds &l, int n, int nb, int mmax, int threads = kBlueThreads)
 {
-    int top = n / 2 > kBlueThreads - 1 ? n / 2 : kBlueThreads - 1;
+    int top = n / 2 > threads - 1 ? n / 2 : threads - 1;
     top = top > mmax ? top : mmax;
     top = top > nb - 1 ? top : nb - 1;
     const int need = fast_pad(top) + 1;
@@ -345,6 +366,7 @@ struct sht_plan_s {
     // caller's complex128 Delta (sht_delta2map), which that path does not take
     sht::RingClass bcls[sht::kNumRingClasses];
     std::vector<int> ring_sclass;  // synthesis class of each ring
+    std::vector<int> ring_mlive;   // RingDesc::mlive of each ring
     int fwd_chains;      // ring pairs per lane of the FP64 forward Legendre kernel (1, 2, 4)
     int adj_chains;      // ring pairs per lane of the adjoint Legendre kernel (1, 2, 4, 8)
     int fwd_group;       // maps that a wave of it takes together (1..4)

@@ -81,13 +81,14 @@ int best_smooth7(long long L)
 // points: the cheapest by the same per-pass costs among the lengths in
 // [L, min(1.3 L, kBlueMaxN)] whose radix list holds one butterfly per thread
 // in every pass; 0 if there is none.
-int best_blue_nb(long long L)
+int best_blue_nb(long long L, int threads = sht::kBlueThreads, int max_n = sht::kBlueMaxN,
+                 bool fours = false)
 {
     double best = 1e300;
     int pick = 0;
-    for (long long c = L; c <= sht::kBlueMaxN && c <= (L * 13) / 10 + 1; ++c) {
+    for (long long c = L; c <= max_n && c <= (L * 13) / 10 + 1; ++c) {
         unsigned long long rads = 0;
-        const int np = smooth7(c) ? sht::blue_radices((int)c, &rads) : 0;
+        const int np = smooth7(c) ? sht::blue_radices((int)c, &rads, threads, max_n, fours) : 0;
         if (np == 0) continue;
         double cost = 0.0;
         for (int q = 0; q < np; ++q) {
@@ -496,6 +497,17 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
     sht::RingLds bclass_lds[sht::kNumRingClasses] = {};
     // the Bluestein fast path takes complex64 Delta (the mixed forms)
     const bool blue_ok = d->precision != SHT_FP64 && mval.back() < sht::kFastMaxModes;
+    // convolution length and class of the complex128 Bluestein fast path for a
+    // half length h, 0 if no class takes it
+    auto blue64 = [&](int h, int &q) {
+        for (q = 0; q < sht::kNumBlue64 && d->precision == SHT_FP64; ++q) {
+            const int nb = best_blue_nb((long long)h - 1, sht::kBlue64Threads[q],
+                                        sht::kBlue64MaxN[q], true);
+            if (nb > 0) return nb;
+        }
+        q = -1;
+        return 0;
+    };
     for (int r = 0; r < R; ++r) {
         const long long n = d->nphi[r];
         RingDesc &g = rings[r];
@@ -506,7 +518,7 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
         g.clen = (int)((n % 2 == 0) ? n / 2 : n);
         g.tw = g.tch = g.twb = g.bq = -1;
         const int spec = (n % 2 == 0) ? g.clen + 1 : g.clen;  // F_k entries
-        int fftlen;
+        int fftlen, b64 = -1;   // b64: class of the complex128 Bluestein fast path
         unsigned long long fr = 0;
         if (smooth7(g.clen) && g.clen <= 8192) {
             g.nb = 0;
@@ -514,8 +526,9 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
             // an even ring of 7-smooth half length that the fast path cannot
             // take (a pass would hold too many butterflies per thread) joins
             // the Bluestein fast path
-            if (blue_ok && n % 2 == 0 && g.clen % 2 == 0 && sht::fast_radices(g.clen, &fr) == 0) {
-                const int nbb = best_blue_nb((long long)g.clen - 1);
+            if (n % 2 == 0 && g.clen % 2 == 0 && sht::fast_radices(g.clen, &fr) == 0) {
+                const int nbb = blue_ok ? best_blue_nb((long long)g.clen - 1)
+                                        : blue64(g.clen, b64);
                 if (nbb > 0) {
                     g.half = 1;
                     g.nb = nbb;
@@ -526,7 +539,7 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
             // split into the even- and odd-indexed halves: Bluestein of
             // length clen / 2 needs a convolution of only clen - 1 points
             g.half = 1;
-            const int nbb = blue_ok ? best_blue_nb((long long)g.clen - 1) : 0;
+            const int nbb = blue_ok ? best_blue_nb((long long)g.clen - 1) : blue64(g.clen, b64);
             g.nb = nbb > 0 ? nbb : best_smooth7((long long)g.clen - 1);
             if (g.nb > 8192) return SHT_ERR_UNSUPPORTED;
             fftlen = g.nb;
@@ -551,6 +564,13 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
         if (direct || (g.np > 0 && g.nb == 0)) {
             ring_sclass[r] = sht::kFastClass;
             sht::fast_lds_add(sclass_lds[sht::kFastClass], g.n, mval.back());
+        } else if (b64 >= 0) {
+            // (its LDS goes by the ring's live modes, once they are known)
+            g.np = sht::blue_radices(g.nb, &g.rads, sht::kBlue64Threads[b64],
+                                     sht::kBlue64MaxN[b64], true);
+            ring_sclass[r] = sht::kBlue64Class + b64;
+            ring_bclass[r] = c;
+            sht::ring_lds_add(bclass_lds[c], c, g.n, g.nb, need);
         } else if (g.np > 0) {
             ring_sclass[r] = sht::kBlueClass;
             sht::blue_lds_add(sclass_lds[sht::kBlueClass], g.n, g.nb, mval.back());
@@ -560,9 +580,9 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
             ring_sclass[r] = c;
             sht::ring_lds_add(sclass_lds[c], c, g.n, g.nb, need);
         }
-        // the analysis takes the fast path's rings on its own fast path, in
-        // every precision, and the others by size class
-        if (ring_sclass[r] == sht::kFastClass)
+        // the analysis takes the fast paths' rings (complex128) on fast paths of
+        // its own, and the others by size class
+        if (ring_sclass[r] == sht::kFastClass || ring_sclass[r] >= sht::kBlue64Class)
             ring_class[r] = -1;
         else
             sht::ring_lds_add(class_lds[c], c, g.n, g.nb, need);
@@ -736,6 +756,18 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
     }
     if (st == SHT_OK) st = upload(&p->d_rings, rings, &tb);
     if (st == SHT_OK) st = build_live_table(p, pairs, &tb);
+    if (st == SHT_OK &&
+        hipMemcpy(rings.data(), p->d_rings, rings.size() * sizeof(RingDesc),
+                  hipMemcpyDeviceToHost) != hipSuccess)
+        st = SHT_ERR_HIP;
+    p->ring_mlive.resize(R);
+    for (int r = 0; r < R; ++r) {
+        p->ring_mlive[r] = rings[r].mlive;
+        const int q = ring_sclass[r] - sht::kBlue64Class;
+        if (q >= 0)
+            sht::blue_lds_add(sclass_lds[ring_sclass[r]], rings[r].n, rings[r].nb,
+                              rings[r].mlive, sht::kBlue64Threads[q]);
+    }
     if (st == SHT_OK) st = upload(&p->d_pool, pb.pool, &tb);
     // longest rings first (tail balance); rings of equal length adjacent so
     // that consecutive workgroups, which the kernels place on one XCD, share
@@ -829,9 +861,10 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
     p->magic = sht::kPlanMagic;
     if (sht::log_enabled()) {
         static const char *kPrec[] = {"fp64", "fp32_mfma", "bf16x3_mfma", "f16x2_mfma"};
-        int nblue = 0, nfast = 0;
+        int nblue = 0, nblue64 = 0, nfast = 0;
         for (int r = 0; r < R; ++r) {
             nblue += rings[r].nb != 0 && ring_sclass[r] < sht::kNumRingClasses;
+            nblue64 += ring_sclass[r] >= sht::kBlue64Class;
             nfast += ring_sclass[r] == sht::kFastClass;
         }
         sht::log_line("plan l_max=%d nm=%d m_max=%d rings=%d pairs=%d maps=%d precision=%s "
@@ -840,7 +873,7 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
         sht::log_line("plan synthesis rings: fast path %d (Stockham in registers), Bluestein "
                       "fast path %d, size classes %d / %d / %d (256 / 512 / 1024 threads), of "
                       "which Bluestein %d",
-                      nfast, p->scls[sht::kBlueClass].count, p->scls[0].count,
+                      nfast, p->scls[sht::kBlueClass].count + nblue64, p->scls[0].count,
                       p->scls[1].count, p->scls[2].count, nblue);
         // the radix lists of the three longest fast-path ring lengths
         std::map<int, int> longest;   // nphi -> a ring of that length
