@@ -23,8 +23,6 @@
 // zero (a padded copy of the table per super-block), so u stays bounded
 // there and its product with the zero coefficients is zero, never 0 * inf.
 //
-// there, and its product with the zero coefficients is zero, never 0 * inf.
-//
 // Fragments.  A 32x32x16 fragment holds K = 0..7 of its 32 columns in lanes
 // 0-31 and K = 8..15 in lanes 32-63; a lane's 16 same-parity values are
 // exchanged across the wave halves as FP32 and then split (one packed

@@ -1741,7 +1741,7 @@ __global__ __launch_bounds__(kBlueThreads, 4) void k_ring_synth_blue(
 // issue slots idle).  Rings of one map, against the size-class kernels: nside
 // 512, synthesis 47 to 37 us for the stage, transform 176 to 161 us; nside
 // 2048, analysis 740 to 540 us, transform 4.50 to 4.23 ms; a batch of 64 maps
-// of l_max 200 to 2000, 3.3 to 2.4 ms for the stage.
+// of l_max 256 to 2048, 3.3 to 2.4 ms for the stage.
 template <int NT>
 __device__ __attribute__((always_inline)) inline void synth_blue64(
     double2 *X, const RingLds &lds, const RingDesc &d, const double2 *__restrict__ pool,
@@ -1799,6 +1799,40 @@ __global__ __launch_bounds__(NT, 4) void k_ring_synth_blue64(
     const RingDesc d = rings[r];
     synth_blue64<NT>(buf, lds, d, pool, delta + b * dl.map + dl.row(r), dl.mstride(r), minv,
                      mcontig, map + b * npix + d.start);
+}
+
+// The rings of the first complex128 Bluestein class (the first bblocks
+// workgroups, bitems rounded up to a multiple of 8) and the fast path's in one
+// launch, one workgroup per map and ring: at l_max 512 either alone leaves most
+// of the CUs idle (one map: 31.5 us in two launches, 24.5 in this; 8 maps at
+// l_max 1024: 365 us one after the other, 264).  Not persistent: the modes of a next
+// ring held through the passes take 218 registers and leave two workgroups on a
+// CU; this takes 113, and four workgroups hide the loads better.
+__global__ __launch_bounds__(kFastThreads, 4) void k_ring_synth_both(
+    int bblocks, const int *__restrict__ bids, int bcount, RingLds blds,
+    const int *__restrict__ fids, int fcount, RingLds flds, int nmaps,
+    const RingDesc *__restrict__ rings, const double2 *__restrict__ pool,
+    const double2 *__restrict__ delta, const int *__restrict__ minv, int mcontig, DeltaLayout dl,
+    double *__restrict__ map, long long npix)
+{
+    extern __shared__ double2 buf[];
+    const int block = (int)blockIdx.x;
+    int i, b;
+    if (block < bblocks) {
+        if (block >= bcount * nmaps) return;
+        ring_item<false>(xcd_logical(block, bcount * nmaps), bcount, nmaps, i, b);
+        const int r = bids[i];
+        const RingDesc d = rings[r];
+        synth_blue64<kFastThreads>(buf, blds, d, pool, delta + b * dl.map + dl.row(r),
+                                   dl.mstride(r), minv, mcontig, map + b * npix + d.start);
+        return;
+    }
+    ring_item<false>(xcd_logical(block - bblocks, fcount * nmaps), fcount, nmaps, i, b);
+    const int r = fids[i];
+    const RingDesc d = rings[r];
+    synth_fast<kFastThreads, double2>(buf, buf + flds.fft_entries, d, pool,
+                                      delta + b * dl.map + dl.row(r), dl.mstride(r), minv,
+                                      mcontig, d.mlive, map + b * npix + d.start);
 }
 
 template <int NT>
@@ -2054,16 +2088,15 @@ __device__ __attribute__((always_inline)) inline void anal_modes(
     }
 }
 
-__global__ __launch_bounds__(kFastThreads, 2) void k_ring_anal_fast(
-    const int *__restrict__ ids, const RingDesc *__restrict__ rings,
+// Ring r of map b.
+__device__ __attribute__((always_inline)) inline void anal_fast(
+    double2 *buf, int r, int b, const RingDesc *__restrict__ rings,
     const double2 *__restrict__ pool, const double *__restrict__ map, long long npix,
-    const int *__restrict__ mval, int mcontig, int nm, DeltaLayout dl, double2 *__restrict__ dt,
-    int mfull, RingLds lds, const double *__restrict__ rw, double cfac)
+    const int *__restrict__ mval, int mcontig, int nm, const DeltaLayout &dl,
+    double2 *__restrict__ dt, int mfull, const RingLds &lds, const double *__restrict__ rw,
+    double cfac)
 {
-    extern __shared__ double2 buf[];
     double2 *T = buf + lds.fft_entries;
-    const int r = ids[xcd_logical(blockIdx.x, gridDim.x)];
-    const int b = blockIdx.y;
     const RingDesc d = rings[r];
     const int tid = threadIdx.x;
     const double *in = map + (long long)b * npix + d.start;
@@ -2094,18 +2127,27 @@ __global__ __launch_bounds__(kFastThreads, 2) void k_ring_anal_fast(
                              cfac);
 }
 
-// The Bluestein fast path of the analysis (FP64 plans).
-template <int NT>
-__global__ __launch_bounds__(NT, 4) void k_ring_anal_blue64(
+__global__ __launch_bounds__(kFastThreads, 2) void k_ring_anal_fast(
     const int *__restrict__ ids, const RingDesc *__restrict__ rings,
     const double2 *__restrict__ pool, const double *__restrict__ map, long long npix,
     const int *__restrict__ mval, int mcontig, int nm, DeltaLayout dl, double2 *__restrict__ dt,
     int mfull, RingLds lds, const double *__restrict__ rw, double cfac)
 {
     extern __shared__ double2 buf[];
-    double2 *X = buf, *Y = X + lds.fft_entries, *TW = Y + lds.y_entries, *TB = TW + lds.tw_entries;
-    const int r = ids[xcd_logical(blockIdx.x, gridDim.x)];
-    const int b = blockIdx.y;
+    anal_fast(buf, ids[xcd_logical(blockIdx.x, gridDim.x)], blockIdx.y, rings, pool, map, npix,
+              mval, mcontig, nm, dl, dt, mfull, lds, rw, cfac);
+}
+
+// The Bluestein fast path of the analysis (FP64 plans): ring r of map b.
+template <int NT>
+__device__ __attribute__((always_inline)) inline void anal_blue64(
+    double2 *X, int r, int b, const RingDesc *__restrict__ rings,
+    const double2 *__restrict__ pool, const double *__restrict__ map, long long npix,
+    const int *__restrict__ mval, int mcontig, int nm, const DeltaLayout &dl,
+    double2 *__restrict__ dt, int mfull, const RingLds &lds, const double *__restrict__ rw,
+    double cfac)
+{
+    double2 *Y = X + lds.fft_entries, *TW = Y + lds.y_entries, *TB = TW + lds.tw_entries;
     const RingDesc d = rings[r];
     load_tw<NT>(TW, pool + d.tw, d.n);
     load_tw<NT>(TB, pool + d.twb, d.nb);
@@ -2115,6 +2157,41 @@ __global__ __launch_bounds__(NT, 4) void k_ring_anal_blue64(
     blue_conv<double2, NT>(X, Y, TW, TB, d, br, kBlueInPix, kBlueOutZ);
     anal_modes<NT>(X, TW, d, mval, mcontig, nm, ring_mmax(d, mfull), dt + b * dl.map + dl.row(r),
                    dl.mstride(r), rw ? rw[r] : 1.0, rw != nullptr, cfac);
+}
+
+template <int NT>
+__global__ __launch_bounds__(NT, 4) void k_ring_anal_blue64(
+    const int *__restrict__ ids, const RingDesc *__restrict__ rings,
+    const double2 *__restrict__ pool, const double *__restrict__ map, long long npix,
+    const int *__restrict__ mval, int mcontig, int nm, DeltaLayout dl, double2 *__restrict__ dt,
+    int mfull, RingLds lds, const double *__restrict__ rw, double cfac)
+{
+    extern __shared__ double2 buf[];
+    anal_blue64<NT>(buf, ids[xcd_logical(blockIdx.x, gridDim.x)], blockIdx.y, rings, pool, map,
+                    npix, mval, mcontig, nm, dl, dt, mfull, lds, rw, cfac);
+}
+
+// Both in one launch (see k_ring_synth_both): the first bblocks workgroups of a
+// map, bcount rounded up to a multiple of 8, take the Bluestein rings.  One map
+// at l_max 512: 41 to 21 us; at 2048 (first class only), 93 to 75 us.
+__global__ __launch_bounds__(kFastThreads, 4) void k_ring_anal_both(
+    const int *__restrict__ fids, int fcount, RingLds flds, const int *__restrict__ bids,
+    int bcount, RingLds blds, int bblocks, const RingDesc *__restrict__ rings,
+    const double2 *__restrict__ pool, const double *__restrict__ map, long long npix,
+    const int *__restrict__ mval, int mcontig, int nm, DeltaLayout dl, double2 *__restrict__ dt,
+    int mfull, const double *__restrict__ rw, double cfac)
+{
+    extern __shared__ double2 buf[];
+    const int block = (int)blockIdx.x;
+    if (block < bblocks) {
+        if (block < bcount)
+            anal_blue64<kFastThreads>(buf, bids[xcd_logical(block, bcount)], blockIdx.y, rings,
+                                      pool, map, npix, mval, mcontig, nm, dl, dt, mfull, blds, rw,
+                                      cfac);
+        return;
+    }
+    anal_fast(buf, fids[xcd_logical(block - bblocks, fcount)], blockIdx.y, rings, pool, map, npix,
+              mval, mcontig, nm, dl, dt, mfull, flds, rw, cfac);
 }
 
 // Spectrum of the Bluestein kernel b_k = conj(c_k) (wrapped to negative k),
@@ -2186,6 +2263,62 @@ hipError_t anal_class(const sht_plan_s *p, int c, const double *map, double2 *dt
                        dim3(NT), lds, st, rc.d_ids, p->d_rings, p->d_pool, map, p->npix,
                        p->d_mval, p->mcontig, p->nm, delta_layout(p, dt, full), dt,
                        full ? p->mmax : -1, rc.lds, rw, cfac);
+    return hipGetLastError();
+}
+
+// One launch for the fast path and the first complex128 Bluestein class (if the
+// plan has any of it) where four of their workgroups fit on a CU side by side
+// (fast-path rings of up to about 4100 pixels); beyond that the longer rings'
+// LDS would throttle the shorter ones, and the launches stay apart.
+bool rings_together(const sht_plan_s *p)
+{
+    static_assert(kBlue64Threads[0] == kFastThreads, "one workgroup size for both");
+    const RingClass &f = p->scls[kFastClass], &b = p->scls[kBlue64Class];
+    return f.count > 0 && f.lds.total() <= kTogetherEntries &&
+           (b.count == 0 || b.lds.total() <= kTogetherEntries);
+}
+
+size_t together_lds(const sht_plan_s *p)
+{
+    const RingClass &b = p->scls[kBlue64Class];
+    const int f = p->scls[kFastClass].lds.total(), l = b.count > 0 ? b.lds.total() : 0;
+    return (size_t)(f > l ? f : l) * sizeof(double2);
+}
+
+hipError_t anal_together(const sht_plan_s *p, const double *map, double2 *dt, bool full,
+                         hipStream_t st, const double *rw, double cfac)
+{
+    const RingClass &f = p->scls[kFastClass], &b = p->scls[kBlue64Class];
+    const size_t lds = together_lds(p);
+    hipError_t e = set_lds((const void *)k_ring_anal_both, lds);
+    if (e != hipSuccess) return e;
+    const int bblocks = (b.count + 7) / 8 * 8;
+    hipLaunchKernelGGL(k_ring_anal_both, dim3((unsigned)(bblocks + f.count), (unsigned)p->nmaps),
+                       dim3(kFastThreads), lds, st, f.d_ids, f.count, f.lds, b.d_ids, b.count,
+                       b.lds, bblocks, p->d_rings, p->d_pool, map, p->npix, p->d_mval, p->mcontig,
+                       p->nm, delta_layout(p, dt, full), dt, full ? p->mmax : -1, rw, cfac);
+    return hipGetLastError();
+}
+
+// only an FP64 plan's own Delta is taken together
+hipError_t synth_together(const sht_plan_s *, const float2 *, double *, hipStream_t)
+{
+    return hipErrorInvalidValue;
+}
+
+hipError_t synth_together(const sht_plan_s *p, const double2 *delta, double *map, hipStream_t st)
+{
+    const RingClass &f = p->scls[kFastClass], &b = p->scls[kBlue64Class];
+    const size_t lds = together_lds(p);
+    hipError_t e = set_lds((const void *)k_ring_synth_both, lds);
+    if (e != hipSuccess) return e;
+    const long long bblocks = ((long long)b.count * p->nmaps + 7) / 8 * 8;
+    const long long blocks = bblocks + (long long)f.count * p->nmaps;
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    hipLaunchKernelGGL(k_ring_synth_both, dim3((unsigned)blocks), dim3(kFastThreads), lds, st,
+                       (int)bblocks, b.d_ids, b.count, b.lds, f.d_ids, f.count, f.lds, p->nmaps,
+                       p->d_rings, p->d_pool, delta, p->d_minv, p->mcontig,
+                       delta_layout(p, delta, false), map, p->npix);
     return hipGetLastError();
 }
 
@@ -2317,7 +2450,7 @@ hipError_t synth_blue_class(const sht_plan_s *p, const double2 *delta, double *m
     if (!full) {
         hipError_t e = synth_blue64_class<2>(p, delta, map, st);
         if (e == hipSuccess) e = synth_blue64_class<1>(p, delta, map, st);
-        if (e == hipSuccess) e = synth_blue64_class<0>(p, delta, map, st);
+        if (e == hipSuccess && !rings_together(p)) e = synth_blue64_class<0>(p, delta, map, st);
         return e;
     }
     hipError_t e = synth_class<1024, 8192, double2>(p, p->bcls[2], delta, map, full, st);
@@ -2337,16 +2470,25 @@ hipError_t synth_blue_class(const sht_plan_s *p, const double2 *delta, double *m
 // Small plans launch everything on `st` (a fork costs microseconds).
 constexpr long long kForkItems = 4096;
 
+template <typename DT> constexpr bool own_complex128(bool full)
+{
+    return sizeof(DT) == sizeof(double2) && !full;
+}
+
 template <typename DT>
 static hipError_t ring_synth_dt(const sht_plan_s *p, const DT *delta, double *map, bool full,
                                 hipStream_t st)
 {
-    const long long fast = (long long)p->scls[kFastClass].count * p->nmaps;
-    const long long rest = (long long)(p->scls[0].count + p->scls[1].count + p->scls[2].count +
-                                       p->scls[kBlueClass].count + p->scls[kBlue64Class].count +
-                                       p->scls[kBlue64Class + 1].count +
-                                       p->scls[kBlue64Class + 2].count) *
-                           p->nmaps;
+    const bool both = own_complex128<DT>(full) && rings_together(p);
+    long long fast = p->scls[kFastClass].count, rest = 0;
+    for (int q = 0; q < kNumSynthClasses; ++q)
+        if (q != kFastClass) rest += p->scls[q].count;
+    if (both) {
+        fast += p->scls[kBlue64Class].count;
+        rest -= p->scls[kBlue64Class].count;
+    }
+    fast *= p->nmaps;
+    rest *= p->nmaps;
     const bool fork = p->aux_stream && fast > 0 && rest > 0 && fast + rest >= kForkItems;
     // the fork and join events belong to the plan: calls from several host
     // threads take turns through the whole sequence
@@ -2357,7 +2499,9 @@ static hipError_t ring_synth_dt(const sht_plan_s *p, const DT *delta, double *ma
         e = hipEventRecord(p->ev_fork, st);
         if (e == hipSuccess) e = hipStreamWaitEvent(p->aux_stream, p->ev_fork, 0);
     }
-    if (e == hipSuccess) e = synth_fast_class<DT>(p, delta, map, full, fork ? p->aux_stream : st);
+    const hipStream_t fst = fork ? p->aux_stream : st;
+    if (e == hipSuccess)
+        e = both ? synth_together(p, delta, map, fst) : synth_fast_class<DT>(p, delta, map, full, fst);
     if (e == hipSuccess) e = synth_blue_class(p, delta, map, full, st);
     if (e == hipSuccess) e = synth_class<1024, 8192, DT>(p, p->scls[2], delta, map, full, st);
     if (e == hipSuccess) e = synth_class<512, 4096, DT>(p, p->scls[1], delta, map, full, st);
@@ -2432,10 +2576,12 @@ hipError_t launch_widen_delta(const sht_plan_s *p, const float2 *s, double2 *d, 
 hipError_t launch_ring_anal(const sht_plan_s *p, const double *map, double2 *dt, bool full,
                             hipStream_t st, const double *rw, double cfac)
 {
-    hipError_t e = anal_fast_class(p, map, dt, full, st, rw, cfac);
+    const bool both = rings_together(p);
+    hipError_t e = both ? anal_together(p, map, dt, full, st, rw, cfac)
+                        : anal_fast_class(p, map, dt, full, st, rw, cfac);
     if (e == hipSuccess) e = anal_blue64_class<2>(p, map, dt, full, st, rw, cfac);
     if (e == hipSuccess) e = anal_blue64_class<1>(p, map, dt, full, st, rw, cfac);
-    if (e == hipSuccess) e = anal_blue64_class<0>(p, map, dt, full, st, rw, cfac);
+    if (e == hipSuccess && !both) e = anal_blue64_class<0>(p, map, dt, full, st, rw, cfac);
     if (e == hipSuccess) e = anal_class<1024, 8192>(p, 2, map, dt, full, st, rw, cfac);
     if (e == hipSuccess) e = anal_class<512, 4096>(p, 1, map, dt, full, st, rw, cfac);
     if (e == hipSuccess) e = anal_class<256, 2048>(p, 0, map, dt, full, st, rw, cfac);

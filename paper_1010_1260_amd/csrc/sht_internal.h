@@ -160,6 +160,8 @@ constexpr int kNumBlue64 = 3;
 constexpr int kNumSynthClasses = kBlue64Class + kNumBlue64;
 constexpr int kBlue64MaxN[kNumBlue64] = {1024, 2048, 4096};
 constexpr int kBlue64Threads[kNumBlue64] = {256, 512, 512};
+// LDS entries of a workgroup, four of which fill a CU's 160 KiB
+constexpr int kTogetherEntries = 160 * 1024 / 16 / 4;
 constexpr int kFastThreads = 256;
 constexpr int kFastMaxH = 4096;
 constexpr int kFastMaxModes = 17 * kFastThreads;   // the fold holds m < 4352 in registers
