@@ -515,7 +515,7 @@ __device__ inline int xcd_logical(int b, int total)
 // DRAM pages: for [map][m][ring] Delta map by map, ring by ring
 // (neighbouring rings of one map; measured faster than grouping a few rings'
 // items of all maps together, which would keep each ring's tables in L2 but
-// spreads the Delta reads over all maps); for [m][ring][map] Delta ring by
+// spreads the Delta reads over all maps); for Delta with the maps of a ring contiguous, ring by
 // ring, map by map (all maps of one ring).
 template <bool RM>
 __device__ inline void ring_item(long long it, int count, int nmaps, int &i, int &b)
@@ -564,7 +564,7 @@ __device__ inline void xcd_item(long long k, int count, int nmaps, int x, int sh
     }
 }
 
-// complex64 Delta (the mixed forms') is [m][ring][map], its items ring by ring
+// complex64 Delta (the mixed forms') has the maps of a ring contiguous: ring by ring
 template <typename DT> struct RingMajor {
     static constexpr bool value = false;
 };
@@ -1351,8 +1351,8 @@ __global__ __launch_bounds__(kFast2Threads, 4) void k_ring_synth_fast2(
     }
 }
 
-//
-// Persistent: the grid is a multiple of 8 workgroups; the (map, ring) items,
+// The fast path where fewer than four workgroups fit on a CU, or the Delta is a
+// caller's.  Persistent: the grid is a multiple of 8 workgroups; the (map, ring) items,
 // in the order of ring_item, are split into 8 contiguous ranges, one per XCD
 // (workgroups are dealt to the XCDs round-robin), and the workgroups of an
 // XCD take its items in turn.  The loads of a workgroup's
@@ -1660,7 +1660,7 @@ __device__ __attribute__((always_inline)) inline void blue_conv(C *X, C *Y, cons
     blue_dir<C, NT, +1>(X, Y, TW, TB, d, br, kBlueInBq, outl);
 }
 
-// Persistent like k_ring_synth_fast; complex64 Delta [m][ring][map] only.
+// Persistent like k_ring_synth_fast; complex64 Delta only.
 // Items are (ring, map pair), ring by ring: one 16-byte load per mode brings
 // the modes of maps 2p and 2p + 1 and the two maps
 // are then folded and transformed one after the other in the same buffers
