@@ -1193,7 +1193,11 @@ __device__ __attribute__((always_inline)) inline void load_fast2(
     }
 }
 
-// fold_fast for both maps (same order of additions per map).
+// fold_fast of 256 threads for both maps, on 512: the same phases and the same
+// order of additions per map, so that the outputs do not depend on how many
+// threads share a ring.  A thread's modes are every second one of those that
+// thread tid % 256 would take alone, and its phases the same powers of
+// e^{i 256 phi0}, one product at a time.
 template <int NT>
 __device__ __attribute__((always_inline)) inline void fold_fast2(float2 *X0, float2 *X1,
                                                                  const RingDesc &d,
@@ -1201,15 +1205,17 @@ __device__ __attribute__((always_inline)) inline void fold_fast2(float2 *X0, flo
                                                                  int mmax)
 {
     constexpr int QM = FastModes2<NT>::Q;
+    static_assert(NT == 2 * kFastThreads, "two phases of a 256-thread fold per round");
     const int tid = threadIdx.x;
-    double2 ph, step;
+    double2 ph, step;   // e^{i m phi0} of this thread's mode, e^{i 256 phi0}
     {
         double sn, cs;
-        sincos((double)tid * d.phi0, &sn, &cs);
+        sincos((double)(tid % kFastThreads) * d.phi0, &sn, &cs);
         ph = make_double2(cs, sn);
-        sincos((double)NT * d.phi0, &sn, &cs);
+        sincos((double)kFastThreads * d.phi0, &sn, &cs);
         step = make_double2(cs, sn);
     }
+    if (tid >= kFastThreads) ph = cmul(ph, step);
 #pragma unroll
     for (int q = 0; q < QM; ++q) {
         const int m = tid + q * NT;
@@ -1222,7 +1228,7 @@ __device__ __attribute__((always_inline)) inline void fold_fast2(float2 *X0, flo
             X0[PadIdx::at(m)] = cvt<float2>(cmul(ph, v0));
             X1[PadIdx::at(m)] = cvt<float2>(cmul(ph, v1));
         }
-        ph = cmul(ph, step);
+        ph = cmul(cmul(ph, step), step);
     }
     __syncthreads();
     const int n = d.n;
