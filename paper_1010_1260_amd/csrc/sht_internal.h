@@ -165,6 +165,12 @@ constexpr int kTogetherEntries = 160 * 1024 / 16 / 4;
 constexpr int kFastThreads = 256;
 constexpr int kFastMaxH = 4096;
 constexpr int kFastMaxModes = 17 * kFastThreads;   // the fold holds m < 4352 in registers
+// The first buffer of the complex128 Bluestein path holds every live mode of the ring.  Up to
+// kFastMaxModes of them the longest ring and convolution take 9296 of a CU's
+// 10240 entries; a ring with more (undersampled: 12287 modes on 8188 pixels at
+// nside 4096, say) stays with the size classes, whose buffers do not grow with
+// the modes.
+inline bool blue64_holds(int mlive) { return mlive < kFastMaxModes; }
 // FP64 plans also take even rings of any half length up to kDirectMax on the
 // fast path, as one direct DFT (radix list 0): four threads per output point.
 // Bluestein's two dozen passes over so few points are all latency: the 18
@@ -358,7 +364,6 @@ struct sht_plan_s {
     size_t table_bytes;
     size_t pool_entries;
     int mcontig;         // m-set is 0..nm-1
-    std::vector<int> ring_class;  // size class of each ring's Fourier step
     std::vector<int> ring_need;   // LDS double2 entries of each ring's spectrum / FFT
     std::vector<int> ring_n;      // pixels of each ring
     std::vector<int> ring_nb;     // Bluestein length of each ring (0: none)

@@ -565,12 +565,11 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
             ring_sclass[r] = sht::kFastClass;
             sht::fast_lds_add(sclass_lds[sht::kFastClass], g.n, mval.back());
         } else if (b64 >= 0) {
-            // (its LDS goes by the ring's live modes, once they are known)
+            // (if it holds the ring's live modes, once they are known)
             g.np = sht::blue_radices(g.nb, &g.rads, sht::kBlue64Threads[b64],
                                      sht::kBlue64MaxN[b64], true);
             ring_sclass[r] = sht::kBlue64Class + b64;
             ring_bclass[r] = c;
-            sht::ring_lds_add(bclass_lds[c], c, g.n, g.nb, need);
         } else if (g.np > 0) {
             ring_sclass[r] = sht::kBlueClass;
             sht::blue_lds_add(sclass_lds[sht::kBlueClass], g.n, g.nb, mval.back());
@@ -611,8 +610,6 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
     p->moff[0] = 0;
     for (int i = 0; i < d->nm; ++i) p->moff[i + 1] = p->moff[i] + (d->lmax - mval[i] + 1);
     p->nalm = p->moff.back();
-    p->ring_class = ring_class;
-    p->ring_sclass = ring_sclass;
     p->ring_need.resize(R);
     p->ring_n.resize(R);
     p->ring_nb.resize(R);
@@ -764,10 +761,21 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
     for (int r = 0; r < R; ++r) {
         p->ring_mlive[r] = rings[r].mlive;
         const int q = ring_sclass[r] - sht::kBlue64Class;
-        if (q >= 0)
-            sht::blue_lds_add(sclass_lds[ring_sclass[r]], rings[r].n, rings[r].nb,
-                              rings[r].mlive, sht::kBlue64Threads[q]);
+        if (q < 0) continue;
+        const RingDesc &g = rings[r];
+        const int c = ring_bclass[r];   // size class of the ring
+        if (sht::blue64_holds(g.mlive)) {
+            sht::blue_lds_add(sclass_lds[ring_sclass[r]], g.n, g.nb, g.mlive,
+                              sht::kBlue64Threads[q]);
+            sht::ring_lds_add(bclass_lds[c], c, g.n, g.nb, p->ring_need[r]);
+        } else {
+            ring_class[r] = ring_sclass[r] = c;
+            ring_bclass[r] = -1;
+            sht::ring_lds_add(class_lds[c], c, g.n, g.nb, p->ring_need[r]);
+            sht::ring_lds_add(sclass_lds[c], c, g.n, g.nb, p->ring_need[r]);
+        }
     }
+    p->ring_sclass = ring_sclass;
     if (st == SHT_OK) st = upload(&p->d_pool, pb.pool, &tb);
     // longest rings first (tail balance); rings of equal length adjacent so
     // that consecutive workgroups, which the kernels place on one XCD, share
