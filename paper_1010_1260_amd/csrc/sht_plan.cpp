@@ -655,7 +655,9 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
     // ---- twiddle / chirp / Bluestein tables
     PoolBuilder pb;
     std::vector<int> prep_ids;
-    std::map<int, long long> bq_of_len;
+    // kernel spectra by (Bluestein length, convolution length): the paths choose
+    // the convolution length of a Bluestein length each by their own passes
+    std::map<std::pair<int, int>, long long> bq_of;
     for (int r = 0; r < R; ++r) {
         RingDesc &g = rings[r];
         g.tw = pb.roots(g.n);
@@ -663,10 +665,10 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
             const int blen = g.half ? g.clen / 2 : g.clen;   // Bluestein length
             g.tch = pb.chirp(blen);
             g.twb = pb.roots(g.nb);
-            auto it = bq_of_len.find(blen);
-            if (it == bq_of_len.end()) {
+            auto it = bq_of.find({blen, g.nb});
+            if (it == bq_of.end()) {
                 g.bq = pb.reserve(g.nb);
-                bq_of_len[blen] = g.bq;
+                bq_of[{blen, g.nb}] = g.bq;
                 prep_ids.push_back(r);
             } else {
                 g.bq = it->second;
