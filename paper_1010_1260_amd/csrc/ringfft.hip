@@ -1311,7 +1311,7 @@ __global__ __launch_bounds__(kFast2Threads, 4) void k_ring_synth_fast2(
     const int *__restrict__ ids, int count, int nmaps, const RingDesc *__restrict__ rings,
     const float2 *__restrict__ pool32, const float2 *__restrict__ delta,
     const int *__restrict__ minv, int mcontig, DeltaLayout dl,
-    double *__restrict__ map, long long npix, RingLds lds)
+    double *__restrict__ map, long long npix, RingLds lds, int gshift)
 {
     extern __shared__ double2 lds_raw[];
     float2 *X0 = reinterpret_cast<float2 *>(lds_raw);
@@ -1322,11 +1322,11 @@ __global__ __launch_bounds__(kFast2Threads, 4) void k_ring_synth_fast2(
     const int per = (int)(gridDim.x / 8);
     const int x = (int)(blockIdx.x % 8), w = (int)(blockIdx.x / 8);
     long long lo, hi;
-    xcd_share<true>(count, npairs, x, dl.shift, lo, hi);
+    xcd_share<true>(count, npairs, x, gshift, lo, hi);
     long long it = lo + w;
     if (it >= hi) return;
     int i, pi;
-    xcd_item<true>(it, count, npairs, x, dl.shift, i, pi);
+    xcd_item<true>(it, count, npairs, x, gshift, i, pi);
     int r = ids[i];
     long long b = 2LL * pi;
     bool two = b + 1 < nmaps;
@@ -1344,7 +1344,7 @@ __global__ __launch_bounds__(kFast2Threads, 4) void k_ring_synth_fast2(
         fold_fast2<kFast2Threads>(X0, X1, d, raw, d.mlive);
         const long long nx = it + per;
         if (nx < hi) {
-            xcd_item<true>(nx, count, npairs, x, dl.shift, i, pi);
+            xcd_item<true>(nx, count, npairs, x, gshift, i, pi);
             r = ids[i];
             b = 2LL * pi;
             two = b + 1 < nmaps;
@@ -1676,7 +1676,7 @@ __global__ __launch_bounds__(kBlueThreads, 4) void k_ring_synth_blue(
     const int *__restrict__ ids, int count, int nmaps, const RingDesc *__restrict__ rings,
     const float2 *__restrict__ pool32, const float2 *__restrict__ delta,
     const int *__restrict__ minv, int mcontig, DeltaLayout dl,
-    double *__restrict__ map, long long npix, RingLds lds)
+    double *__restrict__ map, long long npix, RingLds lds, int gshift)
 {
     typedef float2 C;
     constexpr int QM = FastModes2<kBlueThreads>::Q;
@@ -1690,11 +1690,11 @@ __global__ __launch_bounds__(kBlueThreads, 4) void k_ring_synth_blue(
     const int per = (int)(gridDim.x / 8);
     const int x = (int)(blockIdx.x % 8), w = (int)(blockIdx.x / 8);
     long long lo, hi;
-    xcd_share<true>(count, npairs, x, dl.shift, lo, hi);
+    xcd_share<true>(count, npairs, x, gshift, lo, hi);
     long long it = lo + w;
     if (it >= hi) return;
     int i, pi;
-    xcd_item<true>(it, count, npairs, x, dl.shift, i, pi);
+    xcd_item<true>(it, count, npairs, x, gshift, i, pi);
     int r = ids[i];
     long long b = 2LL * pi;
     bool two = b + 1 < nmaps;
@@ -1723,7 +1723,7 @@ __global__ __launch_bounds__(kBlueThreads, 4) void k_ring_synth_blue(
         }
         const long long nx = it + per;
         if (nx < hi) {
-            xcd_item<true>(nx, count, npairs, x, dl.shift, i, pi);
+            xcd_item<true>(nx, count, npairs, x, gshift, i, pi);
             r = ids[i];
             b = 2LL * pi;
             two = b + 1 < nmaps;
@@ -2420,9 +2420,11 @@ hipError_t synth_fast_class<float2>(const sht_plan_s *p, const float2 *delta, do
     long long grid = 2LL * (p->num_cus > 0 ? p->num_cus : 256);
     if (grid > items) grid = items;
     grid = ((grid + 7) / 8) * 8;
+    const DeltaLayout dl = delta_layout(p, delta, full);
     hipLaunchKernelGGL(k_ring_synth_fast2, dim3((unsigned)grid), dim3(kFast2Threads), lds, st,
                        rc.d_ids, rc.count, p->nmaps, p->d_rings, p->d_pool32, delta, p->d_minv,
-                       p->mcontig, delta_layout(p, delta, full), map, p->npix, rc.lds);
+                       p->mcontig, dl, map, p->npix, rc.lds,
+                       ring_group(rc.count, (p->nmaps + 1) / 2, grid, dl.shift));
     return hipGetLastError();
 }
 
@@ -2441,9 +2443,11 @@ hipError_t synth_blue_class(const sht_plan_s *p, const float2 *delta, double *ma
     long long grid = 2LL * (p->num_cus > 0 ? p->num_cus : 256);
     if (grid > items) grid = items;
     grid = ((grid + 7) / 8) * 8;
+    const DeltaLayout dl = delta_layout(p, delta, full);
     hipLaunchKernelGGL(k_ring_synth_blue, dim3((unsigned)grid), dim3(kBlueThreads), lds, st,
                        rc.d_ids, rc.count, p->nmaps, p->d_rings, p->d_pool32, delta, p->d_minv,
-                       p->mcontig, delta_layout(p, delta, full), map, p->npix, rc.lds);
+                       p->mcontig, dl, map, p->npix, rc.lds,
+                       ring_group(rc.count, (p->nmaps + 1) / 2, grid, dl.shift));
     return hipGetLastError();
 }
 
@@ -2473,8 +2477,13 @@ hipError_t synth_blue_class(const sht_plan_s *p, const double2 *delta, double *m
 // share the CUs and fill each other's tails (FP64 size classes: 10.6 -> 10.2
 // ms for 16 maps at l_max 4096 / nside 2048; with the mixed forms' two fast
 // paths: 5.93 -> 5.84 ms).
-// Small plans launch everything on `st` (a fork costs microseconds).
+// Small plans launch everything on `st` (a fork costs microseconds).  The
+// mixed forms' two kernels fill the CUs each by itself and only gain from
+// larger launches on (FP16x2, 16 maps, transform forked against in turn: nside
+// 192 238 and 224 us, 200 288 and 230, 216 334 and 275, 300 416 and 409, 400
+// and 500 alike; 600 1095 and 1103).
 constexpr long long kForkItems = 4096;
+constexpr long long kForkItemsMixed = 32768;
 
 template <typename DT> constexpr bool own_complex128(bool full)
 {
@@ -2495,7 +2504,8 @@ static hipError_t ring_synth_dt(const sht_plan_s *p, const DT *delta, double *ma
     }
     fast *= p->nmaps;
     rest *= p->nmaps;
-    const bool fork = p->aux_stream && fast > 0 && rest > 0 && fast + rest >= kForkItems;
+    const bool fork = p->aux_stream && fast > 0 && rest > 0 &&
+                      fast + rest >= (sizeof(DT) == sizeof(float2) ? kForkItemsMixed : kForkItems);
     // the fork and join events belong to the plan: calls from several host
     // threads take turns through the whole sequence
     std::unique_lock<std::mutex> lock(const_cast<sht_plan_s *>(p)->fork_mu, std::defer_lock);

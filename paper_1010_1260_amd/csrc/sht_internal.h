@@ -299,6 +299,24 @@ inline void ring_lds_add(RingLds &l, int c, int n, int nb, int need)
     }
 }
 
+// Rings that the persistent ring-by-ring kernels (grid workgroups, nitems items
+// per ring) deal to an XCD together, as a shift: the rings that share lines of
+// Delta, as long as that costs no XCD a round of its workgroups more than
+// single rings would.  Whole blocks of 16 of a short list leave most XCDs
+// idle: one FP16x2 map at l_max 64 / nside 32 (109 smooth rings) takes 85 us so,
+// 35 by this rule.
+inline int ring_group(int count, int nitems, long long grid, int shift)
+{
+    const long long per = grid / 8;
+    auto rounds = [&](int s) {
+        const long long all = count >> (s + 3), rest = count - (all << (s + 3));
+        const long long share = (all << s) + (rest < (1LL << s) ? rest : 1LL << s);   // XCD 0
+        return (share * nitems + per - 1) / per;
+    };
+    while (shift > 0 && rounds(shift) > rounds(0)) --shift;
+    return shift;
+}
+
 // One map of a batch of plans (device side): the plan's tables plus the
 // offsets of the map's buffers inside the batch workspace.
 struct BatchMap {
