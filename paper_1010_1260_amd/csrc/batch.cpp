@@ -153,6 +153,7 @@ sht_status sht_plan_batch(sht_batch_t *out, const sht_plan_t *plans, int32_t n)
         std::memset(&m, 0, sizeof m);
         m.pairs = p->d_pairs; m.mval = p->d_mval; m.moff = p->d_moff;
         m.A = p->d_A; m.cn = p->d_cn; m.minv = p->d_minv; m.rings = p->d_rings;
+        m.crings = p->d_crings;
         m.pool = p->d_pool;
         m.live = p->live;
         m.dl = sht::delta_blocked(p->nm, p->nrings);
@@ -212,7 +213,7 @@ sht_status sht_plan_batch(sht_batch_t *out, const sht_plan_t *plans, int32_t n)
                         sht::blue_lds_add(lds, p->ring_n[r], p->ring_nb[r], p->ring_mlive[r],
                                           sht::kBlue64Threads[c - sht::kBlue64Class]);
                     else
-                        sht::ring_lds_add(lds, c, p->ring_n[r], p->ring_nb[r], p->ring_need[r]);
+                        sht::ring_lds_add(lds, c, p->ring_n[r], p->ring_cnb[r], p->ring_need[r]);
                 }
         }
         b->cls[c].count = (int)items.size();

@@ -910,15 +910,25 @@ struct FastModes {
 };
 
 // Loads of the fold: modes m = tid + q NT of one ring, all at once; they are on
-// their way during the passes of the ring before.
-template <int NT, typename DT>
+// their way during the passes of the ring before.  paced: each waits for the
+// one before it.  The loads of all workgroups then move through the m rows of
+// a caller's [m][ring] Delta together, so that the DRAM rows they open serve
+// the neighbouring rings too; all at once they reach a Delta beyond the last
+// cache as a burst over thousands of rows (delta2map of one l_max 4096 map: 775
+// us, paced 736; l_max 2048, whose Delta the cache holds, 217 and 224).
+template <int NT, bool PACED = false, typename DT>
 __device__ __attribute__((always_inline)) inline void load_fast(FastModes<NT, DT> &raw,
                                                                 const DT *__restrict__ drow,
                                                                 long long dstride,
                                                                 const int *__restrict__ minv,
-                                                                int mcontig, int mmax)
+                                                                int mcontig, int mmax,
+                                                                bool paced = false)
 {
     constexpr int QM = FastModes<NT, DT>::Q;
+    auto pace = [&] {
+        // s_waitcnt vmcnt(0) expcnt(7) lgkmcnt(15)
+        if (PACED && paced) __builtin_amdgcn_s_waitcnt(0x0F70);
+    };
     // an opaque thread index keeps the per-q addresses from being hoisted
     // out of the persistent kernels' ring loop (where they would stay live)
     int tid = threadIdx.x;
@@ -930,6 +940,7 @@ __device__ __attribute__((always_inline)) inline void load_fast(FastModes<NT, DT
             raw.v[q] = DT{};
             // uniform: nothing for the rounds of modes that are dead on the ring
             if (q * NT <= mmax && m <= mmax) raw.v[q] = drow[(long long)m * dstride];
+            if (q + 1 < QM) pace();
         }
     } else {
         // every position lookup first, then the loads
@@ -942,6 +953,7 @@ __device__ __attribute__((always_inline)) inline void load_fast(FastModes<NT, DT
 #pragma unroll
         for (int q = 0; q < QM; ++q) {
             raw.v[q] = (pos[q] >= 0) ? drow[(long long)pos[q] * dstride] : DT{};
+            if (q + 1 < QM) pace();
         }
     }
 }
@@ -1378,7 +1390,7 @@ template <typename DT>
 __global__ __launch_bounds__(kFastThreads, FastPrec<DT>::kBlocks) void k_ring_synth_fast(
     const int *__restrict__ ids, int count, int nmaps, const RingDesc *__restrict__ rings,
     const double2 *__restrict__ pool, const DT *__restrict__ delta,
-    const int *__restrict__ minv, int mcontig, int mfull, DeltaLayout dl,
+    const int *__restrict__ minv, int mcontig, int mfull, int paced, DeltaLayout dl,
     double *__restrict__ map, long long npix, RingLds lds)
 {
     typedef typename FastPrec<DT>::C C;
@@ -1396,8 +1408,8 @@ __global__ __launch_bounds__(kFastThreads, FastPrec<DT>::kBlocks) void k_ring_sy
     long long b = bi;
     int r = ids[i];
     FastModes<kFastThreads, DT> raw;
-    load_fast<kFastThreads>(raw, delta + b * dl.map + dl.row(r), dl.mstride(r), minv, mcontig,
-                            ring_mmax(rings[r], mfull));
+    load_fast<kFastThreads, true>(raw, delta + b * dl.map + dl.row(r), dl.mstride(r), minv,
+                                  mcontig, ring_mmax(rings[r], mfull), paced != 0);
     for (bool first = true;; first = false) {
         const RingDesc d = rings[r];
         double *out = map + b * npix + d.start;
@@ -1409,8 +1421,8 @@ __global__ __launch_bounds__(kFastThreads, FastPrec<DT>::kBlocks) void k_ring_sy
             xcd_item<RingMajor<DT>::value>(nx, count, nmaps, x, dl.shift, i, bi);
             b = bi;
             r = ids[i];
-            load_fast<kFastThreads>(raw, delta + b * dl.map + dl.row(r), dl.mstride(r), minv, mcontig,
-                            ring_mmax(rings[r], mfull));
+            load_fast<kFastThreads, true>(raw, delta + b * dl.map + dl.row(r), dl.mstride(r), minv,
+                                  mcontig, ring_mmax(rings[r], mfull), paced != 0);
         }
         fft_fast<kFastThreads, C>(buf, T, d, out, threadIdx.x, true);
         if (nx >= hi) break;
@@ -1884,7 +1896,7 @@ __global__ __launch_bounds__(NT, 4) void k_ring_synth_batch(
     extern __shared__ double2 buf[];
     const int2 it = items[xcd_logical(blockIdx.x, gridDim.x)];
     const BatchMap &bm = maps[it.x];
-    const RingDesc d = bm.rings[it.y];
+    const RingDesc d = bm.crings[it.y];
     const double2 *delta = reinterpret_cast<const double2 *>(ws + bm.delta_off);
     double2 *tw = buf + lds.fft_entries;
     const RingTables rt = {tw, tw + lds.tw_entries};
@@ -2249,7 +2261,7 @@ hipError_t synth_class(const sht_plan_s *p, const RingClass &rc, const DT *delta
     const long long items = (long long)rc.count * p->nmaps;
     if (items > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL((k_ring_synth<NT, MAXN, DT>), dim3((unsigned)items), dim3(NT), lds, st,
-                       rc.d_ids, rc.count, p->nmaps, p->d_rings, p->d_pool, delta, p->d_minv,
+                       rc.d_ids, rc.count, p->nmaps, p->d_crings, p->d_pool, delta, p->d_minv,
                        p->mcontig, full ? p->mmax : -1, delta_layout(p, delta, full), map, p->npix,
                        rc.lds);
     return hipGetLastError();
@@ -2266,7 +2278,7 @@ hipError_t anal_class(const sht_plan_s *p, int c, const double *map, double2 *dt
     hipError_t e = set_lds((const void *)k_ring_anal<NT, MAXN>, lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((k_ring_anal<NT, MAXN>), dim3((unsigned)rc.count, (unsigned)p->nmaps),
-                       dim3(NT), lds, st, rc.d_ids, p->d_rings, p->d_pool, map, p->npix,
+                       dim3(NT), lds, st, rc.d_ids, p->d_crings, p->d_pool, map, p->npix,
                        p->d_mval, p->mcontig, p->nm, delta_layout(p, dt, full), dt,
                        full ? p->mmax : -1, rc.lds, rw, cfac);
     return hipGetLastError();
@@ -2397,10 +2409,12 @@ hipError_t synth_fast_class(const sht_plan_s *p, const DT *delta, double *map, b
     long long grid = (long long)FastPrec<DT>::kBlocks * (p->num_cus > 0 ? p->num_cus : 256);
     if (grid > items) grid = items;
     grid = ((grid + 7) / 8) * 8;
+    // one map's Delta against the last cache's 256 MB
+    const bool past_cache = (long long)p->nm * p->nrings * (long long)sizeof(DT) > (256LL << 20);
     hipLaunchKernelGGL((k_ring_synth_fast<DT>), dim3((unsigned)grid), dim3(kFastThreads), lds,
                        st, rc.d_ids, rc.count, p->nmaps, p->d_rings, p->d_pool, delta,
-                       p->d_minv, p->mcontig, full ? p->mmax : -1, delta_layout(p, delta, full), map,
-                       p->npix, rc.lds);
+                       p->d_minv, p->mcontig, full ? p->mmax : -1, full && past_cache ? 1 : 0,
+                       delta_layout(p, delta, full), map, p->npix, rc.lds);
     return hipGetLastError();
 }
 
@@ -2673,15 +2687,15 @@ hipError_t launch_ring_synth_batch(const BatchClass *cls, const BatchMap *maps,
     return e;
 }
 
-hipError_t launch_bluestein_prep(const sht_plan_s *p, const int *ring_ids, int nids,
-                                 hipStream_t st)
+hipError_t launch_bluestein_prep(const sht_plan_s *p, const RingDesc *rings, const int *ring_ids,
+                                 int nids, hipStream_t st)
 {
     if (nids <= 0) return hipSuccess;
     const size_t lds = (size_t)(8192 + kTwEntries) * sizeof(double2);
     hipError_t e = set_lds((const void *)k_bluestein_prep, lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_bluestein_prep, dim3((unsigned)nids), dim3(512), lds, st,
-                       p->d_rings, ring_ids, p->d_pool);
+                       rings, ring_ids, p->d_pool);
     return hipGetLastError();
 }
 

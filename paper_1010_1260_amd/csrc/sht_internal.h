@@ -327,6 +327,7 @@ struct BatchMap {
     const double *cn;
     const int32_t *minv;
     const RingDesc *rings;
+    const RingDesc *crings;   // as the size-class kernels take them
     const double2 *pool;
     LiveTab live;
     DeltaLayout dl;
@@ -377,14 +378,16 @@ struct sht_plan_s {
     double *d_Asb;       // [nsuper][128] d_A per super-block, zero past each m's last row
     long long nsuper;    // 128-row super-blocks over all m
     sht::RingDesc *d_rings;
+    sht::RingDesc *d_crings;   // the rings as the size-class kernels take them
     double2 *d_pool;     // twiddle and Bluestein tables
     float2 *d_pool32;    // complex64 copy of d_pool (plans with a Bluestein fast path)
     size_t table_bytes;
     size_t pool_entries;
     int mcontig;         // m-set is 0..nm-1
-    std::vector<int> ring_need;   // LDS double2 entries of each ring's spectrum / FFT
+    std::vector<int> ring_need;   // LDS double2 entries of each ring's spectrum / FFT (size classes)
     std::vector<int> ring_n;      // pixels of each ring
-    std::vector<int> ring_nb;     // Bluestein length of each ring (0: none)
+    std::vector<int> ring_nb;     // convolution length of each ring (0: none)
+    std::vector<int> ring_cnb;    // the same in the size classes
     sht::RingClass cls[sht::kNumRingClasses];     // analysis: the rings off the fast path
     sht::RingClass scls[sht::kNumSynthClasses];   // synthesis
     // the Bluestein fast path's rings by size class, for synthesis from a
@@ -481,7 +484,7 @@ sht_status check_plan_device(sht_plan_t p);
 sht_status forward_transform(sht_plan_t p, const double *alm, double *map, void *ws,
                              hipStream_t st);
 // Plan time: spectra of the Bluestein chirp kernels.
-hipError_t launch_bluestein_prep(const sht_plan_s *p, const int *ring_ids, int nids,
-                                 hipStream_t st);
+hipError_t launch_bluestein_prep(const sht_plan_s *p, const RingDesc *rings, const int *ring_ids,
+                                 int nids, hipStream_t st);
 
 }  // namespace sht

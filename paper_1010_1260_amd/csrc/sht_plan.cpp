@@ -227,7 +227,7 @@ sht_status upload(T **dst, const std::vector<T> &src, size_t *acc)
 void free_tables(sht_plan_s *p)
 {
     void *ptrs[] = {p->d_pairs, p->d_mval, p->d_moff, p->d_mu, p->d_A, p->d_cn,
-                    p->d_minv, p->d_rings, p->d_pool, p->d_boff, p->d_boff16, p->d_bm16,
+                    p->d_minv, p->d_rings, p->d_crings, p->d_pool, p->d_boff, p->d_boff16, p->d_bm16,
                     p->d_bm32, p->d_soff, p->d_sbm, p->d_Asb, p->d_pool32,
                     const_cast<double2 *>(p->live.st), const_cast<uint16_t *>(p->live.je),
                     const_cast<ushort2 *>(p->live.jr), const_cast<uint16_t *>(p->live.jq)};
@@ -245,6 +245,7 @@ void free_tables(sht_plan_s *p)
     }
     p->d_pairs = nullptr; p->d_mval = nullptr; p->d_moff = nullptr; p->d_mu = nullptr;
     p->d_A = nullptr; p->d_cn = nullptr; p->d_minv = nullptr; p->d_rings = nullptr;
+    p->d_crings = nullptr;
     p->d_pool = nullptr; p->d_boff = nullptr; p->d_boff16 = nullptr; p->d_bm16 = nullptr;
     p->d_bm32 = nullptr; p->d_soff = nullptr; p->d_sbm = nullptr; p->d_Asb = nullptr;
     p->d_pool32 = nullptr;
@@ -488,8 +489,14 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
     }
     if (d->npix < 0 || (d->npix > 0 && d->npix < npix)) return SHT_ERR_INVALID_ARG;
     if (d->npix > 0) npix = d->npix;
-    // ---- Fourier classification per ring
-    std::vector<RingDesc> rings(R);
+    // ---- Fourier classification per ring: its description for the path that
+    // takes it, and for the size classes, which the complex128 Bluestein path's
+    // rings go to with a caller's Delta, or when that path cannot hold their
+    // modes.  The two differ in those rings: each path has the convolution
+    // length that is cheapest for its own passes (2 x 1501 points: 3136, in the
+    // size classes 3072), and the size classes run a 7-smooth length without a
+    // convolution.
+    std::vector<RingDesc> rings(R), crings(R);
     std::vector<int> ring_class(R), ring_sclass(R);
     sht::RingLds class_lds[sht::kNumRingClasses] = {};
     sht::RingLds sclass_lds[sht::kNumSynthClasses] = {};
@@ -518,7 +525,7 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
         g.clen = (int)((n % 2 == 0) ? n / 2 : n);
         g.tw = g.tch = g.twb = g.bq = -1;
         const int spec = (n % 2 == 0) ? g.clen + 1 : g.clen;  // F_k entries
-        int fftlen, b64 = -1;   // b64: class of the complex128 Bluestein fast path
+        int fftlen;
         unsigned long long fr = 0;
         if (smooth7(g.clen) && g.clen <= 8192) {
             g.nb = 0;
@@ -526,9 +533,8 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
             // an even ring of 7-smooth half length that the fast path cannot
             // take (a pass would hold too many butterflies per thread) joins
             // the Bluestein fast path
-            if (n % 2 == 0 && g.clen % 2 == 0 && sht::fast_radices(g.clen, &fr) == 0) {
-                const int nbb = blue_ok ? best_blue_nb((long long)g.clen - 1)
-                                        : blue64(g.clen, b64);
+            if (blue_ok && n % 2 == 0 && g.clen % 2 == 0 && sht::fast_radices(g.clen, &fr) == 0) {
+                const int nbb = best_blue_nb((long long)g.clen - 1);
                 if (nbb > 0) {
                     g.half = 1;
                     g.nb = nbb;
@@ -539,7 +545,7 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
             // split into the even- and odd-indexed halves: Bluestein of
             // length clen / 2 needs a convolution of only clen - 1 points
             g.half = 1;
-            const int nbb = blue_ok ? best_blue_nb((long long)g.clen - 1) : blue64(g.clen, b64);
+            const int nbb = blue_ok ? best_blue_nb((long long)g.clen - 1) : 0;
             g.nb = nbb > 0 ? nbb : best_smooth7((long long)g.clen - 1);
             if (g.nb > 8192) return SHT_ERR_UNSUPPORTED;
             fftlen = g.nb;
@@ -548,14 +554,19 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
             if (g.nb > 8192) return SHT_ERR_UNSUPPORTED;
             fftlen = g.nb;
         }
+        crings[r] = g;
         const int need = std::max(spec, fftlen);
         const int c = fftlen <= 2048 ? 0 : (fftlen <= 4096 ? 1 : 2);
         ring_class[r] = c;
         g.np = (n % 2 == 0 && g.nb == 0 && mval.back() < sht::kFastMaxModes)
                    ? sht::fast_radices(g.clen, &g.rads) : 0;
-        // a short half length that has no radix list: one direct pass
+        // FP64 plans: a short half length that has no radix list in one direct
+        // pass, other even ones on the complex128 Bluestein path
         const bool direct = g.np == 0 && d->precision == SHT_FP64 && n % 2 == 0 &&
                             g.clen <= sht::kDirectMax && mval.back() < sht::kFastMaxModes;
+        int b64 = -1;
+        const int nb64 = g.np == 0 && !direct && n % 2 == 0 && g.clen % 2 == 0
+                             ? blue64(g.clen, b64) : 0;
         if (direct) {
             g.np = 1;
             g.rads = 0;
@@ -566,6 +577,8 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
             sht::fast_lds_add(sclass_lds[sht::kFastClass], g.n, mval.back());
         } else if (b64 >= 0) {
             // (if it holds the ring's live modes, once they are known)
+            g.half = 1;
+            g.nb = nb64;
             g.np = sht::blue_radices(g.nb, &g.rads, sht::kBlue64Threads[b64],
                                      sht::kBlue64MaxN[b64], true);
             ring_sclass[r] = sht::kBlue64Class + b64;
@@ -613,12 +626,15 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
     p->ring_need.resize(R);
     p->ring_n.resize(R);
     p->ring_nb.resize(R);
+    p->ring_cnb.resize(R);
     for (int r = 0; r < R; ++r) {
         const RingDesc &g = rings[r];
         const int spec = (g.n % 2 == 0) ? g.clen + 1 : g.clen;
-        p->ring_need[r] = std::max(spec, g.nb ? g.nb : g.clen);
+        const int cnb = crings[r].nb;
+        p->ring_need[r] = std::max(spec, cnb ? cnb : g.clen);
         p->ring_n[r] = g.n;
         p->ring_nb[r] = g.nb;
+        p->ring_cnb[r] = cnb;
     }
     p->mcontig = 1;
     for (int i = 0; i < d->nm; ++i)
@@ -654,27 +670,27 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
 
     // ---- twiddle / chirp / Bluestein tables
     PoolBuilder pb;
-    std::vector<int> prep_ids;
+    std::vector<int> prep_ids, cprep_ids;   // rings whose kernel spectra are to be made
     // kernel spectra by (Bluestein length, convolution length): the paths choose
     // the convolution length of a Bluestein length each by their own passes
     std::map<std::pair<int, int>, long long> bq_of;
-    for (int r = 0; r < R; ++r) {
-        RingDesc &g = rings[r];
+    auto ring_tables = [&](RingDesc &g, int r, std::vector<int> &prep) {
         g.tw = pb.roots(g.n);
-        if (g.nb) {
-            const int blen = g.half ? g.clen / 2 : g.clen;   // Bluestein length
-            g.tch = pb.chirp(blen);
-            g.twb = pb.roots(g.nb);
-            auto it = bq_of.find({blen, g.nb});
-            if (it == bq_of.end()) {
-                g.bq = pb.reserve(g.nb);
-                bq_of[{blen, g.nb}] = g.bq;
-                prep_ids.push_back(r);
-            } else {
-                g.bq = it->second;
-            }
+        if (!g.nb) return;
+        const int blen = g.half ? g.clen / 2 : g.clen;   // Bluestein length
+        g.tch = pb.chirp(blen);
+        g.twb = pb.roots(g.nb);
+        auto it = bq_of.find({blen, g.nb});
+        if (it == bq_of.end()) {
+            g.bq = pb.reserve(g.nb);
+            bq_of[{blen, g.nb}] = g.bq;
+            prep.push_back(r);
+        } else {
+            g.bq = it->second;
         }
-    }
+    };
+    for (int r = 0; r < R; ++r) ring_tables(rings[r], r, prep_ids);
+    for (int r = 0; r < R; ++r) ring_tables(crings[r], r, cprep_ids);
     p->pool_entries = pb.pool.size();
 
     sht_status st = SHT_OK;
@@ -761,7 +777,7 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
         st = SHT_ERR_HIP;
     p->ring_mlive.resize(R);
     for (int r = 0; r < R; ++r) {
-        p->ring_mlive[r] = rings[r].mlive;
+        crings[r].mlive = p->ring_mlive[r] = rings[r].mlive;
         const int q = ring_sclass[r] - sht::kBlue64Class;
         if (q < 0) continue;
         const RingDesc &g = rings[r];
@@ -769,14 +785,15 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
         if (sht::blue64_holds(g.mlive)) {
             sht::blue_lds_add(sclass_lds[ring_sclass[r]], g.n, g.nb, g.mlive,
                               sht::kBlue64Threads[q]);
-            sht::ring_lds_add(bclass_lds[c], c, g.n, g.nb, p->ring_need[r]);
+            sht::ring_lds_add(bclass_lds[c], c, g.n, p->ring_cnb[r], p->ring_need[r]);
         } else {
             ring_class[r] = ring_sclass[r] = c;
             ring_bclass[r] = -1;
-            sht::ring_lds_add(class_lds[c], c, g.n, g.nb, p->ring_need[r]);
-            sht::ring_lds_add(sclass_lds[c], c, g.n, g.nb, p->ring_need[r]);
+            sht::ring_lds_add(class_lds[c], c, g.n, p->ring_cnb[r], p->ring_need[r]);
+            sht::ring_lds_add(sclass_lds[c], c, g.n, p->ring_cnb[r], p->ring_need[r]);
         }
     }
+    if (st == SHT_OK) st = upload(&p->d_crings, crings, &tb);
     p->ring_sclass = ring_sclass;
     if (st == SHT_OK) st = upload(&p->d_pool, pb.pool, &tb);
     // longest rings first (tail balance); rings of equal length adjacent so
@@ -809,19 +826,22 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
         p->bcls[c].lds = bclass_lds[c];
         st = upload(&p->bcls[c].d_ids, ids, &tb);
     }
-    if (st == SHT_OK && !prep_ids.empty()) {
+    auto make_spectra = [&](const RingDesc *d_desc, const std::vector<int> &ids) {
+        if (st != SHT_OK || ids.empty()) return;
         int *d_ids = nullptr;
-        if (hipMalloc((void **)&d_ids, prep_ids.size() * sizeof(int)) != hipSuccess) {
+        if (hipMalloc((void **)&d_ids, ids.size() * sizeof(int)) != hipSuccess) {
             st = SHT_ERR_OOM;
-        } else {
-            if (hipMemcpy(d_ids, prep_ids.data(), prep_ids.size() * sizeof(int),
-                          hipMemcpyHostToDevice) != hipSuccess ||
-                sht::launch_bluestein_prep(p, d_ids, (int)prep_ids.size(), nullptr) != hipSuccess ||
-                hipDeviceSynchronize() != hipSuccess)
-                st = SHT_ERR_HIP;
-            (void)hipFree(d_ids);
+            return;
         }
-    }
+        if (hipMemcpy(d_ids, ids.data(), ids.size() * sizeof(int), hipMemcpyHostToDevice) !=
+                hipSuccess ||
+            sht::launch_bluestein_prep(p, d_desc, d_ids, (int)ids.size(), nullptr) != hipSuccess ||
+            hipDeviceSynchronize() != hipSuccess)
+            st = SHT_ERR_HIP;
+        (void)hipFree(d_ids);
+    };
+    make_spectra(p->d_rings, prep_ids);
+    make_spectra(p->d_crings, cprep_ids);
     // the mixed forms' fast paths read their tables (twiddles, kernel
     // spectra) in complex64: 8-byte loads, no conversions in the passes
     if (st == SHT_OK && delta_f32(p) &&
