@@ -36,7 +36,9 @@
 //    convolutions run side by side in two buffers, with the chirps, the kernel
 //    spectrum, the pre-processing and the stores inside the passes.
 //  - everything else (odd lengths, half lengths above 4096 or odd and not
-//    smooth, mixed-form analysis, a caller's whole Delta): size classes by FFT
+//    smooth; in the mixed forms' analysis all Bluestein rings, and for short
+//    rings the smooth ones too; a caller's whole Delta on Bluestein rings):
+//    size classes by FFT
 //    length (up to 2048, 4096 and 8192 points) on 256-, 512- and 1024-thread
 //    workgroups.  DFTs of 7-smooth length run as an in-place Stockham FFT
 //    (radices 8, 4, 2, 3, 5 and 7; every pass loads its butterfly inputs into
@@ -2606,9 +2608,12 @@ hipError_t launch_widen_delta(const sht_plan_s *p, const float2 *s, double2 *d, 
 hipError_t launch_ring_anal(const sht_plan_s *p, const double *map, double2 *dt, bool full,
                             hipStream_t st, const double *rw, double cfac)
 {
-    const bool both = rings_together(p);
-    hipError_t e = both ? anal_together(p, map, dt, full, st, rw, cfac)
-                        : anal_fast_class(p, map, dt, full, st, rw, cfac);
+    const bool both = p->anal_fast && rings_together(p);
+    hipError_t e = hipSuccess;
+    if (both)
+        e = anal_together(p, map, dt, full, st, rw, cfac);
+    else if (p->anal_fast)
+        e = anal_fast_class(p, map, dt, full, st, rw, cfac);
     if (e == hipSuccess) e = anal_blue64_class<2>(p, map, dt, full, st, rw, cfac);
     if (e == hipSuccess) e = anal_blue64_class<1>(p, map, dt, full, st, rw, cfac);
     if (e == hipSuccess && !both) e = anal_blue64_class<0>(p, map, dt, full, st, rw, cfac);

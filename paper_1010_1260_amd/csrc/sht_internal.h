@@ -388,7 +388,8 @@ struct sht_plan_s {
     std::vector<int> ring_n;      // pixels of each ring
     std::vector<int> ring_nb;     // convolution length of each ring (0: none)
     std::vector<int> ring_cnb;    // the same in the size classes
-    sht::RingClass cls[sht::kNumRingClasses];     // analysis: the rings off the fast path
+    sht::RingClass cls[sht::kNumRingClasses];     // analysis: the rings off the fast paths
+    bool anal_fast;                               // analysis: the fast path is one of them
     sht::RingClass scls[sht::kNumSynthClasses];   // synthesis
     // the Bluestein fast path's rings by size class, for synthesis from a
     // caller's complex128 Delta (sht_delta2map), which that path does not take

@@ -515,6 +515,16 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
         q = -1;
         return 0;
     };
+    // The mixed forms' analysis has its Bluestein rings in the size classes; the
+    // smooth ones take the fast path only where that pays for the second
+    // launch.  map2delta_adjoint, all by size class against both: one map at
+    // l_max 64 16 and 24 us, 512 32 and 39, 640 55 and 48, 1024 94 and 76, 4096
+    // 1079 and 744; four maps at 512 99 and 85; 7 maps at 512 124 and 127, at 800
+    // 237 and 248; 8 maps at 1024 388 and 395; four at 2048 790 and 630.
+    int longest = 0;
+    for (int r = 0; r < R; ++r) longest = std::max(longest, (int)d->nphi[r]);
+    const bool anal_fast = d->precision == SHT_FP64 || longest > 2048 ||
+                           (d->nmaps < 7 && (long long)R * d->nmaps >= 1200);
     for (int r = 0; r < R; ++r) {
         const long long n = d->nphi[r];
         RingDesc &g = rings[r];
@@ -594,7 +604,8 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
         }
         // the analysis takes the fast paths' rings (complex128) on fast paths of
         // its own, and the others by size class
-        if (ring_sclass[r] == sht::kFastClass || ring_sclass[r] >= sht::kBlue64Class)
+        if ((ring_sclass[r] == sht::kFastClass && anal_fast) ||
+            ring_sclass[r] >= sht::kBlue64Class)
             ring_class[r] = -1;
         else
             sht::ring_lds_add(class_lds[c], c, g.n, g.nb, need);
@@ -611,6 +622,7 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
     p->nmaps = d->nmaps;
     p->precision = d->precision;
     p->flags = d->flags;
+    p->anal_fast = anal_fast;
     p->num_cus = 0;
     if (hipDeviceGetAttribute(&p->num_cus, hipDeviceAttributeMultiprocessorCount, p->device) !=
         hipSuccess) {
