@@ -360,7 +360,7 @@ hipError_t launch_legendre_mfma_bf16x3(const sht_plan_s *p, const void *Bb, floa
     if (f16_super_rows() != kSuperRows) return hipErrorInvalidConfiguration;
     if (total <= 0 || total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(k_legendre_mfma_bf16x3, dim3((unsigned)total), dim3(64), 0, st,
-                       p->d_pairs, p->npairs, p->live, pblocks, p->d_mval, p->d_boff, p->d_soff,
+                       p->d_pairs, p->npairs, p->live32, pblocks, p->d_mval, p->d_boff, p->d_soff,
                        p->nm, nmpairs, p->lmax, p->d_Asb, reinterpret_cast<const v4u *>(Bb),
                        p->nblk32, delta, delta_blocked_maps(p->nm, p->nrings, p->nmaps), p->nmaps, groups, full ? 1 : 0);
     return hipGetLastError();

@@ -517,7 +517,7 @@ hipError_t launch_legendre_mfma_f16x2(const sht_plan_s *p, const void *Bb, float
     const long long total = 8LL * ((nmpairs + 7) / 8) * pblocks * groups;
     if (total <= 0 || total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(k_legendre_mfma_f16x2, dim3((unsigned)total), dim3(64), 0, st,
-                       p->d_pairs, p->npairs, p->live, pblocks, p->d_mval, p->d_soff, p->nm,
+                       p->d_pairs, p->npairs, p->live32, pblocks, p->d_mval, p->d_soff, p->nm,
                        nmpairs, p->lmax, p->d_Asb, reinterpret_cast<const v4u *>(Bb), p->nsuper,
                        delta, delta_blocked_maps(p->nm, p->nrings, p->nmaps), p->nmaps, groups, full ? 1 : 0);
     return hipGetLastError();

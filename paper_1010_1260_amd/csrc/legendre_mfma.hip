@@ -235,7 +235,7 @@ __device__ __forceinline__ void store_delta(const Sums<NP> &tot, int i,
 {
     if (p >= npairs) return;
     const PairDesc d = pairs[p];
-    if (!full && i >= d.ilim) return;   // dead on the ring, not read
+    if (!full && i >= d.ilim32) return;   // dead on the ring, not read
     const int rs = d.rs >= 0 ? d.rs : d.rn;
     float2 *__restrict__ dn = delta + dl.row(d.rn) + i * dl.mstride(d.rn);
     float2 *__restrict__ ds = delta + dl.row(rs) + i * dl.mstride(rs);
@@ -334,7 +334,7 @@ hipError_t launch_group(const sht_plan_s *p, const float *Bp, float2 *delta, int
     const long long total = 8LL * ((nmpairs + 7) / 8) * pblocks * groups;
     if (total <= 0 || total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(k_legendre_mfma_f32<NP>, dim3((unsigned)total), dim3(64), 0, st, p->d_pairs,
-                       p->npairs, p->live, pblocks, p->d_mval, p->d_soff, p->d_boff16, p->nm,
+                       p->npairs, p->live32, pblocks, p->d_mval, p->d_soff, p->d_boff16, p->nm,
                        nmpairs, p->lmax, p->d_Asb, Bp + b_offset(p, first), p->nblk16, delta,
                        delta_blocked_maps(p->nm, p->nrings, p->nmaps), first, p->nmaps, groups, full ? 1 : 0);
     return hipGetLastError();

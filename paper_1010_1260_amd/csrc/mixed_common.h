@@ -38,7 +38,7 @@ __device__ __forceinline__ void add_tiles(MfmaTiles &tot, const MfmaTiles &acc)
 
 // A lane's recurrence on one m: zero until its start row, where it takes the
 // start table's values (`stash`, its LDS slot).  Before it the true values are
-// below 2^-180, which is zero in FP32, so a lane's operands need no mask, and
+// below 2^-160, which is zero in FP32, so a lane's operands need no mask, and
 // from there on they are plain FP64 values bounded by sqrt((2l+1)/4pi)/c_l <
 // 2^9 (addition theorem).
 struct Lane {
@@ -98,7 +98,7 @@ __device__ __forceinline__ void m_store(const MfmaTiles &tot, int i, float2 *__r
         const int pp = pb * 64 + h * 32 + col;
         if (pp < npairs) {
             const PairDesc d = pairs[pp];
-            if (!full && i >= d.ilim) continue;   // dead on the ring, not read
+            if (!full && i >= d.ilim32) continue;   // dead on the ring, not read
             const int rs = d.rs >= 0 ? d.rs : d.rn;
             float2 *__restrict__ dn = d2 + dl.row(d.rn) + i * dl.mstride(d.rn);
             float2 *__restrict__ ds = d2 + dl.row(rs) + i * dl.mstride(rs);

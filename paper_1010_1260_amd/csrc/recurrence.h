@@ -40,11 +40,6 @@ __device__ inline void seed_mm(double mu, double s, int m, double &v, int &k)
     k = kk;
 }
 
-__device__ inline double final_scale(int k)
-{
-    return k == 0 ? 1.0 : (k == -1 ? kTwoMinusS : 0.0);
-}
-
 // Wave-uniform data that no kernel writes while it reads it comes through the
 // constant address space: scalar loads, also where the compiler cannot prove
 // that the kernel's stores leave it alone (the batch's workspace holds both

@@ -592,7 +592,13 @@ __device__ inline double2 load_mode(const DT *__restrict__ drow, long long dstri
 // Modes of a ring: the Legendre stage of the plan leaves the m beyond the
 // ring's mlive out (they are dead there, live.hip), so its rings fold
 // m <= mlive (mfull < 0).  A caller's Delta has all of them: m <= mfull.
-__device__ inline int ring_mmax(const RingDesc &d, int mfull) { return mfull < 0 ? d.mlive : mfull; }
+template <typename DT> __device__ inline int ring_live(const RingDesc &d) { return d.mlive; }
+template <> __device__ inline int ring_live<float2>(const RingDesc &d) { return d.mlive32; }
+template <typename DT = double2>
+__device__ inline int ring_mmax(const RingDesc &d, int mfull)
+{
+    return mfull < 0 ? ring_live<DT>(d) : mfull;
+}
 
 // Synthesis: one workgroup per (ring of this size class, map).  LDS: the
 // spectrum / FFT buffer, the twiddle tables and the alias staging slots
@@ -1348,14 +1354,14 @@ __global__ __launch_bounds__(kFast2Threads, 4) void k_ring_synth_fast2(
     const int half = threadIdx.x / kFastThreads, htid = threadIdx.x % kFastThreads;
     float2 *const X = half ? X1 : X0;
     load_fast2<kFast2Threads>(raw, delta + b * dl.map + dl.row(r), dl.mstride(r), minv, mcontig,
-                             rings[r].mlive, aligned, two);
+                             rings[r].mlive32, aligned, two);
     for (bool first = true;; first = false) {
         const RingDesc d = rings[r];
         const bool mine = two || half == 0;
         double *out = map + (mine ? b + half : b) * npix + d.start;
         if (!first) __syncthreads();   // the previous ring's last pass has read X0, X1, T
         load_tw<kFast2Threads>(T, pool32 + d.tw, d.n);
-        fold_fast2<kFast2Threads>(X0, X1, d, raw, d.mlive);
+        fold_fast2<kFast2Threads>(X0, X1, d, raw, d.mlive32);
         const long long nx = it + per;
         if (nx < hi) {
             xcd_item<true>(nx, count, npairs, x, gshift, i, pi);
@@ -1363,7 +1369,7 @@ __global__ __launch_bounds__(kFast2Threads, 4) void k_ring_synth_fast2(
             b = 2LL * pi;
             two = b + 1 < nmaps;
             load_fast2<kFast2Threads>(raw, delta + b * dl.map + dl.row(r), dl.mstride(r), minv, mcontig,
-                                     rings[r].mlive, aligned, two);
+                                     rings[r].mlive32, aligned, two);
         }
         fft_fast<kFastThreads, float2>(X, T, d, out, htid, mine);
         if (nx >= hi) break;
@@ -1714,7 +1720,7 @@ __global__ __launch_bounds__(kBlueThreads, 4) void k_ring_synth_blue(
     bool two = b + 1 < nmaps;
     FastModes2<kBlueThreads> raw;
     load_fast2<kBlueThreads>(raw, delta + b * dl.map + dl.row(r), dl.mstride(r), minv, mcontig,
-                             rings[r].mlive, aligned, two);
+                             rings[r].mlive32, aligned, two);
     for (bool first = true;; first = false) {
         const RingDesc d = rings[r];
         BlueRing<C> br = blue_ring<C>(d, pool32);
@@ -1726,14 +1732,14 @@ __global__ __launch_bounds__(kBlueThreads, 4) void k_ring_synth_blue(
         FastModes<kBlueThreads, float2> one;
 #pragma unroll
         for (int q = 0; q < QM; ++q) one.v[q] = make_float2(raw.v[q].x, raw.v[q].y);
-        fold_fast<kBlueThreads>(X, d, one, d.mlive);
+        fold_fast<kBlueThreads>(X, d, one, d.mlive32);
         blue_conv<C, kBlueThreads>(X, Y, TW, TB, d, br, kBlueInZ, kBlueOutPix);
         br.out += npix;
         if (twoB) {
 #pragma unroll
             for (int q = 0; q < QM; ++q) one.v[q] = make_float2(raw.v[q].z, raw.v[q].w);
             __syncthreads();   // the first map's last pass has read X and Y
-            fold_fast<kBlueThreads>(X, d, one, d.mlive);
+            fold_fast<kBlueThreads>(X, d, one, d.mlive32);
         }
         const long long nx = it + per;
         if (nx < hi) {
@@ -1742,7 +1748,7 @@ __global__ __launch_bounds__(kBlueThreads, 4) void k_ring_synth_blue(
             b = 2LL * pi;
             two = b + 1 < nmaps;
             load_fast2<kBlueThreads>(raw, delta + b * dl.map + dl.row(r), dl.mstride(r), minv, mcontig,
-                                     rings[r].mlive, aligned, two);
+                                     rings[r].mlive32, aligned, two);
         }
         if (twoB) {
             blue_conv<C, kBlueThreads>(X, Y, TW, TB, d, br, kBlueInZ, kBlueOutPix);
@@ -1886,7 +1892,7 @@ __global__ __launch_bounds__(NT, 4) void k_ring_synth(
     const RingTables rt = {tw, tw + lds.tw_entries};
     synth_ring<NT, MAXN, false, false>(buf, rt, d,
                                pool, delta + b * dl.map + dl.row(r), dl.mstride(r), minv,
-                               mcontig, ring_mmax(d, mfull), map + b * npix + d.start);
+                               mcontig, ring_mmax<DT>(d, mfull), map + b * npix + d.start);
 }
 
 // Batched synthesis: work item (map, ring) of a batch of plans.

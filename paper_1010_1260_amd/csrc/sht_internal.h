@@ -18,7 +18,7 @@ constexpr uint64_t kDeadMagic = 0xdeadbeefdeadbeefull;
 // v * 2^(kScaleStep * k), k <= 0 (Sec. 2.2.2: real-time rescaling).  A value is
 // rescaled when its magnitude exceeds 2^kScaleStep; checks happen every 8
 // steps, over which the normalised recurrence grows by less than 2^140 for
-// l <= 16383, so |v| < 2^652 always.  Values with k <= -2 are below 2^-372.
+// l <= 16383, so |v| < 2^652 always.
 constexpr int kScaleStep = 512;
 
 // Per-ring description for the Fourier kernels (device side).
@@ -37,6 +37,7 @@ struct RingDesc {
                       // chirp, nb and kernel spectrum are those of length clen / 2
     int np;           // synthesis fast path: number of Stockham passes (0: not on it)
     int mlive;        // greatest m with a live row on the ring (live.hip), -1 if none
+    int mlive32;      // the same for the mixed forms' synthesis
     unsigned long long rads;  // their radices (16, 8, 4, 2, 7, 5, 3; product clen),
                               // 5 bits each, pass p at bits 5p..5p+4
 };
@@ -49,13 +50,13 @@ struct PairDesc {
     int rn;       // ring index of the northern member
     int rs;       // ring index of the southern member, -1 if unpaired
     int ilim;     // the m at positions >= ilim of the set are dead on the pair (live.hip)
-    int pad;
+    int ilim32;   // the same for the mixed forms' synthesis
 };
 
 // Where the recurrence of every (m, ring pair) starts (live.hip): the P_lm of
-// an m grow from far below the smallest double, and the terms before a
-// pair's start row are too small to count.  Rows are l - m in units of
-// kLiveRows; a pair with no live row of an m has kNeverLive.
+// an m grow from far below the smallest double, and before a pair's start row
+// they are below anything that its kernel can represent.  Rows are l - m in
+// units of kLiveRows; a pair with no live row of an m has kNeverLive.
 constexpr int kLiveRows = 8;
 constexpr int kNeverLive = 0xffff;
 struct LiveTab {
@@ -64,7 +65,7 @@ struct LiveTab {
     const ushort2 *jr;     // [nm][np / 64] least and greatest start row of 64 pairs
                            // (kNeverLive, 0 if none is live)
     const uint16_t *jq;    // [nm][np / 64] first row from which a |u| of 64 pairs passes
-                           // 2^-32 (kNeverLive: none does)
+                           // 2^-32 (kNeverLive: none does); the mixed forms' table only
     int np;                // ring pairs, rounded up to 512 (the most a wave takes)
     int nb;                // np / 64
 };
@@ -151,7 +152,8 @@ constexpr int kBlueClass = 4;
 // FP64 plans have the same path in complex128, for synthesis and analysis, in
 // classes by convolution length (kBlue64MaxN points, kBlue64Threads threads),
 // so that short rings do not reserve the LDS of long ones: two buffers of
-// 1024, 2048 or 4096 points leave four, two or one workgroup on a CU. One map
+// 1024, 2048 or 4096 points leave four, two or one workgroup on a CU, and a
+// ring whose live modes need more goes a class up (blue64_class). One map
 // at nside 2048, against the size-class kernels: analysis 0.74 to 0.54 ms,
 // synthesis (beside the fast path) 1.1 to 0.58 ms; without the third class
 // the analysis takes 0.62 ms.
@@ -264,6 +266,20 @@ inline void blue_lds_add(RingLds &l, int n, int nb, int mmax, int threads = kBlu
     l.tb_entries = l.tb_entries > tb ? l.tb_entries : tb;
 }
 
+// Class of a complex128 Bluestein ring whose convolution fits class q: the first
+// buffer holds the ring's live modes too, and a ring with more of them than
+// leave the class's four (two) workgroups on a CU goes to the next one, which
+// has the threads for it (its radix list serves any larger class).
+inline int blue64_class(int q, int n, int nb, int mlive)
+{
+    for (; q + 1 < kNumBlue64; ++q) {
+        RingLds l = {};
+        blue_lds_add(l, n, nb, mlive, kBlue64Threads[q]);
+        if (l.total() <= kTogetherEntries << q) break;
+    }
+    return q;
+}
+
 // Grows the fast class layout by one ring of n pixels (n even, fast path)
 // for modes 0..mmax: the padded buffer holds the phased modes, the spectrum
 // (bins 0..n/2), the alias staging of rings with fewer bins than threads and
@@ -364,7 +380,8 @@ struct sht_plan_s {
     long long *d_moff;
     double *d_mu;        // mu_m for each m of the set (Eq. pmm)
     double *d_A;         // [nalm] normalised recurrence coefficient, see legendre.hip
-    sht::LiveTab live;   // recurrence start of every (m, ring pair)
+    sht::LiveTab live;   // recurrence start of every (m, ring pair), FP64 kernels
+    sht::LiveTab live32; // the same for the mixed forms' Legendre kernels (their plans only)
     double *d_cn;        // [nalm] normalisation c_lm folded into the coefficients
     int32_t *d_minv;     // [mmax + 1] index of m in the set, -1 if absent
     long long *d_boff;   // [nm] first 32-step block of each m (split-BF16 operand packing)
@@ -418,11 +435,10 @@ namespace sht {
 // the entry point's own launches.
 inline void clear_stale_error() { (void)hipGetLastError(); }
 
-// Plan time (live.hip): fills the start table of the plan (d_pairs, d_mval,
-// d_moff, d_mu and d_A uploaded), the pairs' ilim and the rings' mlive.
-// `scratch`: nm doubles on the device, free again once `st` has drained;
-// `pmax`: the pair with the largest sin(theta).
-hipError_t launch_live_table(const sht_plan_s *p, double *scratch, int pmax, hipStream_t st);
+// Plan time (live.hip): fills a start table of the plan (d_pairs, d_mval,
+// d_moff, d_mu and d_A uploaded), the pairs' ilim and the rings' mlive; f32:
+// the mixed forms' one, ilim32 and mlive32.
+hipError_t launch_live_table(const sht_plan_s *p, const LiveTab &t, bool f32, hipStream_t st);
 
 // Launchers (legendre.hip / ringfft.hip).  All enqueue on `st` only.
 hipError_t launch_prescale(const sht_plan_s *p, const double *alm, double2 *ap, hipStream_t st);

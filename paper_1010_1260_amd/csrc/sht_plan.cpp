@@ -230,7 +230,9 @@ void free_tables(sht_plan_s *p)
                     p->d_minv, p->d_rings, p->d_crings, p->d_pool, p->d_boff, p->d_boff16, p->d_bm16,
                     p->d_bm32, p->d_soff, p->d_sbm, p->d_Asb, p->d_pool32,
                     const_cast<double2 *>(p->live.st), const_cast<uint16_t *>(p->live.je),
-                    const_cast<ushort2 *>(p->live.jr), const_cast<uint16_t *>(p->live.jq)};
+                    const_cast<ushort2 *>(p->live.jr), const_cast<double2 *>(p->live32.st),
+                    const_cast<uint16_t *>(p->live32.je), const_cast<ushort2 *>(p->live32.jr),
+                    const_cast<uint16_t *>(p->live32.jq)};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
     for (int c = 0; c < sht::kNumSynthClasses; ++c) {
@@ -249,30 +251,25 @@ void free_tables(sht_plan_s *p)
     p->d_pool = nullptr; p->d_boff = nullptr; p->d_boff16 = nullptr; p->d_bm16 = nullptr;
     p->d_bm32 = nullptr; p->d_soff = nullptr; p->d_sbm = nullptr; p->d_Asb = nullptr;
     p->d_pool32 = nullptr;
-    p->live = sht::LiveTab{};
+    p->live = p->live32 = sht::LiveTab{};
 }
 
-// Device memory of the start table, then its kernels (live.hip).
-sht_status build_live_table(sht_plan_s *p, const std::vector<PairDesc> &pairs, size_t *acc)
+// Device memory of a start table, then its kernels (live.hip).
+sht_status build_live_table(sht_plan_s *p, sht::LiveTab &t, bool f32, size_t *acc)
 {
-    int pmax = 0;
-    for (int i = 1; i < p->npairs; ++i)
-        if (pairs[i].s > pairs[pmax].s) pmax = i;
-    sht::LiveTab &t = p->live;
     t.np = (int)align_up((size_t)p->npairs, 512);
     t.nb = t.np / 64;
     const size_t n = (size_t)p->nm * (size_t)t.np, nj = (size_t)p->nm * (size_t)t.nb;
-    double *scratch = nullptr;
     if (hipMalloc((void **)&t.st, n * sizeof *t.st) != hipSuccess) { t.st = nullptr; return SHT_ERR_OOM; }
     if (hipMalloc((void **)&t.je, n * sizeof *t.je) != hipSuccess) { t.je = nullptr; return SHT_ERR_OOM; }
     if (hipMalloc((void **)&t.jr, nj * sizeof *t.jr) != hipSuccess) { t.jr = nullptr; return SHT_ERR_OOM; }
-    if (hipMalloc((void **)&t.jq, nj * sizeof *t.jq) != hipSuccess) { t.jq = nullptr; return SHT_ERR_OOM; }
-    if (hipMalloc((void **)&scratch, (size_t)p->nm * sizeof(double)) != hipSuccess)
-        return SHT_ERR_OOM;
-    *acc += n * (sizeof *t.st + sizeof *t.je) + nj * (sizeof *t.jr + sizeof *t.jq);
-    const bool ok = sht::launch_live_table(p, scratch, pmax, nullptr) == hipSuccess &&
+    *acc += n * (sizeof *t.st + sizeof *t.je) + nj * sizeof *t.jr;
+    if (f32) {
+        if (hipMalloc((void **)&t.jq, nj * sizeof *t.jq) != hipSuccess) { t.jq = nullptr; return SHT_ERR_OOM; }
+        *acc += nj * sizeof *t.jq;
+    }
+    const bool ok = sht::launch_live_table(p, t, f32, nullptr) == hipSuccess &&
                     hipDeviceSynchronize() == hipSuccess;
-    (void)hipFree(scratch);
     return ok ? SHT_OK : SHT_ERR_HIP;
 }
 
@@ -782,7 +779,8 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
         if (st == SHT_OK) st = upload(&p->d_Asb, Asb, &tb);
     }
     if (st == SHT_OK) st = upload(&p->d_rings, rings, &tb);
-    if (st == SHT_OK) st = build_live_table(p, pairs, &tb);
+    if (st == SHT_OK) st = build_live_table(p, p->live, false, &tb);
+    if (st == SHT_OK && delta_f32(p)) st = build_live_table(p, p->live32, true, &tb);
     if (st == SHT_OK &&
         hipMemcpy(rings.data(), p->d_rings, rings.size() * sizeof(RingDesc),
                   hipMemcpyDeviceToHost) != hipSuccess)
@@ -790,11 +788,14 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
     p->ring_mlive.resize(R);
     for (int r = 0; r < R; ++r) {
         crings[r].mlive = p->ring_mlive[r] = rings[r].mlive;
-        const int q = ring_sclass[r] - sht::kBlue64Class;
+        crings[r].mlive32 = rings[r].mlive32;
+        int q = ring_sclass[r] - sht::kBlue64Class;
         if (q < 0) continue;
         const RingDesc &g = rings[r];
         const int c = ring_bclass[r];   // size class of the ring
         if (sht::blue64_holds(g.mlive)) {
+            q = sht::blue64_class(q, g.n, g.nb, g.mlive);
+            ring_sclass[r] = sht::kBlue64Class + q;
             sht::blue_lds_add(sclass_lds[ring_sclass[r]], g.n, g.nb, g.mlive,
                               sht::kBlue64Threads[q]);
             sht::ring_lds_add(bclass_lds[c], c, g.n, p->ring_cnb[r], p->ring_need[r]);

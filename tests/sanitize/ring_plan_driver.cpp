@@ -48,6 +48,13 @@ static int blue64_classes()
                     CHECK(l.fft_entries > sht::fast_pad(nt - 1));
                     CHECK(l.y_entries > sht::fast_pad(nb - 1));
                     sht::blue_lds_add(cls, 2 * h, nb, mlive, nt);
+                    // the class it ends in has the threads and the room
+                    const int e = sht::blue64_class(q, 2 * h, nb, mlive);
+                    CHECK(e >= q && e < sht::kNumBlue64);
+                    sht::RingLds m = {};
+                    sht::blue_lds_add(m, 2 * h, nb, mlive, sht::kBlue64Threads[e]);
+                    CHECK(e == sht::kNumBlue64 - 1 || m.total() <= sht::kTogetherEntries << e);
+                    CHECK(nb <= sht::kBlue64MaxN[e] && sht::kBlue64Threads[e] >= nt);
                 }
             }
         }
