@@ -162,6 +162,9 @@ sht_status sht_plan_batch(sht_batch_t *out, const sht_plan_t *plans, int32_t n)
         off = align_up(off + (size_t)p->nalm * sizeof(double2), 256);
         m.delta_off = (long long)off;
         off = align_up(off + (size_t)p->nrings * (size_t)p->nm * sizeof(double2), 256);
+        m.nbad = (int)((p->nalm + 255) / 256);
+        m.bad_off = (long long)off;
+        off = align_up(off + (size_t)m.nbad, 256);
         m.lmax = p->lmax; m.mmax = p->mmax; m.nm = p->nm; m.nrings = p->nrings;
         m.npairs = p->npairs; m.mcontig = p->mcontig;
         m.m0len = (p->mval[0] == 0) ? p->lmax + 1 : 0;

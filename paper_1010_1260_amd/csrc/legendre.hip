@@ -41,27 +41,59 @@
 namespace sht {
 namespace {
 
+// Infinite and NaN inputs.  A coefficient that is one makes its map so on every
+// ring, and a pixel every coefficient, as a sum over all terms does; the start
+// table leaves terms out.  So the prescale notes which blocks of coefficients
+// hold one, and the wave that has the set's first m, which no ring leaves out
+// (PairDesc::ilim), adds it to that m's Delta.  The adjoint's first m of a ring
+// is NaN with any pixel of it: the wave that has that m notes it for its ring
+// block, and the block sum adds it to every coefficient.
+
+__host__ __device__ inline long long bad_stride(int nbad) { return (nbad + 15LL) / 16 * 16; }
+
+// The wave's NB flags to a workgroup's one byte.
+template <int NB>
+__device__ inline void store_bad(unsigned f, unsigned char *__restrict__ to)
+{
+    __shared__ unsigned any;
+    if (threadIdx.x == 0) any = 0;
+    __syncthreads();
+    unsigned w = 0;
+#pragma unroll
+    for (int b = 0; b < NB; ++b) w |= __ballot(f >> b & 1u) ? 1u << b : 0u;
+    if (w && (threadIdx.x & 63) == 0) atomicOr(&any, w);
+    __syncthreads();
+    if (threadIdx.x == 0) *to = (unsigned char)any;
+}
+
 // a'_lm = c_lm a_lm of NB maps, interleaved [lm][map] for the waves that take
-// the NB maps together.
+// the NB maps together.  bad[k] (if given; the groups of maps bad_stride(nbad)
+// apart): bit b is set if any of block k's 256 a'_lm of map b is infinite or NaN.
 template <int NB>
 __global__ __launch_bounds__(256) void k_prescale(const double2 *__restrict__ alm,
                                                   const double *__restrict__ cn,
                                                   double2 *__restrict__ ap, long long nalm,
-                                                  long long m0len)
+                                                  long long m0len, int nbad,
+                                                  unsigned char *__restrict__ bad)
 {
     const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     const long long g = (long long)blockIdx.y * NB;
-    if (e >= nalm) return;
-    const double c = cn[e];
-    double2 a[NB];
+    unsigned f = 0;
+    if (e < nalm) {
+        const double c = cn[e];
+        double2 a[NB];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) a[b] = alm[(g + b) * nalm + e];
+        for (int b = 0; b < NB; ++b) a[b] = alm[(g + b) * nalm + e];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-        a[b].x *= c;
-        a[b].y = (e < m0len) ? 0.0 : a[b].y * c;
-        ap[g * nalm + e * NB + b] = a[b];
+        for (int b = 0; b < NB; ++b) {
+            a[b].x *= c;
+            a[b].y = (e < m0len) ? 0.0 : a[b].y * c;
+            ap[g * nalm + e * NB + b] = a[b];
+            f |= (isfinite(a[b].x) && isfinite(a[b].y)) ? 0u : 1u << b;
+        }
     }
+    if (!bad) return;
+    store_bad<NB>(f, bad + blockIdx.y * bad_stride(nbad) + blockIdx.x);
 }
 
 template <int CH>
@@ -110,9 +142,11 @@ template <int CH, int NB>
 __device__ inline void fwd_one_m(const Chains<CH> &g, const LiveTab &lt, int blk0, int m, int i,
                                  long long off, int lmax, const double *__restrict__ A,
                                  const double2 *__restrict__ ap, double2 *__restrict__ delta,
-                                 const DeltaLayout &dl, bool full)
+                                 const DeltaLayout &dl, bool full, int nbad,
+                                 const unsigned char *__restrict__ bad)
 {
     constexpr int KR = NB == 1 ? 4 : 2;   // two chunks fit the scalar registers
+    const int lane = (int)threadIdx.x;
     const int len = lmax - m + 1;
     const CDp Am = (CDp)(A + off);
     const CDp am = (CDp)(ap + off * NB);   // (re, im) pairs
@@ -126,6 +160,28 @@ __device__ inline void fwd_one_m(const Chains<CH> &g, const LiveTab &lt, int blk
             lo = min(lo, v & 0xffff);
             hi = max(hi, (int)((unsigned)v >> 16));
         }
+    }
+    // the maps with an infinite or NaN coefficient: any, with the set's first m;
+    // or, where every m is written, those in the rows of this m that are not
+    // read below
+    unsigned f = 0;
+    if (full) {
+        for (int j = lane; j < min(lo * kLiveRows, len); j += 64)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const double2 v = ap[(off + j) * NB + b];
+                f |= (isfinite(v.x) && isfinite(v.y)) ? 0u : 1u << b;
+            }
+    } else if (i == 0) {
+        // 16 flags a load: the walk is on the critical path of a few waves
+        const uint4 *b16 = reinterpret_cast<const uint4 *>(bad);
+        for (int k = lane; k < nbad / 16; k += 64) {
+            const uint4 v = b16[k];
+            f |= v.x | v.y | v.z | v.w;
+        }
+        if (lane < nbad % 16) f |= bad[nbad - 1 - lane];
+        f |= f >> 16;
+        f |= f >> 8;
     }
     double Er[CH][NB], Ei[CH][NB], Or[CH][NB], Oi[CH][NB];
 #pragma unroll
@@ -224,6 +280,14 @@ __device__ inline void fwd_one_m(const Chains<CH> &g, const LiveTab &lt, int blk
             }
         }
     }
+    if (full || i == 0) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+            if (__ballot(f >> b & 1u)) {
+#pragma unroll
+                for (int c = 0; c < CH; ++c) Er[c][b] = Ei[c][b] = __builtin_nan("");
+            }
+    }
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
         if (!full && i >= g.ilim[c]) continue;
@@ -246,7 +310,8 @@ __global__ __launch_bounds__(64) void k_legendre_fwd(
     const PairDesc *__restrict__ pairs, LiveTab lt, int pblocks,
     const int *__restrict__ mval, const long long *__restrict__ moff, int nm, int nmpairs,
     int lmax, const double *__restrict__ A, const double2 *__restrict__ ap, long long nalm,
-    double2 *__restrict__ delta, DeltaLayout dl, int ngroups, int full)
+    double2 *__restrict__ delta, DeltaLayout dl, int ngroups, int full, int nbad,
+    const unsigned char *__restrict__ bad)
 {
     // XCD x takes the m-pairs q = x mod 8, one after the other for all ring
     // blocks of all maps: the waves that share an m-pair's coefficients run
@@ -267,7 +332,8 @@ __global__ __launch_bounds__(64) void k_legendre_fwd(
         const int i = (t == 0) ? q : nm - 1 - q;
         if (t == 1 && i == q) break;
         fwd_one_m<CH, NB>(g, lt, pb * CH, ((CIp)mval)[i], i, ((CLp)moff)[i], lmax, A, apb,
-                          delta + b * dl.map, dl, full != 0);
+                          delta + b * dl.map, dl, full != 0, nbad,
+                          bad + (rest % ngroups) * bad_stride(nbad));
     }
 }
 
@@ -360,14 +426,15 @@ __device__ inline void adj_one_m(const PairDesc *__restrict__ pairs, const LiveT
                                  int blk0, int m, int i, long long off,
                                  int lmax, const double *__restrict__ A,
                                  const double2 *__restrict__ dt, const DeltaLayout &dl,
-                                 double2 *__restrict__ part, double2 (*st)[64])
+                                 double2 *__restrict__ part, double2 (*st)[64],
+                                 int *__restrict__ bad)
 {
     const int len = lmax - m + 1;
     const int lane = threadIdx.x;
     const CIp jr = (CIp)(lt.jr + (long long)i * lt.nb);
     const CDp Am = (CDp)(A + off);
     int j0 = adj_first_row<CH>(jr, blk0);
-    if (j0 >= len) return;
+    if (j0 >= len && !bad) return;
     int lo[CH], hi[CH];    // rows where the block's pairs start
     int je[CH];
     double x[CH], u0[CH], u1[CH];
@@ -394,6 +461,18 @@ __device__ inline void adj_one_m(const PairDesc *__restrict__ pairs, const LiveT
         const int rn = max(d[c].rn, 0), rs = d[c].rs >= 0 ? d[c].rs : rn;
         wn[c] = dt[dl.row(rn) + i * dl.mstride(rn)];
         ws[c] = dt[dl.row(rs) + i * dl.mstride(rs)];
+    }
+    if (bad) {   // the dead ones too
+        bool f = false;
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            const bool fin = isfinite(wn[c].x) && isfinite(wn[c].y) && isfinite(ws[c].x) &&
+                             isfinite(ws[c].y);
+            f = f || (d[c].rn >= 0 && !fin);
+        }
+        const int any = __ballot(f) != 0;
+        if (lane == 0) *bad = any;
+        if (j0 >= len) return;
     }
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
@@ -456,7 +535,7 @@ __global__ __launch_bounds__(64, CH == 8 ? 2 : CH == 1 ? 4 : 3) void k_legendre_
     const PairDesc *__restrict__ pairs, LiveTab lt, int pblocks,
     const int *__restrict__ mval, const long long *__restrict__ moff, int nm, int nmpairs,
     int lmax, const double *__restrict__ A, const double2 *__restrict__ dt, DeltaLayout dl,
-    double2 *__restrict__ part, long long nalm, int nmaps)
+    double2 *__restrict__ part, long long nalm, int nmaps, int badm, int *__restrict__ bad)
 {
     __shared__ double2 st[CH][64];
     // the same walk as the forward kernel's
@@ -472,7 +551,8 @@ __global__ __launch_bounds__(64, CH == 8 ? 2 : CH == 1 ? 4 : 3) void k_legendre_
         const int i = (t == 0) ? q : nm - 1 - q;
         if (t == 1 && i == q) break;
         adj_one_m<CH>(pairs, lt, pb * CH, ((CIp)mval)[i], i, ((CLp)moff)[i], lmax, A,
-                      dt + b * dl.map, dl, pp, st);
+                      dt + b * dl.map, dl, pp, st,
+                      i < badm ? bad + ((long long)b * pblocks + pb) * badm + i : nullptr);
     }
 }
 
@@ -482,7 +562,8 @@ template <int CH>
 __global__ __launch_bounds__(256) void k_adj_reduce(
     const double2 *__restrict__ part, const double *__restrict__ cn, LiveTab lt,
     const int *__restrict__ mval, const long long *__restrict__ moff, int lmax,
-    double *__restrict__ alm, long long nalm, int pblocks, int accumulate)
+    double *__restrict__ alm, long long nalm, int pblocks, int accumulate, int badm,
+    const int *__restrict__ bad)
 {
     const int i = blockIdx.y;
     const long long b = blockIdx.z;
@@ -491,7 +572,12 @@ __global__ __launch_bounds__(256) void k_adj_reduce(
     if (j >= lmax - m + 1) return;
     const CIp jr = (CIp)(lt.jr + (long long)i * lt.nb);
     const long long e = moff[i] + j;
-    double sr = 0.0, si = 0.0;
+    // NaN if a ring of any block has an infinite or NaN Delta~ of this m (a
+    // caller's), or of the set's first one (the analysis')
+    const CIp bi = (CIp)(bad + b * pblocks * badm + (badm > 1 ? i : 0));
+    int f = 0;
+    for (int k = 0; k < pblocks; ++k) f |= bi[k * badm];
+    double sr = f ? __builtin_nan("") : 0.0, si = sr;
     const double2 *p = part + b * pblocks * nalm + e;
     for (int k = 0; k < pblocks; ++k) {
         if (j >= adj_first_row<CH>(jr, k * CH)) {
@@ -523,18 +609,24 @@ __global__ __launch_bounds__(256) void k_adj_reduce(
 
 __global__ void k_batch_reset(int *counter) { *counter = 0; }
 
-__global__ void k_batch_prescale(const BatchMap *__restrict__ maps,
-                                 const double *const *__restrict__ alms, char *__restrict__ ws)
+__global__ __launch_bounds__(256) void k_batch_prescale(
+    const BatchMap *__restrict__ maps, const double *const *__restrict__ alms,
+    char *__restrict__ ws)
 {
     const BatchMap &bm = maps[blockIdx.y];
+    if ((int)blockIdx.x >= bm.nbad) return;
     const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= bm.nalm) return;
-    const double2 *a = reinterpret_cast<const double2 *>(alms[blockIdx.y]);
-    double2 v = a[e];
-    const double c = bm.cn[e];
-    v.x *= c;
-    v.y = (e < bm.m0len) ? 0.0 : v.y * c;
-    reinterpret_cast<double2 *>(ws + bm.ap_off)[e] = v;
+    unsigned f = 0;
+    if (e < bm.nalm) {
+        const double2 *a = reinterpret_cast<const double2 *>(alms[blockIdx.y]);
+        double2 v = a[e];
+        const double c = bm.cn[e];
+        v.x *= c;
+        v.y = (e < bm.m0len) ? 0.0 : v.y * c;
+        reinterpret_cast<double2 *>(ws + bm.ap_off)[e] = v;
+        f = (isfinite(v.x) && isfinite(v.y)) ? 0u : 1u;
+    }
+    store_bad<1>(f, reinterpret_cast<unsigned char *>(ws + bm.bad_off) + blockIdx.x);
 }
 
 template <int CH>
@@ -564,7 +656,8 @@ __global__ __launch_bounds__(64) void k_legendre_fwd_batch(const BatchTile *__re
             const int i = (u == 0) ? q : bm.nm - 1 - q;
             if (u == 1 && i == q) break;
             fwd_one_m<CH, 1>(g, bm.live, tile.pblock * CH, ((CIp)bm.mval)[i], i,
-                             ((CLp)bm.moff)[i], bm.lmax, bm.A, ap, delta, bm.dl, false);
+                             ((CLp)bm.moff)[i], bm.lmax, bm.A, ap, delta, bm.dl, false, bm.nbad,
+                             reinterpret_cast<const unsigned char *>(ws + bm.bad_off));
         }
     }
 }
@@ -591,14 +684,25 @@ static hipError_t for_map_groups(const sht_plan_s *p, const F &f)
     return e;
 }
 
-hipError_t launch_prescale(const sht_plan_s *p, const double *alm, double2 *ap, hipStream_t st)
+// Blocks of 256 coefficients, and the bytes that note the infinite and NaN ones of
+// every group of maps.
+static int bad_blocks(const sht_plan_s *p) { return (int)((p->nalm + 255) / 256); }
+size_t fwd_bad_bytes(const sht_plan_s *p)
+{
+    return p->precision == SHT_FP64 ? (size_t)p->nmaps * (size_t)bad_stride(bad_blocks(p)) : 0;
+}
+
+hipError_t launch_prescale(const sht_plan_s *p, const double *alm, double2 *ap,
+                           unsigned char *bad, hipStream_t st)
 {
     const long long m0len = (p->mval[0] == 0) ? (p->lmax + 1) : 0;
+    const int nbad = bad_blocks(p);
     return for_map_groups(p, [&](int first, int groups, auto nb) {
-        dim3 grid((unsigned)((p->nalm + 255) / 256), (unsigned)groups);
+        dim3 grid((unsigned)nbad, (unsigned)groups);
         hipLaunchKernelGGL(k_prescale<decltype(nb)::value>, grid, dim3(256), 0, st,
                            reinterpret_cast<const double2 *>(alm) + first * p->nalm, p->d_cn,
-                           ap + first * p->nalm, p->nalm, m0len);
+                           ap + first * p->nalm, p->nalm, m0len, nbad,
+                           bad ? bad + first * bad_stride(nbad) : nullptr);
         return hipGetLastError();
     });
 }
@@ -623,8 +727,8 @@ static auto fwd_kernel(int chains) -> decltype(&k_legendre_fwd<1, NB>)
                          : nullptr;
 }
 
-hipError_t launch_legendre_fwd(const sht_plan_s *p, const double2 *ap, double2 *delta, bool full,
-                               hipStream_t st)
+hipError_t launch_legendre_fwd(const sht_plan_s *p, const double2 *ap, const unsigned char *bad,
+                               double2 *delta, bool full, hipStream_t st)
 {
     const int pblocks = fwd_pblocks(p);
     const int nmpairs = (p->nm + 1) / 2;
@@ -637,44 +741,53 @@ hipError_t launch_legendre_fwd(const sht_plan_s *p, const double2 *ap, double2 *
         hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(64), 0, st, p->d_pairs, p->live,
                            pblocks, p->d_mval, p->d_moff, p->nm, nmpairs, p->lmax, p->d_A,
                            ap + first * p->nalm, p->nalm,
-                           delta + first * dl.map, dl, groups, full ? 1 : 0);
+                           delta + first * dl.map, dl, groups, full ? 1 : 0, bad_blocks(p),
+                           bad ? bad + first * bad_stride(bad_blocks(p)) : nullptr);
         return hipGetLastError();
     });
 }
 
+static size_t adj_sums(const sht_plan_s *p)
+{
+    return (size_t)p->nmaps * (size_t)adj_pblocks(p) * (size_t)p->nalm;
+}
+// the sums of the ring blocks, then one flag per (map, ring block, m)
 size_t adj_part_bytes(const sht_plan_s *p)
 {
-    return (size_t)p->nmaps * (size_t)adj_pblocks(p) * (size_t)p->nalm * sizeof(double2);
+    return adj_sums(p) * sizeof(double2) +
+           (size_t)p->nmaps * (size_t)adj_pblocks(p) * (size_t)p->nm * sizeof(int);
 }
 
 template <int CH>
-static hipError_t adj_launch(const sht_plan_s *p, const double2 *dt, const DeltaLayout &dl,
-                             double2 *part, double *alm, hipStream_t st, bool accumulate)
+static hipError_t adj_launch(const sht_plan_s *p, const double2 *dt, bool plain, double2 *part,
+                             double *alm, hipStream_t st, bool accumulate)
 {
+    const DeltaLayout dl = plain ? delta_plain(p->nm, p->nrings) : delta_blocked(p->nm, p->nrings);
+    const int badm = plain ? p->nm : 1;   // flags per ring block: of every m, or of the first
+    int *bad = reinterpret_cast<int *>(part + adj_sums(p));
     const int pblocks = adj_pblocks(p);
     const int nmpairs = (p->nm + 1) / 2;
     const long long total = 8LL * ((nmpairs + 7) / 8) * pblocks * p->nmaps;
     if (total <= 0 || total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     hipLaunchKernelGGL(k_legendre_adj<CH>, dim3((unsigned)total), dim3(64), 0, st, p->d_pairs,
                        p->live, pblocks, p->d_mval, p->d_moff, p->nm, nmpairs, p->lmax,
-                       p->d_A, dt, dl, part, p->nalm, p->nmaps);
+                       p->d_A, dt, dl, part, p->nalm, p->nmaps, badm, bad);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int longest = p->lmax - p->mval[0] + 1;
     dim3 grid((unsigned)((longest + 255) / 256), (unsigned)p->nm, (unsigned)p->nmaps);
     hipLaunchKernelGGL(k_adj_reduce<CH>, grid, dim3(256), 0, st, part, p->d_cn, p->live, p->d_mval,
-                       p->d_moff, p->lmax, alm, p->nalm, pblocks, accumulate ? 1 : 0);
+                       p->d_moff, p->lmax, alm, p->nalm, pblocks, accumulate ? 1 : 0, badm, bad);
     return hipGetLastError();
 }
 
 hipError_t launch_legendre_adj_ws(const sht_plan_s *p, const double2 *dt, bool plain,
                                   double2 *part, double *alm, hipStream_t st, bool accumulate)
 {
-    const DeltaLayout dl = plain ? delta_plain(p->nm, p->nrings) : delta_blocked(p->nm, p->nrings);
     switch (p->adj_chains) {
-    case 1: return adj_launch<1>(p, dt, dl, part, alm, st, accumulate);
-    case 2: return adj_launch<2>(p, dt, dl, part, alm, st, accumulate);
-    case 8: return adj_launch<8>(p, dt, dl, part, alm, st, accumulate);
+    case 1: return adj_launch<1>(p, dt, plain, part, alm, st, accumulate);
+    case 2: return adj_launch<2>(p, dt, plain, part, alm, st, accumulate);
+    case 8: return adj_launch<8>(p, dt, plain, part, alm, st, accumulate);
     default: return hipErrorInvalidValue;
     }
 }

@@ -6,7 +6,11 @@
 
 // The workspace of sht_alm2map_noalloc.  In host code the name is a stand-in
 // only: its device address comes from hipGetSymbolAddress, once per device.
-static __device__ __align__(256) unsigned char scratch[SHT_NOALLOC_SCRATCH_BYTES];
+// It has room beside the documented size for the flags of the infinite and NaN
+// coefficients (16 bytes per map and one per 256 coefficients of 16 bytes), so
+// that they refuse no plan of fewer than some 10^5 maps.
+constexpr size_t kFlagRoom = SHT_NOALLOC_SCRATCH_BYTES / 32;
+static __device__ __align__(256) unsigned char scratch[SHT_NOALLOC_SCRATCH_BYTES + kFlagRoom];
 
 namespace {
 
@@ -35,7 +39,9 @@ extern "C" sht_status sht_alm2map_noalloc(sht_plan_t p, const double *alm, doubl
     sht_status s = sht::check_plan_device(p);
     if (s != SHT_OK) return s;
     if (!alm || !map) return SHT_ERR_INVALID_ARG;
-    if (sht::forward_workspace(p) > (size_t)SHT_NOALLOC_SCRATCH_BYTES) return SHT_ERR_WORKSPACE;
+    if (sht::forward_workspace(p) - p->ws_bad_bytes > (size_t)SHT_NOALLOC_SCRATCH_BYTES ||
+        sht::forward_workspace(p) > sizeof scratch)
+        return SHT_ERR_WORKSPACE;
     if (p->device < 0 || p->device >= kMaxDevices) return SHT_ERR_UNSUPPORTED;
     void *ws = scratch_on(p->device);
     if (!ws) return SHT_ERR_HIP;

@@ -49,7 +49,8 @@ struct PairDesc {
     double s;     // sin(theta)
     int rn;       // ring index of the northern member
     int rs;       // ring index of the southern member, -1 if unpaired
-    int ilim;     // the m at positions >= ilim of the set are dead on the pair (live.hip)
+    int ilim;     // the m at positions >= ilim of the set are dead on the pair (live.hip);
+                  // at least 1: the first m of the set is always transformed
     int ilim32;   // the same for the mixed forms' synthesis
 };
 
@@ -350,7 +351,8 @@ struct BatchMap {
     long long nalm;
     long long ap_off;     // prescaled coefficients (double2 [nalm]) in the workspace
     long long delta_off;  // Delta (complex128, layout dl) in the workspace
-    int lmax, mmax, nm, nrings, npairs, mcontig, m0len, pad;
+    long long bad_off;    // flags of the blocks of 256 coefficients, nbad bytes
+    int lmax, mmax, nm, nrings, npairs, mcontig, m0len, nbad;
 };
 
 // A tile of the persistent Legendre launch: map, m-pair, ring-pair block.
@@ -418,6 +420,7 @@ struct sht_plan_s {
     int fwd_group;       // maps that a wave of it takes together (1..4)
     int num_cus;         // compute units of the plan's device
     size_t ws_ap_bytes;  // workspace: prescaled coefficients
+    size_t ws_bad_bytes; // workspace, after Delta: which of them are infinite or NaN
     // the fast-path synthesis of large plans runs on aux_stream beside the
     // size-class kernels on the caller's stream (fork / join by the events)
     hipStream_t aux_stream;
@@ -441,12 +444,15 @@ inline void clear_stale_error() { (void)hipGetLastError(); }
 hipError_t launch_live_table(const sht_plan_s *p, const LiveTab &t, bool f32, hipStream_t st);
 
 // Launchers (legendre.hip / ringfft.hip).  All enqueue on `st` only.
-hipError_t launch_prescale(const sht_plan_s *p, const double *alm, double2 *ap, hipStream_t st);
+// bad: fwd_bad_bytes(p) of flags that the Legendre stage reads; none with `full`.
+size_t fwd_bad_bytes(const sht_plan_s *p);
+hipError_t launch_prescale(const sht_plan_s *p, const double *alm, double2 *ap,
+                           unsigned char *bad, hipStream_t st);
 // full: Delta is a caller's: [map][m][ring], and every entry is written, also
 // those of the m that are dead on a ring, which the ring synthesis of the same
 // plan does not read.
-hipError_t launch_legendre_fwd(const sht_plan_s *p, const double2 *ap, double2 *delta, bool full,
-                               hipStream_t st);
+hipError_t launch_legendre_fwd(const sht_plan_s *p, const double2 *ap, const unsigned char *bad,
+                               double2 *delta, bool full, hipStream_t st);
 int fwd_pblocks(const sht_plan_s *p);
 // plain: dt is a caller's [map][m][ring], otherwise the analysis' own layout
 hipError_t launch_legendre_adj_ws(const sht_plan_s *p, const double2 *dt, bool plain,

@@ -398,10 +398,12 @@ static sht_status legendre_stage(sht_plan_t p, const double *alm, void *ws, void
         if (e == hipSuccess && ev_mid) e = hipEventRecord(ev_mid, st);
         if (e == hipSuccess) e = sht::launch_legendre_mfma_f16x2(p, ws, d32, full, st);
     } else {
-        e = sht::launch_prescale(p, alm, (double2 *)ws, st);
+        unsigned char *bad =
+            full ? nullptr : (unsigned char *)ws + p->ws_ap_bytes + p->ws_delta_bytes;
+        e = sht::launch_prescale(p, alm, (double2 *)ws, bad, st);
         if (e == hipSuccess && ev_mid) e = hipEventRecord(ev_mid, st);
         if (e == hipSuccess)
-            e = sht::launch_legendre_fwd(p, (const double2 *)ws, (double2 *)delta, full, st);
+            e = sht::launch_legendre_fwd(p, (const double2 *)ws, bad, (double2 *)delta, full, st);
     }
     return e == hipSuccess ? SHT_OK : SHT_ERR_HIP;
 }
@@ -664,11 +666,11 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
                 const int rs = it->second.back();
                 it->second.pop_back();
                 used[r] = used[rs] = 1;
-                pairs.push_back({d->cth[r], d->sth[r], r, rs, 0, 0});
+                pairs.push_back({d->cth[r], d->sth[r], r, rs, 1, 0});
             }
         }
         for (int r = 0; r < R; ++r)
-            if (!used[r]) pairs.push_back({d->cth[r], d->sth[r], r, -1, 0, 0});
+            if (!used[r]) pairs.push_back({d->cth[r], d->sth[r], r, -1, 1, 0});
     }
     p->npairs = (int)pairs.size();
 
@@ -887,6 +889,7 @@ sht_status sht_plan(sht_plan_t *out, const sht_geometry_desc *d)
     p->ws_delta_bytes = align_up((size_t)p->nmaps * (size_t)R * (size_t)p->nm *
                                      (delta_f32(p) ? sizeof(float2) : sizeof(double2)),
                                  256);
+    p->ws_bad_bytes = align_up(sht::fwd_bad_bytes(p), 256);
     p->fwd_chains = default_fwd_chains(p);
     p->fwd_group = default_fwd_group(p);
     p->adj_chains = default_adj_chains(p);
@@ -959,7 +962,7 @@ sht_status sht_plan_destroy(sht_plan_t p)
 // Delta~ and the per-ring-block partial sums, which dominate for many maps.
 static size_t fwd_workspace_bytes(const sht_plan_s *p)
 {
-    return p->ws_ap_bytes + p->ws_delta_bytes;
+    return p->ws_ap_bytes + p->ws_delta_bytes + p->ws_bad_bytes;
 }
 
 static size_t workspace_bytes(const sht_plan_s *p)
