@@ -574,9 +574,8 @@ template <> struct RingMajor<float2> {
     static constexpr bool value = true;
 };
 
-// Delta_m for mode m of a ring (zero for m outside the set); Delta is laid
-// out [m][ring], so the ring's modes are `dstride` entries apart.  DT is the
-// stored element: complex128, or complex64 from the mixed-precision
+// Delta_m for mode m of a ring (zero for m outside the set); the ring's modes
+// are `dstride` entries apart (DeltaLayout).  DT is the stored element: complex128, or complex64 from the mixed-precision
 // Legendre stage (widened exactly).
 __device__ inline double2 widen(double2 v) { return v; }
 __device__ inline double2 widen(float2 v) { return make_double2((double)v.x, (double)v.y); }
@@ -1089,17 +1088,15 @@ __device__ __attribute__((always_inline)) inline void synth_fast(C *buf, C *T,
     fft_fast<NT, C>(buf, T, d, out, threadIdx.x, true);
 }
 
-// The Stockham passes of a fast-path ring (after the fold) and the pixel
-// stores of the last one.
 // DFT with positive sign of the h <= kDirectMax points buf[0..h - 1], in
 // place, by direct sums: four threads per output take every fourth term, and
 // their sums are added in a fixed order.  T: the 2h-th roots.  The buffer
 // holds at least NT entries.  Ends with a barrier.
-template <int NT, typename C>
-__device__ __attribute__((noinline)) void direct_dft(C *buf, const C *T, int h)
+template <int NT>
+__device__ __attribute__((noinline)) void direct_dft(double2 *buf, const double2 *T, int h)
 {
     const int tid = threadIdx.x, j = tid % kDirectMax, g = tid / kDirectMax;
-    C acc = cplx<C>(0.0, 0.0);
+    double2 acc = make_double2(0.0, 0.0);
     if (j < h && g < 4) {
         int t = (j * g) % h;
         const int step = (4 * j) % h;
@@ -1113,13 +1110,15 @@ __device__ __attribute__((noinline)) void direct_dft(C *buf, const C *T, int h)
     if (g < 4) buf[PadIdx::at(tid)] = acc;
     __syncthreads();
     if (tid < h) {
-        C z = acc;
+        double2 z = acc;
         for (int q = 1; q < 4; ++q) z = cadd(z, buf[PadIdx::at(q * kDirectMax + tid)]);
         buf[PadIdx::at(tid)] = z;
     }
     __syncthreads();
 }
 
+// The Stockham passes of a fast-path ring (after the fold) and the pixel
+// stores of the last one.
 template <int NT, typename C>
 __device__ __attribute__((always_inline)) inline void fft_fast(C *buf, const C *T,
                                                                const RingDesc &d,
@@ -1127,23 +1126,27 @@ __device__ __attribute__((always_inline)) inline void fft_fast(C *buf, const C *
                                                                bool store)
 {
     const int h = d.n / 2;
-    if (d.rads == 0) {   // no radix list: the direct path
-        C z;
-        if (tid < h) {
-            const C Fk = buf[PadIdx::at(tid)], Fk2 = buf[PadIdx::at(h - tid)];
-            const C e1 = cadd(Fk, conjd(Fk2)), o1 = csub(Fk, conjd(Fk2));
-            z = cadd(e1, muli(cmul(tw_at(T, tid), o1), +1));
+    // no radix list: the direct path, of complex128 rings only (the plan), whose
+    // NT threads are the whole workgroup
+    if constexpr (sizeof(C) == sizeof(double2)) {
+        if (d.rads == 0) {
+            C z;
+            if (tid < h) {
+                const C Fk = buf[PadIdx::at(tid)], Fk2 = buf[PadIdx::at(h - tid)];
+                const C e1 = cadd(Fk, conjd(Fk2)), o1 = csub(Fk, conjd(Fk2));
+                z = cadd(e1, muli(cmul(tw_at(T, tid), o1), +1));
+            }
+            __syncthreads();
+            if (tid < h) buf[PadIdx::at(tid)] = z;
+            __syncthreads();
+            direct_dft<NT>(buf, T, h);
+            if (tid < h && store) {
+                z = buf[PadIdx::at(tid)];
+                out[2 * tid] = z.x;
+                out[2 * tid + 1] = z.y;
+            }
+            return;
         }
-        __syncthreads();
-        if (tid < h) buf[PadIdx::at(tid)] = z;
-        __syncthreads();
-        direct_dft<NT, C>(buf, T, h);
-        if (tid < h && store) {
-            z = buf[PadIdx::at(tid)];
-            out[2 * tid] = (double)z.x;
-            out[2 * tid + 1] = (double)z.y;
-        }
-        return;
     }
     int Ns = 1;
     for (int p = 0; p < d.np; ++p) {
@@ -1324,8 +1327,8 @@ __device__ __attribute__((always_inline)) inline void fold_fast2(float2 *X0, flo
     __syncthreads();
 }
 
-// Persistent over (ring, map pair) items, ring by ring (XCD x takes the
-// rings i = x mod 8).  LDS: two spectra of lds.fft_entries each, then the
+// Persistent over (ring, map pair) items, ring by ring (groups of 2^gshift
+// rings go to the XCDs in turn, ring_group).  LDS: two spectra of lds.fft_entries each, then the
 // twiddle table.
 __global__ __launch_bounds__(kFast2Threads, 4) void k_ring_synth_fast2(
     const int *__restrict__ ids, int count, int nmaps, const RingDesc *__restrict__ rings,
@@ -1388,34 +1391,27 @@ __global__ __launch_bounds__(kFast2Threads, 4) void k_ring_synth_fast2(
 // passes run in complex128, two workgroups per CU.  The mixed forms'
 // complex64 Delta goes to k_ring_synth_fast2 (two maps per workgroup, the
 // passes in complex64).
-template <typename DT> struct FastPrec;
-template <> struct FastPrec<double2> {
-    typedef double2 C;
-    static constexpr int kBlocks = 2;
-};
+constexpr int kFastBlocks = 2;
 
-template <typename DT>
-__global__ __launch_bounds__(kFastThreads, FastPrec<DT>::kBlocks) void k_ring_synth_fast(
+__global__ __launch_bounds__(kFastThreads, kFastBlocks) void k_ring_synth_fast(
     const int *__restrict__ ids, int count, int nmaps, const RingDesc *__restrict__ rings,
-    const double2 *__restrict__ pool, const DT *__restrict__ delta,
+    const double2 *__restrict__ pool, const double2 *__restrict__ delta,
     const int *__restrict__ minv, int mcontig, int mfull, int paced, DeltaLayout dl,
     double *__restrict__ map, long long npix, RingLds lds)
 {
-    typedef typename FastPrec<DT>::C C;
-    extern __shared__ double2 lds_raw[];
-    C *buf = reinterpret_cast<C *>(lds_raw);
-    C *T = buf + lds.fft_entries;
+    extern __shared__ double2 buf[];
+    double2 *T = buf + lds.fft_entries;
     const int per = (int)(gridDim.x / 8);
     const int x = (int)(blockIdx.x % 8), w = (int)(blockIdx.x / 8);
     long long lo, hi;
-    xcd_share<RingMajor<DT>::value>(count, nmaps, x, dl.shift, lo, hi);
+    xcd_share<false>(count, nmaps, x, dl.shift, lo, hi);
     long long it = lo + w;
     if (it >= hi) return;
     int i, bi;
-    xcd_item<RingMajor<DT>::value>(it, count, nmaps, x, dl.shift, i, bi);
+    xcd_item<false>(it, count, nmaps, x, dl.shift, i, bi);
     long long b = bi;
     int r = ids[i];
-    FastModes<kFastThreads, DT> raw;
+    FastModes<kFastThreads, double2> raw;
     load_fast<kFastThreads, true>(raw, delta + b * dl.map + dl.row(r), dl.mstride(r), minv,
                                   mcontig, ring_mmax(rings[r], mfull), paced != 0);
     for (bool first = true;; first = false) {
@@ -1426,13 +1422,13 @@ __global__ __launch_bounds__(kFastThreads, FastPrec<DT>::kBlocks) void k_ring_sy
         fold_fast<kFastThreads>(buf, d, raw, ring_mmax(d, mfull));
         const long long nx = it + per;
         if (nx < hi) {
-            xcd_item<RingMajor<DT>::value>(nx, count, nmaps, x, dl.shift, i, bi);
+            xcd_item<false>(nx, count, nmaps, x, dl.shift, i, bi);
             b = bi;
             r = ids[i];
             load_fast<kFastThreads, true>(raw, delta + b * dl.map + dl.row(r), dl.mstride(r), minv,
                                   mcontig, ring_mmax(rings[r], mfull), paced != 0);
         }
-        fft_fast<kFastThreads, C>(buf, T, d, out, threadIdx.x, true);
+        fft_fast<kFastThreads>(buf, T, d, out, threadIdx.x, true);
         if (nx >= hi) break;
         it = nx;
     }
@@ -2131,7 +2127,7 @@ __device__ __attribute__((always_inline)) inline void anal_fast(
     if (d.rads == 0) {
         if (tid < h) buf[PadIdx::at(tid)] = make_double2(in[2 * tid], -in[2 * tid + 1]);
         __syncthreads();
-        direct_dft<kFastThreads, double2>(buf, T, h);
+        direct_dft<kFastThreads>(buf, T, h);
     } else {
         int Ns = 1;
         for (int p = 0; p < d.np; ++p) {
@@ -2326,12 +2322,7 @@ hipError_t anal_together(const sht_plan_s *p, const double *map, double2 *dt, bo
     return hipGetLastError();
 }
 
-// only an FP64 plan's own Delta is taken together
-hipError_t synth_together(const sht_plan_s *, const float2 *, double *, hipStream_t)
-{
-    return hipErrorInvalidValue;
-}
-
+// (only an FP64 plan's own Delta is taken together)
 hipError_t synth_together(const sht_plan_s *p, const double2 *delta, double *map, hipStream_t st)
 {
     const RingClass &f = p->scls[kFastClass], &b = p->scls[kBlue64Class];
@@ -2403,23 +2394,22 @@ hipError_t anal_fast_class(const sht_plan_s *p, const double *map, double2 *dt, 
 // Size classes (FFT length limit): 0 -> 2048, 1 -> 4096, 2 -> 8192.
 static_assert(kClassThreads[0] == 256 && kClassThreads[1] == 512 && kClassThreads[2] == 1024,
               "class thread counts must match the kernel instantiations");
-template <typename DT>
-hipError_t synth_fast_class(const sht_plan_s *p, const DT *delta, double *map, bool full,
+hipError_t synth_fast_class(const sht_plan_s *p, const double2 *delta, double *map, bool full,
                             hipStream_t st)
 {
     const RingClass &rc = p->scls[kFastClass];
     if (rc.count == 0) return hipSuccess;
-    const size_t lds = (size_t)rc.lds.total() * sizeof(typename FastPrec<DT>::C);
-    hipError_t e = set_lds((const void *)k_ring_synth_fast<DT>, lds);
+    const size_t lds = (size_t)rc.lds.total() * sizeof(double2);
+    hipError_t e = set_lds((const void *)k_ring_synth_fast, lds);
     if (e != hipSuccess) return e;
     // as many workgroups per CU as the LDS of a ring allows (two), a multiple of 8
     const long long items = (long long)rc.count * p->nmaps;
-    long long grid = (long long)FastPrec<DT>::kBlocks * (p->num_cus > 0 ? p->num_cus : 256);
+    long long grid = (long long)kFastBlocks * (p->num_cus > 0 ? p->num_cus : 256);
     if (grid > items) grid = items;
     grid = ((grid + 7) / 8) * 8;
     // one map's Delta against the last cache's 256 MB
-    const bool past_cache = (long long)p->nm * p->nrings * (long long)sizeof(DT) > (256LL << 20);
-    hipLaunchKernelGGL((k_ring_synth_fast<DT>), dim3((unsigned)grid), dim3(kFastThreads), lds,
+    const bool past_cache = (long long)p->nm * p->nrings * (long long)sizeof(double2) > (256LL << 20);
+    hipLaunchKernelGGL(k_ring_synth_fast, dim3((unsigned)grid), dim3(kFastThreads), lds,
                        st, rc.d_ids, rc.count, p->nmaps, p->d_rings, p->d_pool, delta,
                        p->d_minv, p->mcontig, full ? p->mmax : -1, full && past_cache ? 1 : 0,
                        delta_layout(p, delta, full), map, p->npix, rc.lds);
@@ -2427,9 +2417,8 @@ hipError_t synth_fast_class(const sht_plan_s *p, const DT *delta, double *map, b
 }
 
 // complex64 Delta: two maps per workgroup, two workgroups per CU.
-template <>
-hipError_t synth_fast_class<float2>(const sht_plan_s *p, const float2 *delta, double *map,
-                                    bool full, hipStream_t st)
+hipError_t synth_fast_class(const sht_plan_s *p, const float2 *delta, double *map, bool full,
+                            hipStream_t st)
 {
     const RingClass &rc = p->scls[kFastClass];
     if (rc.count == 0) return hipSuccess;
@@ -2538,8 +2527,14 @@ static hipError_t ring_synth_dt(const sht_plan_s *p, const DT *delta, double *ma
         if (e == hipSuccess) e = hipStreamWaitEvent(p->aux_stream, p->ev_fork, 0);
     }
     const hipStream_t fst = fork ? p->aux_stream : st;
-    if (e == hipSuccess)
-        e = both ? synth_together(p, delta, map, fst) : synth_fast_class<DT>(p, delta, map, full, fst);
+    if (e == hipSuccess) {
+        if constexpr (sizeof(DT) == sizeof(double2)) {
+            e = both ? synth_together(p, delta, map, fst)
+                     : synth_fast_class(p, delta, map, full, fst);
+        } else {
+            e = synth_fast_class(p, delta, map, full, fst);
+        }
+    }
     if (e == hipSuccess) e = synth_blue_class(p, delta, map, full, st);
     if (e == hipSuccess) e = synth_class<1024, 8192, DT>(p, p->scls[2], delta, map, full, st);
     if (e == hipSuccess) e = synth_class<512, 4096, DT>(p, p->scls[1], delta, map, full, st);

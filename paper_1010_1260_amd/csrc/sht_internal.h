@@ -71,8 +71,6 @@ struct LiveTab {
     int nb;                // np / 64
 };
 
-// Rings grouped by FFT length for the Fourier kernels (LDS and register
-// budgets differ per class): class 0 up to 2048 points, 1 up to 4096, 2 up to 8192.
 // Where the entries of a Delta buffer lie.  A caller's is [map][m][ring]
 // (complex128).  Between the stages the rings come in blocks of 2^shift, the
 // fewest that fill a 128-byte line: complex128 [map][ring / 8][m][ring % 8]
@@ -133,6 +131,8 @@ struct RingLds {
     int total() const { return fft_entries + y_entries + tw_entries + tb_entries; }
 };
 
+// Rings grouped by FFT length for the Fourier kernels (LDS and register
+// budgets differ per class): class 0 up to 2048 points, 1 up to 4096, 2 up to 8192.
 struct RingClass {
     int count;        // rings in the class
     RingLds lds;
