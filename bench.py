@@ -36,12 +36,14 @@ PEAK_FP32_MFMA = 157.3e12
 PEAK_BF16_MFMA = 2.5e15   # dense
 PEAK_F16_MFMA = 2.5e15    # dense
 # mixed forms: matrix-core peak of the operand type, kernel, matrix-core
-# products per useful product, dtype label
+# products per useful product, dtype label, log2 of the |P_lm| below which the
+# kernel has no products
 FORMS = {
-    "fp32_mfma": (PEAK_FP32_MFMA, "k_legendre_mfma_f32", 1, "f32"),
-    "bf16x3_mfma": (PEAK_BF16_MFMA, "k_legendre_mfma_bf16x3", 6, "bf16x3"),
-    "f16x2_mfma": (PEAK_F16_MFMA, "k_legendre_mfma_f16x2", 3, "f16x2"),
+    "fp32_mfma": (PEAK_FP32_MFMA, "k_legendre_mfma_f32", 1, "f32", -160),
+    "bf16x3_mfma": (PEAK_BF16_MFMA, "k_legendre_mfma_bf16x3", 6, "bf16x3", -160),
+    "f16x2_mfma": (PEAK_F16_MFMA, "k_legendre_mfma_f16x2", 3, "f16x2", -32),
 }
+FLOOR_FP64 = -960
 PEAK_HBM = 8.0e12      # bytes/s
 
 
@@ -79,6 +81,43 @@ def recorded_traffic(key):
         return float(rec["bytes_per_launch"])
     except (OSError, KeyError, ValueError, TypeError):
         return None
+
+
+def live_share(np, lmax, geom, floors, m_step=64, ring_step=32):
+    """Share of the (l, m, ring) terms from the first |P_lm| >= 2^floor of an (m, ring)
+    on, for every floor: the terms that the Legendre kernels work on.  On every
+    m_step-th m and ring_step-th northern ring (within 0.01 of all of them)."""
+    x = geom.cth[:(geom.nrings + 1) // 2:ring_step][None, :]
+    s = geom.sth[:(geom.nrings + 1) // 2:ring_step][None, :]
+    m = np.arange(0, lmax + 1, m_step)[:, None]
+    k = np.arange(1, lmax + 1)
+    lmu = 0.5 * np.log2(1 / (4 * np.pi)) + np.concatenate(
+        [[0.0], np.cumsum(0.5 * np.log2((2 * k + 1) / (2.0 * k)))])
+    with np.errstate(divide="ignore"):
+        e = lmu[m] + np.where(m > 0, m * np.log2(s), 0.0)   # log2 of the scale of u1, u0
+    u0 = np.zeros(e.shape)
+    u1 = np.zeros(e.shape)
+    live = {f: np.zeros(e.shape, bool) for f in floors}
+    count = dict.fromkeys(floors, 0)
+    total = 0
+    b1 = np.ones(m.shape)
+    for l in range(lmax + 1):
+        on = m <= l
+        with np.errstate(divide="ignore", invalid="ignore"):
+            b = np.sqrt((4.0 * l * l - 1) / (1.0 * l * l - m * m))
+            u = np.where(m == l, 1.0, np.where(on, b * (x * u1 - np.where(m + 1 < l, u0 / b1, 0.0)),
+                                               0.0))
+            mag = np.log2(np.abs(u)) + e
+        for f in floors:
+            live[f] |= on & (mag >= f)
+            count[f] += int(live[f].sum())
+        total += int(on.sum()) * e.shape[1]
+        u0, u1, b1 = u1, u, b
+        big = np.abs(u1) > 2.0 ** 300
+        if big.any():
+            u0, u1 = np.where(big, u0 * 2.0 ** -300, u0), np.where(big, u1 * 2.0 ** -300, u1)
+            e = np.where(big, e + 300, e)
+    return {f: count[f] / total for f in floors}
 
 
 def run_plan(plan, alm, steps, warmup, lib, hip, torch, np):
@@ -443,10 +482,13 @@ def main() -> int:
     # FP64, complex64 in the mixed forms) and the map written once
     fft_bytes_fp64 = 16.0 * geom.nrings * (Lmax + 1) + 8.0 * geom.npix
     fft_bytes_mixed = 8.0 * geom.nrings * (Lmax + 1) + 8.0 * geom.npix
+    # the kernels have no work for the (l, m, ring) whose P_lm is below their floor:
+    # flops are counted on the others
+    share = live_share(np, Lmax, geom, [FLOOR_FP64] + sorted({f[4] for f in FORMS.values()}))
     if fp64 is not None:
         t = fp64["wall"] / args.steps
         leg = float(fp64["st"][1])
-        flops = float(npairs) * float(nalm) * 8.0
+        flops = float(npairs) * float(nalm) * 8.0 * share[FLOOR_FP64]
         fp64_info = {
             "maps_per_s": 1.0 / t, "ms_per_step": t * 1e3,
             "stages_ms": {"prescale": float(fp64["st"][0]), "legendre": leg,
@@ -454,8 +496,9 @@ def main() -> int:
             "legendre_roofline": {"bound": "alu", "achieved": flops / (leg * 1e-3) / 1e12,
                                   "peak": PEAK_FP64 / 1e12, "unit": "TFLOP/s",
                                   "frac": flops / (leg * 1e-3) / PEAK_FP64,
-                                  "kernel": f"k_legendre_fwd<{fp64['plan'].config}>",
-                                  "flops_per_launch": flops},
+                                  "kernel": f"k_legendre_fwd<{fp64['plan'].config}, 1>",
+                                  "flops_per_launch": flops,
+                                  "live_share_of_terms": share[FLOOR_FP64]},
             "fourier_GBps": fft_bytes_fp64 / (float(fp64["st"][2]) * 1e-3) / 1e9,
             "fourier_frac_hbm": fft_bytes_fp64 / (float(fp64["st"][2]) * 1e-3) / PEAK_HBM,
             "map2alm": fp64["map2alm"],
@@ -469,8 +512,8 @@ def main() -> int:
             # algorithmic contraction flops: 4 per (ring pair, l, m, map) (complex
             # accumulate of a real P_lm); the FP64 recurrence (4 per (pair, l, m))
             # runs on the vector units beside it
-            flops = float(npairs) * float(nalm) * 4.0 * B
-            peak, kern, nprod, _ = FORMS[prec]
+            peak, kern, nprod, _, floor = FORMS[prec]
+            flops = float(npairs) * float(nalm) * 4.0 * B * share[floor]
             executed = flops * nprod
             traffic = recorded_traffic(f"{kern}|lmax={Lmax}|nside={N}|nmaps={B}")
             forms[prec] = {
@@ -481,6 +524,7 @@ def main() -> int:
                              "peak": peak / 1e12, "unit": "TFLOP/s",
                              "frac": flops / (leg * 1e-3) / peak, "traffic": traffic,
                              "kernel": kern, "flops_per_launch": flops,
+                             "live_share_of_terms": share[floor],
                              "executed_mfma_flops_per_launch": executed,
                              "executed_frac": executed / (leg * 1e-3) / peak},
             }

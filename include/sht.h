@@ -29,7 +29,10 @@
  *    alm + 2 * b * nalm (doubles), its pixels at map + b * npix.
  *
  * Ownership and streams
- *  - The plan owns its own device tables, allocated on the device that is
+ *  - The plan owns its own device tables (sht_plan_info.table_bytes; most of
+ *    them say where the recurrence of every (m, ring pair) starts: 18 bytes each
+ *    with the pairs rounded up to 512, 0.3 GB at lmax 4096 / nside 2048, twice
+ *    that on mixed-precision plans), allocated on the device that is
  *    current when sht_plan is called, and one auxiliary stream with two
  *    events: for large plans the synthesis forks part of its Fourier work
  *    onto that stream and joins it back into `stream` before returning, so
@@ -45,6 +48,16 @@
  *    (host threads take turns through the fork and join).  While a call is
  *    being captured into a HIP graph, the plan's auxiliary stream is part of
  *    the capture: do not use the same plan from another thread meanwhile.
+ *
+ * Small and non-finite values
+ *  - SHT_FP64 and every adjoint: all terms a_lm P_lm with |P_lm| above 2^-960
+ *    count to full precision; smaller P_lm are taken as 0.  The mixed forms take
+ *    P_lm below 2^-160 (less than the smallest FP32 number) as 0.
+ *  - SHT_FP64: an infinite or NaN coefficient makes every pixel of its map, and
+ *    every ring of its m in sht_alm2delta, infinite or NaN.  Every adjoint: a
+ *    pixel so makes every coefficient of its map infinite or NaN, an entry of a
+ *    caller's Delta~ those of its m.  In the mixed forms' synthesis it need not
+ *    reach the rings on which its P_lm is taken as 0.
  *
  * Errors: every call returns an sht_status; nothing throws across the ABI.
  * Argument errors are detected on the host before anything is enqueued.
@@ -240,7 +253,9 @@ sht_status sht_alm2map_adjoint(sht_plan_t plan, const double *map, double *alm,
  * device array of SHT_NOALLOC_SCRATCH_BYTES that the library holds on each
  * device until the process ends (its address is looked up on the first call
  * on a device).  Calls nothing that allocates.  Returns SHT_ERR_WORKSPACE when
- * sht_plan_info.forward_workspace_bytes exceeds SHT_NOALLOC_SCRATCH_BYTES.
+ * sht_plan_info.forward_workspace_bytes exceeds SHT_NOALLOC_SCRATCH_BYTES (not
+ * counting the byte per 256 coefficients in which FP64 plans note the
+ * non-finite ones: the array has room for those beside it).
  * Every call on a device shares that device's array: calls that overlap on
  * one device (different streams, or host threads) race and must be
  * serialised by the caller.  The array's contents on entry are ignored (no

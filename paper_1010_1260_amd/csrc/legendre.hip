@@ -28,11 +28,12 @@
 // A wave processes the m-pair (m_i, m_{nm-1-i}) whose lengths sum to a
 // constant, which balances the triangular work.
 //
-// Bound: FP64 VALU issue.  l_max 4096 / nside 2048, one map: 1.6e9 wave
-// instructions, 2.6 ms at 2.4 GHz (the card runs this kernel near 2.0 GHz),
-// measured 3.84 ms; 4.32 ms with the rows' loads just before their use, 5.63 ms
-// with rescaled chains over all rows.  8 maps at l_max 1024 / nside 512 with
-// prescale: 432 us in fours, 578 us one by one.
+// Bound: FP64 VALU issue.  l_max 4096 / nside 2048, one map: 1.8e9 wave
+// instructions, 2.9 ms at 2.4 GHz (the card runs this kernel near 2.0 GHz),
+// measured 3.97 ms; 5.63 ms with rescaled chains over all rows.  (With a start
+// table that leaves out what is below 2^-192 of an m's largest value 3.61 ms,
+// 4.32 with the rows' loads just before their use; but live.hip.)  8 maps at
+// l_max 1024 / nside 512: 475 us in fours.
 #include <type_traits>
 
 #include "recurrence.h"
@@ -353,9 +354,9 @@ __global__ __launch_bounds__(64) void k_legendre_fwd(
 // The reduction costs 124 instructions per tile whatever CH, against 64 per
 // chain: more chains per lane make it cheap, but leave fewer waves.
 //
-// Bound: VALU issue.  l_max 4096 / nside 2048, one map, with the block sum: 5.94
+// Bound: VALU issue.  l_max 4096 / nside 2048, one map, with the block sum: 6.47
 // ms (10.47 ms with the lanes' partials reduced through LDS, four chains and
-// every row from l = m on); l_max 1024 / nside 512, 8 maps: 942 us (1405).
+// every row from l = m on); l_max 1024 / nside 512, 8 maps: 927 us (1405).
 constexpr int kAdjTile = 16;
 
 __device__ inline double2 halves_swapped(double a, double b, bool rows16)

@@ -29,7 +29,7 @@
 // the products of a parity among the vector work that follows it.
 //
 // Bound: vector issue (300 vector instructions and 24 MFMA per 32 rows, which
-// overlap).  16 maps at l_max 1024 / nside 512: 266 us, the whole transform at
+// overlap).  16 maps at l_max 1024 / nside 512: 251 us, the whole transform at
 // l_max 4096 / nside 2048 18.2 ms; 340 us and 21.9 ms as workgroups of four
 // waves with the coefficients in LDS, every row from l = m on.
 #include <type_traits>

@@ -33,7 +33,7 @@
 //
 // Bound: the matrix core (8 cycles per row and two maps) plus the vector work
 // (12 cycles per row); FP32 matrix and FP64 vector instructions take turns.
-// l_max 1999 / nside 999, 5 maps: 1.26 ms; 2.71 ms on 32x32x2 tiles of 16 maps,
+// l_max 1999 / nside 999, 5 maps: 1.14 ms; 2.71 ms on 32x32x2 tiles of 16 maps,
 // four waves sharing the coefficients in LDS, every row from l = m on.  The
 // whole transform at l_max 1024 / nside 512: one map 521 -> 213 us, 8 maps 819
 // -> 596 us, 16 maps 1209 -> 1128 us; l_max 4096, 16 maps 27.3 -> 23.2 ms.

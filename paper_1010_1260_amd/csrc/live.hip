@@ -25,7 +25,7 @@
 // plans have both, since the adjoint is FP64.
 //
 // Of the (l, m, ring) terms at l_max 4096 / nside 2048 17% lie below 2^-960 and
-// 27% below 2^-160 (l_max 1024: 6 and 18%).  A table takes 18 bytes per (m,
+// 28% below 2^-160 (l_max 1024: 6 and 20%).  A table takes 18 bytes per (m,
 // pair), 0.6 of a map's complex128 Delta.
 #include "recurrence.h"
 #include "sht_internal.h"

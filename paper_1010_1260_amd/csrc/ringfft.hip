@@ -1759,11 +1759,10 @@ __global__ __launch_bounds__(kBlueThreads, 4) void k_ring_synth_blue(
 // Against the size-class kernels it has both convolutions in one set of passes
 // and the chirps, the kernel spectrum, the pre-processing and the stores inside
 // them: a third of the barriers.
-// Bound by the latency of its passes (LDS and barriers, 50-60 % of the FP64
-// issue slots idle).  Rings of one map, against the size-class kernels: nside
-// 512, synthesis 47 to 37 us for the stage, transform 176 to 161 us; nside
-// 2048, analysis 740 to 540 us, transform 4.50 to 4.23 ms; a batch of 64 maps
-// of l_max 256 to 2048, 3.3 to 2.4 ms for the stage.
+// Bound by the latency of its passes (LDS and barriers).  Rings of one map,
+// against the size-class kernels: nside 512, synthesis 47 to 37 us for the
+// stage; nside 2048, analysis 740 to 540 us, synthesis 1.1 to 0.58 ms; a batch
+// of 64 maps of l_max 256 to 2048, 3.3 to 2.4 ms for the stage.
 template <int NT>
 __device__ __attribute__((always_inline)) inline void synth_blue64(
     double2 *X, const RingLds &lds, const RingDesc &d, const double2 *__restrict__ pool,
@@ -1826,8 +1825,8 @@ __global__ __launch_bounds__(NT, 4) void k_ring_synth_blue64(
 // The rings of the first complex128 Bluestein class (the first bblocks
 // workgroups, bitems rounded up to a multiple of 8) and the fast path's in one
 // launch, one workgroup per map and ring: at l_max 512 either alone leaves most
-// of the CUs idle (one map: 31.5 us in two launches, 24.5 in this; 8 maps at
-// l_max 1024: 365 us one after the other, 264).  Not persistent: the modes of a next
+// of the CUs idle (one map: 31.5 us in two launches, 23 in this; 8 maps at
+// l_max 1024: 365 us one after the other, 263).  Not persistent: the modes of a next
 // ring held through the passes take 218 registers and leave two workgroups on a
 // CU; this takes 113, and four workgroups hide the loads better.
 __global__ __launch_bounds__(kFastThreads, 4) void k_ring_synth_both(

@@ -161,10 +161,10 @@ int default_fwd_chains(const sht_plan_s *p)
 // 4 n.  It pays once the waves that are left fill the chip; with fewer, the
 // wait for the longer rows of coefficients shows.  Same key as above (waves
 // per CU at one pair per lane and one map per wave).  Measured, Legendre
-// stage with prescale, two pairs per lane: key 32 (l_max 512 / nside 256, 4
-// maps) 61 us alone, 84 in pairs; key 64 (8 maps) 99 alone, 90 in pairs, 96
-// in fours; key 128 (l_max 1024 / nside 512, 4 maps) 304, 288, 228; key 256 (8
-// maps) 578, 495, 432.  The switches sit between measured points.
+// stage with prescale, one / two / four maps: key 16 (l_max 256 / nside 128, 8
+// maps) 28 / 46 / 50 us; key 32 (512, 4 maps) 60 / 84 / 88; key 64 (512, 8 maps) 98
+// / 89 / 95; key 64 (1024, 2 maps) 169 / 152; key 128 (1024, 4 maps) 299 / 284 /
+// 217; key 256 (8 maps) 587 / 506 / 420.  The switches sit between measured points.
 struct GroupRule {
     double max_waves_per_cu;
     int maps;
@@ -192,9 +192,9 @@ int default_fwd_group(const sht_plan_s *p)
 // Ring pairs per lane of the adjoint Legendre kernel: its reduction over the
 // lanes costs as much as two pairs' rows whatever their number, so more pairs
 // are cheaper as long as enough waves are left.  Same key.  Measured, Legendre
-// adjoint with the block sum, 1 / 2 / 4 / 8 pairs: key 2 (l_max 256) 19 / 22 / 29 /
-// 30 us; key 8 (512) 50 / 42 / 53 / 77; key 32 (1024) 277 / 199 / 212 / 240; key
-// 64 (1024, 2 maps) 515 / 361 / 297 / 287; key 512 (4096) 11.5 / 7.7 / 6.2 / 5.9 ms.
+// adjoint with the block sum, 1 / 2 / 8 pairs: key 2 (l_max 256) 20 / 22 / 33 us;
+// key 4.5 (384) 38 / 31 / 54; key 8 (512) 50 / 43 / 81; key 32 (1024) 263 / 186 /
+// 232; key 64 (1024, 2 maps) 501 / 335 / 270; key 512 (4096) 12.9 / 8.5 / 6.4 ms.
 constexpr ChainRule kAdjChainTable[] = {
     {4.0, 1},
     {48.0, 2},
