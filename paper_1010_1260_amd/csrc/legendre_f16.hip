@@ -451,23 +451,24 @@ __device__ __forceinline__ void m_compute(MState &st, const double2 *stash, int 
 
 // One wave per (64 ring pairs, m-pair, 16 maps), nothing shared between waves:
 // no barrier, and a wave's dead rows cost it nothing.
-__global__ __launch_bounds__(64, 2) void k_legendre_mfma_f16x2(
+template <int W>
+__global__ __launch_bounds__(64 * W, 2) void k_legendre_mfma_f16x2(
     const PairDesc *__restrict__ pairs, int npairs, LiveTab lt, int pblocks,
     const int *__restrict__ mval, const long long *__restrict__ soff, int nm, int nmpairs,
     int lmax, const double *__restrict__ Asb, const v4u *__restrict__ Bb, long long nsuper,
     float2 *__restrict__ delta, DeltaLayout dl, int nmaps, int groups, int full)
 {
-    __shared__ double2 start[64];
+    __shared__ double2 start[64 * W];
     // XCD x takes the m-pairs q = x mod 8 (see the FP64 kernel)
     const int xcd = (int)(blockIdx.x % 8);
-    const int w = (int)(blockIdx.x / 8);
+    const int w = xcd_wave<W>();
     const int pb = w % pblocks;
     const int rest = w / pblocks;
     const int grp = rest % groups;
     const int q = xcd + 8 * (rest / groups);
     if (q >= nmpairs) return;
-    const int lane = threadIdx.x;
-    double2 *stash = start + lane;
+    const int lane = (int)threadIdx.x & 63;
+    double2 *stash = start + threadIdx.x;
     const v4u *Bg = Bb + (long long)grp * nsuper * kSuperElems;
     MState st;
     MfmaTiles tot;
@@ -514,9 +515,12 @@ hipError_t launch_legendre_mfma_f16x2(const sht_plan_s *p, const void *Bb, float
     const int pblocks = (p->npairs + 63) / 64;
     const int nmpairs = (p->nm + 1) / 2;
     const int groups = (p->nmaps + 15) / 16;
-    const long long total = 8LL * ((nmpairs + 7) / 8) * pblocks * groups;
-    if (total <= 0 || total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(k_legendre_mfma_f16x2, dim3((unsigned)total), dim3(64), 0, st,
+    const int W = waves_per_group(p, (long long)nmpairs * pblocks * groups);
+    const long long xcd = (long long)((nmpairs + 7) / 8) * pblocks * groups;   // an XCD's waves
+    const long long grid = 8 * ((xcd + W - 1) / W);
+    if (grid <= 0 || grid > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    const auto kern = W == 4 ? k_legendre_mfma_f16x2<4> : k_legendre_mfma_f16x2<1>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3((unsigned)(64 * W)), 0, st,
                        p->d_pairs, p->npairs, p->live32, pblocks, p->d_mval, p->d_soff, p->nm,
                        nmpairs, p->lmax, p->d_Asb, reinterpret_cast<const v4u *>(Bb), p->nsuper,
                        delta, delta_blocked_maps(p->nm, p->nrings, p->nmaps), p->nmaps, groups, full ? 1 : 0);

@@ -268,25 +268,25 @@ __device__ __forceinline__ void store_delta(const Sums<NP> &tot, int i,
 }
 
 // Groups of 2 NP maps from map0 on.
-template <int NP>
-__global__ __launch_bounds__(64) void k_legendre_mfma_f32(
+template <int NP, int W>
+__global__ __launch_bounds__(64 * W) void k_legendre_mfma_f32(
     const PairDesc *__restrict__ pairs, int npairs, LiveTab lt, int pblocks,
     const int *__restrict__ mval, const long long *__restrict__ soff,
     const long long *__restrict__ boff16, int nm, int nmpairs, int lmax,
     const double *__restrict__ Asb, const float *__restrict__ Bp, long long nblocks,
     float2 *__restrict__ delta, DeltaLayout dl, int map0, int nmaps, int groups, int full)
 {
-    __shared__ double2 start[64];
+    __shared__ double2 start[64 * W];
     // XCD x takes the m-pairs q = x mod 8 (see the FP64 kernel)
     const int xcd = (int)(blockIdx.x % 8);
-    const int w = (int)(blockIdx.x / 8);
+    const int w = xcd_wave<W>();
     const int pb = w % pblocks;
     const int rest = w / pblocks;
     const int grp = rest % groups;
     const int q = xcd + 8 * (rest / groups);
     if (q >= nmpairs) return;
-    const int lane = threadIdx.x;
-    double2 *stash = start + lane;
+    const int lane = (int)threadIdx.x & 63;
+    double2 *stash = start + threadIdx.x;
     const float *Bg = Bp + (long long)grp * nblocks * (NP * 64);
     const int m0 = map0 + grp * 2 * NP;
     const int p = pb * 64 + lane;
@@ -331,9 +331,12 @@ hipError_t launch_group(const sht_plan_s *p, const float *Bp, float2 *delta, int
 {
     const int pblocks = (p->npairs + 63) / 64;
     const int nmpairs = (p->nm + 1) / 2;
-    const long long total = 8LL * ((nmpairs + 7) / 8) * pblocks * groups;
-    if (total <= 0 || total > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(k_legendre_mfma_f32<NP>, dim3((unsigned)total), dim3(64), 0, st, p->d_pairs,
+    const int W = waves_per_group(p, (long long)nmpairs * pblocks * groups);
+    const long long xcd = (long long)((nmpairs + 7) / 8) * pblocks * groups;   // an XCD's waves
+    const long long grid = 8 * ((xcd + W - 1) / W);
+    if (grid <= 0 || grid > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    const auto kern = W == 4 ? k_legendre_mfma_f32<NP, 4> : k_legendre_mfma_f32<NP, 1>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3((unsigned)(64 * W)), 0, st, p->d_pairs,
                        p->npairs, p->live32, pblocks, p->d_mval, p->d_soff, p->d_boff16, p->nm,
                        nmpairs, p->lmax, p->d_Asb, Bp + b_offset(p, first), p->nblk16, delta,
                        delta_blocked_maps(p->nm, p->nrings, p->nmaps), first, p->nmaps, groups, full ? 1 : 0);

@@ -36,6 +36,28 @@ __device__ __forceinline__ void add_tiles(MfmaTiles &tot, const MfmaTiles &acc)
     tot.e0 += acc.e0; tot.e1 += acc.e1; tot.o0 += acc.o0; tot.o1 += acc.o1;
 }
 
+// Waves to a workgroup.  They share nothing, and one each suits most launches (a
+// wave that is done makes room for the next; up to three to a CU have a SIMD
+// each).  With about one to a SIMD single waves land unevenly on the SIMDs, and
+// four to a workgroup take less time (Legendre stage of 16 maps and 64 m at
+// l_max 2048 / nside 1024, 1024 waves: FP32 435 and 327 us, FP16x2 210 and 174,
+// BF16x3 277 and 239; with 768 waves 283 and 289, 140 and 143, 204 and 209; with
+// 1280 482 and 493, 258 and 259, 318 and 332).
+inline int waves_per_group(const sht_plan_s *p, long long waves)
+{
+    return waves > 3LL * p->num_cus && 2 * waves <= 9LL * p->num_cus ? 4 : 1;
+}
+
+// This wave's place in an XCD's list of waves (workgroups are dealt to the 8
+// XCDs round-robin).
+template <int W>
+__device__ __forceinline__ int xcd_wave()
+{
+    // uniform over the wave
+    return (int)(blockIdx.x / 8) * W +
+           (W > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) : 0);
+}
+
 // A lane's recurrence on one m: zero until its start row, where it takes the
 // start table's values (`stash`, its LDS slot).  Before it the true values are
 // below 2^-160, which is zero in FP32, so a lane's operands need no mask, and
