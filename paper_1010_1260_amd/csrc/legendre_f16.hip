@@ -39,8 +39,8 @@
 // parity are issued among the vector work that follows it.
 //
 // Bound: vector issue at the power limit.  204 vector instructions and 12 MFMA
-// per 32 rows.  l_max 4096 / nside 2048, 16 maps: 7.71 ms (vector work on 80% of
-// the cycles by that count, at 1.8-2.0 GHz); 10.8 ms as workgroups of four waves that
+// per 32 rows.  l_max 4096 / nside 2048, 16 maps: 7.71 ms (counted: vector issue
+// on 73% of the cycles, at 1.8-2.0 GHz); 10.8 ms as workgroups of four waves that
 // shared the coefficients in LDS with a barrier per super-block, every row
 // from l = m on; 8.63 ms so with the live rows and the interleaved products,
 // 8.14 ms with independent waves.
